@@ -509,3 +509,33 @@ def test_status_waits_for_the_stream_of_the_call(ej):
     assert st == 2
     torch.cuda.synchronize()
     assert int(total.cpu()[0]) == 0
+
+
+# ------------------------------------------------------------------ the queue of the rare path
+@pytest.mark.parametrize("n,share", [(130, 0.02), (300, 0.1), (513, 0.3), (260, 0.7), (300, 1.0)])
+def test_candidate_queue_at_every_density(ej, n, share):
+    """From a lane here and there to every lane of every region holding candidates: less, exactly and several times what the
+    queue of a wavefront takes (16 lanes), with ragged edges and the diagonal, in pair, count and two-set mode."""
+    print(f"candidate queue n={n} share={share}", flush=True)
+    rng = np.random.default_rng(n)
+    X = rng.random((n, 64), dtype=np.float32).astype(np.float16).view(np.uint16)
+    X[n // 2] = X[1]
+    P = orc.decode(X)
+    eps = np.float32(100.0) if share == 1.0 else orc.select_eps_all_pairs(P, share * (n - 1))
+    ora_pairs, ora_d2 = orc.selfjoin_pairs(P, eps)
+    pairs, d2, found = run_pairs(ej, dev(X), eps, capacity=n * n)
+    assert found == pairs.shape[0]
+    parity.check_pair_sets(P, eps, pairs, d2, ora_pairs, ora_d2)
+    counts, total = ej.selfjoin_count(dev(X), eps)
+    two, td2, tfound = parity.to_host_pairs(*ej.join_pairs(dev(X), dev(X[: n - 3]), eps, n * n))
+    torch.cuda.synchronize()
+    ns = pairs[pairs[:, 0] != pairs[:, 1]]
+    hist = np.bincount(ns[:, 0], minlength=n) + np.bincount(ns[:, 1], minlength=n)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), hist) and int(total.cpu()[0]) == found - n
+    if share == 1.0:
+        assert found == n * (n + 1) // 2 and tfound == n * (n - 3)
+    assert np.unique(orc.pair_keys(two)).size == tfound == two.shape[0]
+    dense = ej.dist2_tile(dev(X), 0, 0, n, n).cpu().numpy()
+    off = two[:, 0] != two[:, 1]
+    assert np.array_equal(dense[two[off, 0], two[off, 1]], td2[off])
+    assert abs(int((dense[:, : n - 3] <= eps * eps).sum()) - tfound) <= n  # (the two sums of a pair with itself may round apart)
