@@ -17,33 +17,35 @@
 #endif
 
 constexpr uint32_t EJ_NUM_XCD = 8;  // accelerator complex dies of the MI355X, each with its own L2
-constexpr uint32_t EJ_SB = 16;      // tiles per super-block edge (one super-block = 256 tiles = one pass of the chip)
+constexpr uint32_t EJ_SB = 16;      // rows of tiles by which a launch can be cut (one super-block row = two bands)
+constexpr uint32_t EJ_BAND = 8;     // rows of tiles per band
 
 // Work distribution (the counterpart of the paper's work queue that orders block tiles in small
 // squares for L2 reuse, Section 3.3.1, re-derived for 8 XCDs with private 4 MB L2s):
-//   * the upper triangle of the tile grid is cut into super-blocks of 16 x 16 tiles, enumerated
-//     row-major; one super-block is one pass of the 256 CUs, so at any time the chip works on
-//     (16+16) x 256 rows of X, which the memory-side cache holds;
-//   * inside a super-block each XCD owns an 8 x 4 rectangle of tiles (12 row panels shared by its
-//     32 CUs through its own L2); the rectangle's position rotates with the super-block index so
-//     that partially empty (diagonal, ragged) super-blocks do not starve the same XCD every time;
-//   * workgroup w runs on XCD w % 8 (hardware round-robin, verified on device).  The non-empty tiles
-//     of an XCD's rectangles, in super-block order, form a list; workgroup number k of the XCD takes
-//     entries k, k + 32, k + 64, ... of it.  So every workgroup of an XCD computes the same number of
-//     tiles (+-1), and at any time the 32 of them sit on 32 consecutive entries -- one rectangle,
-//     or the end of one and the start of the next.  That keeps them in step without any
-//     synchronisation or queue, which is what makes the panels they share hit in L2: a schedule
-//     that lets workgroups skip empty tiles individually drifts apart by many tiles and the L2
-//     hit rate collapses (measured: 16 % instead of ~75 %).
+//   * the rows of the tile grid (the upper triangle of the self-join, the whole grid otherwise) are cut into
+//     bands of 8; the tiles of a band are numbered column by column, the bands one after the other.  32 consecutive
+//     tiles are then 4 columns x 8 rows (5 where they start inside a column): 12 row and column panels;
+//   * workgroup w runs on XCD w % 8 (hardware round-robin, verified on device).  In each pass of the 256 CUs
+//     XCD x computes the x-th 32 of the next 256 tiles, one each.  So the 32 workgroups of an XCD share 12
+//     panels through its own L2, all XCDs share the 8 row panels, and -- as long as the grid is a multiple of 64
+//     workgroups -- a workgroup keeps its row panel to the end of the band;
+//   * every workgroup computes the same number of tiles (+-1), whatever the shape of the grid.  That keeps the
+//     workgroups of an XCD in step without any synchronisation or queue, which is what makes the panels they share
+//     hit in L2: a schedule that lets workgroups skip empty tiles individually drifts apart by many tiles and the
+//     L2 hit rate collapses (measured: 16 % instead of ~75 %).
+// Before, each XCD owned the 8 x 4 rectangle of every 16 x 16 super-block whose position rotated with the block's number:
+// the same 12 panels, but the partly empty rectangles of the diagonal and the edge were dealt out unevenly.  Largest number
+// of tiles of a workgroup, with the ideal: 30,011 x 7,001 points 16 (12.9, now 13), 20,011 points 14 (12.3, now 13).
 struct TileCursor {
   uint32_t xcd, wpx;     // this workgroup's XCD; workgroups per XCD
-  uint32_t self, nsbA, nsbB, ntA, ntB;
-  uint32_t rem;          // position of this workgroup's next tile, counted from the first tile of the current rectangle
-  uint32_t P, Q, sbi;    // current super-block: coordinates and linear index
-  uint32_t fast_left;    // steps of the common kind that may follow (see next) ...
-  uint32_t fast_row, fast_col;  // ... and what they need: the tile's place in its rectangle, row already in tiles of the grid
+  uint32_t self, ntA, ntB;
+  uint32_t stride;       // tiles per pass of all workgroups
+  uint32_t band, band_end;
+  uint32_t rem;          // position of this workgroup's next tile, counted from the first tile of the current band
+  uint32_t fast_end;     // steps of the common kind may be taken while rem is below this (see next)
+  uint32_t row, col;     // the tile handed out last
 #ifdef EJOIN_ABL_ROWMAJOR_TILES
-  uint32_t start, stride;  // first tile and stride of this workgroup
+  uint32_t started;
 #endif
   // self_join: upper triangle of an nt x nt grid (nt_a == nt_b); otherwise the whole nt_a x nt_b grid.
   // sb_row_begin .. sb_row_end - 1: the rows of super-blocks this launch covers (a join may be cut into several
@@ -55,134 +57,84 @@ struct TileCursor {
     self = self_join;
     ntA = nt_a;
     ntB = nt_b;
-    nsbA = (nt_a + EJ_SB - 1) / EJ_SB;
-    nsbB = (nt_b + EJ_SB - 1) / EJ_SB;
-    if (sb_row_end < nsbA) nsbA = sb_row_end;  // (the rows past the range are simply not enumerated)
-    rem = block / EJ_NUM_XCD;
-    P = sb_row_begin;
-    Q = self_join ? sb_row_begin : 0;
-    sbi = 0;
-    fast_left = 0;
-    fast_row = fast_col = 0;
-#ifdef EJOIN_ABL_ROWMAJOR_TILES
-    start = block;
     stride = nblocks;
+    const uint32_t per_sb = EJ_SB / EJ_BAND, bands = (nt_a + EJ_BAND - 1) / EJ_BAND;
+    band = sb_row_begin * per_sb;
+    band_end = sb_row_end < (nt_a + EJ_SB - 1) / EJ_SB ? sb_row_end * per_sb : bands;
+    const uint32_t per = nblocks / EJ_NUM_XCD, more = nblocks % EJ_NUM_XCD;  // the first `more` XCDs have one workgroup more
+    rem = xcd * per + (xcd < more ? xcd : more) + block / EJ_NUM_XCD;
+    fast_end = 0;
+    row = col = 0;
+#ifdef EJOIN_ABL_ROWMAJOR_TILES
+    started = 0;
+    rem = block;
 #endif
   }
-  // Tiles of row r (0..7) of a rectangle on the diagonal of the self-join: columns lo .. cj-1, with
-  // lo = max(0, a + r - b), where a and b are the rectangle's row and column offsets in its super-block.
-  static EJ_HD uint32_t diag_row_first(uint32_t a, uint32_t b, uint32_t r) { return a + r > b ? a + r - b : 0u; }
   // next tile of this workgroup; false when the work is exhausted
   EJ_HD bool next(uint32_t& I, uint32_t& J) {
 #ifdef EJOIN_ABL_ROWMAJOR_TILES
-    // tiles of the triangle (or grid) in row-major order, tile t to workgroup t % nblocks; P, Q hold the
-    // row and column of this workgroup's next tile
-    if (rem != 0xFFFFFFFFu) {  // first call
-      rem = 0xFFFFFFFFu;
-      P = 0;
-      Q = start;
+    // tiles of the triangle (or grid) in row-major order, tile t to workgroup t % nblocks
+    if (!started) {
+      started = 1;
+      row = 0;
+      col = rem;
     } else {
-      Q += stride;
+      col += stride;
     }
-    while (P < ntA && Q >= ntB) {
-      Q -= ntB;
-      ++P;
-      if (self) Q += P;  // row P of the triangle starts at column P
+    while (row < ntA && col >= ntB) {
+      col -= ntB;
+      ++row;
+      if (self) col += row;  // row P of the triangle starts at column P
     }
-    if (P >= ntA) return false;
-    I = EJ_UNIFORM(P);
-    J = EJ_UNIFORM(Q);
+    if (row >= ntA) return false;
+    I = EJ_UNIFORM(row);
+    J = EJ_UNIFORM(col);
     return true;
 #endif
-    // Everything here is uniform over the workgroup and meant to stay on the scalar unit: 32-bit counters,
-    // closed forms for the number of tiles of a rectangle, and real branches around the rare cases.
-    //
-    // The common step first.  All eight wavefronts of a workgroup run this code at the same time, between two
-    // tiles, with nothing else to overlap it: every instruction here is paid eight times on the one scalar unit.
-    // Along a row of super-blocks nearly every rectangle is a complete 8 x 4 one; the last tile came from such
-    // a rectangle and the next one sits in the next rectangle, at place (fast_row, fast_col) of it, whose offsets
-    // inside its super-block rotate with the super-block index.  With 32 workgroups per XCD (the whole chip) that
-    // place is the same from rectangle to rectangle and the steps of this kind go on to the end of the row; with
-    // another number the general code below is asked again after each one.  (fast_left: how many may follow.)
+    // Everything here is uniform over the workgroup and meant to stay on the scalar unit.  All eight wavefronts of a
+    // workgroup run it at the same time, between two tiles, with nothing else to overlap it: every instruction is paid
+    // eight times on the one scalar unit.  So the common step comes first: inside a band, right of its diagonal block, a
+    // grid of a multiple of 8 workgroups goes on in the same row, stride / 8 columns further.
 #ifndef EJOIN_CURSOR_NO_FAST_PATH
-    if (fast_left != 0) {
-      --fast_left;
-      ++Q;
-      ++sbi;
-      const uint32_t t = xcd + sbi;  // rectangle number (t % 8): row offset 8 (t / 4 % 2), column offset 4 (t % 4)
-      I = EJ_UNIFORM(fast_row + ((t << 1) & 8u));
-      J = EJ_UNIFORM(Q * EJ_SB + fast_col + ((t << 2) & 12u));
-      rem = rem - 32u + wpx;
+    if (rem < fast_end) {
+      rem += stride;
+      col += stride / EJ_BAND;
+      I = EJ_UNIFORM(row);
+      J = EJ_UNIFORM(col);
       return true;
     }
 #endif
-    while (P < nsbA) {
-      const uint32_t xp = (xcd + sbi) & 7;
-      const uint32_t a = (xp >> 2) * 8, b = (xp & 3) * 4;  // the rectangle's offsets inside its super-block
-      const uint32_t I0 = P * EJ_SB + a, J0 = Q * EJ_SB + b;
-      // columns of the rectangle inside the grid, and rows (in the self-join's off-diagonal super-blocks all 8)
-      const uint32_t cj = J0 >= ntB ? 0u : (ntB - J0 < 4u ? ntB - J0 : 4u);
-      const uint32_t ri = self ? 8u : (I0 >= ntA ? 0u : (ntA - I0 < 8u ? ntA - I0 : 8u));
-      const bool on_diag = self && P == Q;
-      uint32_t v = ri * cj;
-      if (on_diag) {  // one super-block in every row of the self-join
-        v = 0;
-        for (uint32_t r = 0; r < 8; ++r) {
-          const uint32_t lo = diag_row_first(a, b, r);
-          v += lo < cj ? cj - lo : 0u;
+    while (band < band_end) {
+      const uint32_t first = band * EJ_BAND;  // first row
+      const uint32_t h = ntA - first < EJ_BAND ? ntA - first : EJ_BAND;
+      // the self-join's band starts with the triangle of its h columns on the diagonal
+      const uint32_t tri = self ? h * (h + 1) / 2 : 0u, c0 = self ? first + h : 0u;
+      const uint32_t size = tri + h * (ntB - c0);
+      if (rem < size) {
+        if (rem < tri) {
+          uint32_t c = 0, r = rem;
+          while (r > c) r -= ++c;  // column c of the triangle has rows 0 .. c
+          row = first + r;
+          col = first + c;
+        } else if (h == EJ_BAND) {
+          const uint32_t q = rem - tri;
+          row = first + q % EJ_BAND;
+          col = c0 + q / EJ_BAND;
+        } else {
+          const uint32_t q = rem - tri;
+          row = first + q % h;
+          col = c0 + q / h;
         }
-      }
-      if (rem < v) {
-        uint32_t r = 0, c = rem;
-        if (on_diag) {
-          for (; r < 8; ++r) {
-            const uint32_t lo = diag_row_first(a, b, r);
-            const uint32_t cnt = lo < cj ? cj - lo : 0u;
-            if (c < cnt) {
-              c += lo;
-              break;
-            }
-            c -= cnt;
-          }
-        } else if (cj == 4) {
-          r = rem >> 2;
-          c = rem & 3;
-        } else {  // ragged last column of rectangles
-          while (c >= cj) {
-            c -= cj;
-            ++r;
-          }
-        }
-        I = EJ_UNIFORM(I0 + r);
-        J = EJ_UNIFORM(J0 + c);
-        rem += wpx;
-#ifndef EJOIN_CURSOR_NO_FAST_PATH
-        // Super-blocks (P, Q + 1 ..) that are complete: every column inside the grid (Q' < ntB / 16), every
-        // row too (always so right of the diagonal of the self-join, whose rows end before its columns do),
-        // and off the diagonal (Q' > P; the self-join starts each row on the diagonal, so Q >= P here).
-        // A rectangle of 32 tiles maps position p to (p / 4, p % 4) whatever kind it is, so the fast step
-        // may follow any rectangle; it only requires the ones it enters to be complete.
-        // The next tile is entry rem - 32 of the next rectangle, if that is one of its 32.
-        {
-          const uint32_t qf = ntB / EJ_SB;
-          const bool rows_ok = self ? true : (P < ntA / EJ_SB);
-          const uint32_t pos = rem - 32u;
-          uint32_t steps = (v == 32u && rows_ok && Q + 1 < qf && pos < 32u) ? qf - 1 - Q : 0u;
-          if (wpx != 32u && steps > 1u) steps = 1u;
-          fast_left = steps;
-          fast_row = P * EJ_SB + (pos >> 2);
-          fast_col = pos & 3u;
-        }
-#endif
+        I = EJ_UNIFORM(row);
+        J = EJ_UNIFORM(col);
+        fast_end = rem >= tri && h == EJ_BAND && stride % EJ_BAND == 0 ? size : 0u;
+        rem += stride;
         return true;
       }
-      rem -= v;
-      ++sbi;
-      if (++Q == nsbB) {  // super-blocks row-major; the self-join starts each row on the diagonal
-        ++P;
-        Q = self ? P : 0;
-      }
+      rem -= size;
+      ++band;
     }
+    fast_end = 0;
     return false;
   }
 };

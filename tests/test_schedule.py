@@ -122,3 +122,17 @@ def test_launches_cut_by_rows_of_super_blocks_cover_every_tile_once(sched, self_
         keys.append(I * (nt_b + 1) + J)
     keys = np.concatenate(keys)
     assert keys.size == want and np.unique(keys).size == want
+
+
+@pytest.mark.parametrize("nblocks,self_join,nt_a,nt_b", [c for c in CASES if c[0] == 256] + [(256, True, 79, 79), (256, False, 118, 28), (256, False, 782, 2)])
+def test_every_workgroup_gets_the_same_number_of_tiles(sched, nblocks, self_join, nt_a, nt_b):
+    """Over the whole chip, not only inside an XCD; and a workgroup that goes on inside a band stays in its row."""
+    if sched.kind != "xcd_rectangles":
+        pytest.skip("property of the XCD-aware schedule only")
+    tiles, m, want = sched(nblocks, self_join, nt_a, nt_b)
+    counts = np.bincount(tiles[:, 0], minlength=nblocks)
+    assert counts.max() == -(-want // nblocks) and counts.min() == want // nblocks
+    blk, I, J = (tiles[:, k].astype(np.int64) for k in (0, 2, 3))
+    off_diagonal = J >= (I // 8 + 1) * 8 if self_join else np.ones(m, dtype=bool)
+    on = (blk[1:] == blk[:-1]) & (I[1:] // 8 == I[:-1] // 8) & off_diagonal[1:] & off_diagonal[:-1] & ((I[1:] // 8 + 1) * 8 <= nt_a)
+    assert (I[1:][on] == I[:-1][on]).all() and (J[1:][on] == J[:-1][on] + nblocks // 8).all()
