@@ -133,9 +133,34 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
   if (i < n) p[i] = v;
 }
 
-// Step 1 (Section 3.1): s_i = sum_k x_ik^2.  One wavefront per 16 consecutive points; the 16 x 16
-// Gram block of those points is accumulated with the same MFMA steps, in the same k order, as
-// the join kernel uses, and its diagonal is stored.  That makes s_i bit-identical to a_ii, and
+// The largest of the wavefronts' values of a workgroup, added to *max_bits with one atomic: those on one address are served
+// one after the other, about 11 ns each.
+__device__ __forceinline__ void merge_max(uint32_t bits, uint32_t* max_bits) {
+  __shared__ uint32_t wave_max[8];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, off));
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = bits;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (uint32_t w = 1; w < blockDim.x / 64; ++w) bits = max(bits, wave_max[w]);
+    atomicMax(max_bits, bits);
+  }
+}
+
+// Diagonal of the 16 x 16 Gram block of points row0 .. row0 + 15, whose element (row, col) sits in lane col + 16 * (row / 4),
+// register row % 4: stored to s for points below n.  Returns this lane's norm (0 in a lane that holds none).
+__device__ __forceinline__ float store_diagonal(const float4v& acc, int64_t row0, int64_t n, float* __restrict__ s) {
+  const int lane = threadIdx.x & 63, c = lane & 15;
+  if ((c >> 2) != (lane >> 4) || row0 + c >= n) return 0.f;
+  const float lo = (c & 1) ? acc[1] : acc[0], hi = (c & 1) ? acc[3] : acc[2];
+  const float v = (c & 2) ? hi : lo;
+  s[row0 + c] = v;
+  return v;
+}
+
+// Step 1 (Section 3.1): s_i = sum_k x_ik^2.  One wavefront per 32 consecutive points; the 16 x 16
+// Gram blocks of its two halves are accumulated with the same MFMA steps, in the same k order, as
+// the join kernel uses, and their diagonals are stored.  That makes s_i bit-identical to a_ii, and
 // to a_ij for a duplicate j of i, so duplicates come out at distance exactly 0.  (The paper
 // matches its norm rounding to its tensor cores' for the same reason.)  Also tracks max_i s_i
 // (as FP32 bits; s >= 0 so unsigned order is numeric order, and NaN/Inf sort above every finite value).
@@ -146,51 +171,56 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
 // 16 KB of contiguous memory, so the global->LDS copies of the join are straight 1 KB block copies made of full
 // 128-byte lines (in the row-major X a 32-coordinate slice of a row is half a line, and the L2 would be asked for
 // every line twice), and the `blocks` k-blocks of a panel follow each other (packed_index).  The 16 bytes a lane
-// loads as its part of the MFMA operand (point l%16, chunk l/16 of the k-block) are exactly one chunk of that layout.
+// loads as its part of the MFMA operand (point l%16, chunk l/16 of the k-block) are exactly one chunk of that layout, and
+// the two halves of 32 points together fill 2 KB of it.
+//
+// Bound by memory; what it takes is enough loads in flight (four k-blocks of two halves per wavefront) and few atomics: with
+// 16 points per wavefront and one atomic each it ran at 0.7 TB/s on 10^6 x 128 (725 us with k_aux, now 94 + 12: 5.4 TB/s) and
+// at 1.9 TB/s on 3 10^5 x 384 (244 us, now 86).
+constexpr int NORM_POINTS = 32;  // points per wavefront
 template <bool PACK>
-__global__ __launch_bounds__(256) void k_norms(const uint16_t* __restrict__ X, int64_t n, int64_t npad, int64_t ld, int k32steps,
+__global__ __launch_bounds__(512) void k_norms(const uint16_t* __restrict__ X, int64_t n, int64_t npad, int64_t ld, int k32steps,
                                                float* __restrict__ s, uint32_t* __restrict__ max_bits, uint4* __restrict__ Xp,
                                                int blocks /* k-blocks per panel of Xp: k32steps + 1 */) {
   const int lane = threadIdx.x & 63;
-  const int64_t blk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t row0 = blk * 16;
-  if (row0 >= (PACK ? npad : n)) return;
-  const int64_t row_own = row0 + (lane & 15);
-  int64_t at = 0;
-  if (PACK) at = place_of(row_own, lane >> 4);
-  if (PACK && row0 >= n) {  // padding rows only
-    for (int k = 0; k < k32steps; ++k) Xp[packed_index(at, k, blocks)] = make_uint4(0, 0, 0, 0);
-    return;
-  }
-  const bool valid = row_own < n;
-  const int64_t row = valid ? row_own : n - 1;
-  const half8* p = reinterpret_cast<const half8*>(X + row * ld) + (lane >> 4);
-  float4v acc = {0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < k32steps; ++k) {
-    half8 a = p[4 * k];
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, a, acc, 0, 0, 0);
-    if (PACK) Xp[packed_index(at, k, blocks)] = valid ? __builtin_bit_cast(uint4, a) : make_uint4(0, 0, 0, 0);
-  }
-  // element (row, col) of the 16 x 16 block sits in lane col + 16 * (row / 4), register row % 4
-  const int c = lane & 15, g = lane >> 4;
-  uint32_t bits = 0;
-  if ((c >> 2) == g && row0 + c < n) {
-    const int want = c & 3;
-    float v = 0.f;
+  const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * NORM_POINTS;
+  uint32_t most = 0;
+  if (row0 < (PACK ? npad : n)) {
+    const int64_t own[2] = {row0 + (lane & 15), row0 + 16 + (lane & 15)};
+    const half8* p[2];
+    uint4* out[2];
+    bool valid[2];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (r == want) v = acc[r];
-    s[row0 + c] = v;
-    bits = __float_as_uint(v);
-  }
-  if (max_bits) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const uint32_t o = (uint32_t)__shfl_xor((int)bits, off);
-      bits = bits > o ? bits : o;
+    for (int h = 0; h < 2; ++h) {
+      valid[h] = own[h] < n;
+      p[h] = reinterpret_cast<const half8*>(X + (valid[h] ? own[h] : n - 1) * ld) + (lane >> 4);
+      if (PACK) out[h] = Xp + packed_index(place_of(own[h], lane >> 4), 0, blocks);
     }
-    if (lane == 0) atomicMax(max_bits, bits);
+    float4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    auto steps = [&](int k0, auto count_c) {
+      constexpr int K = decltype(count_c)::value;
+      half8 a[2][K];
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) a[h][k] = p[h][4 * (k0 + k)];
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[h][k], a[h][k], acc[h], 0, 0, 0);
+          if (PACK) out[h][(int64_t)(k0 + k) * 1024] = valid[h] ? __builtin_bit_cast(uint4, a[h][k]) : make_uint4(0, 0, 0, 0);
+        }
+    };
+    int k = 0;
+    for (; k + 4 <= k32steps; k += 4) steps(k, std::integral_constant<int, 4>{});
+    for (; k < k32steps; ++k) steps(k, std::integral_constant<int, 1>{});
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      most = max(most, __float_as_uint(store_diagonal(acc[h], row0 + 16 * h, n, s)));
+    }
   }
+  if (max_bits) merge_max(most, max_bits);
 }
 
 // Rows past the end of the data set carry -60000 c in place of -s/2 (at least the largest norm of the
@@ -1232,14 +1262,19 @@ bool carve_static(unsigned char* base, int64_t pad, int64_t dpad, Workspace& w) 
   return true;
 }
 
+// Workgroup size of the norm kernels.  Large sets: eight wavefronts, so that the atomics of the workgroups (11 ns each) take
+// less time than the data; small sets: one, so that they spread over the CUs.
+int norm_threads(int64_t waves) { return waves >= 2048 ? 512 : (waves >= 512 ? 256 : 64); }
+
 // Norms of X into s (and, with Xp given, the packed copy of X); max_bits may be null.
 int launch_norms(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, int64_t ld, float* s, uint32_t* max_bits, uint4* Xp,
                  hipStream_t st) {
   const int64_t npad = pad_rows(n);
-  const int64_t waves = ((Xp ? npad : n) + 15) / 16;
-  const dim3 grid((unsigned)((waves + 3) / 4));
-  if (Xp) hipLaunchKernelGGL(k_norms<true>, grid, dim3(256), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, k_blocks(d) + 1);
-  else hipLaunchKernelGGL(k_norms<false>, grid, dim3(256), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, 0);
+  const int64_t waves = ((Xp ? npad : n) + NORM_POINTS - 1) / NORM_POINTS;
+  const int threads = norm_threads(waves);
+  const dim3 grid((unsigned)((waves * 64 + threads - 1) / threads));
+  if (Xp) hipLaunchKernelGGL(k_norms<true>, grid, dim3(threads), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, k_blocks(d) + 1);
+  else hipLaunchKernelGGL(k_norms<false>, grid, dim3(threads), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, 0);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }

@@ -56,6 +56,22 @@ def test_norms_against_oracle(ej, workload, n):
     assert np.all(np.abs(s - want) <= (d / 16 + 1) * 2.0**-24 * want)
 
 
+@pytest.mark.parametrize("n,d", [(1, 64), (31, 128), (33, 96), (16352, 32), (16385, 64), (65505, 40), (65537, 160)])
+def test_norms_at_the_edges_of_their_workgroup_sizes(ej, n, d):
+    """Partial wavefronts (32 points) and workgroups (1, 4, 8 wavefronts), k-blocks in fours and the rest."""
+    print(f"norms n={n} d={d}", flush=True)
+    rng = np.random.default_rng(n + d)
+    X = pad(rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16), (d + 63) // 64 * 64)
+    s = ej.norms(dev(X), d=d).cpu().numpy().astype(np.float64)
+    want = orc.norms(orc.decode(X))
+    assert np.all(np.abs(s - want) <= (d / 16 + 1) * 2.0**-24 * want)  # (bound as above)
+    # the packed copy and the largest norm of the same pass: every point's duplicate is found at distance 0, last point included
+    Y = X.copy()
+    Y[: n // 2] = Y[n - n // 2:]
+    pairs, d2, found = run_pairs(ej, dev(Y), 0.0, capacity=2 * n + 8, d=d)
+    assert found == n + n // 2 and np.all(d2 == 0.0) and ej.status() == 0
+
+
 # ------------------------------------------------------------------ Steps 2-3: dense tile
 @pytest.mark.parametrize("workload,n,i0,j0,rows,cols", [(1, 600, 0, 0, 600, 600), (3, 500, 37, 250, 301, 199), (4, 400, 390, 5, 10, 33)])
 def test_dist2_tile_against_oracle(ej, workload, n, i0, j0, rows, cols):
