@@ -384,6 +384,18 @@ def test_convert_f32_matches_the_oracle_bit_for_bit(ej):
     parity.check_pair_sets(P, eps, pairs, d2, ora_pairs, ora_d2)
 
 
+@pytest.mark.parametrize("n,d,extra", [(1, 7, 0), (127, 64, 1), (129, 71, 0), (65, 130, 3), (31, 200, 5), (33, 320, 0), (15, 512, 2), (17, 1000, 1)])
+def test_convert_f32_at_every_row_width(ej, n, d, extra):
+    """Rows of 8 to 128 chunks (8 to 64 side by side in a workgroup), ragged last rows and columns, rows that start at any float."""
+    print(f"convert n={n} d={d} extra={extra}", flush=True)
+    rng = np.random.default_rng(d)
+    buf = torch.from_numpy((rng.standard_normal((n, d + extra)) * 40).astype(np.float32)).cuda()
+    c = (rng.standard_normal(d) * 10).astype(np.float32)
+    X32 = buf[:, extra:]
+    got = ej.convert_f32(X32, 0.5, torch.from_numpy(c).cuda()).cpu().numpy().view(np.uint16)
+    assert np.array_equal(got, orc.convert_f32(X32.cpu().numpy(), 0.5, c))
+
+
 def test_centring_and_scaling_recover_accuracy_on_offset_data(ej):
     """Data far from the origin converts badly to FP16 (Section 5): shifted and scaled ingestion brings the
     result set back to that of the FP64 join on the original FP32 data (overlap accuracy, Eq. 3)."""
