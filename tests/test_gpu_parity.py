@@ -567,3 +567,28 @@ def test_candidate_queue_at_every_density(ej, n, share):
     off = two[:, 0] != two[:, 1]
     assert np.array_equal(dense[two[off, 0], two[off, 1]], td2[off])
     assert abs(int((dense[:, : n - 3] <= eps * eps).sum()) - tfound) <= n  # (the two sums of a pair with itself may round apart)
+
+
+# ------------------------------------------------------------------ as many k-blocks as hold a coordinate
+@pytest.mark.parametrize("d", [31, 32, 33, 64, 65, 95, 96, 97, 160, 161, 200])
+def test_odd_numbers_of_slices(ej, d):
+    """Tiles of 2, 3, 4 ... slices, several tiles per workgroup: self-join, two sets, prepared set, all with one arithmetic."""
+    print(f"odd slices d={d}", flush=True)
+    n = 6500
+    rng = np.random.default_rng(d)
+    X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    P = orc.decode(X)
+    eps = orc.select_eps_sample(P[np.sort(rng.choice(n, size=1200, replace=False))], 6, n)
+    ora_pairs, ora_d2 = orc.selfjoin_pairs(P, eps)
+    Xd = dev(pad(X, (d + 63) // 64 * 64))
+    pairs, d2, found = run_pairs(ej, Xd, eps, capacity=ora_pairs.shape[0] * 2 + 1024, d=d)
+    assert found == pairs.shape[0]
+    parity.check_pair_sets(P, eps, pairs, d2, ora_pairs, ora_d2)
+    dense = ej.dist2_tile(Xd, 0, 0, 500, 500, d=d).cpu().numpy()
+    low = (pairs < 500).all(axis=1)
+    assert np.array_equal(dense[pairs[low, 0], pairs[low, 1]], d2[low])
+    s = ej.prepare(Xd, d=d)
+    a, _, at = s.join_count(Xd[:300], float(eps))
+    b, _, bt = ej.join_count(Xd, Xd[:300], float(eps), d=d)
+    assert torch.equal(a, b) and torch.equal(at, bt)
+    s.close()
