@@ -436,60 +436,140 @@ __global__ __launch_bounds__(256) void k_norms_packed(const uint4* __restrict__ 
   if (lane == 0) atomicMax(max_bits, bits);
 }
 
-// Dense block of squared distances with the join's arithmetic: one wavefront per 32 x 32 region, computed
-// the way the join kernel computes a region of its wave tile: four 16 x 16 blocks accumulated with
-// v_mfma_f32_16x16x32_f16, then one v_mfma_f32_32x32x16_f16 on the four blocks' registers side by side that
+// Dense block of squared distances with the join's arithmetic: a workgroup of 2 x 2 wavefronts per TS x TS tile of the block,
+// every 32 x 32 region of it computed the way the join kernel computes a region of its wave tile: four 16 x 16 blocks
+// accumulated with v_mfma_f32_16x16x32_f16, then one v_mfma_f32_32x32x16_f16 on the four blocks' registers side by side that
 // adds -s_i/2 - s_j/2 (operand layout: see the augmentation step of k_join).
-__global__ __launch_bounds__(64) void k_dist2_tile(const uint16_t* __restrict__ X, const uint4* __restrict__ H,
-                                                  const uint32_t* __restrict__ status, int64_t n, int64_t ld, int k32steps,
-                                                  int64_t i0, int64_t j0, int rows, int cols, float* __restrict__ out) {
+// Bound by writing the block and by how the operands reach the CUs: they are read from X as it is (64 coordinates of a row at a
+// time, whole lines), DEPTH slices ahead in registers, and go through two LDS stages in the arrangement of panel_layout.h, with
+// the 16-byte positions permuted further so that the stores too hit all banks (48 us without, for the block below).
+// With one wavefront per 32 x 32 region and its operands straight from memory, 4,000 x 5,000 at d = 384 took 119 us, now 44.
+// TS = 128 needs half the operand traffic of TS = 64, which gives four times the workgroups.  The line lies at three
+// workgroups of the larger kind for two CUs: at 1,280 of them (4,000 x 5,000, d = 384) 58 against 71 us a call, at 384
+// (3,000 x 2,000, d = 960) 48 against 50, at 144 (1,500 x 1,500, d = 384) 26 against 22.  DEPTH: one slice suffices where
+// two workgroups share a CU (TS = 128: 44 us, two slices 45), small blocks are latency and get four.
+template <int TS, int DEPTH>
+__global__ __launch_bounds__(256) void k_dist2_tile(const uint16_t* __restrict__ X, const uint4* __restrict__ H,
+                                                    const uint32_t* __restrict__ status, int64_t n, int64_t ld, int slices,
+                                                    int64_t i0, int64_t j0, int rows, int cols, float* __restrict__ out) {
+  constexpr int W = TS / 2, MT = W / 16;              // wave tile, 16 x 16 blocks along its edge
+  constexpr int LOADS = TS * 8 / 256;                 // 16-byte chunks per thread, operand and slice
+  constexpr int KB_BYTES = TS * 64, OP_BYTES = 2 * KB_BYTES, ST_BYTES = 2 * OP_BYTES;
+  __shared__ __attribute__((aligned(1024))) char lds[2 * ST_BYTES];
   if (*status != ST_OK) return;
-  const int lane = threadIdx.x & 63;
-  const int bi = blockIdx.y * 32, bj = blockIdx.x * 32;
-  const int r16 = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = (wave >> 1) * W, wn = (wave & 1) * W;
+  // workgroup -> tile: a contiguous part of the tiles for every XCD, in bands of eight rows, column by column
+  const uint32_t tr = (uint32_t)(rows + TS - 1) / TS, tc = (uint32_t)(cols + TS - 1) / TS, tiles = tr * tc;
+  const uint32_t t = blockIdx.x % EJ_NUM_XCD * ((tiles + EJ_NUM_XCD - 1) / EJ_NUM_XCD) + blockIdx.x / EJ_NUM_XCD;
+  if (t >= tiles) return;
+  const uint32_t band = t / (EJ_BAND * tc), in_band = t - band * EJ_BAND * tc;
+  const uint32_t h = tr - band * EJ_BAND < EJ_BAND ? tr - band * EJ_BAND : EJ_BAND;
+  const int bi = (int)(band * EJ_BAND + in_band % h) * TS, bj = (int)(in_band / h) * TS;
   auto row_a = [&](int local) { const int64_t r = i0 + bi + local; return r >= n ? n - 1 : r; };
   auto row_b = [&](int local) { const int64_t r = j0 + bj + local; return r >= n ? n - 1 : r; };
-  const half8* pa0 = reinterpret_cast<const half8*>(X + row_a(r16) * ld) + g;
-  const half8* pa1 = reinterpret_cast<const half8*>(X + row_a(16 + r16) * ld) + g;
-  const half8* pb0 = reinterpret_cast<const half8*>(X + row_b(r16) * ld) + g;
-  const half8* pb1 = reinterpret_cast<const half8*>(X + row_b(16 + r16) * ld) + g;
-  float4v acc[2][2];
-  for (int a = 0; a < 2; ++a)
-    for (int c = 0; c < 2; ++c) acc[a][c] = float4v{0.f, 0.f, 0.f, 0.f};
-  for (int k = 0; k < k32steps; ++k) {
-    const half8 a0 = pa0[4 * k], a1 = pa1[4 * k], b0 = pb0[4 * k], b1 = pb1[4 * k];
-    acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b0, acc[0][0], 0, 0, 0);
-    acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b1, acc[0][1], 0, 0, 0);
-    acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, b0, acc[1][0], 0, 0, 0);
-    acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, b1, acc[1][1], 0, 0, 0);
-  }
-  // augmentation operands: H_x = { p1, p2, p3, 0, c, c, c, 0 } (16 bytes): pieces in .x .y, constant in .z .w
-  const int m = lane & 31;
-  uint4 ha, hb;
-  {
-    const int ra = aug_row_point(m), rb = aug_col_point(m);
-    const uint4 h0 = H[row_a(ra)], h1 = H[row_a(ra + 4)];
-    const uint4 q0 = H[row_b(rb)], q1 = H[row_b(rb + 16)];
-    // the four chunks of the operand rows (panel_layout.h, "the augmentation step"), built here from the H rows
-    const uint4 chunks_a[4] = {make_uint4(h0.x, h0.y, h1.x, h1.y), make_uint4(0, 0, 0, 0), make_uint4(h0.z, h0.w, 0, 0), make_uint4(0, 0, h0.z, h0.w)};
-    const uint4 chunks_b[4] = {make_uint4(0, 0, 0, 0), make_uint4(q0.x, q0.y, q1.x, q1.y), make_uint4(q0.z, q0.w, 0, 0), make_uint4(0, 0, q0.z, q0.w)};
-    const int ca = aug_chunk_a(lane), cb = aug_chunk_b(lane);
-    ha = chunks_a[0];
-    hb = chunks_b[1];
+  auto lds_place = [](int row, int chunk, int kb) -> uint32_t {
+    return kb * KB_BYTES + (row ^ (kb << 1)) * 64 + ((chunk ^ swz(row) ^ ((row >> 3) & 2)) << 4);
+  };
+  const half8* ga[LOADS];
+  const half8* gb[LOADS];
+  uint32_t at[LOADS];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (c == ca) ha = chunks_a[c];
-      if (c == cb) hb = chunks_b[c];
+  for (int q = 0; q < LOADS; ++q) {
+    const int r = (tid + 256 * q) >> 3, c = tid & 7;  // eight lanes read a line of X
+    ga[q] = reinterpret_cast<const half8*>(X + row_a(r) * ld) + c;
+    gb[q] = reinterpret_cast<const half8*>(X + row_b(r) * ld) + c;
+    // the panel layout, with what eight lanes store for one row spread over all banks as well
+    const int64_t place = place_of(r, c & 3);
+    at[q] = lds_place((int)(place >> 2), (int)(place & 3) ^ swz((int)(place >> 2)), c >> 2);
+  }
+  half8 ra[DEPTH][LOADS], rb[DEPTH][LOADS];
+  auto load = [&](int slice, int set) {  // (past the last slice: the last one again, never used)
+    const int at_slice = (slice < slices ? slice : slices - 1) * 8;
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) {
+      ra[set][q] = ga[q][at_slice];
+      rb[set][q] = gb[q][at_slice];
+    }
+  };
+  auto store = [&](int slice, int set) {
+    char* st = lds + (slice & 1) * ST_BYTES;
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) {
+      *reinterpret_cast<half8*>(st + at[q]) = ra[set][q];
+      *reinterpret_cast<half8*>(st + OP_BYTES + at[q]) = rb[set][q];
+    }
+  };
+  uint32_t off[2][2];  // (as fragment_offset)
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int f = 0; f < 2; ++f) off[kb][f] = lds_place(lane & 31, 2 * f + (lane >> 5), kb);
+  float4v acc[MT][MT];
+#pragma unroll
+  for (int a = 0; a < MT; ++a)
+#pragma unroll
+    for (int c = 0; c < MT; ++c) acc[a][c] = float4v{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int slice) {
+    const char* st = lds + (slice & 1) * ST_BYTES;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      half8 fa[MT], fb[MT];
+#pragma unroll
+      for (int f = 0; f < MT; ++f) {
+        fa[f] = *reinterpret_cast<const half8*>(st + wm * 64 + (f >> 1) * 2048 + off[kb][f & 1]);
+        fb[f] = *reinterpret_cast<const half8*>(st + OP_BYTES + wn * 64 + (f >> 1) * 2048 + off[kb][f & 1]);
+      }
+#pragma unroll
+      for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int c = 0; c < MT; ++c) acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[a], fb[c], acc[a][c], 0, 0, 0);
+    }
+  };
+  // slice s goes to LDS stage s % 2 and is loaded into register set s % DEPTH
+#pragma unroll
+  for (int u = 0; u < DEPTH; ++u) load(u, u);
+  store(0, 0);
+  load(DEPTH, 0);
+  __syncthreads();
+  for (int s0 = 0; s0 < slices; s0 += DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+      const int s = s0 + u;
+      if (s < slices) {  // (uniform) the stage written here was last read for slice s - 1, before the barrier
+        store(s + 1, (u + 1) % DEPTH);
+        load(s + 1 + DEPTH, (u + 1) % DEPTH);
+        compute(s);
+        __syncthreads();
+      }
     }
   }
-  const float16v res = __builtin_amdgcn_mfma_f32_32x32x16_f16(as_half8(ha), as_half8(hb), cat4(acc[0][0], acc[0][1], acc[1][0], acc[1][1]), 0, 0, 0);
+  const int m = lane & 31;
+  const int ca = aug_chunk_a(lane), cb = aug_chunk_b(lane);
+  // augmentation operands: H_x = { p1, p2, p3, 0, c, c, c, 0 } (16 bytes): pieces in .x .y, constant in .z .w;
+  // the four chunks of the operand rows (panel_layout.h, "the augmentation step") are built here from the H rows
+  half8 ha[MT / 2], hb[MT / 2];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    int pi, pj;
-    region_pair(lane, q, pi, pj);
-    const int rr = bi + pi, cc = bj + pj;
-    if (rr < rows && cc < cols) out[(int64_t)rr * cols + cc] = (i0 + rr == j0 + cc) ? 0.f : fmaxf(-2.f * res[q], 0.f);
+  for (int R = 0; R < MT / 2; ++R) {
+    const int xa = wm + 32 * R + aug_row_point(m), xb = wn + 32 * R + aug_col_point(m);
+    const uint4 h0 = H[row_a(xa)], h1 = H[row_a(xa + 4)], q0 = H[row_b(xb)], q1 = H[row_b(xb + 16)];
+    ha[R] = as_half8(ca == 0 ? make_uint4(h0.x, h0.y, h1.x, h1.y) : (ca == 2 ? make_uint4(h0.z, h0.w, 0, 0) : make_uint4(0, 0, h0.z, h0.w)));
+    hb[R] = as_half8(cb == 1 ? make_uint4(q0.x, q0.y, q1.x, q1.y) : (cb == 2 ? make_uint4(q0.z, q0.w, 0, 0) : make_uint4(0, 0, q0.z, q0.w)));
   }
+#pragma unroll
+  for (int Ra = 0; Ra < MT / 2; ++Ra)
+#pragma unroll
+    for (int Rb = 0; Rb < MT / 2; ++Rb) {
+      const float16v res = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+          ha[Ra], hb[Rb], cat4(acc[2 * Ra][2 * Rb], acc[2 * Ra][2 * Rb + 1], acc[2 * Ra + 1][2 * Rb], acc[2 * Ra + 1][2 * Rb + 1]), 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        int pi, pj;
+        region_pair(lane, q, pi, pj);
+        const int rr = bi + wm + 32 * Ra + pi, cc = bj + wn + 32 * Rb + pj;
+        if (rr < rows && cc < cols) out[(int64_t)rr * cols + cc] = (i0 + rr == j0 + cc) ? 0.f : fmaxf(-2.f * res[q], 0.f);
+      }
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1845,7 +1925,12 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   EJ_RC(begin_call(ctx, w, true, st));  // (no join kernel follows: the status block stays marked for a reset)
   EJ_RC(launch_norms(ctx, X, n, d, ld, w.s, w.status + 1, nullptr, st));
   EJ_RC(launch_aux(ctx, w.status, w.s, n, w.H, nullptr, 0, nullptr, nullptr, st));
-  hipLaunchKernelGGL(k_dist2_tile, dim3((cols + 31) / 32, (rows + 31) / 32), dim3(64), 0, st, X, w.H, w.status, n, ld, k_blocks(d), i0, j0, rows, cols, out);
+  const int slices = (k_blocks(d) + 1) / 2;  // (rows are padded to a multiple of 64 coordinates)
+  auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
+  if (2 * blocks(128) >= 3 * ctx->num_cu)  // (see the kernel)
+    hipLaunchKernelGGL((k_dist2_tile<128, 1>), dim3((unsigned)blocks(128)), dim3(256), 0, st, X, w.H, w.status, n, ld, slices, i0, j0, rows, cols, out);
+  else
+    hipLaunchKernelGGL((k_dist2_tile<64, 4>), dim3((unsigned)blocks(64)), dim3(256), 0, st, X, w.H, w.status, n, ld, slices, i0, j0, rows, cols, out);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }

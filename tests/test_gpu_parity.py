@@ -108,6 +108,28 @@ def test_selfjoin_pairs_against_oracle(ej, workload, n, S):
     assert abs(st["dist_err_mean"]) < 1e-4
 
 
+@pytest.mark.parametrize("d,rows,cols", [(40, 1100, 6000), (128, 2049, 3011), (200, 6300, 1025)])
+def test_dist2_tile_sizes_agree_bit_for_bit(ej, d, rows, cols):
+    """Large blocks are computed in tiles of 128, small ones in tiles of 64: a large block at any offset (crossing the diagonal)
+    against the oracle, and its parts, asked for one by one, against it bit for bit."""
+    print(f"dist2_tile sizes d={d} {rows}x{cols}", flush=True)
+    n = 7001
+    rng = np.random.default_rng(d)
+    X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    Xd = dev(pad(X, (d + 63) // 64 * 64))
+    i0, j0 = 17, n - cols
+    got = ej.dist2_tile(Xd, i0, j0, rows, cols, d=d)
+    for r, c, h, w in [(0, 0, 1, 1), (rows - 65, cols - 63, 65, 63), (127, 129, 130, 64), (rows // 2, 5, 33, 700)]:
+        assert torch.equal(ej.dist2_tile(Xd, i0 + r, j0 + c, h, w, d=d), got[r:r + h, c:c + w])
+    P = orc.decode(X)
+    s = orc.norms(P)
+    take = np.sort(rng.choice(rows, size=60, replace=False))
+    for r in take:
+        want = orc.dist2_block(P, i0 + int(r), 1, j0, cols)
+        tol = parity.value_tolerance(want, s[i0 + r] + s[None, j0:j0 + cols], s.max())
+        assert np.all(np.abs(got[int(r)].cpu().numpy().astype(np.float64) - want[0]) <= tol[0])
+
+
 def test_join_dist2_is_bit_identical_to_dense_tile(ej):
     X, P, eps = small_case(2, 1500, 40)
     Xd = dev(X)
