@@ -37,6 +37,10 @@ constexpr int KSLICE = 32;    // coordinates per LDS stage (64 B per row)
 // same results.  EJOIN_ABL_NSTAGE=3 (one LDS stage less), EJOIN_ABL_NOSWIZZLE (plain LDS rows),
 // EJOIN_ABL_ROWMAJOR_TILES (tiles dealt round-robin in row-major order), EJOIN_ABL_NOALIGN (workgroups of
 // an XCD never re-aligned), EJOIN_ABL_NOPREFILTER (every block goes through the exact path).
+#if defined(EJOIN_ABL_NSTAGE) || defined(EJOIN_ABL_NOSWIZZLE) || defined(EJOIN_ABL_ROWMAJOR_TILES) || defined(EJOIN_ABL_NOALIGN) || \
+    defined(EJOIN_ABL_NOPREFILTER) || defined(EJOIN_EXP_HOT_PANELS) || defined(EJOIN_EXP_NO_COPIES) || defined(EJOIN_EXP_CYCLE_MARKS)
+#define EJOIN_ONLY_K_JOIN  // these builds are about k_join: problems of every size go to it
+#endif
 #ifndef EJOIN_ABL_NSTAGE
 #define EJOIN_ABL_NSTAGE 4
 #endif
@@ -133,18 +137,20 @@ __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
   if (i < n) p[i] = v;
 }
 
-// The largest of the wavefronts' values of a workgroup, added to *max_bits with one atomic: those on one address are served
-// one after the other, about 11 ns each.
-__device__ __forceinline__ void merge_max(uint32_t bits, uint32_t* max_bits) {
+// The largest of the values of a workgroup's lanes (the same for all of them).
+__device__ __forceinline__ uint32_t max_of_group(uint32_t bits) {
   __shared__ uint32_t wave_max[8];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, off));
   if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = bits;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    for (uint32_t w = 1; w < blockDim.x / 64; ++w) bits = max(bits, wave_max[w]);
-    atomicMax(max_bits, bits);
-  }
+  for (uint32_t w = 0; w < blockDim.x / 64; ++w) bits = max(bits, wave_max[w]);
+  return bits;
+}
+// ... and added to *max_bits with one atomic: those on one address are served one after the other, about 11 ns each.
+__device__ __forceinline__ void merge_max(uint32_t bits, uint32_t* max_bits) {
+  bits = max_of_group(bits);
+  if (threadIdx.x == 0) atomicMax(max_bits, bits);
 }
 
 // Diagonal of the 16 x 16 Gram block of points row0 .. row0 + 15, whose element (row, col) sits in lane col + 16 * (row / 4),
@@ -178,48 +184,52 @@ __device__ __forceinline__ float store_diagonal(const float4v& acc, int64_t row0
 // 16 points per wavefront and one atomic each it ran at 0.7 TB/s on 10^6 x 128 (725 us with k_aux, now 94 + 12: 5.4 TB/s) and
 // at 1.9 TB/s on 3 10^5 x 384 (244 us, now 86).
 constexpr int NORM_POINTS = 32;  // points per wavefront
+template <bool PACK>  // returns the pattern of this lane's largest norm
+__device__ __forceinline__ uint32_t norms_of_wave(int64_t row0, const uint16_t* __restrict__ X, int64_t n, int64_t ld, int k32steps,
+                                                  float* __restrict__ s, uint4* __restrict__ Xp, int blocks) {
+  const int lane = threadIdx.x & 63;
+  const int64_t own[2] = {row0 + (lane & 15), row0 + 16 + (lane & 15)};
+  const half8* p[2];
+  uint4* out[2];
+  bool valid[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    valid[h] = own[h] < n;
+    p[h] = reinterpret_cast<const half8*>(X + (valid[h] ? own[h] : n - 1) * ld) + (lane >> 4);
+    if (PACK) out[h] = Xp + packed_index(place_of(own[h], lane >> 4), 0, blocks);
+  }
+  float4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  auto steps = [&](int k0, auto count_c) {
+    constexpr int K = decltype(count_c)::value;
+    half8 a[2][K];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) a[h][k] = p[h][4 * (k0 + k)];
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[h][k], a[h][k], acc[h], 0, 0, 0);
+        if (PACK) out[h][(int64_t)(k0 + k) * 1024] = valid[h] ? __builtin_bit_cast(uint4, a[h][k]) : make_uint4(0, 0, 0, 0);
+      }
+  };
+  int k = 0;
+  for (; k + 4 <= k32steps; k += 4) steps(k, std::integral_constant<int, 4>{});
+  for (; k < k32steps; ++k) steps(k, std::integral_constant<int, 1>{});
+  uint32_t most = 0;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) most = max(most, __float_as_uint(store_diagonal(acc[h], row0 + 16 * h, n, s)));
+  return most;
+}
+
 template <bool PACK>
 __global__ __launch_bounds__(512) void k_norms(const uint16_t* __restrict__ X, int64_t n, int64_t npad, int64_t ld, int k32steps,
                                                float* __restrict__ s, uint32_t* __restrict__ max_bits, uint4* __restrict__ Xp,
                                                int blocks /* k-blocks per panel of Xp: k32steps + 1 */) {
-  const int lane = threadIdx.x & 63;
   const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * NORM_POINTS;
   uint32_t most = 0;
-  if (row0 < (PACK ? npad : n)) {
-    const int64_t own[2] = {row0 + (lane & 15), row0 + 16 + (lane & 15)};
-    const half8* p[2];
-    uint4* out[2];
-    bool valid[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      valid[h] = own[h] < n;
-      p[h] = reinterpret_cast<const half8*>(X + (valid[h] ? own[h] : n - 1) * ld) + (lane >> 4);
-      if (PACK) out[h] = Xp + packed_index(place_of(own[h], lane >> 4), 0, blocks);
-    }
-    float4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-    auto steps = [&](int k0, auto count_c) {
-      constexpr int K = decltype(count_c)::value;
-      half8 a[2][K];
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) a[h][k] = p[h][4 * (k0 + k)];
-#pragma unroll
-      for (int k = 0; k < K; ++k)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[h][k], a[h][k], acc[h], 0, 0, 0);
-          if (PACK) out[h][(int64_t)(k0 + k) * 1024] = valid[h] ? __builtin_bit_cast(uint4, a[h][k]) : make_uint4(0, 0, 0, 0);
-        }
-    };
-    int k = 0;
-    for (; k + 4 <= k32steps; k += 4) steps(k, std::integral_constant<int, 4>{});
-    for (; k < k32steps; ++k) steps(k, std::integral_constant<int, 1>{});
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      most = max(most, __float_as_uint(store_diagonal(acc[h], row0 + 16 * h, n, s)));
-    }
-  }
+  if (row0 < (PACK ? npad : n)) most = norms_of_wave<PACK>(row0, X, n, ld, k32steps, s, Xp, blocks);
   if (max_bits) merge_max(most, max_bits);
 }
 
@@ -248,6 +258,35 @@ constexpr uint32_t P1_OUT_OF_RANGE = 0xFB53u;  // -60000 in FP16
 // The kernel also clears what the join kernel expects to find zero (the join kernel of the call before has
 // finished by now): the XCD alignment counters, the call's result counter `counter` and, in count mode,
 // the per-point counts `counts` (n entries; may be null).
+struct NormScale {
+  uint32_t st;  // status of the data
+  int m;        // (only if st is OK)
+  _Float16 c;
+};
+__device__ __forceinline__ uint32_t fp16_bits(_Float16 x) { return (uint32_t)__builtin_bit_cast(uint16_t, x); }
+__device__ __forceinline__ NormScale norm_scale(uint32_t max_bits) {
+  NormScale r;
+  r.m = 0;
+  r.st = ST_OK;
+  if (max_bits >= 0x7f800000u) r.st = ST_NONFINITE;  // Inf or NaN among the norms
+  else {
+    const int e = (int)(max_bits >> 23) - 127;  // max s < 2^(e+1)
+    r.m = e - 15 < -14 ? -14 : e - 15;
+    if (r.m > 15) r.st = ST_NORM_RANGE;  // 2^m must be an FP16 value: needs max s < 2^31
+  }
+  r.c = (_Float16)ldexpf(1.f, r.m > 15 ? 15 : r.m);
+  return r;
+}
+// The pieces of the point of norm s (or, where it lies past the end, the marker) as two 32-bit words { p1 | p2 << 16, p3 }.
+__device__ __forceinline__ uint2 norm_pieces(float s, int m) {
+  const float v = ldexpf(-0.5f * s, -m);
+  const _Float16 p1 = (_Float16)v;
+  const float r1 = v - (float)p1;
+  const _Float16 p2 = (_Float16)r1;
+  const _Float16 p3 = (_Float16)(r1 - (float)p2);
+  return make_uint2(fp16_bits(p1) | (fp16_bits(p2) << 16), fp16_bits(p3));
+}
+
 __global__ void k_aux(const float* __restrict__ s, int64_t n, int64_t npad, uint32_t* __restrict__ status_and_max,
                       uint4* __restrict__ H, uint4* __restrict__ Xp, int aug_kb, int blocks,
                       unsigned long long* __restrict__ counter, uint32_t* __restrict__ counts) {
@@ -258,34 +297,20 @@ __global__ void k_aux(const float* __restrict__ s, int64_t n, int64_t npad, uint
     if (threadIdx.x == 8 && counter) *counter = 0;
   }
   if (counts && i < n) counts[i] = 0;
-  int m = 0;
-  uint32_t st = ST_OK;
-  if (mb >= 0x7f800000u) st = ST_NONFINITE;  // Inf or NaN among the norms
-  else {
-    const int e = (int)(mb >> 23) - 127;  // max s < 2^(e+1)
-    m = e - 15 < -14 ? -14 : e - 15;
-    if (m > 15) st = ST_NORM_RANGE;  // 2^m must be an FP16 value: needs max s < 2^31
-  }
-  const _Float16 c = (_Float16)ldexpf(1.f, m > 15 ? 15 : m);
-  auto bits = [](_Float16 x) { return (uint32_t)__builtin_bit_cast(uint16_t, x); };
+  const NormScale ns = norm_scale(mb);
+  const uint32_t st = ns.st, c = fp16_bits(ns.c);
   if (i == 0) {
     status_and_max[0] = st;
-    status_and_max[2] = bits(c) | (bits(c) << 16);
-    status_and_max[3] = bits(c);
+    status_and_max[2] = c | (c << 16);
+    status_and_max[3] = c;
   }
   if (i >= npad) return;
-  // the pieces of point x as two 32-bit words { p1 | p2 << 16, p3 }
   auto pieces = [&](int64_t x) -> uint2 {
     if (x >= n) return make_uint2(P1_OUT_OF_RANGE, 0u);
     if (st != ST_OK) return make_uint2(0u, 0u);
-    const float v = ldexpf(-0.5f * s[x], -m);
-    const _Float16 p1 = (_Float16)v;
-    const float r1 = v - (float)p1;
-    const _Float16 p2 = (_Float16)r1;
-    const _Float16 p3 = (_Float16)(r1 - (float)p2);
-    return make_uint2(bits(p1) | (bits(p2) << 16), bits(p3));
+    return norm_pieces(s[x], ns.m);
   };
-  const uint2 cc = (i >= n || st == ST_OK) ? make_uint2(bits(c) | (bits(c) << 16), bits(c)) : make_uint2(0u, 0u);
+  const uint2 cc = (i >= n || st == ST_OK) ? make_uint2(c | (c << 16), c) : make_uint2(0u, 0u);
   const uint2 own = pieces(i);
   H[i] = make_uint4(own.x, own.y, cc.x, cc.y);
   if (Xp) {
@@ -1222,6 +1247,331 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
 }
 
 
+
+// ------------------------------------------------------------------------------------------
+// The join of small problems
+// ------------------------------------------------------------------------------------------
+// Two launches instead of three: k_prep (norms and packed copies of both sets, in one launch, and everything the call needs
+// zero) and k_join_small, which works out the operands of the augmentation step from the norms by itself.  The largest norm
+// passes from one to the other as one value per workgroup of k_prep: nothing has to be zero before or after.
+struct PrepSet {
+  const uint16_t* X;  // null: a set prepared before
+  int64_t n, npad, ld;
+  float* s;
+  uint4* Xp;
+  uint32_t groups;  // workgroups that work on it
+};
+struct PrepArgs {
+  PrepSet a, b;
+  int k32steps;
+  uint32_t* maxima;  // one per workgroup
+  unsigned long long* counter;
+  uint32_t* counts;  // count mode: cleared (may be null)
+  int64_t ncounts;
+  uint32_t* counts_b;
+  int64_t ncounts_b;
+};
+__global__ __launch_bounds__(512) void k_prep(const PrepArgs a) {
+  const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, all = (int64_t)gridDim.x * blockDim.x;
+  if (at == 0) *a.counter = 0;
+  if (a.counts)
+    for (int64_t i = at; i < a.ncounts; i += all) a.counts[i] = 0;
+  if (a.counts_b)
+    for (int64_t i = at; i < a.ncounts_b; i += all) a.counts_b[i] = 0;
+  const bool second = blockIdx.x >= a.a.groups;
+  const PrepSet& set = second ? a.b : a.a;
+  const int64_t row0 = ((int64_t)(blockIdx.x - (second ? a.a.groups : 0u)) * (blockDim.x >> 6) + (threadIdx.x >> 6)) * NORM_POINTS;
+  uint32_t most = 0;
+  if (row0 < set.npad) most = norms_of_wave<true>(row0, set.X, set.n, set.ld, a.k32steps, set.s, set.Xp, a.k32steps + 1);
+  most = max_of_group(most);
+  if (threadIdx.x == 0 && blockIdx.x < a.a.groups + a.b.groups) a.maxima[blockIdx.x] = most;  // (the others only clear counts)
+}
+
+struct SmallArgs {
+  JoinArgs j;  // (ntilesA, ntilesB in tiles of TS)
+  const float* sA;
+  const float* sB;
+  const uint32_t* maxima;
+  uint32_t nmaxima;
+  const uint32_t* set_max;  // largest norm of a prepared set, or null
+};
+
+// Tiles of TS x TS points, a workgroup of 2 x 2 wavefronts each (wave tile TS/2 x TS/2), several workgroups to a CU, which
+// hide each other's latencies: no copying wavefronts, no augmentation copies, no alignment.  The arithmetic is k_join's, step
+// by step (16 x 16 blocks over k in ascending order, one augmentation step per 32 x 32 region), and so are the results, bit
+// for bit.  Count mode adds up a tile's counts in the LDS and sends one atomic per row and column: the small problems are the
+// dense ones, hits per tile grow as 1/n.
+//
+// Workgroups on a CU and LDS stages: at TS = 128 three workgroups with two stages each (136 registers, 48 KB), not two with
+// three: 768 tiles at a time instead of 512 (4,096 points, d = 128: 17.9 against 23.9 us a call; up to 512 tiles the deeper
+// pipeline would be 5 to 10 % faster at d = 960).  Four workgroups leave the staging too small (10,000 points, d = 384, 64
+// neighbours: join 98 against 64 us).
+template <int TS>
+constexpr int small_stages() { return TS == 64 ? 3 : 2; }
+template <int TS>
+constexpr int small_groups_per_cu() { return TS == 64 ? 4 : 3; }
+constexpr int SMALL_STG_CAP = 256;
+template <bool COUNT, int TS>
+constexpr int small_lds_bytes() {
+  return small_stages<TS>() * 2 * TS * 64 + 2 * TS * 16 + 64 + (COUNT ? 2 * TS * 4 : 4 * SMALL_STG_CAP * 12) + 64;
+}
+template <bool COUNT, int TS>
+__global__ __launch_bounds__(256, small_groups_per_cu<TS>()) void k_join_small(const SmallArgs args) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  constexpr int W = TS / 2, MT = W / 16, NR = W / 32;
+  constexpr int OP_BYTES = TS * 64, ST_BYTES = 2 * OP_BYTES;
+  constexpr int COPIES = TS / 64;  // copy instructions per wavefront, operand and slice
+  constexpr int STAGES = small_stages<TS>();
+  constexpr int AUG = STAGES * ST_BYTES, AUG_B = AUG + TS * 16, AUG_CONST = AUG_B + TS * 16;
+  constexpr int TAIL = AUG_CONST + 64;                                     // staging (pairs) or counters (counts)
+  constexpr int SUMS = TAIL + (COUNT ? 2 * TS * 4 : 4 * SMALL_STG_CAP * 12);  // 64 bytes
+  const JoinArgs& a = args.j;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave >> 1) * W, wn = (wave & 1) * W;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int nsl = a.nslices;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+  TileCursor tc;
+  tc.init(blockIdx.x, gridDim.x, (uint32_t)a.self, a.ntilesA, a.ntilesB);
+  uint32_t I = 0, J = 0;
+  bool have = tc.next(I, J);
+  if (!have) return;
+  const int64_t panel_stride = (int64_t)(nsl + 1) * PANEL_BYTES;
+  const uint32_t voff = lane * 16 + wave * 1024;
+  const char *pa = nullptr, *pb = nullptr;
+  auto uniform_ptr = [](const char* p) -> const char* {
+    const uint64_t b = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+  };
+  auto issue = [&](int ks, int stage) {  // slice ks of the tile at (pa, pb)
+    const char* ga = uniform_ptr(pa + (int64_t)ks * PANEL_BYTES);
+    const char* gb = uniform_ptr(pb + (int64_t)ks * PANEL_BYTES);
+    const uint32_t at = __builtin_amdgcn_readfirstlane(lds0 + stage * ST_BYTES + wave * 1024);
+    copy16_to_lds<0>(at, ga, voff);
+    if constexpr (COPIES == 2) copy16_to_lds<4096>(at, ga, voff + 4096);
+    copy16_to_lds<OP_BYTES>(at, gb, voff);
+    if constexpr (COPIES == 2) copy16_to_lds<OP_BYTES + 4096>(at, gb, voff + 4096);
+  };
+  auto start_tile = [&]() {
+    pa = reinterpret_cast<const char*>(a.XpA) + (int64_t)(I * TS / TILE) * panel_stride + (I * TS % TILE) * 64;
+    pb = reinterpret_cast<const char*>(a.XpB) + (int64_t)(J * TS / TILE) * panel_stride + (J * TS % TILE) * 64;
+#pragma unroll
+    for (int ks = 0; ks < STAGES - 1; ++ks) issue(ks, ks);
+  };
+  start_tile();
+  uint32_t mb = args.set_max ? *args.set_max : 0u;
+  for (uint32_t q = tid; q < args.nmaxima; q += 256) mb = max(mb, args.maxima[q]);
+  const NormScale ns = norm_scale(max_of_group(mb));
+  if (blockIdx.x == 0 && tid == 0) a.status[0] = ns.st;
+  if (ns.st != ST_OK) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the copies must land before the wave ends
+    return;
+  }
+  if (tid < 4) {  // the constant chunks of the augmentation step (2 and 3)
+    const uint32_t c = fp16_bits(ns.c), c0 = c | (c << 16);
+    *reinterpret_cast<uint2*>(lds + AUG_CONST + tid * 8) = tid == 0 || tid == 3 ? make_uint2(c0, c) : make_uint2(0u, 0u);
+  }
+  uint32_t* cnt = reinterpret_cast<uint32_t*>(lds + TAIL);
+  if (COUNT && tid < 2 * TS) cnt[tid] = 0;
+  uint32_t* stg = reinterpret_cast<uint32_t*>(lds + TAIL + wave * (SMALL_STG_CAP * 12));
+  uint32_t fill = 0;     // (pairs) entries staged, wave-uniform
+  uint32_t hits = 0;     // (counts) of this lane
+  bool dirty = false;
+  auto store_staged = [&](unsigned long long base) {
+    for (uint32_t e = lane; e < fill; e += 64) {
+      const unsigned long long idx = base + e;
+      if (idx < a.capacity) {
+        reinterpret_cast<uint2*>(a.pairs)[idx] = make_uint2(stg[3 * e], stg[3 * e + 1]);
+        if (a.dist2) a.dist2[idx] = __uint_as_float(stg[3 * e + 2]);
+      }
+    }
+  };
+  auto append = [&](unsigned long long mask, bool pass, uint32_t i, uint32_t j, uint32_t d2_bits) {
+    const uint32_t more = __popcll(mask);
+    if (fill + more > SMALL_STG_CAP) {
+      unsigned long long base = 0;
+      if (lane == 0) base = atomicAdd(a.n_pairs, (unsigned long long)fill);
+      const uint32_t blo = __builtin_amdgcn_readfirstlane((uint32_t)base), bhi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+      store_staged(((unsigned long long)bhi << 32) | blo);
+      fill = 0;
+      dirty = true;
+    }
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    if (pass) {
+      const uint32_t e = fill + rank;
+      stg[3 * e] = i;
+      stg[3 * e + 1] = j;
+      stg[3 * e + 2] = d2_bits;
+    }
+    fill += more;
+  };
+  // fragment and augmentation operand addresses (see k_join)
+  const uint32_t frag0 = fragment_offset(lane, 0), frag1 = fragment_offset(lane, 1);
+  const int ca = aug_chunk_a(lane), cb = aug_chunk_b(lane);
+  const char* aug_a = lds + (ca == 0 ? AUG + 16 * (wm + (lane & 31)) : AUG_CONST + 16 * (ca - 2));
+  const char* aug_b = lds + (cb == 1 ? AUG_B + 16 * (wn + (lane & 31)) : AUG_CONST + 16 * (cb - 2));
+  const int step_a = ca == 0 ? 512 : 0, step_b = cb == 1 ? 512 : 0;
+  const uint32_t nnA = (uint32_t)a.nA, nnB = (uint32_t)a.nB;
+
+  while (have) {
+    // ---- operands of the augmentation step: thread t row t of the tile's A panel, then of its B panel (panel_layout.h)
+    if (tid < 2 * TS) {
+      const bool col = tid >= TS;
+      const int row = tid & (TS - 1), in = row & 31;
+      const uint32_t x = (col ? J : I) * TS + (row & ~31) + (col ? aug_col_point(in) : aug_row_point(in));
+      const uint32_t y = x + (col ? 16u : 4u), nn = col ? nnB : nnA;
+      const float* s = col ? args.sB : args.sA;
+      uint2 p = make_uint2(P1_OUT_OF_RANGE, 0u), q = p;
+      if (x < nn) p = norm_pieces(s[x], ns.m);
+      if (y < nn) q = norm_pieces(s[y], ns.m);
+      *reinterpret_cast<uint4*>(lds + (col ? AUG_B : AUG) + row * 16) = make_uint4(p.x, p.y, q.x, q.y);
+    }
+    // ---- the slices: two ahead in flight
+    float4v acc[MT][MT];
+#pragma unroll
+    for (int x = 0; x < MT; ++x)
+#pragma unroll
+      for (int y = 0; y < MT; ++y) acc[x][y] = float4v{0.f, 0.f, 0.f, 0.f};
+    int stage = 0;
+    for (int ks = 0; ks < nsl; ++ks) {
+      // this wavefront's copies of slice ks have landed once only those of slice ks + 1 are outstanding; what else it has
+      // written to the LDS must be there for the others too
+      if (STAGES == 3 && ks + 1 < nsl) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * COPIES) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+      wg_barrier();  // slice ks is there for everybody, and everybody is done with slice ks - 1
+      if (ks + STAGES - 1 < nsl) issue(ks + STAGES - 1, stage == 0 ? STAGES - 1 : stage - 1);
+      const char* st = lds + stage * ST_BYTES;
+      half8 fa[MT], fb[MT];
+#pragma unroll
+      for (int f = 0; f < MT; ++f) {
+        fa[f] = *reinterpret_cast<const half8*>(st + wm * 64 + (f >> 1) * 2048 + ((f & 1) ? frag1 : frag0));
+        fb[f] = *reinterpret_cast<const half8*>(st + OP_BYTES + wn * 64 + (f >> 1) * 2048 + ((f & 1) ? frag1 : frag0));
+      }
+#pragma unroll
+      for (int y = 0; y < MT; ++y)
+#pragma unroll
+        for (int u = 0; u < MT; ++u) {
+          const int x = (y & 1) ? MT - 1 - u : u;
+          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[x], fb[y], acc[x][y], 0, 0, 0);
+        }
+      stage = stage == STAGES - 1 ? 0 : stage + 1;
+    }
+    half8 ha[NR], hb[NR];
+#pragma unroll
+    for (int t = 0; t < NR; ++t) {
+      ha[t] = *reinterpret_cast<const half8*>(aug_a + t * step_a);
+      hb[t] = *reinterpret_cast<const half8*>(aug_b + t * step_b);
+    }
+    const uint32_t i_tile = I * TS, j_tile = J * TS;
+    const bool diag = a.self && I == J;
+    have = tc.next(I, J);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    wg_barrier();  // everybody has read the last slice and the augmentation operands
+    if (have) start_tile();
+    // ---- filter and rare path
+    const bool partial = diag || i_tile + TS > nnA || j_tile + TS > nnB;
+    if (diag && !COUNT && wave < TS / 64) {  // (i, i) belongs to the result by definition
+      const uint32_t i = i_tile + tid;
+      append(__ballot(i < nnA), i < nnA, i, i, 0u);
+    }
+#pragma unroll
+    for (int Ra = 0; Ra < NR; ++Ra)
+#pragma unroll
+      for (int Rb = 0; Rb < NR; ++Rb) {
+        const float16v v = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+            ha[Ra], hb[Rb], cat4(acc[2 * Ra][2 * Rb], acc[2 * Ra][2 * Rb + 1], acc[2 * Ra + 1][2 * Rb], acc[2 * Ra + 1][2 * Rb + 1]), 0, 0, 0);
+        // bit r of hit: register r of this lane passes
+        uint32_t hit = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) hit |= v[r] >= a.thr ? 1u << r : 0u;
+        if (__ballot(hit != 0) == 0) continue;
+        const uint32_t il = wm + 32 * Ra + 4 * g, jl = wn + 32 * Rb + r16;  // register 0's place in the tile (region_pair)
+        if (partial) {
+          uint32_t keep = 0;
+#pragma unroll 1
+          for (int r = 15; r >= 0; --r) {
+            const uint32_t i = i_tile + il + 16 * (r >> 3) + (r & 3), j = j_tile + jl + 16 * ((r >> 2) & 1);
+            keep = 2 * keep + (i < nnA && j < nnB && (!diag || i < j) ? 1u : 0u);
+          }
+          hit &= keep;
+        }
+        if constexpr (COUNT) {
+          hits += __popc(hit);
+          // columns 16 c + l % 16: registers with bit 2 equal to c; rows 16 a + 4 g + r % 4: two registers each
+          const uint32_t c0 = __popc(hit & 0x0F0Fu), c1 = __popc(hit & 0xF0F0u);
+          if (c0) atomicAdd(cnt + TS + jl, c0);
+          if (c1) atomicAdd(cnt + TS + jl + 16, c1);
+          uint32_t rows = (hit | (hit >> 4)) & 0x0F0Fu;
+          while (__ballot(rows != 0)) {
+            if (rows) {
+              const uint32_t r = (uint32_t)__builtin_ctz(rows);
+              atomicAdd(cnt + il + 2 * (r & 8u) + (r & 3u), ((hit >> r) & 1u) + ((hit >> (r + 4)) & 1u));
+              rows &= rows - 1;
+            }
+          }
+        } else {
+          // every round takes one hit of each lane that has any left
+          for (unsigned long long mask = __ballot(hit != 0); mask; mask = __ballot(hit != 0)) {
+            const uint32_t r = (uint32_t)__builtin_ctz(hit | 0x10000u);
+            const bool b0 = r & 1u, b1 = r & 2u, b2 = r & 4u, b3 = r & 8u;
+            auto four = [&](float w, float x, float y, float z) {
+              const float lo = b0 ? x : w, hi = b0 ? z : y;
+              return b1 ? hi : lo;
+            };
+            const float q0 = four(v[0], v[1], v[2], v[3]), q1 = four(v[4], v[5], v[6], v[7]);
+            const float q2 = four(v[8], v[9], v[10], v[11]), q3 = four(v[12], v[13], v[14], v[15]);
+            const float lo = b2 ? q1 : q0, hi = b2 ? q3 : q2;
+            append(mask, hit != 0, i_tile + il + 2 * (r & 8u) + (r & 3u), j_tile + jl + 4 * (r & 4u),
+                   __float_as_uint(fmaxf(-2.f * (b3 ? hi : lo), 0.f)));
+            hit &= hit - 1;
+          }
+        }
+      }
+    if constexpr (COUNT) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      wg_barrier();
+      if (tid < 2 * TS) {
+        const uint32_t v = cnt[tid];
+        if (v) {
+          cnt[tid] = 0;
+          uint32_t* to = tid < TS ? a.counts : (a.self ? a.counts : a.counts_b);
+          if (to) atomicAdd(to + (tid < TS ? i_tile + tid : j_tile + (tid - TS)), v);
+        }
+      }
+      dirty = true;
+    }
+    // (stores and atomics count on vmcnt like the copies, but complete in any order)
+    if (dirty) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      dirty = false;
+    }
+  }
+  // ---- what is left, with one atomic for the workgroup (see k_join)
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(lds + SUMS);
+  if constexpr (COUNT) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) hits += (uint32_t)__shfl_xor((int)hits, off);
+  }
+  if (lane == 0) sums[wave] = COUNT ? hits : fill;
+  __syncthreads();
+  if (tid == 0) {
+    unsigned long long total = 0;
+    for (int w = 0; w < 4; ++w) {
+      const unsigned long long v = sums[w];
+      sums[w] = total;
+      total += v;
+    }
+    if (COUNT && total) atomicAdd(a.total, total);
+    if (!COUNT) sums[4] = total ? atomicAdd(a.n_pairs, total) : 0ull;
+  }
+  if (!COUNT) {
+    __syncthreads();
+    store_staged(sums[4] + sums[wave]);
+  }
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------------------------------
@@ -1450,10 +1800,8 @@ int begin_call(ejoin_ctx* ctx, const Workspace& w, bool own, hipStream_t st) {
   return EJOIN_OK;
 }
 
-// The join kernel on two packed operand sets whose augmentation blocks are in place.
-template <bool COUNT>
-int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, const Operand& B, bool self, int nslices, float eps,
-                const Results& r, hipStream_t st, uint32_t sb_row_begin = 0, uint32_t sb_row_end = 0xFFFFFFFFu) {
+// What the join kernels of every size take.
+JoinArgs join_args(const Workspace& w, const Operand& A, const Operand& B, bool self, int nslices, float eps, const Results& r, int tile) {
   JoinArgs a;
   memset(&a, 0, sizeof(a));
   a.XpA = A.Xp;
@@ -1464,10 +1812,9 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
   a.status = w.status;
   a.nslices = nslices;
   a.thr = -0.5f * (eps * eps);
-  a.ntilesA = (uint32_t)(A.pad / TILE);
-  a.ntilesB = (uint32_t)(B.pad / TILE);
-  a.sb_row_begin = sb_row_begin;
-  a.sb_row_end = sb_row_end;
+  a.ntilesA = (uint32_t)((A.n + tile - 1) / tile);
+  a.ntilesB = (uint32_t)((B.n + tile - 1) / tile);
+  a.sb_row_end = 0xFFFFFFFFu;
   a.pairs = r.pairs;
   a.dist2 = r.dist2;
   a.capacity = r.capacity;
@@ -1475,6 +1822,16 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
   a.counts = r.counts;
   a.counts_b = r.counts_b;
   a.total = reinterpret_cast<unsigned long long*>(r.total);
+  return a;
+}
+
+// The join kernel on two packed operand sets whose augmentation blocks are in place.
+template <bool COUNT>
+int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, const Operand& B, bool self, int nslices, float eps,
+                const Results& r, hipStream_t st, uint32_t sb_row_begin = 0, uint32_t sb_row_end = 0xFFFFFFFFu) {
+  JoinArgs a = join_args(w, A, B, self, nslices, eps, r, TILE);
+  a.sb_row_begin = sb_row_begin;
+  a.sb_row_end = sb_row_end;
   a.xcd_bar = w.status + 8;
   {
     // re-align the workgroups of each XCD every few hundred microseconds: about 512 slices
@@ -1500,6 +1857,86 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
   return EJOIN_OK;
 }
 
+// Which tile k_join_small should work a problem in, or 0: k_join.  In tiles of 64 up to 300 of them (1,000 points, 136 tiles:
+// 13.0 us a call against 14.0 in tiles of 128 and 23.7 by k_join; 2,000 points, 528 tiles: 15.5, 14.2, 21.8).  In tiles of 128
+// where the CUs, which hold 768 of them, need no more rounds for them than k_join for its 256 at a time (at d = 64, 384 and
+// 960: one round 10 + 4.5, 7 + 10.5, 0 + 24 us, further ones 4.5, 10.5, 24; k_join 10.5 + 5, 11 + 11, 11 + 22), or one more
+// where it is at least the fourth and a tile has few slices (9,000 points, d = 64: 30.8 us against 33.6; d = 960: 101 against
+// 97).  Two sets: two rounds at most, the operands of a long thin grid are read once and k_join's copies keep ahead better
+// (200,000 x 60, d = 384: 67 us against 60).
+int small_tile(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nslices) {
+  auto tiles = [&](int64_t t) {
+    const int64_t a = (nA + t - 1) / t, b = (nB + t - 1) / t;
+    return self ? a * (a + 1) / 2 : a * b;
+  };
+#ifdef EJOIN_ONLY_K_JOIN
+  return 0;
+#endif
+  if (tiles(64) <= 300) return 64;
+  const int64_t held = (int64_t)ctx->num_cu * small_groups_per_cu<128>();
+  const int64_t rounds = (tiles(128) + held - 1) / held, other = (tiles(TILE) + ctx->num_cu - 1) / ctx->num_cu;
+  if (!self) return rounds <= 2 && rounds <= other ? 128 : 0;
+  return rounds <= other + (rounds >= 4 && nslices <= 12 ? 1 : 0) ? 128 : 0;
+}
+
+template <bool COUNT, int TS>
+int launch_small(ejoin_ctx* ctx, const SmallArgs& a, hipStream_t st) {
+  const int64_t tiles = a.j.self ? (int64_t)a.j.ntilesA * (a.j.ntilesA + 1) / 2 : (int64_t)a.j.ntilesA * a.j.ntilesB;
+  const int64_t most = (int64_t)ctx->num_cu * small_groups_per_cu<TS>();  // what the CUs hold at a time
+  const int64_t groups = (tiles + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
+  hipLaunchKernelGGL((k_join_small<COUNT, TS>), dim3((unsigned)(groups < most ? groups : most)), dim3(256), (small_lds_bytes<COUNT, TS>()), st, a);
+  EJ_TRY(hipGetLastError());
+  return EJOIN_OK;
+}
+
+// A join by k_prep and k_join_small.  B.npad == 0: self-join of A.  A.X == nullptr: A is a prepared set (its largest norm: set_max).
+// Neither kernel reads or leaves anything in the status block but the status word.
+template <bool COUNT>
+int run_small(ejoin_ctx* ctx, const Workspace& w, int tile, PrepSet A, PrepSet B, const uint32_t* set_max, int nkb, float eps, const Results& r,
+              hipStream_t st) {
+  const bool self = B.npad == 0;
+  if (ctx->profiling) EJ_TRY(hipEventRecord(ctx->ev[0], st));
+  ctx->last_status = w.status;
+  ctx->last_stream = st;
+  const int64_t wavesA = A.X ? A.npad / NORM_POINTS : 0, wavesB = B.npad / NORM_POINTS;
+  const int threads = norm_threads(wavesA + wavesB), per = threads / 64;
+  A.groups = (uint32_t)((wavesA + per - 1) / per);
+  B.groups = (uint32_t)((wavesB + per - 1) / per);
+  PrepArgs p;
+  memset(&p, 0, sizeof(p));
+  p.a = A;
+  p.b = B;
+  p.k32steps = nkb;
+  p.maxima = reinterpret_cast<uint32_t*>(w.H);
+  p.counter = r.counter(COUNT);
+  p.counts = r.counts;
+  p.ncounts = A.n;
+  p.counts_b = r.counts_b;
+  p.ncounts_b = B.n;
+  // enough workgroups that none clears more than 16 counts per thread
+  const uint32_t clearing = r.counts ? (uint32_t)((A.n + 16 * threads - 1) / (16 * threads)) : 0u, norming = A.groups + B.groups;
+  hipLaunchKernelGGL(k_prep, dim3(clearing > norming ? clearing : norming), dim3(threads), 0, st, p);
+  EJ_TRY(hipGetLastError());
+  const Operand OA{A.Xp, A.n, A.npad}, OB{self ? A.Xp : B.Xp, self ? A.n : B.n, self ? A.npad : B.npad};
+  SmallArgs a;
+  a.j = join_args(w, OA, OB, self, nkb, eps, r, tile);
+  a.sA = A.s;
+  a.sB = self ? A.s : B.s;
+  a.maxima = p.maxima;
+  a.nmaxima = A.groups + B.groups;
+  a.set_max = set_max;
+  if (ctx->profiling) {
+    EJ_TRY(hipEventRecord(ctx->ev[1], st));
+    EJ_TRY(hipEventRecord(ctx->ev[2], st));
+  }
+  EJ_RC(tile == 64 ? (launch_small<COUNT, 64>(ctx, a, st)) : (launch_small<COUNT, 128>(ctx, a, st)));
+  if (ctx->profiling) {
+    EJ_TRY(hipEventRecord(ctx->ev[3], st));
+    ctx->ev_valid = 1;
+  }
+  return EJOIN_OK;
+}
+
 // Join of FP16 rows in workspace w (the context's own, or a carving of the static scratch).  XB == nullptr: self-join of XA.
 // batch_rows (self-join, pair mode only): null, or nbatches + 1 ascending bounds in rows of super-blocks; the join kernel is
 // then launched once per range, and after each launch the pair counter is copied to ctx->batch_count[b] and
@@ -1517,6 +1954,8 @@ int run_join(ejoin_ctx* ctx, const Workspace& w, bool own, const uint16_t* XA, i
   uint4* HB = w.H + padA;
   uint4* XpA = w.Xp;
   uint4* XpB = w.Xp + padA * (int64_t)(nkb + 1) * 4;
+  if (const int tile = batch_rows ? 0 : small_tile(ctx, nA, self ? nA : nB, self, nkb))
+    return run_small<COUNT>(ctx, w, tile, PrepSet{XA, nA, padA, ldA, sA, XpA, 0}, PrepSet{XB, nB, padB, ldB, sB, XpB, 0}, nullptr, nkb, eps, r, st);
   EJ_RC(begin_call(ctx, w, own, st));
   EJ_RC(launch_norms(ctx, XA, nA, d, ldA, sA, w.status + 1, XpA, st));
   if (!self) EJ_RC(launch_norms(ctx, XB, nB, d, ldB, sB, w.status + 1, XpB, st));
@@ -1570,6 +2009,9 @@ int run_join_prepared(ejoin_ctx* ctx, const ejoin_set* P, const uint16_t* XQ, in
   EJ_RC(ensure_workspace(ctx, padQ, pad_dims(d)));
   const Workspace& w = ctx->ws;
   const int nkb = k_blocks(d);
+  if (const int tile = small_tile(ctx, P->n, nQ, false, nkb))
+    return run_small<COUNT>(ctx, w, tile, PrepSet{nullptr, P->n, P->pad, 0, P->s, P->Xp, 0}, PrepSet{XQ, nQ, padQ, ldQ, w.s, w.Xp, 0}, P->max_bits,
+                            nkb, eps, r, st);
   EJ_RC(begin_call(ctx, w, true, st));
   EJ_RC(launch_norms(ctx, XQ, nQ, d, ldQ, w.s, w.status + 1, w.Xp, st));
   hipLaunchKernelGGL(k_merge_max, dim3(1), dim3(64), 0, st, w.status + 1, P->max_bits);

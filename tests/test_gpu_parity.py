@@ -614,3 +614,87 @@ def test_odd_numbers_of_slices(ej, d):
     b, _, bt = ej.join_count(Xd, Xd[:300], float(eps), d=d)
     assert torch.equal(a, b) and torch.equal(at, bt)
     s.close()
+
+
+# ------------------------------------------------------------------ the kernel of small problems against the general one
+def by_general_kernel(ej, Xd, eps, capacity, d):
+    """The pairs of the self-join by the launches of the batched return, which the general kernel does at every size."""
+    pairs = torch.zeros((capacity, 2), dtype=torch.int32, device="cuda")
+    d2 = torch.zeros(capacity, dtype=torch.float32, device="cuda")
+    hp, hd = torch.zeros((capacity, 2), dtype=torch.int32), torch.zeros(capacity, dtype=torch.float32)
+    found = ej.selfjoin_pairs_to_host(Xd, float(eps), 1, pairs, d2, hp, hd, d=d)
+    assert found <= capacity
+    return hp[:found].numpy().view(np.uint32), hd[:found].numpy()
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 129, 255, 257, 1000, 1537, 2500, 4097, 6500, 8100])
+@pytest.mark.parametrize("d", [20, 96, 130])
+@pytest.mark.parametrize("share", [0.003, 0.2])
+def test_small_problems_give_the_results_of_the_general_kernel(ej, n, d, share):
+    """Tiles of 64 and of 128, one and several per workgroup, ragged edges, sparse and dense results: pairs, distances and
+    counts of the general kernel, bit for bit."""
+    if share > 0.1 and n > 2500:
+        pytest.skip("dense results at the smaller sizes")
+    print(f"small n={n} d={d} share={share}", flush=True)
+    rng = np.random.default_rng(n + d)
+    X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    X[n // 2] = X[0]
+    ld = (d + 63) // 64 * 64
+    Xd = dev(pad(X, ld))
+    P = orc.decode(X[np.sort(rng.choice(n, size=min(n, 900), replace=False))])
+    eps = orc.eps_for_pair_rank(orc.all_pairs_dist2(P), max(1, int(share * P.shape[0] * (P.shape[0] - 1) / 2))) if n > 2 else np.float32(1.0)
+    cap = int(n + 2 * share * n * n / 2 + 4096)
+    want, want_d2 = by_general_kernel(ej, Xd, eps, cap, d)
+    got, got_d2, found = run_pairs(ej, Xd, eps, capacity=cap, d=d)
+    assert found == got.shape[0] == want.shape[0]
+    kw, kg = orc.pair_keys(want), orc.pair_keys(got)
+    ow, og = np.argsort(kw), np.argsort(kg)
+    assert np.array_equal(kw[ow], kg[og]) and np.array_equal(want_d2[ow], got_d2[og])
+    counts, total = ej.selfjoin_count(Xd, float(eps), d=d)
+    ns = want[want[:, 0] != want[:, 1]]
+    hist = np.bincount(ns[:, 0], minlength=n) + np.bincount(ns[:, 1], minlength=n)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), hist) and int(total.cpu()[0]) == ns.shape[0]
+    # two sets, and the first of them prepared: the pairs (i, j), i in the first part, of the same distances
+    m = max(1, n // 3)
+    two, two_d2, tfound = parity.to_host_pairs(*ej.join_pairs(Xd[:m], Xd, float(eps), 2 * cap, d=d))
+    assert tfound == two.shape[0]
+    off = two[:, 0] < two[:, 1]
+    sub = want[:, 0] < m
+    kt = orc.pair_keys(two[off])
+    ks = orc.pair_keys(want[sub & (want[:, 0] != want[:, 1])])
+    assert np.array_equal(np.sort(kt), np.sort(ks))
+    prepared = ej.prepare(Xd[:m], d=d)
+    cp, cq, ct = prepared.join_count(Xd, float(eps))
+    assert int(ct.cpu()[0]) == tfound
+    assert np.array_equal(cp.cpu().numpy().view(np.uint32), np.bincount(two[:, 0], minlength=m))
+    assert np.array_equal(cq.cpu().numpy().view(np.uint32), np.bincount(two[:, 1], minlength=n))
+    prepared.close()
+
+
+def test_small_problems_overflow_status_and_captured_replays(ej):
+    rng = np.random.default_rng(3)
+    X = rng.random((1500, 64), dtype=np.float32).astype(np.float16).view(np.uint16)
+    Xd = dev(X)
+    full, full_d2, found = run_pairs(ej, Xd, 2.6, capacity=1500 * 750)
+    some, some_d2, again = run_pairs(ej, Xd, 2.6, capacity=1000)
+    assert again == found > 1000 and some.shape[0] == 1000 and np.isin(orc.pair_keys(some), orc.pair_keys(full)).all()
+    bad = Xd.clone()
+    bad[1499, 3] = 0x7C00  # infinity
+    counts, total = ej.selfjoin_count(bad, 2.6)
+    assert ej.status() == 2 and int(total.cpu()[0]) == 0 and int(counts.abs().sum().cpu()) == 0
+    counts, total = ej.selfjoin_count(Xd, 2.6)  # nothing of it stays behind
+    assert ej.status() == 0 and int(total.cpu()[0]) == found - 1500
+    work = Xd.clone()
+    c2, t2 = torch.empty_like(counts), torch.empty_like(total)
+    ej.selfjoin_count(work, 2.6, counts=c2, total=t2)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        ej.selfjoin_count(work, 2.6, counts=c2, total=t2)
+    for r in range(4):  # replays on data whose largest norm goes up and down, with eager work between
+        work.copy_(dev((X.view(np.float16) * np.float16([1.0, 0.25, 8.0, 0.5][r])).view(np.uint16)))
+        g.replay()
+        torch.cuda.synchronize()
+        got = c2.clone()
+        eager, et = ej.selfjoin_count(work, 2.6)
+        assert torch.equal(got, eager) and torch.equal(t2, et)
