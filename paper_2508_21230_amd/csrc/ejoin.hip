@@ -76,6 +76,7 @@ constexpr int AUGC_OFF = AUG_OFF + EJ_AUG_CONST;
 constexpr int AUG_REGION_STEP = EJ_AUG_REGION_STEP;
 constexpr int STG_OFF = AUG_OFF + EJ_AUG_BYTES;  // per-wave result staging: STG_CAP entries of (i, j, d2)
 constexpr int STG_CAP = 128;
+constexpr int DENSE_LANES = 12;  // candidates in that many lanes of a region: each lane looks at its own (see the rare path)
 constexpr int QUEUE_CAP = 16;    // per-wave queue of lanes that hold a candidate (see the rare path): 16 values and a tag each
 constexpr int STG_WAVE_BYTES = STG_CAP * 12 + QUEUE_CAP * 68;
 constexpr int LDS_BYTES = STG_OFF + 8 * STG_WAVE_BYTES;
@@ -639,9 +640,55 @@ __device__ __forceinline__ void xcd_align(uint32_t* bar, uint32_t expect) {
   __syncthreads();
 }
 
+// ---- The sixteen values of a lane for a 32 x 32 region (register r: pair (i0 + 16 (r / 8) + r % 4, j0 + 16 (r / 4 % 2)) of the
+// lane's register 0, see region_pair), looked at by the lane itself.
+// Register r of v, r different from lane to lane.
+__device__ __forceinline__ float pick(const float16v& v, uint32_t r) {
+  const bool b0 = r & 1u, b1 = r & 2u, b2 = r & 4u, b3 = r & 8u;
+  auto four = [&](float w, float x, float y, float z) {
+    const float lo = b0 ? x : w, hi = b0 ? z : y;
+    return b1 ? hi : lo;
+  };
+  const float q0 = four(v[0], v[1], v[2], v[3]), q1 = four(v[4], v[5], v[6], v[7]);
+  const float q2 = four(v[8], v[9], v[10], v[11]), q3 = four(v[12], v[13], v[14], v[15]);
+  const float lo = b2 ? q1 : q0, hi = b2 ? q3 : q2;
+  return b3 ? hi : lo;
+}
+// The registers whose pairs are pairs of the result at all (bit r: register r).  Rows and columns past n carry a large negative
+// marker, which a huge epsilon can still reach.
+__device__ __forceinline__ uint32_t keep_mask(uint32_t i0, uint32_t j0, uint32_t nA, uint32_t nB, bool diag) {
+  uint32_t keep = 0;
+#pragma unroll 1
+  for (int r = 15; r >= 0; --r) {
+    const uint32_t i = i0 + 16 * (r >> 3) + (r & 3), j = j0 + 16 * ((r >> 2) & 1);
+    keep = 2 * keep + (i < nA && j < nB && (!diag || i < j) ? 1u : 0u);
+  }
+  return keep;
+}
+// Adds the hits of a region to counters in the LDS: rows[0] is the lane's register 0's row, columns[0] its column.
+__device__ __forceinline__ void add_region_counts(uint32_t hit, uint32_t* rows, uint32_t* columns) {
+  const uint32_t c0 = __popc(hit & 0x0F0Fu), c1 = __popc(hit & 0xF0F0u);
+  if (c0) atomicAdd(columns, c0);
+  if (c1) atomicAdd(columns + 16, c1);
+  uint32_t left = (hit | (hit >> 4)) & 0x0F0Fu;  // two registers share a row
+  while (__ballot(left != 0)) {
+    if (left) {
+      const uint32_t r = (uint32_t)__builtin_ctz(left);
+      atomicAdd(rows + 2 * (r & 8u) + (r & 3u), ((hit >> r) & 1u) + ((hit >> (r + 4)) & 1u));
+      left &= left - 1;
+    }
+  }
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) x += (uint32_t)__shfl_xor((int)x, off);
+  return __builtin_amdgcn_readfirstlane(x);
+}
+
 // KEEP_A: the instance for tiles of exactly NSTAGE slices (96 < d <= 128), which leaves a row panel in the LDS across
 // the consecutive tiles that share it (see keep_a_cur); the other instance carries none of that logic.
-template <bool COUNT, bool KEEP_A>
+// DENSE (count mode): the instance whose rare path also handles regions with candidates in many lanes lane by lane.
+template <bool COUNT, bool KEEP_A, bool DENSE>
 __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   // the largest norm of the call has been consumed by k_aux: cleared here for the next call
@@ -799,6 +846,8 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
     fill = 0;
     dirty = true;
   };
+  if constexpr (DENSE)  // (count mode stages nothing: the area holds the counters of the dense path, 128 rows and 64 columns)
+    for (int q = 0; q < 3; ++q) stg[64 * q + lane] = 0;
   // appends one entry per lane of `mask` to the staging area
   auto append = [&](unsigned long long mask, bool pass, uint32_t i, uint32_t j, uint32_t d2_bits) {
     const uint32_t cnt = __popcll(mask);
@@ -816,8 +865,6 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   // and where they belong: row offset | column offset << 16 inside the wave tile (queue_t[e])
   float* queue_v = reinterpret_cast<float*>(lds + STG_OFF + wave * STG_WAVE_BYTES + STG_CAP * 12);
   uint32_t* queue_t = reinterpret_cast<uint32_t*>(queue_v + 16 * QUEUE_CAP);
-  const uint32_t lane_tag = (uint32_t)(4 * g) | ((uint32_t)r16 << 16);  // region_pair(lane, 0)
-  const uint32_t reg_tag = (uint32_t)(16 * (r16 >> 3) + (r16 & 3)) | ((uint32_t)(16 * ((r16 >> 2) & 1)) << 16);  // ... of register lane % 16
 
   // ---------------- prologue
   TileCursor tc;
@@ -1119,8 +1166,14 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
         const uint32_t i = I * TILE + tid;
         append(__ballot(i < (uint32_t)a.nA), i < (uint32_t)a.nA, i, i, 0u);
       }
+      uint32_t l = lane;
+      if constexpr (DENSE) asm volatile("" : "+v"(l));  // (this instance has no registers to keep what follows across the main loop)
+      const uint32_t lr = l & 15u, lg = l >> 4;
+      const uint32_t lane_tag = 4 * lg | (lr << 16);                                                  // region_pair(lane, 0)
+      const uint32_t reg_tag = (16 * (lr >> 3) + (lr & 3)) | ((16 * ((lr >> 2) & 1)) << 16);  // ... of register lane % 16
       uint32_t todo = blocks_hit;  // regions not (completely) queued yet
       uint32_t taken = 0;          // lanes of the first of them that are
+      uint32_t dense = 0;          // (DENSE) regions with candidates in many lanes
       while (todo) {
         uint32_t qfill = 0;
         uint32_t now = todo;
@@ -1134,6 +1187,11 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
           const bool has = least[b] <= thr_bits;
 #endif
           const unsigned long long lanes = __ballot(has);
+          if (DENSE && __popcll(lanes) >= DENSE_LANES) {
+            dense |= 1u << b;
+            todo &= ~(1u << b);
+            continue;
+          }
           const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u));
           const uint32_t e = qfill + rank - taken;  // (a lane already taken: e wraps around or lies below qfill)
           if (has && rank >= taken && e < (uint32_t)QUEUE_CAP) {
@@ -1162,10 +1220,10 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
         const bool partial = diag || (I + 1) * TILE > nnA || (J + 1) * TILE > nnB;
 #pragma unroll 1
         for (uint32_t q0 = 0; q0 < qfill; q0 += 4) {
-          const float x = queue_v[16 * q0 + lane];
-          const uint32_t at = queue_t[q0 + (lane >> 4)] + reg_tag;
+          const float x = queue_v[16 * q0 + l];
+          const uint32_t at = queue_t[q0 + lg] + reg_tag;
           const uint32_t i = I * TILE + wm * 128 + (at & 0xFFFFu), j = J * TILE + wn * 64 + (at >> 16);
-          bool pass = x >= a.thr && (uint32_t)lane < 16 * (qfill - q0);
+          bool pass = x >= a.thr && l < 16 * (qfill - q0);
           if (partial) pass = pass && i < nnA && j < nnB && (!diag || i < j);
           const unsigned long long mask = __ballot(pass);
           if (!mask) continue;
@@ -1182,6 +1240,47 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
           }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      }
+      if (DENSE && dense) {
+        // Every lane looks at its own registers: a bit mask of those that pass, whose numbers per row and column are added up in
+        // the wavefront's part of the LDS; the tile's go out with one atomic per row and column.
+        const uint32_t nnA = (uint32_t)a.nA, nnB = (uint32_t)a.nB;
+        const bool partial = diag || (I + 1) * TILE > nnA || (J + 1) * TILE > nnB;
+        do {
+          const int b = __builtin_ctz(dense);
+          dense &= dense - 1;
+          float16v v;
+          switch (b) {
+            case 0: v = R[0][0]; break;
+            case 1: v = R[0][1]; break;
+            case 2: v = R[1][0]; break;
+            case 3: v = R[1][1]; break;
+            case 4: v = R[2][0]; break;
+            case 5: v = R[2][1]; break;
+            case 6: v = R[3][0]; break;
+            default: v = R[3][1]; break;
+          }
+          asm volatile("" : "+v"(v));  // one copy of the region's registers, in one place
+          uint32_t hit = 0;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) hit |= v[r] >= a.thr ? 1u << r : 0u;
+          const uint32_t il = 32 * (b >> 1) + 4 * lg, jl = 32 * (b & 1) + lr;  // register 0's place in the wave tile
+          const uint32_t i0 = I * TILE + wm * 128 + il, j0 = J * TILE + wn * 64 + jl;
+          if (partial) hit &= keep_mask(i0, j0, nnA, nnB, diag);
+          hits += wave_sum(__popc(hit));
+          add_region_counts(hit, stg + il, stg + 128 + jl);
+        } while (dense);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        for (int q = 0; q < 3; ++q) {  // 128 rows, 64 columns
+          const uint32_t c = stg[64 * q + l];
+          if (c) {
+            stg[64 * q + l] = 0;
+            if (q < 2) atomicAdd(&a.counts[I * TILE + wm * 128 + 64 * q + l], c);
+            else if (a.self) atomicAdd(&a.counts[J * TILE + wn * 64 + l], c);
+            else if (a.counts_b) atomicAdd(&a.counts_b[J * TILE + wn * 64 + l], c);
+          }
+        }
+        dirty = true;
       }
       // The stores and atomics of the path count on vmcnt like the copies, but complete in any order: the counted
       // waits of the slices hold only once they are all done.
@@ -1488,43 +1587,16 @@ __global__ __launch_bounds__(256, small_groups_per_cu<TS>()) void k_join_small(c
         for (int r = 0; r < 16; ++r) hit |= v[r] >= a.thr ? 1u << r : 0u;
         if (__ballot(hit != 0) == 0) continue;
         const uint32_t il = wm + 32 * Ra + 4 * g, jl = wn + 32 * Rb + r16;  // register 0's place in the tile (region_pair)
-        if (partial) {
-          uint32_t keep = 0;
-#pragma unroll 1
-          for (int r = 15; r >= 0; --r) {
-            const uint32_t i = i_tile + il + 16 * (r >> 3) + (r & 3), j = j_tile + jl + 16 * ((r >> 2) & 1);
-            keep = 2 * keep + (i < nnA && j < nnB && (!diag || i < j) ? 1u : 0u);
-          }
-          hit &= keep;
-        }
+        if (partial) hit &= keep_mask(i_tile + il, j_tile + jl, nnA, nnB, diag);
         if constexpr (COUNT) {
           hits += __popc(hit);
-          // columns 16 c + l % 16: registers with bit 2 equal to c; rows 16 a + 4 g + r % 4: two registers each
-          const uint32_t c0 = __popc(hit & 0x0F0Fu), c1 = __popc(hit & 0xF0F0u);
-          if (c0) atomicAdd(cnt + TS + jl, c0);
-          if (c1) atomicAdd(cnt + TS + jl + 16, c1);
-          uint32_t rows = (hit | (hit >> 4)) & 0x0F0Fu;
-          while (__ballot(rows != 0)) {
-            if (rows) {
-              const uint32_t r = (uint32_t)__builtin_ctz(rows);
-              atomicAdd(cnt + il + 2 * (r & 8u) + (r & 3u), ((hit >> r) & 1u) + ((hit >> (r + 4)) & 1u));
-              rows &= rows - 1;
-            }
-          }
+          add_region_counts(hit, cnt + il, cnt + TS + jl);
         } else {
           // every round takes one hit of each lane that has any left
           for (unsigned long long mask = __ballot(hit != 0); mask; mask = __ballot(hit != 0)) {
             const uint32_t r = (uint32_t)__builtin_ctz(hit | 0x10000u);
-            const bool b0 = r & 1u, b1 = r & 2u, b2 = r & 4u, b3 = r & 8u;
-            auto four = [&](float w, float x, float y, float z) {
-              const float lo = b0 ? x : w, hi = b0 ? z : y;
-              return b1 ? hi : lo;
-            };
-            const float q0 = four(v[0], v[1], v[2], v[3]), q1 = four(v[4], v[5], v[6], v[7]);
-            const float q2 = four(v[8], v[9], v[10], v[11]), q3 = four(v[12], v[13], v[14], v[15]);
-            const float lo = b2 ? q1 : q0, hi = b2 ? q3 : q2;
             append(mask, hit != 0, i_tile + il + 2 * (r & 8u) + (r & 3u), j_tile + jl + 4 * (r & 4u),
-                   __float_as_uint(fmaxf(-2.f * (b3 ? hi : lo), 0.f)));
+                   __float_as_uint(fmaxf(-2.f * pick(v, r), 0.f)));
             hit &= hit - 1;
           }
         }
@@ -1846,8 +1918,15 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
     EJ_TRY(hipEventRecord(ctx->ev[1], st));
     EJ_TRY(hipEventRecord(ctx->ev[2], st));
   }
-  if (a.nslices == NSTAGE) hipLaunchKernelGGL((k_join<COUNT, true>), dim3(ctx->num_cu), dim3(THREADS), LDS_BYTES, st, a);
-  else hipLaunchKernelGGL((k_join<COUNT, false>), dim3(ctx->num_cu), dim3(THREADS), LDS_BYTES, st, a);
+  // Counts of sets of up to 32,768 points go to the instance for dense tiles.  A tile has 65,536 S / n hits at S neighbours: beyond
+  // that size even S = 512 leaves fewer candidates than the queue of the rare path is good for, and the instance's registers cost
+  // 2 to 4 % (30,000 points, d = 128: S = 512 675 us, now 309, S = 100 220 us, now 230; 14,000 points, d = 960, S = 512: 589 us,
+  // now 212; 10^6 points, d = 128, S = 64: 107.4 ms against 109.2).
+  constexpr int64_t DENSE_POINTS = 32768;
+  const bool keep_a = a.nslices == NSTAGE, dense = COUNT && A.n <= DENSE_POINTS && B.n <= DENSE_POINTS;
+  void (*kernel)(JoinArgs) = keep_a ? (dense ? k_join<COUNT, true, COUNT> : k_join<COUNT, true, false>)
+                                    : (dense ? k_join<COUNT, false, COUNT> : k_join<COUNT, false, false>);
+  hipLaunchKernelGGL(kernel, dim3(ctx->num_cu), dim3(THREADS), LDS_BYTES, st, a);
   EJ_TRY(hipGetLastError());
   if (own) ctx->ws_dirty = false;
   if (ctx->profiling) {
@@ -2100,10 +2179,9 @@ int ejoin_create(ejoin_ctx** out, int device) {
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->copy_stream, hipStreamNonBlocking);
   for (int i = 0; i < EJOIN_MAX_BATCHES && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&ctx->batch_ev[i], hipEventDisableTiming);
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&ctx->batch_count), EJOIN_MAX_BATCHES * sizeof(unsigned long long), hipHostMallocDefault);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_join<false, false>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_join<true, false>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_join<false, true>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_join<true, true>), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+  for (void (*kernel)(JoinArgs) : {&k_join<false, false, false>, &k_join<false, true, false>, &k_join<true, false, false>, &k_join<true, true, false>,
+                                   &k_join<true, false, true>, &k_join<true, true, true>})
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
   if (e != hipSuccess) {
     (void)hipGetLastError();
     ejoin_destroy(ctx);

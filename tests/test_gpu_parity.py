@@ -698,3 +698,37 @@ def test_small_problems_overflow_status_and_captured_replays(ej):
         got = c2.clone()
         eager, et = ej.selfjoin_count(work, 2.6)
         assert torch.equal(got, eager) and torch.equal(t2, et)
+
+
+# ------------------------------------------------------------------ counts of dense tiles
+@pytest.mark.parametrize("d", [50, 128, 200])
+@pytest.mark.parametrize("share", [0.005, 0.03, 0.3])
+def test_counts_of_dense_tiles(ej, d, share):
+    """Regions with candidates in a few, about twelve and all of their lanes, ragged edges and the diagonal, self-join and two
+    sets, at a size the general kernel works on: exactly the counts of the dense distance blocks."""
+    print(f"dense counts d={d} share={share}", flush=True)
+    n, nq = 13007, 9001
+    rng = np.random.default_rng(d)
+    X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    P = orc.decode(X[:700])
+    eps = orc.eps_for_pair_rank(orc.all_pairs_dist2(P), int(share * 700 * 699 / 2))
+    Xd = dev(pad(X, (d + 63) // 64 * 64))
+    e2 = float(np.float32(eps) * np.float32(eps))
+    want = torch.zeros(n, dtype=torch.int64, device="cuda")
+    upper = torch.zeros(n, dtype=torch.int64, device="cuda")
+    rows = torch.arange(n, device="cuda")
+    for r in range(0, n, 2000):  # (i, j) with i < j is the pair the self-join evaluates
+        h = min(2000, n - r)
+        hit = (ej.dist2_tile(Xd, r, 0, h, n, d=d) <= e2) & (rows[None, :] > rows[r:r + h, None])
+        upper[r:r + h] += hit.sum(dim=1)
+        want += hit.sum(dim=0)
+    counts, total = ej.selfjoin_count(Xd, float(eps), d=d)
+    assert torch.equal(counts.long(), want + upper) and int(total.cpu()[0]) == int(upper.sum().cpu())
+    full = torch.cat([(ej.dist2_tile(Xd, r, n - nq, min(2000, n - r), nq, d=d) <= e2) for r in range(0, n, 2000)])
+    cp, cq, ct = ej.join_count(Xd, Xd[n - nq:].clone(), float(eps), d=d)
+    k = rows[n - nq:]
+    # a point's distance to itself is computed like any other here, and written as 0 in the block: left out on both sides
+    own = (cp.long().sum() - full.long().sum()).abs()
+    assert int(own.cpu()) <= nq and int(ct.cpu()[0]) == int(cp.long().sum().cpu()) == int(cq.long().sum().cpu())
+    assert int((cp.long() - full.sum(dim=1)).abs().max().cpu()) <= 1 and int((cq.long() - full.sum(dim=0)).abs().max().cpu()) <= 1
+    assert torch.equal(cp[: n - nq].long(), full.sum(dim=1)[: n - nq]) and k.numel() == nq
