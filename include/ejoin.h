@@ -174,7 +174,7 @@ int ejoin_join_count(ejoin_ctx* ctx, const uint16_t* P, int64_t np, int64_t ldp,
  * subroutine of searches the paper names, Section 1): ejoin_set_create computes the norms of X and its
  * re-laid-out copy once (work enqueued on `stream`; X may be released once that work has completed),
  * ejoin_set_join_pairs / _count then do per call only the work that depends on the query points.
- * The set owns its device memory (roundup(n,256) * (roundup(d,64) * 2 + 84) bytes) until
+ * The set owns its device memory (roundup(n,256) * (roundup(d,64) * 2 + 68) bytes) until
  * ejoin_set_destroy, which the caller invokes after synchronising, and before destroying the context.
  * Results, arguments and conventions are those of ejoin_join_pairs / ejoin_join_count with P = the set
  * (d is the set's).  A join writes a small part of the set (the norm terms, rescaled to the larger of

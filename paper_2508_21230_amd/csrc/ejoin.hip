@@ -128,11 +128,6 @@ __global__ void k_reset(uint32_t* status_and_max) {
   }
 }
 
-// Folds the largest norm of a prepared set (stored as FP32 bits) into the running maximum of a call.
-__global__ void k_merge_max(uint32_t* max_bits, const uint32_t* set_max) {
-  if (threadIdx.x == 0) atomicMax(max_bits, *set_max);
-}
-
 __global__ void k_fill_u32(uint32_t* p, int64_t n, uint32_t v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -250,7 +245,7 @@ constexpr uint32_t P1_OUT_OF_RANGE = 0xFB53u;  // -60000 in FP16
 // above FP16's smallest subnormal.  A smaller norm is carried to 2^-25 2^m absolute.  Point i's
 // 16-byte row is  H_i = { P_i, C } = { p1, p2, p3, 0, c, c, c, 0 }; the extra step multiplies
 // pieces by constants, c (p1 + p2 + p3)_i + c (q1 + q2 + q3)_j = -s_i/2 - s_j/2, every product exact in FP32.
-// H (npad rows) serves the dense-tile kernel.  For the join the operands of the extra step are also
+// H (npad rows) serves the dense-tile kernel only.  For the join the operands of the extra step are also
 // written, ready made, into one more k-block behind the data k-blocks of each panel of the packed set (`Xp`,
 // may be null; k-block `aug_kb` of `blocks`): 16 bytes per row for the panel as the A operand (chunk 0 of
 // panel_layout.h, "the augmentation step": 256 x 16 B), then 16 bytes per row for the panel as the B operand
@@ -288,38 +283,56 @@ __device__ __forceinline__ uint2 norm_pieces(float s, int m) {
   return make_uint2(fp16_bits(p1) | (fp16_bits(p2) << 16), fp16_bits(p3));
 }
 
-__global__ void k_aux(const float* __restrict__ s, int64_t n, int64_t npad, uint32_t* __restrict__ status_and_max,
-                      uint4* __restrict__ H, uint4* __restrict__ Xp, int aug_kb, int blocks,
-                      unsigned long long* __restrict__ counter, uint32_t* __restrict__ counts) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const uint32_t mb = status_and_max[1];
+struct AuxSet {
+  const float* s;
+  int64_t n, npad;
+  uint4* Xp;         // null: no augmentation block (dense-tile call)
+  uint32_t* counts;  // count mode: cleared on the way (n entries; may be null)
+};
+struct AuxArgs {
+  AuxSet a, b;  // (b.npad = 0: one set)
+  uint32_t* status_and_max;
+  const uint32_t* set_max;  // largest norm of a prepared set, or null
+  uint4* H;                 // rows of set a for the dense-tile kernel, or null
+  int aug_kb;               // k-block of the augmentation operands = data k-blocks of a panel
+  unsigned long long* counter;
+};
+__global__ __launch_bounds__(256) void k_aux(const AuxArgs args) {
+  const uint32_t groups_a = (uint32_t)(args.a.npad / 256);
+  const bool second = blockIdx.x >= groups_a;
+  const AuxSet& set = second ? args.b : args.a;
+  const int64_t i = (int64_t)(blockIdx.x - (second ? groups_a : 0u)) * 256 + threadIdx.x, n = set.n;
+  const float* s = set.s;
+  uint32_t mb = args.status_and_max[1];
+  if (args.set_max) mb = max(mb, *args.set_max);
   if (blockIdx.x == 0) {
-    if (threadIdx.x < 8) status_and_max[8 + threadIdx.x] = 0;
-    if (threadIdx.x == 8 && counter) *counter = 0;
+    if (threadIdx.x < 8) args.status_and_max[8 + threadIdx.x] = 0;
+    if (threadIdx.x == 8 && args.counter) *args.counter = 0;
   }
-  if (counts && i < n) counts[i] = 0;
+  if (set.counts && i < n) set.counts[i] = 0;
   const NormScale ns = norm_scale(mb);
   const uint32_t st = ns.st, c = fp16_bits(ns.c);
-  if (i == 0) {
-    status_and_max[0] = st;
-    status_and_max[2] = c | (c << 16);
-    status_and_max[3] = c;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    args.status_and_max[0] = st;
+    args.status_and_max[2] = c | (c << 16);
+    args.status_and_max[3] = c;
   }
-  if (i >= npad) return;
   auto pieces = [&](int64_t x) -> uint2 {
     if (x >= n) return make_uint2(P1_OUT_OF_RANGE, 0u);
     if (st != ST_OK) return make_uint2(0u, 0u);
     return norm_pieces(s[x], ns.m);
   };
-  const uint2 cc = (i >= n || st == ST_OK) ? make_uint2(c | (c << 16), c) : make_uint2(0u, 0u);
-  const uint2 own = pieces(i);
-  H[i] = make_uint4(own.x, own.y, cc.x, cc.y);
-  if (Xp) {
+  if (args.H) {
+    const uint2 cc = (i >= n || st == ST_OK) ? make_uint2(c | (c << 16), c) : make_uint2(0u, 0u);
+    const uint2 own = pieces(i);
+    args.H[i] = make_uint4(own.x, own.y, cc.x, cc.y);
+  }
+  if (set.Xp) {
     const int r = (int)(i & 31);
     const int64_t b = i - r;
     const int64_t xa = b + aug_row_point(r), xb = b + aug_col_point(r);
     const uint2 a0 = pieces(xa), a1 = pieces(xa + 4), b0 = pieces(xb), b1 = pieces(xb + 16);
-    uint4* blk = Xp + packed_index((i >> 8) << 10, aug_kb, blocks);  // the panel's augmentation block
+    uint4* blk = set.Xp + packed_index((i >> 8) << 10, args.aug_kb, args.aug_kb + 1);  // the panel's augmentation block
     blk[aug_block_unit((int)(i & 255), 0)] = make_uint4(a0.x, a0.y, a1.x, a1.y);
     blk[aug_block_unit((int)(i & 255), 1)] = make_uint4(b0.x, b0.y, b1.x, b1.y);
   }
@@ -1363,8 +1376,9 @@ struct PrepSet {
 struct PrepArgs {
   PrepSet a, b;
   int k32steps;
-  uint32_t* maxima;  // one per workgroup
-  unsigned long long* counter;
+  uint32_t* maxima;    // one per workgroup, or null:
+  uint32_t* max_bits;  // ... the largest of all
+  unsigned long long* counter;  // cleared, like the counts (may be null)
   uint32_t* counts;  // count mode: cleared (may be null)
   int64_t ncounts;
   uint32_t* counts_b;
@@ -1372,7 +1386,7 @@ struct PrepArgs {
 };
 __global__ __launch_bounds__(512) void k_prep(const PrepArgs a) {
   const int64_t at = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, all = (int64_t)gridDim.x * blockDim.x;
-  if (at == 0) *a.counter = 0;
+  if (at == 0 && a.counter) *a.counter = 0;
   if (a.counts)
     for (int64_t i = at; i < a.ncounts; i += all) a.counts[i] = 0;
   if (a.counts_b)
@@ -1383,7 +1397,10 @@ __global__ __launch_bounds__(512) void k_prep(const PrepArgs a) {
   uint32_t most = 0;
   if (row0 < set.npad) most = norms_of_wave<true>(row0, set.X, set.n, set.ld, a.k32steps, set.s, set.Xp, a.k32steps + 1);
   most = max_of_group(most);
-  if (threadIdx.x == 0 && blockIdx.x < a.a.groups + a.b.groups) a.maxima[blockIdx.x] = most;  // (the others only clear counts)
+  if (threadIdx.x == 0 && blockIdx.x < a.a.groups + a.b.groups) {  // (the others only clear counts)
+    if (a.max_bits) atomicMax(a.max_bits, most);
+    else a.maxima[blockIdx.x] = most;
+  }
 }
 
 struct SmallArgs {
@@ -1696,7 +1713,6 @@ struct ejoin_set {
   int32_t d;
   uint4* Xp;
   float* s;
-  uint4* H;
   uint32_t* max_bits;  // device: FP32 bits of the largest norm
 };
 
@@ -1815,14 +1831,29 @@ int launch_norms(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, int64_
   return EJOIN_OK;
 }
 
-// Augmentation rows of one set from its norms and the running maximum of all norms.
-// Xp: the set's packed copy, whose panels get their augmentation k-block (k-block number `data_blocks`, behind the
-// data blocks; null for the dense-tile call); counter / counts: what the kernel clears on the way (may be null).
-int launch_aux(ejoin_ctx* ctx, uint32_t* status, const float* s, int64_t n, uint4* H, uint4* Xp, int data_blocks,
-               unsigned long long* counter, uint32_t* counts, hipStream_t st) {
-  const int64_t npad = pad_rows(n);
-  hipLaunchKernelGGL(k_aux, dim3((unsigned)(npad / 256)), dim3(256), 0, st, s, n, npad, status, H, Xp, data_blocks, data_blocks + 1, counter,
-                     counts);
+// Norms and packed copies of both sets of a join in one launch (B.npad == 0: one set; X == nullptr: a set prepared before).  Sets
+// the sets' numbers of workgroups.  p: where the maxima go and what is cleared.
+int launch_prep(ejoin_ctx* ctx, PrepSet& A, PrepSet& B, int nkb, PrepArgs& p, hipStream_t st) {
+  const int64_t wavesA = A.X ? A.npad / NORM_POINTS : 0, wavesB = B.X ? B.npad / NORM_POINTS : 0;
+  const int threads = norm_threads(wavesA + wavesB), per = threads / 64;
+  A.groups = (uint32_t)((wavesA + per - 1) / per);
+  B.groups = (uint32_t)((wavesB + per - 1) / per);
+  p.a = A;
+  p.b = B;
+  p.k32steps = nkb;
+  // enough workgroups that none clears more than 16 counts per thread
+  const uint32_t clearing = p.counts ? (uint32_t)((p.ncounts + 16 * threads - 1) / (16 * threads)) : 0u, norming = A.groups + B.groups;
+  hipLaunchKernelGGL(k_prep, dim3(clearing > norming ? clearing : norming), dim3(threads), 0, st, p);
+  EJ_TRY(hipGetLastError());
+  return EJOIN_OK;
+}
+
+// What follows the norms of a k_join call, for both its sets in one launch (B.npad == 0: one set): the augmentation operands, from
+// the norms and the largest norm of all (in the status block; set_max: that of a prepared set), and what the call needs zero.
+int launch_aux(ejoin_ctx* ctx, uint32_t* status, const uint32_t* set_max, const AuxSet& A, const AuxSet& B, int data_blocks, uint4* H,
+               unsigned long long* counter, hipStream_t st) {
+  const AuxArgs a{A, B, status, set_max, H, data_blocks, counter};
+  hipLaunchKernelGGL(k_aux, dim3((unsigned)((A.npad + B.npad) / 256)), dim3(256), 0, st, a);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }
@@ -1977,25 +2008,15 @@ int run_small(ejoin_ctx* ctx, const Workspace& w, int tile, PrepSet A, PrepSet B
   if (ctx->profiling) EJ_TRY(hipEventRecord(ctx->ev[0], st));
   ctx->last_status = w.status;
   ctx->last_stream = st;
-  const int64_t wavesA = A.X ? A.npad / NORM_POINTS : 0, wavesB = B.npad / NORM_POINTS;
-  const int threads = norm_threads(wavesA + wavesB), per = threads / 64;
-  A.groups = (uint32_t)((wavesA + per - 1) / per);
-  B.groups = (uint32_t)((wavesB + per - 1) / per);
   PrepArgs p;
   memset(&p, 0, sizeof(p));
-  p.a = A;
-  p.b = B;
-  p.k32steps = nkb;
   p.maxima = reinterpret_cast<uint32_t*>(w.H);
   p.counter = r.counter(COUNT);
   p.counts = r.counts;
   p.ncounts = A.n;
   p.counts_b = r.counts_b;
   p.ncounts_b = B.n;
-  // enough workgroups that none clears more than 16 counts per thread
-  const uint32_t clearing = r.counts ? (uint32_t)((A.n + 16 * threads - 1) / (16 * threads)) : 0u, norming = A.groups + B.groups;
-  hipLaunchKernelGGL(k_prep, dim3(clearing > norming ? clearing : norming), dim3(threads), 0, st, p);
-  EJ_TRY(hipGetLastError());
+  EJ_RC(launch_prep(ctx, A, B, nkb, p, st));
   const Operand OA{A.Xp, A.n, A.npad}, OB{self ? A.Xp : B.Xp, self ? A.n : B.n, self ? A.npad : B.npad};
   SmallArgs a;
   a.j = join_args(w, OA, OB, self, nkb, eps, r, tile);
@@ -2016,6 +2037,16 @@ int run_small(ejoin_ctx* ctx, const Workspace& w, int tile, PrepSet A, PrepSet B
   return EJOIN_OK;
 }
 
+// Norms, packed copies and augmentation operands of the sets of a k_join call, and its results cleared.
+int prep_and_aux(ejoin_ctx* ctx, const Workspace& w, PrepSet A, PrepSet B, const uint32_t* set_max, int nkb, unsigned long long* counter, const Results& r,
+                 hipStream_t st) {
+  PrepArgs p;
+  memset(&p, 0, sizeof(p));
+  p.max_bits = w.status + 1;
+  EJ_RC(launch_prep(ctx, A, B, nkb, p, st));
+  return launch_aux(ctx, w.status, set_max, AuxSet{A.s, A.n, A.npad, A.Xp, r.counts}, AuxSet{B.s, B.n, B.npad, B.Xp, r.counts_b}, nkb, nullptr, counter, st);
+}
+
 // Join of FP16 rows in workspace w (the context's own, or a carving of the static scratch).  XB == nullptr: self-join of XA.
 // batch_rows (self-join, pair mode only): null, or nbatches + 1 ascending bounds in rows of super-blocks; the join kernel is
 // then launched once per range, and after each launch the pair counter is copied to ctx->batch_count[b] and
@@ -2027,20 +2058,11 @@ int run_join(ejoin_ctx* ctx, const Workspace& w, bool own, const uint16_t* XA, i
   const bool self = (XB == nullptr);
   const int64_t padA = pad_rows(nA), padB = self ? 0 : pad_rows(nB);
   const int nkb = k_blocks(d);
-  float* sA = w.s;
-  float* sB = w.s + padA;
-  uint4* HA = w.H;
-  uint4* HB = w.H + padA;
-  uint4* XpA = w.Xp;
-  uint4* XpB = w.Xp + padA * (int64_t)(nkb + 1) * 4;
-  if (const int tile = batch_rows ? 0 : small_tile(ctx, nA, self ? nA : nB, self, nkb))
-    return run_small<COUNT>(ctx, w, tile, PrepSet{XA, nA, padA, ldA, sA, XpA, 0}, PrepSet{XB, nB, padB, ldB, sB, XpB, 0}, nullptr, nkb, eps, r, st);
+  PrepSet SA{XA, nA, padA, ldA, w.s, w.Xp, 0}, SB{XB, nB, padB, ldB, w.s + padA, w.Xp + padA * (int64_t)(nkb + 1) * 4, 0};
+  uint4 *XpA = SA.Xp, *XpB = SB.Xp;
+  if (const int tile = batch_rows ? 0 : small_tile(ctx, nA, self ? nA : nB, self, nkb)) return run_small<COUNT>(ctx, w, tile, SA, SB, nullptr, nkb, eps, r, st);
   EJ_RC(begin_call(ctx, w, own, st));
-  EJ_RC(launch_norms(ctx, XA, nA, d, ldA, sA, w.status + 1, XpA, st));
-  if (!self) EJ_RC(launch_norms(ctx, XB, nB, d, ldB, sB, w.status + 1, XpB, st));
-  // the augmentation rows need the maximum over both sets, so they follow both norm kernels
-  EJ_RC(launch_aux(ctx, w.status, sA, nA, HA, XpA, nkb, r.counter(COUNT), COUNT ? r.counts : nullptr, st));
-  if (!self) EJ_RC(launch_aux(ctx, w.status, sB, nB, HB, XpB, nkb, nullptr, COUNT ? r.counts_b : nullptr, st));
+  EJ_RC(prep_and_aux(ctx, w, SA, SB, nullptr, nkb, r.counter(COUNT), r, st));
   const Operand A{XpA, nA, padA}, B{self ? XpA : XpB, self ? nA : nB, self ? padA : padB};
   if (!batch_rows) return launch_join<COUNT>(ctx, w, own, A, B, self, nkb, eps, r, st);
   for (int b = 0; b < nbatches; ++b) {
@@ -2073,8 +2095,7 @@ int run_join_split(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, int64
     hipLaunchKernelGGL(k_norms_packed, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, XpA, XpB, n, pad, 3 * nkb, w.s, w.status + 1);
     EJ_TRY(hipGetLastError());
   }
-  EJ_RC(launch_aux(ctx, w.status, w.s, n, w.H, XpA, 3 * nkb, r.counter(COUNT), COUNT ? r.counts : nullptr, st));
-  EJ_RC(launch_aux(ctx, w.status, w.s, n, w.H, XpB, 3 * nkb, nullptr, nullptr, st));
+  EJ_RC(launch_aux(ctx, w.status, nullptr, AuxSet{w.s, n, pad, XpA, r.counts}, AuxSet{w.s, n, pad, XpB, nullptr}, 3 * nkb, nullptr, r.counter(COUNT), st));
   const Operand A{XpA, n, pad}, B{XpB, n, pad};
   return launch_join<COUNT>(ctx, w, true, A, B, true, 3 * nkb, eps, r, st);
 }
@@ -2088,16 +2109,11 @@ int run_join_prepared(ejoin_ctx* ctx, const ejoin_set* P, const uint16_t* XQ, in
   EJ_RC(ensure_workspace(ctx, padQ, pad_dims(d)));
   const Workspace& w = ctx->ws;
   const int nkb = k_blocks(d);
-  if (const int tile = small_tile(ctx, P->n, nQ, false, nkb))
-    return run_small<COUNT>(ctx, w, tile, PrepSet{nullptr, P->n, P->pad, 0, P->s, P->Xp, 0}, PrepSet{XQ, nQ, padQ, ldQ, w.s, w.Xp, 0}, P->max_bits,
-                            nkb, eps, r, st);
+  PrepSet SP{nullptr, P->n, P->pad, 0, P->s, P->Xp, 0}, SQ{XQ, nQ, padQ, ldQ, w.s, w.Xp, 0};
+  if (const int tile = small_tile(ctx, P->n, nQ, false, nkb)) return run_small<COUNT>(ctx, w, tile, SP, SQ, P->max_bits, nkb, eps, r, st);
   EJ_RC(begin_call(ctx, w, true, st));
-  EJ_RC(launch_norms(ctx, XQ, nQ, d, ldQ, w.s, w.status + 1, w.Xp, st));
-  hipLaunchKernelGGL(k_merge_max, dim3(1), dim3(64), 0, st, w.status + 1, P->max_bits);
-  EJ_TRY(hipGetLastError());
   // the augmentation rows of both sets are scaled to the largest norm of the two: those of the prepared set are rewritten
-  EJ_RC(launch_aux(ctx, w.status, P->s, P->n, P->H, P->Xp, nkb, r.counter(COUNT), COUNT ? r.counts : nullptr, st));
-  EJ_RC(launch_aux(ctx, w.status, w.s, nQ, w.H, w.Xp, nkb, nullptr, COUNT ? r.counts_b : nullptr, st));
+  EJ_RC(prep_and_aux(ctx, w, SP, SQ, P->max_bits, nkb, r.counter(COUNT), r, st));
   const Operand A{P->Xp, P->n, P->pad}, B{w.Xp, nQ, padQ};
   return launch_join<COUNT>(ctx, w, true, A, B, false, nkb, eps, r, st);
 }
@@ -2363,7 +2379,6 @@ int ejoin_set_create(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   set->d = d;
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&set->Xp), (size_t)packed_bytes(set->pad, pad_dims(d)));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&set->s), (size_t)set->pad * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&set->H), (size_t)set->pad * sizeof(uint4));
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&set->max_bits), 256);
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -2387,7 +2402,6 @@ int ejoin_set_destroy(ejoin_set* set) {
   DeviceGuard guard(set->ctx->device);
   if (set->Xp) (void)hipFree(set->Xp);
   if (set->s) (void)hipFree(set->s);
-  if (set->H) (void)hipFree(set->H);
   if (set->max_bits) (void)hipFree(set->max_bits);
   delete set;
   return EJOIN_OK;
@@ -2444,7 +2458,7 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   hipStream_t st = static_cast<hipStream_t>(stream);
   EJ_RC(begin_call(ctx, w, true, st));  // (no join kernel follows: the status block stays marked for a reset)
   EJ_RC(launch_norms(ctx, X, n, d, ld, w.s, w.status + 1, nullptr, st));
-  EJ_RC(launch_aux(ctx, w.status, w.s, n, w.H, nullptr, 0, nullptr, nullptr, st));
+  EJ_RC(launch_aux(ctx, w.status, nullptr, AuxSet{w.s, n, pad_rows(n), nullptr, nullptr}, AuxSet{}, 0, w.H, nullptr, st));
   const int slices = (k_blocks(d) + 1) / 2;  // (rows are padded to a multiple of 64 coordinates)
   auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
   if (2 * blocks(128) >= 3 * ctx->num_cu)  // (see the kernel)
