@@ -146,8 +146,8 @@ int ejoin_selfjoin_pairs_noalloc(ejoin_ctx* ctx, const uint16_t* X, int64_t n, i
  * hi.hi + lo.hi + hi.lo on the matrix cores (FP32 accumulation, 3 x the work of the FP16 join); norms,
  * threshold, result conventions, capacity / n_pairs / dist2 / counts and the data-range rule
  * (|x| <= 65504, s < 2^31) are those of ejoin_selfjoin_pairs / ejoin_selfjoin_count.  d <= 16384.
- * The workspace holds two re-laid-out copies of the split data, 12 * roundup(n,256) * roundup(d,64) bytes;
- * ejoin_reserve(ctx, 2 * n, 3 * roundup(d,64)) sizes it ahead of time. */
+ * The workspace holds the two halves of the split data, 4 * roundup(n,256) * (roundup(d,64) + 16) bytes;
+ * ejoin_reserve(ctx, n, 2 * roundup(d,64)) sizes it ahead of time (more is fine). */
 int ejoin_selfjoin_pairs_f32(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, int64_t ld32, float eps,
                              uint32_t* pairs, float* dist2, uint64_t capacity, uint64_t* n_pairs, void* stream);
 int ejoin_selfjoin_count_f32(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, int64_t ld32, float eps,

@@ -401,78 +401,109 @@ __global__ __launch_bounds__(256) void k_convert_f32(const float* __restrict__ X
 
 // Split-FP16 variant (higher accuracy for FP32 inputs).  Each FP32 coordinate is cut into two FP16
 // numbers, x ~ hi + lo with hi = fp16(x), lo = fp16(x - hi) (22 significant bits together), and the
-// inner product is taken as hi.hi + lo.hi + hi.lo (the lo.lo term is below the 22 bits kept).  That is
-// an ordinary inner product of the 3d-dimensional rows A' = [hi | lo | hi] and B' = [hi | hi | lo], so
-// the join kernel runs unchanged on two packed arrays: row operands come from A', column operands from
-// B'.  This kernel writes both arrays straight from the FP32 rows, in the packed k-block layout of
-// k_norms<true> (nkb blocks per part, 3 nkb blocks per array; rows n .. npad-1 and columns d .. are zero).
-// Thread t handles the 8 coordinates of one 16-byte chunk.
-__global__ void k_split_pack(const float* __restrict__ X32, int64_t n, int64_t npad, int32_t d, int64_t ld32, int nkb,
-                             uint4* __restrict__ XpA, uint4* __restrict__ XpB) {
-  const int blocks = 3 * nkb + 1;  // k-blocks per panel of either array
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t total = (int64_t)nkb * npad * 4;
-  if (t >= total) return;
-  const int p = (int)(t & 3);
-  const int64_t rk = t >> 2;
-  const int64_t kb = rk / npad, r = rk - kb * npad;
-  int64_t point;
-  int chunk;
-  stored_at(r, p, point, chunk);
-  const int k0 = (int)kb * KSLICE + (chunk << 3);  // first coordinate of the chunk stored here
-  half8 hi, lo;
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const float x = (point < n && k0 + k < d) ? X32[point * ld32 + k0 + k] : 0.f;
-    const _Float16 h = (_Float16)x;
-    float rest = x - (float)h;
-    asm volatile("" : "+v"(rest));  // the residual is an FP32 number: no fused subtract-convert
-    hi[k] = h;
-    lo[k] = (_Float16)rest;
-  }
-  const uint4 vh = __builtin_bit_cast(uint4, hi), vl = __builtin_bit_cast(uint4, lo);
-  const int64_t place = r * 4 + p;
-  const int64_t i0 = packed_index(place, (int)kb, blocks), i1 = packed_index(place, nkb + (int)kb, blocks),
-                i2 = packed_index(place, 2 * nkb + (int)kb, blocks);
-  XpA[i0] = vh;
-  XpA[i1] = vl;
-  XpA[i2] = vh;
-  XpB[i0] = vh;
-  XpB[i1] = vh;
-  XpB[i2] = vl;
-}
-
-// Norms for the split variant: s_i = A'_i . B'_i, accumulated by the same MFMA steps in the same
-// order as the join kernel accumulates a_ii (k-blocks in order, one 32-wide step per block), read
-// from the packed arrays.  One wavefront per 16 consecutive points, like k_norms.
-__global__ __launch_bounds__(256) void k_norms_packed(const uint4* __restrict__ XpA, const uint4* __restrict__ XpB, int64_t n,
-                                                      int64_t npad, int nkb_total, float* __restrict__ s,
-                                                      uint32_t* __restrict__ max_bits) {
+// inner product is taken as hi.hi + lo.hi + hi.lo (the lo.lo term is below the 22 bits kept): an ordinary inner product of the
+// 3d-dimensional rows A' = [hi | lo | hi] and B' = [hi | hi | lo].  The packed copy (the k-block layout of k_norms<true>) holds
+// hi and lo once, nkb blocks each; the join kernels take the k-blocks of A' and B' from them (split_block_a, split_block_b).
+//
+// One pass over the FP32 rows writes both and accumulates the norms s_i = A'_i . B'_i with the MFMA steps, and in the order, in
+// which the join accumulates a_ii; the second and third part of that order read the rows again, from the caches.  Bound by
+// memory.  Before, two copies of three parts each were written, 32 bytes of FP32 per thread and chunk, and the norms read back
+// from them with one atomic per 16 points: 122 us for 50,000 x 300, now 45.
+constexpr int split_block_a(int ks, int nkb) { return ks >= 2 * nkb ? ks - 2 * nkb : ks; }
+constexpr int split_block_b(int ks, int nkb) { return ks >= nkb ? ks - nkb : ks; }
+struct SplitArgs {
+  const float* X32;
+  int64_t n, npad, ld32;
+  int32_t d;
+  int nkb;
+  float* s;
+  uint4* Xp;           // 2 nkb + 1 k-blocks per panel
+  uint32_t* maxima;    // one per workgroup, or null:
+  uint32_t* max_bits;  // ... the largest of all
+  unsigned long long* counter;  // cleared, like the counts (may be null)
+  uint32_t* counts;
+};
+__global__ __launch_bounds__(512) void k_split_prep(const SplitArgs a) {
   const int lane = threadIdx.x & 63;
-  const int64_t blk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int64_t row0 = blk * 16;
-  if (row0 >= n) return;
-  const int g = lane >> 4;
-  const int64_t at = place_of(row0 + (lane & 15), g);  // (< npad: points past n are zero)
-  float4v acc = {0.f, 0.f, 0.f, 0.f};
-  for (int kb = 0; kb < nkb_total; ++kb) {
-    const int64_t off = packed_index(at, kb, nkb_total + 1);
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(as_half8(XpA[off]), as_half8(XpB[off]), acc, 0, 0, 0);
-  }
-  const int c = lane & 15;
-  uint32_t bits = 0;
-  if ((c >> 2) == g && row0 + c < n) {
-    const int want = c & 3;
-    float v = 0.f;
+  const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * NORM_POINTS;
+  if (blockIdx.x == 0 && threadIdx.x == 0 && a.counter) *a.counter = 0;
+  uint32_t most = 0;
+  if (row0 < a.npad) {
+    if (a.counts && lane < NORM_POINTS && row0 + lane < a.n) a.counts[row0 + lane] = 0;
+    const int c0 = (lane >> 4) * 8;  // first coordinate of this lane's chunk in a k-block
+    const float* p[2];
+    uint4* out[2];
+    bool valid[2];
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (r == want) v = acc[r];
-    s[row0 + c] = v;
-    bits = v < 0.f ? 0u : __float_as_uint(v);  // (a sum that rounds below zero counts as zero; NaN stays NaN)
-  }
+    for (int h = 0; h < 2; ++h) {
+      const int64_t own = row0 + 16 * h + (lane & 15);
+      valid[h] = own < a.n;
+      p[h] = a.X32 + (valid[h] ? own : a.n - 1) * a.ld32 + c0;
+      out[h] = a.Xp + packed_index(place_of(own, lane >> 4), 0, 2 * a.nkb + 1);
+    }
+    auto load = [&](int h, int kb, half8& hi, half8& lo) {
+      const int k0 = kb * KSLICE + c0;
+      const float* q = p[h] + kb * KSLICE;
+      float x[8];
+      if (k0 + 8 <= a.d) {
+        const float4u u = *reinterpret_cast<const float4u*>(q), v = *reinterpret_cast<const float4u*>(q + 4);
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, off));
-  if (lane == 0) atomicMax(max_bits, bits);
+        for (int k = 0; k < 4; ++k) {
+          x[k] = u[k];
+          x[4 + k] = v[k];
+        }
+      } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = k0 + k < a.d ? q[k] : 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float y = valid[h] ? x[k] : 0.f;
+        const _Float16 t = (_Float16)y;
+        float rest = y - (float)t;
+        asm volatile("" : "+v"(rest));  // the residual is an FP32 number: no fused subtract-convert
+        hi[k] = t;
+        lo[k] = (_Float16)rest;
+      }
+    };
+    float4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    auto steps = [&](auto part_c, int kb0, auto count_c) {
+      constexpr int PART = decltype(part_c)::value, K = decltype(count_c)::value;
+      half8 hi[2][K], lo[2][K];
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) load(h, kb0 + k, hi[h][k], lo[h][k]);
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(PART == 1 ? lo[h][k] : hi[h][k], PART == 2 ? lo[h][k] : hi[h][k], acc[h], 0, 0, 0);
+          if (PART == 0) {
+            out[h][(int64_t)(kb0 + k) * 1024] = __builtin_bit_cast(uint4, hi[h][k]);
+            out[h][(int64_t)(a.nkb + kb0 + k) * 1024] = __builtin_bit_cast(uint4, lo[h][k]);
+          }
+        }
+    };
+    auto part = [&](auto part_c) {
+      int kb = 0;
+      for (; kb + 2 <= a.nkb; kb += 2) steps(part_c, kb, std::integral_constant<int, 2>{});
+      if (kb < a.nkb) steps(part_c, kb, std::integral_constant<int, 1>{});
+    };
+    part(std::integral_constant<int, 0>{});
+    part(std::integral_constant<int, 1>{});
+    part(std::integral_constant<int, 2>{});
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float v = store_diagonal(acc[h], row0 + 16 * h, a.n, a.s);
+      most = max(most, v < 0.f ? 0u : __float_as_uint(v));  // (a sum that rounds below zero counts as zero; NaN stays NaN)
+    }
+  }
+  most = max_of_group(most);
+  if (threadIdx.x == 0) {
+    if (a.max_bits) atomicMax(a.max_bits, most);
+    else a.maxima[blockIdx.x] = most;
+  }
 }
 
 // Dense block of squared distances with the join's arithmetic: a workgroup of 2 x 2 wavefronts per TS x TS tile of the block,
@@ -701,7 +732,8 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
 // KEEP_A: the instance for tiles of exactly NSTAGE slices (96 < d <= 128), which leaves a row panel in the LDS across
 // the consecutive tiles that share it (see keep_a_cur); the other instance carries none of that logic.
 // DENSE (count mode): the instance whose rare path also handles regions with candidates in many lanes lane by lane.
-template <bool COUNT, bool KEEP_A, bool DENSE>
+// SPLIT: the k-blocks of the slices are those of a split-FP16 set (see k_split_prep).
+template <bool COUNT, bool KEEP_A, bool DENSE, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   // the largest norm of the call has been consumed by k_aux: cleared here for the next call
@@ -730,7 +762,9 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   const char* XbA = reinterpret_cast<const char*>(a.XpA);
   const char* XbB = reinterpret_cast<const char*>(a.XpB);
   // a panel's k-blocks (16 KB each) follow each other in memory: the data blocks, then the augmentation block
-  const int64_t panel_stride = (int64_t)(nsl + 1) * PANEL_BYTES;
+  const int third = SPLIT ? nsl / 3 : 0;
+  const int data_blocks = SPLIT ? 2 * third : nsl;
+  const int64_t panel_stride = (int64_t)(data_blocks + 1) * PANEL_BYTES;
   const int cw = wave & 3;
   const bool copier = wave >= 4;
   const uint32_t voff0 = lane * 16 + cw * 1024;
@@ -775,8 +809,8 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
     if (aug_copied) return;
     aug_copied = true;
 #endif
-    const char* ga = uniform_ptr(XbA + (int64_t)EJ_PANEL_A(I) * panel_stride + (int64_t)nsl * PANEL_BYTES);
-    const char* gb = uniform_ptr(XbB + (int64_t)EJ_PANEL_B(J) * panel_stride + (int64_t)nsl * PANEL_BYTES);
+    const char* ga = uniform_ptr(XbA + (int64_t)EJ_PANEL_A(I) * panel_stride + (int64_t)data_blocks * PANEL_BYTES);
+    const char* gb = uniform_ptr(XbB + (int64_t)EJ_PANEL_B(J) * panel_stride + (int64_t)data_blocks * PANEL_BYTES);
     copy16_to_lds<AUG_OFF>(lds0 + cw * 1024, ga, voff0);
     copy16_to_lds<AUG_OFF + AUG_PART_BYTES>(lds0 + cw * 1024, gb, voff0 + AUG_PART_BYTES);
   };
@@ -930,7 +964,12 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
     }
     pa += PANEL_BYTES;
     pb += PANEL_BYTES;
-    if (++iks == nsl) {
+    ++iks;
+    if constexpr (SPLIT) {
+      if (iks == third) pb -= (int64_t)third * PANEL_BYTES;           // B' = [hi | hi | lo]
+      if (iks == 2 * third) pa -= (int64_t)(2 * third) * PANEL_BYTES;  // A' = [hi | lo | hi]
+    }
+    if (iks == nsl) {
       iks = 0;
       ++ahead;
       const bool first_after = ahead == 1;
@@ -1410,6 +1449,8 @@ struct SmallArgs {
   const uint32_t* maxima;
   uint32_t nmaxima;
   const uint32_t* set_max;  // largest norm of a prepared set, or null
+  int data_blocks;          // k-blocks of data per panel
+  int nkb_split;            // split-FP16 set: k-blocks of each part (see k_split_prep); else 0x3FFFFFFF
 };
 
 // Tiles of TS x TS points, a workgroup of 2 x 2 wavefronts each (wave tile TS/2 x TS/2), several workgroups to a CU, which
@@ -1453,7 +1494,7 @@ __global__ __launch_bounds__(256, small_groups_per_cu<TS>()) void k_join_small(c
   uint32_t I = 0, J = 0;
   bool have = tc.next(I, J);
   if (!have) return;
-  const int64_t panel_stride = (int64_t)(nsl + 1) * PANEL_BYTES;
+  const int64_t panel_stride = (int64_t)(args.data_blocks + 1) * PANEL_BYTES;
   const uint32_t voff = lane * 16 + wave * 1024;
   const char *pa = nullptr, *pb = nullptr;
   auto uniform_ptr = [](const char* p) -> const char* {
@@ -1462,8 +1503,8 @@ __global__ __launch_bounds__(256, small_groups_per_cu<TS>()) void k_join_small(c
     return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
   };
   auto issue = [&](int ks, int stage) {  // slice ks of the tile at (pa, pb)
-    const char* ga = uniform_ptr(pa + (int64_t)ks * PANEL_BYTES);
-    const char* gb = uniform_ptr(pb + (int64_t)ks * PANEL_BYTES);
+    const char* ga = uniform_ptr(pa + (int64_t)split_block_a(ks, args.nkb_split) * PANEL_BYTES);
+    const char* gb = uniform_ptr(pb + (int64_t)split_block_b(ks, args.nkb_split) * PANEL_BYTES);
     const uint32_t at = __builtin_amdgcn_readfirstlane(lds0 + stage * ST_BYTES + wave * 1024);
     copy16_to_lds<0>(at, ga, voff);
     if constexpr (COPIES == 2) copy16_to_lds<4096>(at, ga, voff + 4096);
@@ -1931,7 +1972,7 @@ JoinArgs join_args(const Workspace& w, const Operand& A, const Operand& B, bool 
 // The join kernel on two packed operand sets whose augmentation blocks are in place.
 template <bool COUNT>
 int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, const Operand& B, bool self, int nslices, float eps,
-                const Results& r, hipStream_t st, uint32_t sb_row_begin = 0, uint32_t sb_row_end = 0xFFFFFFFFu) {
+                const Results& r, hipStream_t st, bool split = false, uint32_t sb_row_begin = 0, uint32_t sb_row_end = 0xFFFFFFFFu) {
   JoinArgs a = join_args(w, A, B, self, nslices, eps, r, TILE);
   a.sb_row_begin = sb_row_begin;
   a.sb_row_end = sb_row_end;
@@ -1955,8 +1996,9 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
   // now 212; 10^6 points, d = 128, S = 64: 107.4 ms against 109.2).
   constexpr int64_t DENSE_POINTS = 32768;
   const bool keep_a = a.nslices == NSTAGE, dense = COUNT && A.n <= DENSE_POINTS && B.n <= DENSE_POINTS;
-  void (*kernel)(JoinArgs) = keep_a ? (dense ? k_join<COUNT, true, COUNT> : k_join<COUNT, true, false>)
-                                    : (dense ? k_join<COUNT, false, COUNT> : k_join<COUNT, false, false>);
+  void (*kernel)(JoinArgs) = split    ? (dense ? k_join<COUNT, false, COUNT, true> : k_join<COUNT, false, false, true>)
+                             : keep_a ? (dense ? k_join<COUNT, true, COUNT, false> : k_join<COUNT, true, false, false>)
+                                      : (dense ? k_join<COUNT, false, COUNT, false> : k_join<COUNT, false, false, false>);
   hipLaunchKernelGGL(kernel, dim3(ctx->num_cu), dim3(THREADS), LDS_BYTES, st, a);
   EJ_TRY(hipGetLastError());
   if (own) ctx->ws_dirty = false;
@@ -1999,32 +2041,53 @@ int launch_small(ejoin_ctx* ctx, const SmallArgs& a, hipStream_t st) {
   return EJOIN_OK;
 }
 
-// A join by k_prep and k_join_small.  B.npad == 0: self-join of A.  A.X == nullptr: A is a prepared set (its largest norm: set_max).
+// The preparation of a split-FP16 join; groups: its number of workgroups.
+int launch_split_prep(ejoin_ctx* ctx, const SplitArgs& a, uint32_t& groups, hipStream_t st) {
+  const int64_t waves = a.npad / NORM_POINTS;
+  const int threads = norm_threads(waves);
+  groups = (uint32_t)((waves * 64 + threads - 1) / threads);
+  hipLaunchKernelGGL(k_split_prep, dim3(groups), dim3(threads), 0, st, a);
+  EJ_TRY(hipGetLastError());
+  return EJOIN_OK;
+}
+
+// A join by k_prep (split: k_split_prep) and k_join_small.  B.npad == 0: self-join of A.  A.X == nullptr: A is a prepared set (its largest norm: set_max).
 // Neither kernel reads or leaves anything in the status block but the status word.
 template <bool COUNT>
 int run_small(ejoin_ctx* ctx, const Workspace& w, int tile, PrepSet A, PrepSet B, const uint32_t* set_max, int nkb, float eps, const Results& r,
-              hipStream_t st) {
+              hipStream_t st, SplitArgs* split = nullptr) {
   const bool self = B.npad == 0;
   if (ctx->profiling) EJ_TRY(hipEventRecord(ctx->ev[0], st));
   ctx->last_status = w.status;
   ctx->last_stream = st;
-  PrepArgs p;
-  memset(&p, 0, sizeof(p));
-  p.maxima = reinterpret_cast<uint32_t*>(w.H);
-  p.counter = r.counter(COUNT);
-  p.counts = r.counts;
-  p.ncounts = A.n;
-  p.counts_b = r.counts_b;
-  p.ncounts_b = B.n;
-  EJ_RC(launch_prep(ctx, A, B, nkb, p, st));
-  const Operand OA{A.Xp, A.n, A.npad}, OB{self ? A.Xp : B.Xp, self ? A.n : B.n, self ? A.npad : B.npad};
+  uint32_t* maxima = reinterpret_cast<uint32_t*>(w.H);
   SmallArgs a;
-  a.j = join_args(w, OA, OB, self, nkb, eps, r, tile);
+  if (split) {
+    split->maxima = maxima;
+    split->counter = r.counter(COUNT);
+    split->counts = r.counts;
+    EJ_RC(launch_split_prep(ctx, *split, a.nmaxima, st));
+  } else {
+    PrepArgs p;
+    memset(&p, 0, sizeof(p));
+    p.maxima = maxima;
+    p.counter = r.counter(COUNT);
+    p.counts = r.counts;
+    p.ncounts = A.n;
+    p.counts_b = r.counts_b;
+    p.ncounts_b = B.n;
+    EJ_RC(launch_prep(ctx, A, B, nkb, p, st));
+    a.nmaxima = A.groups + B.groups;
+  }
+  const Operand OA{A.Xp, A.n, A.npad}, OB{self ? A.Xp : B.Xp, self ? A.n : B.n, self ? A.npad : B.npad};
+  const int nslices = split ? 3 * nkb : nkb;
+  a.j = join_args(w, OA, OB, self, nslices, eps, r, tile);
   a.sA = A.s;
   a.sB = self ? A.s : B.s;
-  a.maxima = p.maxima;
-  a.nmaxima = A.groups + B.groups;
+  a.maxima = maxima;
   a.set_max = set_max;
+  a.data_blocks = split ? 2 * nkb : nkb;
+  a.nkb_split = split ? nkb : 0x3FFFFFFF;
   if (ctx->profiling) {
     EJ_TRY(hipEventRecord(ctx->ev[1], st));
     EJ_TRY(hipEventRecord(ctx->ev[2], st));
@@ -2070,34 +2133,30 @@ int run_join(ejoin_ctx* ctx, const Workspace& w, bool own, const uint16_t* XA, i
       hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, st, w.status + 8, (int64_t)NUM_XCD, 0u);
       EJ_TRY(hipGetLastError());
     }
-    EJ_RC(launch_join<COUNT>(ctx, w, own, A, B, self, nkb, eps, r, st, batch_rows[b], batch_rows[b + 1]));
+    EJ_RC(launch_join<COUNT>(ctx, w, own, A, B, self, nkb, eps, r, st, false, batch_rows[b], batch_rows[b + 1]));
     EJ_TRY(hipMemcpyAsync(ctx->batch_count + b, r.n_pairs, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     EJ_TRY(hipEventRecord(ctx->batch_ev[b], st));
   }
   return EJOIN_OK;
 }
 
-// Split-FP16 self-join of FP32 rows (see k_split_pack): the same join kernel on 3 * nkb k-blocks.
+// Split-FP16 self-join of FP32 rows (see k_split_prep): the join kernels on 3 * nkb slices.
 template <bool COUNT>
 int run_join_split(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, int64_t ld32, float eps, const Results& r, hipStream_t st) {
   const int64_t pad = pad_rows(n);
-  EJ_RC(ensure_workspace(ctx, 2 * pad, 3 * pad_dims(d)));  // two packed arrays of 3 * nkb data blocks + 1 augmentation block each
+  EJ_RC(ensure_workspace(ctx, pad, 2 * pad_dims(d)));  // 2 * nkb data blocks + 1 augmentation block
   const Workspace& w = ctx->ws;
-  const int nkb = k_blocks(d);
-  uint4* XpA = w.Xp;
-  uint4* XpB = w.Xp + pad * (int64_t)(3 * nkb + 1) * 4;
+  const int nkb = (d + KSLICE - 1) / KSLICE;
+  SplitArgs p{X32, n, pad, ld32, d, nkb, w.s, w.Xp, nullptr, nullptr, nullptr, nullptr};
+  PrepSet S{nullptr, n, pad, 0, w.s, w.Xp, 0}, none{};
+  if (const int tile = small_tile(ctx, n, n, true, 3 * nkb)) return run_small<COUNT>(ctx, w, tile, S, none, nullptr, nkb, eps, r, st, &p);
   EJ_RC(begin_call(ctx, w, true, st));
-  {
-    const int64_t chunks = (int64_t)nkb * pad * 4;
-    hipLaunchKernelGGL(k_split_pack, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, st, X32, n, pad, d, ld32, nkb, XpA, XpB);
-    EJ_TRY(hipGetLastError());
-    const int64_t waves = (n + 15) / 16;
-    hipLaunchKernelGGL(k_norms_packed, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, XpA, XpB, n, pad, 3 * nkb, w.s, w.status + 1);
-    EJ_TRY(hipGetLastError());
-  }
-  EJ_RC(launch_aux(ctx, w.status, nullptr, AuxSet{w.s, n, pad, XpA, r.counts}, AuxSet{w.s, n, pad, XpB, nullptr}, 3 * nkb, nullptr, r.counter(COUNT), st));
-  const Operand A{XpA, n, pad}, B{XpB, n, pad};
-  return launch_join<COUNT>(ctx, w, true, A, B, true, 3 * nkb, eps, r, st);
+  p.max_bits = w.status + 1;
+  uint32_t groups = 0;
+  EJ_RC(launch_split_prep(ctx, p, groups, st));
+  EJ_RC(launch_aux(ctx, w.status, nullptr, AuxSet{w.s, n, pad, w.Xp, r.counts}, AuxSet{}, 2 * nkb, nullptr, r.counter(COUNT), st));
+  const Operand A{w.Xp, n, pad};
+  return launch_join<COUNT>(ctx, w, true, A, A, true, 3 * nkb, eps, r, st, true);
 }
 
 // Two-set join of a prepared point set with query points given as FP16 rows.
@@ -2121,7 +2180,7 @@ int run_join_prepared(ejoin_ctx* ctx, const ejoin_set* P, const uint16_t* XQ, in
 int check_f32(const ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, int64_t ld32) {
   if (!ctx || !X32) return EJOIN_EINVAL;
   if (n < 1 || n >= (int64_t)0xFFFFFFFFll - TILE || d < 1 || d > 65536 / 4 || ld32 < d) return EJOIN_EINVAL;
-  if ((int64_t)pad_rows(n) * (pad_dims(d) / KSLICE) * 4 / 256 > 0x7FFFFFFFll) return EJOIN_EUNSUPPORTED;  // grid of k_split_pack
+  if ((int64_t)pad_rows(n) * (pad_dims(d) / KSLICE) * 4 / 256 > 0x7FFFFFFFll) return EJOIN_EUNSUPPORTED;  // (beyond any device's memory)
   return EJOIN_OK;
 }
 
@@ -2195,8 +2254,10 @@ int ejoin_create(ejoin_ctx** out, int device) {
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&ctx->copy_stream, hipStreamNonBlocking);
   for (int i = 0; i < EJOIN_MAX_BATCHES && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&ctx->batch_ev[i], hipEventDisableTiming);
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&ctx->batch_count), EJOIN_MAX_BATCHES * sizeof(unsigned long long), hipHostMallocDefault);
-  for (void (*kernel)(JoinArgs) : {&k_join<false, false, false>, &k_join<false, true, false>, &k_join<true, false, false>, &k_join<true, true, false>,
-                                   &k_join<true, false, true>, &k_join<true, true, true>})
+  for (void (*kernel)(JoinArgs) :
+       {&k_join<false, false, false, false>, &k_join<false, true, false, false>, &k_join<false, false, false, true>, &k_join<true, false, false, false>,
+        &k_join<true, true, false, false>, &k_join<true, false, false, true>, &k_join<true, false, true, false>, &k_join<true, true, true, false>,
+        &k_join<true, false, true, true>})
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
   if (e != hipSuccess) {
     (void)hipGetLastError();

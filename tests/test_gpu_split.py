@@ -114,3 +114,32 @@ def test_split_join_rejects_bad_arguments_and_reports_out_of_range_data(ej):
     pairs, d2, npairs = ej.selfjoin_pairs_f32(big, 1.0, 100)
     torch.cuda.synchronize()
     assert ej.status() == 2 and int(npairs.cpu()[0]) == 0
+
+
+@pytest.mark.parametrize("d", [20, 33, 130, 400])
+def test_split_results_do_not_depend_on_the_kernel(ej, d):
+    """A set large enough for the general kernel, and its first 1,000 and 2,600 points, which the kernel of small problems takes
+    in tiles of 64 and of 128: the same pairs and counts among them, the same squared distances bit for bit."""
+    n = 14500
+    print(f"split kernels d={d}", flush=True)
+    X = data("uniform", n, d, seed=d)
+    X[700] = X[3]
+    eps = orc.select_eps_sample(X[:900].astype(np.float64), 12, 900)
+    Xd = torch.from_numpy(X).cuda()
+    pairs, d2, found = run_f32(ej, X, eps, 12 * n * 20)
+    assert found == pairs.shape[0]
+    for m in (1000, 2600):
+        want = (pairs < m).all(axis=1)
+        sub, sub_d2, sub_found = run_f32(ej, X[:m], eps, m * m)
+        assert sub_found == sub.shape[0]
+        kw, kg = orc.pair_keys(pairs[want]), orc.pair_keys(sub)
+        ow, og = np.argsort(kw), np.argsort(kg)
+        assert np.array_equal(kw[ow], kg[og]) and np.array_equal(d2[want][ow], sub_d2[og])
+        counts, total = ej.selfjoin_count_f32(Xd[:m], float(eps))
+        ns = sub[sub[:, 0] != sub[:, 1]]
+        hist = np.bincount(ns[:, 0], minlength=m) + np.bincount(ns[:, 1], minlength=m)
+        assert np.array_equal(counts.cpu().numpy().view(np.uint32), hist) and int(total.cpu()[0]) == ns.shape[0]
+    counts, total = ej.selfjoin_count_f32(Xd, float(eps))
+    ns = pairs[pairs[:, 0] != pairs[:, 1]]
+    hist = np.bincount(ns[:, 0], minlength=n) + np.bincount(ns[:, 1], minlength=n)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), hist) and int(total.cpu()[0]) == ns.shape[0]
