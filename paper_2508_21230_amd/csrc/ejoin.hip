@@ -222,11 +222,16 @@ __device__ __forceinline__ uint32_t norms_of_wave(int64_t row0, const uint16_t* 
 template <bool PACK>
 __global__ __launch_bounds__(512) void k_norms(const uint16_t* __restrict__ X, int64_t n, int64_t npad, int64_t ld, int k32steps,
                                                float* __restrict__ s, uint32_t* __restrict__ max_bits, uint4* __restrict__ Xp,
-                                               int blocks /* k-blocks per panel of Xp: k32steps + 1 */) {
+                                               int blocks /* k-blocks per panel of Xp: k32steps + 1 */,
+                                               uint32_t* __restrict__ maxima /* one per workgroup (may be null) */) {
   const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * NORM_POINTS;
   uint32_t most = 0;
   if (row0 < (PACK ? npad : n)) most = norms_of_wave<PACK>(row0, X, n, ld, k32steps, s, Xp, blocks);
   if (max_bits) merge_max(most, max_bits);
+  if (maxima) {
+    most = max_of_group(most);
+    if (threadIdx.x == 0) maxima[blockIdx.x] = most;
+  }
 }
 
 // Rows past the end of the data set carry -60000 c in place of -s/2 (at least the largest norm of the
@@ -293,6 +298,8 @@ struct AuxArgs {
   AuxSet a, b;  // (b.npad = 0: one set)
   uint32_t* status_and_max;
   const uint32_t* set_max;  // largest norm of a prepared set, or null
+  const uint32_t* maxima;   // dense-tile call: largest norms, one per workgroup of k_norms (else the status block holds the largest)
+  uint32_t nmaxima;
   uint4* H;                 // rows of set a for the dense-tile kernel, or null
   int aug_kb;               // k-block of the augmentation operands = data k-blocks of a panel
   unsigned long long* counter;
@@ -303,9 +310,16 @@ __global__ __launch_bounds__(256) void k_aux(const AuxArgs args) {
   const AuxSet& set = second ? args.b : args.a;
   const int64_t i = (int64_t)(blockIdx.x - (second ? groups_a : 0u)) * 256 + threadIdx.x, n = set.n;
   const float* s = set.s;
-  uint32_t mb = args.status_and_max[1];
-  if (args.set_max) mb = max(mb, *args.set_max);
-  if (blockIdx.x == 0) {
+  uint32_t mb;
+  if (args.maxima) {
+    mb = 0;
+    for (uint32_t q = threadIdx.x; q < args.nmaxima; q += 256) mb = max(mb, args.maxima[q]);
+    mb = max_of_group(mb);
+  } else {
+    mb = args.status_and_max[1];
+    if (args.set_max) mb = max(mb, *args.set_max);
+  }
+  if (blockIdx.x == 0 && !args.maxima) {
     if (threadIdx.x < 8) args.status_and_max[8 + threadIdx.x] = 0;
     if (threadIdx.x == 8 && args.counter) *args.counter = 0;
   }
@@ -1718,7 +1732,7 @@ namespace {
 // Device memory one call works in: either the context's own (grown on demand) or a carving of the static scratch.
 struct Workspace {
   uint32_t* status;  // status block, 64 words (see k_reset)
-  float* s;          // norms (4 B per point)
+  float* s;          // norms (4 B per point); the context's own: then one maximum per NORM_POINTS points (dense-tile call)
   uint4* H;          // augmentation rows (16 B per point, padded to a multiple of TILE)
   uint4* Xp;         // packed copy of X plus the augmentation k-block
 };
@@ -1811,7 +1825,7 @@ int ensure_workspace(ejoin_ctx* ctx, int64_t rows, int64_t dpad) {
       w.H = nullptr;
       ctx->s_cap = 0;
     }
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&w.s), (size_t)rows * sizeof(float));
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&w.s), (size_t)(rows + rows / NORM_POINTS) * sizeof(float));  // (+ maxima)
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&w.H), (size_t)rows * sizeof(uint4));
     if (e != hipSuccess) {
       (void)hipGetLastError();
@@ -1861,13 +1875,14 @@ int norm_threads(int64_t waves) { return waves >= 2048 ? 512 : (waves >= 512 ? 2
 
 // Norms of X into s (and, with Xp given, the packed copy of X); max_bits may be null.
 int launch_norms(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, int64_t ld, float* s, uint32_t* max_bits, uint4* Xp,
-                 hipStream_t st) {
+                 hipStream_t st, uint32_t* maxima = nullptr, uint32_t* nmaxima = nullptr) {
   const int64_t npad = pad_rows(n);
   const int64_t waves = ((Xp ? npad : n) + NORM_POINTS - 1) / NORM_POINTS;
   const int threads = norm_threads(waves);
   const dim3 grid((unsigned)((waves * 64 + threads - 1) / threads));
-  if (Xp) hipLaunchKernelGGL(k_norms<true>, grid, dim3(threads), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, k_blocks(d) + 1);
-  else hipLaunchKernelGGL(k_norms<false>, grid, dim3(threads), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, 0);
+  if (nmaxima) *nmaxima = grid.x;
+  if (Xp) hipLaunchKernelGGL(k_norms<true>, grid, dim3(threads), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, k_blocks(d) + 1, maxima);
+  else hipLaunchKernelGGL(k_norms<false>, grid, dim3(threads), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, 0, maxima);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }
@@ -1891,9 +1906,9 @@ int launch_prep(ejoin_ctx* ctx, PrepSet& A, PrepSet& B, int nkb, PrepArgs& p, hi
 
 // What follows the norms of a k_join call, for both its sets in one launch (B.npad == 0: one set): the augmentation operands, from
 // the norms and the largest norm of all (in the status block; set_max: that of a prepared set), and what the call needs zero.
-int launch_aux(ejoin_ctx* ctx, uint32_t* status, const uint32_t* set_max, const AuxSet& A, const AuxSet& B, int data_blocks, uint4* H,
+int launch_aux(ejoin_ctx* ctx, uint32_t* status, const uint32_t* set_max, const AuxSet& A, const AuxSet& B, int data_blocks,
                unsigned long long* counter, hipStream_t st) {
-  const AuxArgs a{A, B, status, set_max, H, data_blocks, counter};
+  const AuxArgs a{A, B, status, set_max, nullptr, 0, nullptr, data_blocks, counter};
   hipLaunchKernelGGL(k_aux, dim3((unsigned)((A.npad + B.npad) / 256)), dim3(256), 0, st, a);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
@@ -2112,7 +2127,7 @@ int prep_and_aux(ejoin_ctx* ctx, const Workspace& w, PrepSet A, PrepSet B, const
   memset(&p, 0, sizeof(p));
   p.max_bits = w.status + 1;
   EJ_RC(launch_prep(ctx, A, B, nkb, p, st));
-  return launch_aux(ctx, w.status, set_max, AuxSet{A.s, A.n, A.npad, A.Xp, r.counts}, AuxSet{B.s, B.n, B.npad, B.Xp, r.counts_b}, nkb, nullptr, counter, st);
+  return launch_aux(ctx, w.status, set_max, AuxSet{A.s, A.n, A.npad, A.Xp, r.counts}, AuxSet{B.s, B.n, B.npad, B.Xp, r.counts_b}, nkb, counter, st);
 }
 
 // Join of FP16 rows in workspace w (the context's own, or a carving of the static scratch).  XB == nullptr: self-join of XA.
@@ -2159,7 +2174,7 @@ int run_join_split(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, int64
   p.max_bits = w.status + 1;
   uint32_t groups = 0;
   EJ_RC(launch_split_prep(ctx, p, groups, st));
-  EJ_RC(launch_aux(ctx, w.status, nullptr, AuxSet{w.s, n, pad, w.Xp, r.counts}, AuxSet{}, 2 * nkb, nullptr, r.counter(COUNT), st));
+  EJ_RC(launch_aux(ctx, w.status, nullptr, AuxSet{w.s, n, pad, w.Xp, r.counts}, AuxSet{}, 2 * nkb, r.counter(COUNT), st));
   const Operand A{w.Xp, n, pad};
   return launch_join<COUNT>(ctx, w, true, A, A, true, 3 * nkb, eps, r, st, true);
 }
@@ -2522,9 +2537,14 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   EJ_RC(ensure_workspace(ctx, pad_rows(n), 0));
   const Workspace& w = ctx->ws;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  EJ_RC(begin_call(ctx, w, true, st));  // (no join kernel follows: the status block stays marked for a reset)
-  EJ_RC(launch_norms(ctx, X, n, d, ld, w.s, w.status + 1, nullptr, st));
-  EJ_RC(launch_aux(ctx, w.status, nullptr, AuxSet{w.s, n, pad_rows(n), nullptr, nullptr}, AuxSet{}, 0, w.H, nullptr, st));
+  ctx->last_status = w.status;
+  ctx->last_stream = st;
+  // (no atomics on the status block: its state between calls is left as it is)
+  uint32_t* maxima = reinterpret_cast<uint32_t*>(w.s + ctx->s_cap);
+  AuxArgs aux{AuxSet{w.s, n, pad_rows(n), nullptr, nullptr}, AuxSet{}, w.status, nullptr, maxima, 0, w.H, 0, nullptr};
+  EJ_RC(launch_norms(ctx, X, n, d, ld, w.s, nullptr, nullptr, st, maxima, &aux.nmaxima));
+  hipLaunchKernelGGL(k_aux, dim3((unsigned)(aux.a.npad / 256)), dim3(256), 0, st, aux);
+  EJ_TRY(hipGetLastError());
   const int slices = (k_blocks(d) + 1) / 2;  // (rows are padded to a multiple of 64 coordinates)
   auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
   if (2 * blocks(128) >= 3 * ctx->num_cu)  // (see the kernel)
