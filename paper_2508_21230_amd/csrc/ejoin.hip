@@ -757,7 +757,7 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
   const int r16 = lane & 15, g = lane >> 4;
-  const int nsl = a.nslices;       // slices per tile (nsl >= 2: d is padded to 64)
+  const int nsl = a.nslices;       // slices per tile (at least 2)
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   // the constant chunks of the augmentation step (made visible by the barrier of the prologue)
   if (tid < 8) {
@@ -956,7 +956,7 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   int ahead = 0;
   bool issue_live = true;       // the issue cursor points at real work
   // KEEP_A (a tile has exactly as many slices as the ring has stages, 96 < d <= 128): slice ks of every tile lands in
-  // stage ks.  Three of four consecutive tiles of a workgroup have the same row panel (tile_cursor.h): the A half of
+  // stage ks.  The consecutive tiles of a workgroup in a band have the same row panel (tile_cursor.h): the A half of
   // each stage then already holds what the next tile needs, and the copies of its A panel are left out (NCOPY / 2 per
   // slice instead of NCOPY; the counted waits are told through the flags of the tile being issued, the tile being
   // computed and the one after it).
