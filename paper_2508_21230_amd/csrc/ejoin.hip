@@ -737,6 +737,19 @@ __device__ __forceinline__ void add_region_counts(uint32_t hit, uint32_t* rows, 
     }
   }
 }
+// The counters of a wave tile (128 rows from i0, 64 columns from j0) to the result, one atomic per row and column; zero again after.
+__device__ __forceinline__ void send_region_counts(uint32_t* counters, uint32_t lane, const JoinArgs& a, uint32_t i0, uint32_t j0) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  for (int q = 0; q < 3; ++q) {
+    const uint32_t c = counters[64 * q + lane];
+    if (c) {
+      counters[64 * q + lane] = 0;
+      if (q < 2) atomicAdd(&a.counts[i0 + 64 * q + lane], c);
+      else if (a.self) atomicAdd(&a.counts[j0 + lane], c);
+      else if (a.counts_b) atomicAdd(&a.counts_b[j0 + lane], c);
+    }
+  }
+}
 __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) x += (uint32_t)__shfl_xor((int)x, off);
@@ -907,7 +920,7 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
     fill = 0;
     dirty = true;
   };
-  if constexpr (DENSE)  // (count mode stages nothing: the area holds the counters of the dense path, 128 rows and 64 columns)
+  if constexpr (COUNT)  // (count mode stages nothing: the area holds the counters of dense wave tiles, 128 rows and 64 columns)
     for (int q = 0; q < 3; ++q) stg[64 * q + lane] = 0;
   // appends one entry per lane of `mask` to the staging area
   auto append = [&](unsigned long long mask, bool pass, uint32_t i, uint32_t j, uint32_t d2_bits) {
@@ -1240,7 +1253,8 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
       uint32_t todo = blocks_hit;  // regions not (completely) queued yet
       uint32_t taken = 0;          // lanes of the first of them that are
       uint32_t dense = 0;          // (DENSE) regions with candidates in many lanes
-      while (todo) {
+      // again_c: a filling after the first
+      auto fill_queue = [&](auto again_c, uint32_t& todo, uint32_t& taken) -> uint32_t {
         uint32_t qfill = 0;
         uint32_t now = todo;
 #pragma unroll
@@ -1250,7 +1264,12 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
 #ifdef EJOIN_ABL_NOPREFILTER
           const bool has = true;
 #else
-          const bool has = least[b] <= thr_bits;
+          bool has = least[b] <= thr_bits;
+          if constexpr (decltype(again_c)::value) {
+            uint32_t h = has;
+            asm volatile("" : "+v"(h));  // (else what both fillings compute is moved ahead of the first, for all eight regions)
+            has = h != 0;
+          }
 #endif
           const unsigned long long lanes = __ballot(has);
           if (DENSE && __popcll(lanes) >= DENSE_LANES) {
@@ -1279,6 +1298,9 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
             now = 0;
           }
         }
+        return qfill;
+      };
+      auto drain_queue = [&](uint32_t qfill, auto lds_c) {  // lds_c: (count mode) into the counters in the LDS
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         const uint32_t nnA = (uint32_t)a.nA, nnB = (uint32_t)a.nB;
         // tiles in which a value that passes may not be a result: on the diagonal, or with rows or columns past the end
@@ -1294,18 +1316,48 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
           const unsigned long long mask = __ballot(pass);
           if (!mask) continue;
           if (COUNT) {
-            if (pass) {
-              atomicAdd(&a.counts[i], 1u);
-              if (a.self) atomicAdd(&a.counts[j], 1u);
-              else if (a.counts_b) atomicAdd(&a.counts_b[j], 1u);
+            if constexpr (decltype(lds_c)::value) {
+              if (pass) {
+                atomicAdd(stg + (at & 0xFFFFu), 1u);
+                atomicAdd(stg + 128 + (at >> 16), 1u);
+              }
+            } else {
+              if (pass) {
+                atomicAdd(&a.counts[i], 1u);
+                if (a.self) atomicAdd(&a.counts[j], 1u);
+                else if (a.counts_b) atomicAdd(&a.counts_b[j], 1u);
+              }
+              dirty = true;
             }
             hits += __popcll(mask);
-            dirty = true;
           } else {
             append(mask, pass, i, j, __float_as_uint(fmaxf(-2.f * x, 0.f)));
           }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      };
+      if constexpr (COUNT && !DENSE) {
+        if (todo) {
+          uint32_t qfill = fill_queue(F_{}, todo, taken);
+          if (!todo) {
+            drain_queue(qfill, F_{});
+          } else {
+            // A dense wave tile: more candidates than the queue takes.  Its hits share rows and columns, and one global atomic per
+            // hit and side is what such counts are bound by (28 10^9 a second), so they are added up in the LDS first.  Against
+            // global atomics (and, in brackets, the ballot per register before the queue): 33,000 points, d = 128, S = 1,500
+            // 2,230 (1,980) us, now 700; S = 4,000 5.4 (4.6) ms, now 1.0; 200,000 x 600, d = 384, S = 5,000 1,100 (750) us, now 290.
+            // Wave tiles whose candidates fit the queue go on as they did: 10^6 points, d = 128, S = 64 109 ms on both.
+            for (;;) {
+              drain_queue(qfill, T_{});
+              if (!todo) break;
+              qfill = fill_queue(T_{}, todo, taken);
+            }
+            send_region_counts(stg, l, a, I * TILE + wm * 128, J * TILE + wn * 64);
+            dirty = true;
+          }
+        }
+      } else {
+        while (todo) drain_queue(fill_queue(F_{}, todo, taken), F_{});
       }
       if (DENSE && dense) {
         // Every lane looks at its own registers: a bit mask of those that pass, whose numbers per row and column are added up in
@@ -1336,16 +1388,7 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
           hits += wave_sum(__popc(hit));
           add_region_counts(hit, stg + il, stg + 128 + jl);
         } while (dense);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        for (int q = 0; q < 3; ++q) {  // 128 rows, 64 columns
-          const uint32_t c = stg[64 * q + l];
-          if (c) {
-            stg[64 * q + l] = 0;
-            if (q < 2) atomicAdd(&a.counts[I * TILE + wm * 128 + 64 * q + l], c);
-            else if (a.self) atomicAdd(&a.counts[J * TILE + wn * 64 + l], c);
-            else if (a.counts_b) atomicAdd(&a.counts_b[J * TILE + wn * 64 + l], c);
-          }
-        }
+        send_region_counts(stg, l, a, I * TILE + wm * 128, J * TILE + wn * 64);
         dirty = true;
       }
       // The stores and atomics of the path count on vmcnt like the copies, but complete in any order: the counted
@@ -2010,10 +2053,12 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
     EJ_TRY(hipEventRecord(ctx->ev[1], st));
     EJ_TRY(hipEventRecord(ctx->ev[2], st));
   }
-  // Counts of sets of up to 32,768 points go to the instance for dense tiles.  A tile has 65,536 S / n hits at S neighbours: beyond
-  // that size even S = 512 leaves fewer candidates than the queue of the rare path is good for, and the instance's registers cost
-  // 2 to 4 % (30,000 points, d = 128: S = 512 675 us, now 309, S = 100 220 us, now 230; 14,000 points, d = 960, S = 512: 589 us,
-  // now 212; 10^6 points, d = 128, S = 64: 107.4 ms against 109.2).
+  // Counts of sets of up to 32,768 points go to the instance for dense tiles.  Points in random order have 65,536 S / n hits a tile
+  // at S neighbours: the smaller the set, the fuller its regions.  It is the better one from a few hundred neighbours on and the
+  // other one below (30,000 points, d = 128: S = 30 171 us against 163, S = 100 245 against 211, S = 512 318 against 364,
+  // S = 4,000 378 against 824); beyond 32,768 points few sets are that dense (10^6 points, S = 64: 109.2 ms against 107.4), and the
+  // other instance counts what dense tiles there are in the LDS, from its queue (100,000 points, d = 128, stored cluster by
+  // cluster, S = 900: 4.4 ms, now 1.4).
   constexpr int64_t DENSE_POINTS = 32768;
   const bool keep_a = a.nslices == NSTAGE, dense = COUNT && A.n <= DENSE_POINTS && B.n <= DENSE_POINTS;
   void (*kernel)(JoinArgs) = split    ? (dense ? k_join<COUNT, false, COUNT, true> : k_join<COUNT, false, false, true>)

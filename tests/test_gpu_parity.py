@@ -732,3 +732,36 @@ def test_counts_of_dense_tiles(ej, d, share):
     assert int(own.cpu()) <= nq and int(ct.cpu()[0]) == int(cp.long().sum().cpu()) == int(cq.long().sum().cpu())
     assert int((cp.long() - full.sum(dim=1)).abs().max().cpu()) <= 1 and int((cq.long() - full.sum(dim=0)).abs().max().cpu()) <= 1
     assert torch.equal(cp[: n - nq].long(), full.sum(dim=1)[: n - nq]) and k.numel() == nq
+
+
+@pytest.mark.parametrize("d,share", [(50, 0.0005), (50, 0.02), (128, 0.0005), (128, 0.003), (128, 0.02), (128, 0.3), (128, 1.0), (200, 0.02)])
+def test_counts_of_dense_tiles_of_large_sets(ej, d, share):
+    """More than 32,768 points: the instance whose wave tiles count from the queue, directly or, once their candidates overflow it,
+    in the LDS.  Some tiles of each kind (share 0.0005: about four candidates a wave tile; the near-duplicates stored next to each
+    other fill tiles on the diagonal), all of them full, and an epsilon that reaches the marker of the rows past the end."""
+    print(f"dense counts of a large set d={d} share={share}", flush=True)
+    n, nq = 33001, 700
+    rng = np.random.default_rng(d)
+    X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    X[5000:5600] = X[5000]
+    X[n - 300:] = X[n - 300]
+    P = orc.decode(X[:700])
+    eps = np.float32(100.0) if share == 1.0 else orc.eps_for_pair_rank(orc.all_pairs_dist2(P), int(share * 700 * 699 / 2))
+    Xd = dev(pad(X, (d + 63) // 64 * 64))
+    e2 = float(np.float32(eps) * np.float32(eps))
+    want, upper = torch.zeros(n, dtype=torch.int64, device="cuda"), torch.zeros(n, dtype=torch.int64, device="cuda")
+    rows = torch.arange(n, device="cuda")
+    for r in range(0, n, 2000):
+        h = min(2000, n - r)
+        hit = (ej.dist2_tile(Xd, r, 0, h, n, d=d) <= e2) & (rows[None, :] > rows[r:r + h, None])
+        upper[r:r + h] += hit.sum(dim=1)
+        want += hit.sum(dim=0)
+    counts, total = ej.selfjoin_count(Xd, float(eps), d=d)
+    assert torch.equal(counts.long(), want + upper) and int(total.cpu()[0]) == int(upper.sum().cpu())
+    # two sets, both ways round: query points that are none of the points
+    Q = rng.random((nq, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    both = dev(pad(np.concatenate([X, Q]), (d + 63) // 64 * 64))
+    hit = torch.cat([ej.dist2_tile(both, r, n, min(2000, n - r), nq, d=d) <= e2 for r in range(0, n, 2000)])
+    for a, b, h in ((both[:n], both[n:].clone(), hit), (both[n:].clone(), both[:n], hit.T)):
+        cp, cq, ct = ej.join_count(a, b, float(eps), d=d)
+        assert torch.equal(cp.long(), h.sum(dim=1)) and torch.equal(cq.long(), h.sum(dim=0)) and int(ct.cpu()[0]) == int(hit.sum().cpu())

@@ -143,3 +143,25 @@ def test_split_results_do_not_depend_on_the_kernel(ej, d):
     ns = pairs[pairs[:, 0] != pairs[:, 1]]
     hist = np.bincount(ns[:, 0], minlength=n) + np.bincount(ns[:, 1], minlength=n)
     assert np.array_equal(counts.cpu().numpy().view(np.uint32), hist) and int(total.cpu()[0]) == ns.shape[0]
+
+
+@pytest.mark.parametrize("d,S", [(20, 1500), (33, 40), (160, 900)])
+def test_split_counts_of_large_sets(ej, d, S):
+    """More than 32,768 points, one, two and five k-blocks a part, wave tiles whose candidates fit the queue and ones that overflow it
+    (the points are stored cluster by cluster): counts = histogram of the pairs."""
+    n = 33100
+    print(f"split counts of a large set d={d} S={S}", flush=True)
+    rng = np.random.default_rng(d)
+    ids = np.sort(rng.integers(0, 33, size=n))
+    X = (rng.random((33, d), dtype=np.float32)[ids] + np.float32(0.03) * rng.standard_normal((n, d)).astype(np.float32)).astype(np.float32)
+    take = np.sort(rng.choice(n, size=1500, replace=False))
+    eps = orc.select_eps_sample(X[take].astype(np.float64), S, n)
+    Xd = torch.from_numpy(X).cuda()
+    pairs, d2, npairs = ej.selfjoin_pairs_f32(Xd, float(eps), 2 * n * S)
+    found = int(npairs.cpu()[0])
+    assert ej.status() == 0 and n < found <= 2 * n * S
+    ns = pairs[:found].long()
+    ns = ns[ns[:, 0] != ns[:, 1]]
+    hist = torch.bincount(ns[:, 0], minlength=n) + torch.bincount(ns[:, 1], minlength=n)
+    counts, total = ej.selfjoin_count_f32(Xd, float(eps))
+    assert torch.equal(counts.long(), hist) and int(total.cpu()[0]) == ns.shape[0]
