@@ -179,54 +179,65 @@ __device__ __forceinline__ float store_diagonal(const float4v& acc, int64_t row0
 // Bound by memory; what it takes is enough loads in flight (four k-blocks of two halves per wavefront) and few atomics: with
 // 16 points per wavefront and one atomic each it ran at 0.7 TB/s on 10^6 x 128 (725 us with k_aux, now 94 + 12: 5.4 TB/s) and
 // at 1.9 TB/s on 3 10^5 x 384 (244 us, now 86).
+// HALVES = 1: 16 points per wavefront.  That is better where there is neither a copy to write nor a largest norm to fold: no atomics
+// to save, so more and smaller workgroups (of one wavefront), and two k-blocks (d <= 64) are loaded together.  With 32 points,
+// one k-block after the other: 10^6 x 64 26.5 us, now 19.6 (16 points, workgroups of 256, one k-block after the other, as
+// before: 23.8); 10^5 x 512 18.4, now 16.1 (17.9).
 constexpr int NORM_POINTS = 32;  // points per wavefront
-template <bool PACK>  // returns the pattern of this lane's largest norm
+template <bool PACK, int HALVES = 2>  // returns the pattern of this lane's largest norm
 __device__ __forceinline__ uint32_t norms_of_wave(int64_t row0, const uint16_t* __restrict__ X, int64_t n, int64_t ld, int k32steps,
                                                   float* __restrict__ s, uint4* __restrict__ Xp, int blocks) {
   const int lane = threadIdx.x & 63;
-  const int64_t own[2] = {row0 + (lane & 15), row0 + 16 + (lane & 15)};
-  const half8* p[2];
-  uint4* out[2];
-  bool valid[2];
+  int64_t own[HALVES];
+  const half8* p[HALVES];
+  uint4* out[HALVES];
+  bool valid[HALVES];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
+  for (int h = 0; h < HALVES; ++h) {
+    own[h] = row0 + 16 * h + (lane & 15);
     valid[h] = own[h] < n;
     p[h] = reinterpret_cast<const half8*>(X + (valid[h] ? own[h] : n - 1) * ld) + (lane >> 4);
     if (PACK) out[h] = Xp + packed_index(place_of(own[h], lane >> 4), 0, blocks);
   }
-  float4v acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  float4v acc[HALVES];
+#pragma unroll
+  for (int h = 0; h < HALVES; ++h) acc[h] = float4v{0.f, 0.f, 0.f, 0.f};
   auto steps = [&](int k0, auto count_c) {
     constexpr int K = decltype(count_c)::value;
-    half8 a[2][K];
+    half8 a[HALVES][K];
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) a[h][k] = p[h][4 * (k0 + k)];
+      for (int h = 0; h < HALVES; ++h) a[h][k] = p[h][4 * (k0 + k)];
 #pragma unroll
     for (int k = 0; k < K; ++k)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
+      for (int h = 0; h < HALVES; ++h) {
         acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[h][k], a[h][k], acc[h], 0, 0, 0);
         if (PACK) out[h][(int64_t)(k0 + k) * 1024] = valid[h] ? __builtin_bit_cast(uint4, a[h][k]) : make_uint4(0, 0, 0, 0);
       }
   };
   int k = 0;
   for (; k + 4 <= k32steps; k += 4) steps(k, std::integral_constant<int, 4>{});
-  for (; k < k32steps; ++k) steps(k, std::integral_constant<int, 1>{});
+  if (k + 2 <= k32steps) {
+    steps(k, std::integral_constant<int, 2>{});
+    k += 2;
+  }
+  if (k < k32steps) steps(k, std::integral_constant<int, 1>{});
   uint32_t most = 0;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) most = max(most, __float_as_uint(store_diagonal(acc[h], row0 + 16 * h, n, s)));
+  for (int h = 0; h < HALVES; ++h) most = max(most, __float_as_uint(store_diagonal(acc[h], row0 + 16 * h, n, s)));
   return most;
 }
 
-template <bool PACK>
+template <bool PACK, int HALVES = 2>
 __global__ __launch_bounds__(512) void k_norms(const uint16_t* __restrict__ X, int64_t n, int64_t npad, int64_t ld, int k32steps,
                                                float* __restrict__ s, uint32_t* __restrict__ max_bits, uint4* __restrict__ Xp,
                                                int blocks /* k-blocks per panel of Xp: k32steps + 1 */,
                                                uint32_t* __restrict__ maxima /* one per workgroup (may be null) */) {
-  const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * NORM_POINTS;
+  const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (16 * HALVES);
   uint32_t most = 0;
-  if (row0 < (PACK ? npad : n)) most = norms_of_wave<PACK>(row0, X, n, ld, k32steps, s, Xp, blocks);
+  if (row0 < (PACK ? npad : n)) most = norms_of_wave<PACK, HALVES>(row0, X, n, ld, k32steps, s, Xp, blocks);
   if (max_bits) merge_max(most, max_bits);
   if (maxima) {
     most = max_of_group(most);
@@ -1920,6 +1931,11 @@ int norm_threads(int64_t waves) { return waves >= 2048 ? 512 : (waves >= 512 ? 2
 int launch_norms(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, int64_t ld, float* s, uint32_t* max_bits, uint4* Xp,
                  hipStream_t st, uint32_t* maxima = nullptr, uint32_t* nmaxima = nullptr) {
   const int64_t npad = pad_rows(n);
+  if (!Xp && !max_bits && !maxima && n < (1ll << 30)) {  // norms alone (a grid has fewer than 2^32 threads)
+    hipLaunchKernelGGL((k_norms<false, 1>), dim3((unsigned)((n + 15) / 16)), dim3(64), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, 0, maxima);
+    EJ_TRY(hipGetLastError());
+    return EJOIN_OK;
+  }
   const int64_t waves = ((Xp ? npad : n) + NORM_POINTS - 1) / NORM_POINTS;
   const int threads = norm_threads(waves);
   const dim3 grid((unsigned)((waves * 64 + threads - 1) / threads));

@@ -72,6 +72,27 @@ def test_norms_at_the_edges_of_their_workgroup_sizes(ej, n, d):
     assert found == n + n // 2 and np.all(d2 == 0.0) and ej.status() == 0
 
 
+@pytest.mark.parametrize("d", [40, 96, 128, 200, 224, 300])
+@pytest.mark.parametrize("n", [1, 15, 17, 47, 1040, 1041])
+def test_norms_alone_are_those_of_the_joins(ej, n, d):
+    """Norms alone (16 points a wavefront, k-blocks in fours, a pair and a single one) and those of the joins (32 points) are the same
+    numbers, bit for bit, and any part of the set has the norms it has in the whole."""
+    print(f"norms n={n} d={d}", flush=True)
+    rng = np.random.default_rng(n * d)
+    X = pad(rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16), (d + 63) // 64 * 64)
+    X[n // 2] = X[0]
+    Xd = dev(X)
+    s = ej.norms(Xd, d=d)
+    want = orc.norms(orc.decode(X))
+    assert np.all(np.abs(s.cpu().numpy().astype(np.float64) - want) <= (d / 16 + 1) * 2.0**-24 * want)  # (bound as above)
+    assert float(s[n // 2]) == float(s[0])
+    for r in (0, n // 3, n - 1):
+        assert torch.equal(ej.norms(Xd[r:], d=d), s[r:])
+    # the distance to the origin is the norm itself: computed from the join's own norm (accumulated with nothing else)
+    Y = torch.cat([Xd, torch.zeros_like(Xd[:1])])
+    assert torch.equal(ej.dist2_tile(Y, 0, n, n, 1, d=d).flatten(), s)
+
+
 # ------------------------------------------------------------------ Steps 2-3: dense tile
 @pytest.mark.parametrize("workload,n,i0,j0,rows,cols", [(1, 600, 0, 0, 600, 600), (3, 500, 37, 250, 301, 199), (4, 400, 390, 5, 10, 33)])
 def test_dist2_tile_against_oracle(ej, workload, n, i0, j0, rows, cols):
