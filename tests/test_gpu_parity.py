@@ -151,6 +151,30 @@ def test_dist2_tile_sizes_agree_bit_for_bit(ej, d, rows, cols):
         assert np.all(np.abs(got[int(r)].cpu().numpy().astype(np.float64) - want[0]) <= tol[0])
 
 
+@pytest.mark.parametrize("n", [524288, 524289, 800001])
+def test_dist2_tile_of_a_large_set_finds_its_largest_norm(ej, n):
+    """One largest norm per 256 points, folded by a launch of its own from 524,289 points on: whichever point has the largest, the
+    block's norm terms are scaled to it (a smaller scale would overflow), and an infinity anywhere is reported."""
+    print(f"dist2_tile largest norm n={n}", flush=True)
+    d = 24
+    rng = np.random.default_rng(n)
+    small = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    Xd = dev(pad(small, 64))
+    for at in (0, n // 2 + 7, n - 1):
+        X = Xd.clone()
+        X[at, :d] = torch.full((d,), 2000.0, dtype=torch.float16, device="cuda").view(torch.int16)  # s = 9.6e7 among s ~ 8
+        i0 = min(max(at - 20, 0), n - 40)
+        got = ej.dist2_tile(X, i0, i0, 40, 40, d=d).cpu().numpy().astype(np.float64)
+        P = orc.decode(X[i0:i0 + 40, :d].cpu().numpy().view(np.uint16))
+        want, s = orc.dist2_block(P, 0, 40, 0, 40), orc.norms(P)
+        assert ej.status() == 0
+        assert np.all(np.abs(got - want) <= parity.value_tolerance(want, s[:, None] + s[None, :], s.max()))
+    X = Xd.clone()
+    X[n - 1, 3] = 0x7C00  # infinity
+    ej.dist2_tile(X, 0, 0, 8, 8, d=d)
+    assert ej.status() == 2
+
+
 def test_join_dist2_is_bit_identical_to_dense_tile(ej):
     X, P, eps = small_case(2, 1500, 40)
     Xd = dev(X)
