@@ -186,15 +186,14 @@ class Case:
     def label(self):
         return (f"configs[{self.w - 1}]: n={self.n}, d={self.d}, {self.spec['kind']}, S={self.S}, eps={self.eps:.7g}, mode={self.mode}")
 
-    def flops(self, pkg):
-        dk = (self.d + 63) // 64 * 64
-        tiles = pkg.tiles_evaluated(self.n) if self.mode != "join" else pkg.tiles_evaluated2(self.n, self.nq)
+    def flops(self, ej):
+        edge, steps, tiles = ej.join_work(self.n, self.d, self.nq if self.mode == "join" else 0, self.mode == "split")
         derived = 2.0 * self.n * self.n * self.d if self.mode != "join" else 2.0 * self.n * self.nq * self.d
-        executed = 2.0 * 256 * 256 * dk * tiles * (3 if self.mode == "split" else 1)  # split: hi.hi + lo.hi + hi.lo
+        executed = 2.0 * edge * edge * 32 * steps * tiles
         return derived, executed, tiles
 
 
-def time_case(ej, pkg, case, steps, warmup, graph=False):
+def time_case(ej, case, steps, warmup, graph=False):
     """Times `steps` steps after `warmup`; returns the measurements of one configuration."""
     import torch
     for _ in range(warmup):
@@ -253,7 +252,7 @@ def time_case(ej, pkg, case, steps, warmup, graph=False):
     found = int(case.npairs.cpu()[0])
     ms = dt / steps * 1e3
     jm = sum(join_ms) / len(join_ms)
-    derived, executed, tiles = case.flops(pkg)
+    derived, executed, tiles = case.flops(ej)
     achieved = executed / (jm * 1e-3) / 1e12
     n, nq, mode = case.n, case.nq, case.mode
     clk = sampler.summary()
@@ -327,7 +326,7 @@ def main():
     single = args.workload is not None
     hw, hS, hmode = (args.workload, args.selectivity or datagen.WORKLOADS[args.workload]["selectivity"][0], args.mode) if single else HEADLINE
     head_case = Case(ej, hw, hS, hmode, n=args.n, eps=args.eps, queries=args.queries, prepared=args.prepared)
-    head = time_case(ej, pkg, head_case, args.steps, args.warmup, graph=args.graph)
+    head = time_case(ej, head_case, args.steps, args.warmup, graph=args.graph)
     traffic, traffic_source = measured_traffic((hw, hS, hmode)) if (args.n is None and args.eps is None) else (None, None)
     out = {
         "metric": "self-join distance TFLOPS (2*n^2*d / t)" if hmode != "join" else "two-set join distance TFLOPS (2*np*nq*d / t)",
@@ -431,7 +430,7 @@ def main():
                 c = Case(ej, w, S, mode, X=cache[w])
                 # small workloads: enough steps for a stable mean (a step of configs[0] is tens of microseconds)
                 steps = max(3, min(200, int(0.25 / max(1e-5, _estimate_s(c)))))
-                r = time_case(ej, pkg, c, steps, 1)
+                r = time_case(ej, c, steps, 1)
                 del c
                 torch.cuda.empty_cache()
             print(f"[bench] {r['workload']}: {r['ms_per_step']:.3f} ms/step, frac {r['frac']:.3f}", file=sys.stderr, flush=True)

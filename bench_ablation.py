@@ -156,7 +156,7 @@ def experiments(args):
         d2 = torch.empty(cap, dtype=torch.float32, device="cuda:0")
         npairs = torch.zeros(1, dtype=torch.int64, device="cuda:0")
         tiles = pkg.tiles_evaluated(n)
-        flop = 2.0 * 65536 * ((d + 63) // 64 * 64) * tiles
+        flop = 2.0 * 65536 * ((d + 31) // 32 * 32) * tiles
         # (no_copies computes every tile on the first tile's operands: compared output-free, epsilon = 0, so that the
         # rare path sees no more than the duplicates in either build)
         for name in ("full", "hot_panels", "full eps=0", "no_copies", "full", "hot_panels", "full eps=0", "no_copies"):

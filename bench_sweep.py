@@ -70,10 +70,10 @@ def main():
                 join.append(b)
             ej.set_profiling(False)
             jm, pm = min(join), min(prep)
-            tiles = pkg.tiles_evaluated(n)
+            edge, steps, tiles = ej.join_work(n, d)
             rec = {"n": n, "d": d, "join_ms": jm, "prep_ms": pm, "pairs_found": int(npairs.cpu()[0]),
                    "derived_tflops": 2.0 * n * n * d / ((jm + pm) * 1e-3) / 1e12,
-                   "executed_tflops": 2.0 * 256 * 256 * d * tiles / (jm * 1e-3) / 1e12}
+                   "executed_tflops": 2.0 * edge * edge * 32 * steps * tiles / (jm * 1e-3) / 1e12}
             rows[(n, d)] = rec
             print(json.dumps(rec), flush=True)
             del pairs

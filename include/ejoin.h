@@ -202,9 +202,9 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
 #define EJOIN_STATUS_NONFINITE 2
 int ejoin_status(ejoin_ctx* ctx, int* status);
 
-/* Number of 256 x 256 output tiles the Gram kernel evaluates for n points (upper triangle,
- * diagonal included): the executed matrix-core work is 2 * 256 * 256 * roundup(d,32) FLOP per tile (d > 32; 64 coordinates
- * for fewer). */
+/* Number of 256 x 256 output tiles of the distance matrix of n points (upper triangle, diagonal included).  These are what the
+ * Gram kernel evaluates, at 2 * 256 * 256 * roundup(d,32) matrix-core FLOP per tile (d > 32; 64 coordinates for fewer), except
+ * for small problems, which are worked in smaller tiles (ejoin_join_work of ejoin_bench.h tells which). */
 int64_t ejoin_tiles_evaluated(int64_t n);
 /* ... and for a two-set join of np x nq points (the full grid of tiles). */
 int64_t ejoin_tiles_evaluated2(int64_t np, int64_t nq);

@@ -80,6 +80,8 @@ def load_library(path: str | None = None) -> C.CDLL:
     lib.ejoin_set_profiling.argtypes = [vp, C.c_int]
     lib.ejoin_last_kernel_ms.restype = C.c_int
     lib.ejoin_last_kernel_ms.argtypes = [vp, C.POINTER(f32), C.POINTER(f32)]
+    lib.ejoin_join_work.restype = C.c_int
+    lib.ejoin_join_work.argtypes = [vp, i64, i64, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i64)]
     lib.ejoin_tiles_evaluated.restype = i64
     lib.ejoin_tiles_evaluated.argtypes = [i64]
     _libs[key] = lib
@@ -307,6 +309,13 @@ class EJoin:
         st = C.c_int()
         self._check(self._lib.ejoin_status(self._h, C.byref(st)), self._h)
         return int(st.value)
+
+    def join_work(self, n: int, d: int, nq: int = 0, split: bool = False):
+        """(tile edge, matrix-core steps per tile, tiles) of the join kernel for a problem of this size (ejoin_join_work)."""
+        edge, steps, tiles = C.c_int32(), C.c_int32(), C.c_int64()
+        self._check(self._lib.ejoin_join_work(self._h, int(n), int(nq), int(d), int(split), C.byref(edge), C.byref(steps),
+                                              C.byref(tiles)), self._h)
+        return edge.value, steps.value, tiles.value
 
     def set_profiling(self, on: bool):
         self._check(self._lib.ejoin_set_profiling(self._h, 1 if on else 0), self._h)

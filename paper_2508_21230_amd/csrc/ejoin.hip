@@ -2665,6 +2665,16 @@ int ejoin_last_kernel_ms(ejoin_ctx* ctx, float* prep_ms, float* join_ms) {
   return EJOIN_OK;
 }
 
+int ejoin_join_work(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int32_t split, int32_t* edge, int32_t* steps, int64_t* tiles) {
+  if (!ctx || !edge || !steps || !tiles || np < 1 || nq < 0 || d < 1 || d > 65536 || (split && nq)) return EJOIN_EINVAL;
+  *steps = split ? 3 * ((d + KSLICE - 1) / KSLICE) : k_blocks(d);
+  const int small = small_tile(ctx, np, nq ? nq : np, nq == 0, *steps);
+  *edge = small ? small : TILE;
+  const int64_t a = (np + *edge - 1) / *edge, b = (nq + *edge - 1) / *edge;
+  *tiles = nq ? a * b : a * (a + 1) / 2;
+  return EJOIN_OK;
+}
+
 int64_t ejoin_tiles_evaluated(int64_t n) {
   if (n < 1) return 0;
   const int64_t t = (n + TILE - 1) / TILE;

@@ -32,6 +32,7 @@ def test_host_only_entry_points():
     assert pkg.tiles_evaluated(1) == 1 and pkg.tiles_evaluated(256) == 1 and pkg.tiles_evaluated(257) == 3
     assert pkg.tiles_evaluated(1_000_000) == 3907 * 3908 // 2
     assert pkg.tiles_evaluated(0) == 0
+    assert lib.ejoin_join_work(None, 1000, 0, 128, 0, None, None, None) == -1
     # argument checks that need no device
     assert lib.ejoin_create(None, 0) == -1
     assert lib.ejoin_destroy(None) == -1

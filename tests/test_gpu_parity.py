@@ -606,6 +606,14 @@ def test_status_waits_for_the_stream_of_the_call(ej):
     assert int(total.cpu()[0]) == 0
 
 
+@pytest.mark.parametrize("n,nq,d,split,want", [(1000, 0, 96, False, (64, 3, 136)), (4096, 0, 128, False, (128, 4, 528)),
+                                               (100000, 0, 20, False, (256, 2, 391 * 392 // 2)), (200000, 500, 300, False, (256, 10, 782 * 2)),
+                                               (200, 70, 64, False, (64, 2, 8)), (50000, 0, 300, True, (256, 30, 196 * 197 // 2)),
+                                               (900, 0, 20, True, (64, 3, 120))])
+def test_join_work_names_the_tiles_of_a_problem(ej, n, nq, d, split, want):
+    assert ej.join_work(n, d, nq, split) == want
+
+
 # ------------------------------------------------------------------ the queue of the rare path
 @pytest.mark.parametrize("n,share", [(130, 0.02), (300, 0.1), (513, 0.3), (260, 0.7), (300, 1.0)])
 def test_candidate_queue_at_every_density(ej, n, share):
