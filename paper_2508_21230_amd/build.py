@@ -34,6 +34,9 @@ EXPERIMENTS = {
     "cycle_marks": ["-DEJOIN_EXP_CYCLE_MARKS"],
 }
 ABLATION_DIR = os.path.join(PKG, "ablation")
+#: the library with problems of every size going to the general join kernel, for its tests on sizes that the small kernel takes
+GENERAL_KERNEL = {"general_kernel": ["-DEJOIN_ONLY_K_JOIN"]}
+GENERAL_KERNEL_LIB = os.path.join(ABLATION_DIR, "libejoin_general_kernel.so")
 
 
 def _compile(out: str, defines=(), verbose: bool = False) -> str:
@@ -57,11 +60,11 @@ def build_library(verbose: bool = False) -> str:
 
 
 def build_ablations(verbose: bool = False) -> dict:
-    """Compile the ablation variants and the two timing-only experiment builds -> ablation/libejoin_<name>.so
-    (measurement only, see bench_ablation.py)."""
+    """Compile the ablation variants, the timing-only experiment builds (measurement only, see bench_ablation.py) and the tests'
+    build of the general kernel -> ablation/libejoin_<name>.so."""
     os.makedirs(ABLATION_DIR, exist_ok=True)
     return {name: _compile(os.path.join(ABLATION_DIR, f"libejoin_{name}.so"), defs, verbose)
-            for name, defs in {**ABLATIONS, **EXPERIMENTS}.items()}
+            for name, defs in {**ABLATIONS, **EXPERIMENTS, **GENERAL_KERNEL}.items()}
 
 
 if __name__ == "__main__":

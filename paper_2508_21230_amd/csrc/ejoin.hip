@@ -39,7 +39,7 @@ constexpr int KSLICE = 32;    // coordinates per LDS stage (64 B per row)
 // an XCD never re-aligned), EJOIN_ABL_NOPREFILTER (every block goes through the exact path).
 #if defined(EJOIN_ABL_NSTAGE) || defined(EJOIN_ABL_NOSWIZZLE) || defined(EJOIN_ABL_ROWMAJOR_TILES) || defined(EJOIN_ABL_NOALIGN) || \
     defined(EJOIN_ABL_NOPREFILTER) || defined(EJOIN_EXP_HOT_PANELS) || defined(EJOIN_EXP_NO_COPIES) || defined(EJOIN_EXP_CYCLE_MARKS)
-#define EJOIN_ONLY_K_JOIN  // these builds are about k_join: problems of every size go to it
+#define EJOIN_ONLY_K_JOIN  // these builds are about k_join: problems of every size go to it (as in the tests' build of that kernel)
 #endif
 #ifndef EJOIN_ABL_NSTAGE
 #define EJOIN_ABL_NSTAGE 4

@@ -13,9 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.fixture(scope="module")
-def ej():
-    import paper_2508_21230_amd as pkg
-    e = pkg.EJoin(0)
+def ej(request):
+    e = parity.open_context(request)
     yield e
     e.close()
 
@@ -116,6 +115,7 @@ def test_dist2_tile_against_oracle(ej, workload, n, i0, j0, rows, cols):
 
 
 # ------------------------------------------------------------------ the join, element by element
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("workload,n,S", [(1, 4096, 32), (2, 5000, 64), (3, 3000, 16), (4, 2500, 128), (5, 3333, 64)])
 def test_selfjoin_pairs_against_oracle(ej, workload, n, S):
     print(f"selfjoin_pairs workload={workload} n={n} S={S}", flush=True)
@@ -187,6 +187,7 @@ def test_join_dist2_is_bit_identical_to_dense_tile(ej):
     assert int((dense[iu] <= e2).sum()) + 1500 == found
 
 
+@parity.BOTH_KERNELS
 def test_count_mode_equals_histogram_of_pair_mode(ej):
     X, P, eps = small_case(5, 4000, 50)
     Xd = dev(X)
@@ -216,6 +217,7 @@ def test_run_to_run_same_set(ej):
 
 
 # ------------------------------------------------------------------ edge cases
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 255, 256, 257, 1000])
 @pytest.mark.parametrize("d", [64, 192])
 def test_edge_sizes(ej, n, d):
@@ -230,14 +232,18 @@ def test_edge_sizes(ej, n, d):
     parity.check_pair_sets(P, eps, pairs, d2, ora_pairs, ora_d2)
 
 
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("n,d", [(6500, 64), (7000, 40), (6200, 128), (5900, 192), (12000, 64), (11000, 24), (12000, 128), (11000, 100)])
 def test_more_tiles_than_workgroups_at_small_d(ej, n, d):
-    """Every workgroup walks several tiles (351 .. 406 tiles on 256 workgroups; 946 and 1128 in the last two cases,
-    four to five per workgroup).  At d <= 64 a tile has two slices and the copy pipeline runs three ahead: the copy
+    """In the general kernel every workgroup walks several tiles (300 .. 406 tiles on 256 workgroups; 946 and 1128 in the last four
+    cases, four to five per workgroup).  At d <= 64 a tile has two slices and the copy pipeline runs three ahead: the copy
     cursor works on the tile after the next one while the current one is still being computed.  At 96 < d <= 128 a tile
     has as many slices as the LDS ring has stages, and a row panel stays in the LDS across the consecutive tiles of a
     workgroup that share it (the last two cases: four to five tiles per workgroup, three of four with the row of the
-    tile before)."""
+    tile before).  The small kernel, which the library's own rule takes for all of these but (7000, 40), walks tiles of 128, two to
+    six per workgroup."""
+    edge, _, tiles = ej.join_work(n, d)
+    assert tiles > (256 if edge == 256 else 768)
     print(f"multi-tile n={n} d={d}", flush=True)
     rng = np.random.default_rng(n + d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
@@ -254,6 +260,7 @@ def test_more_tiles_than_workgroups_at_small_d(ej, n, d):
     assert int(total.cpu()[0]) == found - n
 
 
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("n,d", [(700, 2048), (300, 4096), (900, 1), (900, 33)])
 def test_extreme_dimensionalities(ej, n, d):
     print(f"extreme d: n={n} d={d}", flush=True)
@@ -268,6 +275,7 @@ def test_extreme_dimensionalities(ej, n, d):
     parity.check_pair_sets(P, eps, pairs, d2, ora_pairs, ora_d2)
 
 
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("kind", ["small", "mixed", "tiny_among_large"])
 def test_small_and_mixed_norms(ej, kind):
     """The norm term of the expansion is carried as three FP16 pieces scaled to the largest norm of the data:
@@ -312,6 +320,7 @@ def test_unpadded_d_with_zero_columns(ej):
     parity.check_pair_sets(P, eps, pairs, d2, ora_pairs, ora_d2)
 
 
+@parity.BOTH_KERNELS
 def test_eps_zero_and_duplicates(ej):
     X = datagen.generate(1, n=700)
     X[300] = X[5]
@@ -325,6 +334,7 @@ def test_eps_zero_and_duplicates(ej):
     assert np.array_equal(pairs[k], ora_pairs) and np.all(d2 == 0.0)
 
 
+@parity.BOTH_KERNELS
 def test_all_identical_points_and_eps_huge(ej):
     n = 300
     X = np.tile(datagen.generate(1, n=1), (n, 1))
@@ -338,6 +348,7 @@ def test_all_identical_points_and_eps_huge(ej):
     assert int(total.cpu()[0]) == n * (n - 1) // 2 and np.all(counts.cpu().numpy() == n - 1)
 
 
+@parity.BOTH_KERNELS
 def test_capacity_overflow_reports_found_and_writes_capacity(ej):
     X, P, eps = small_case(1, 1024, 32)
     Xd = dev(X)
@@ -371,6 +382,7 @@ def test_invalid_arguments_are_rejected(ej):
 
 
 # ------------------------------------------------------------------ data range
+@parity.BOTH_KERNELS
 def test_large_norms_use_the_scaled_split(ej):
     # Sift-like data: integer coordinates 0..218 in d = 128 (the paper's Sift10M has epsilon ~ 122-152,
     # data-set table); norms ~ 1e6 exceed the FP16 range of -s/2, so the augmentation rows are scaled.
@@ -390,6 +402,7 @@ def test_large_norms_use_the_scaled_split(ej):
     assert np.array_equal(dense[pairs[:, 0], pairs[:, 1]], d2)
 
 
+@parity.BOTH_KERNELS
 def test_status_reports_out_of_range_and_non_finite_input(ej):
     n, d = 600, 64
     X = datagen.generate(1, n=n)[:, :d].copy()
@@ -484,6 +497,7 @@ def test_centring_and_scaling_recover_accuracy_on_offset_data(ej):
     assert acc["centred"] > 0.99 and acc["centred_scaled"] >= acc["centred"] - 1e-3
 
 
+@parity.BOTH_KERNELS
 def test_join_calls_can_be_captured_in_a_hip_graph_and_replayed(ej):
     """With the workspace reserved a join enqueues kernels only (no allocation, no memset node), so a caller
     may capture it; every replay, on new data in the same buffers, must equal the eager result."""
@@ -615,10 +629,13 @@ def test_join_work_names_the_tiles_of_a_problem(ej, n, nq, d, split, want):
 
 
 # ------------------------------------------------------------------ the queue of the rare path
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("n,share", [(130, 0.02), (300, 0.1), (513, 0.3), (260, 0.7), (300, 1.0)])
 def test_candidate_queue_at_every_density(ej, n, share):
-    """From a lane here and there to every lane of every region holding candidates: less, exactly and several times what the
-    queue of a wavefront takes (16 lanes), with ragged edges and the diagonal, in pair, count and two-set mode."""
+    """From a lane here and there to every lane of every region holding candidates, with ragged edges and the diagonal (the last
+    epsilon reaches the marker of the rows past the end), in pair, count and two-set mode: in the general kernel less, exactly
+    and several times what the queue of a wavefront takes (16 lanes), in the small kernel (tiles of 64) none to all of a lane's
+    registers."""
     print(f"candidate queue n={n} share={share}", flush=True)
     rng = np.random.default_rng(n)
     X = rng.random((n, 64), dtype=np.float32).astype(np.float16).view(np.uint16)
@@ -645,9 +662,11 @@ def test_candidate_queue_at_every_density(ej, n, share):
 
 
 # ------------------------------------------------------------------ as many k-blocks as hold a coordinate
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("d", [31, 32, 33, 64, 65, 95, 96, 97, 160, 161, 200])
 def test_odd_numbers_of_slices(ej, d):
-    """Tiles of 2, 3, 4 ... slices, several tiles per workgroup: self-join, two sets, prepared set, all with one arithmetic."""
+    """Tiles of 2, 3, 4 ... slices, several tiles per workgroup in the general kernel (351 on 256), up to two of 128 in the small one:
+    self-join, two sets, prepared set, all with one arithmetic."""
     print(f"odd slices d={d}", flush=True)
     n = 6500
     rng = np.random.default_rng(d)
@@ -680,14 +699,15 @@ def by_general_kernel(ej, Xd, eps, capacity, d):
     return hp[:found].numpy().view(np.uint32), hd[:found].numpy()
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 129, 255, 257, 1000, 1537, 2500, 4097, 6500, 8100])
+SMALL_SIZES = [1, 2, 63, 64, 65, 127, 129, 255, 257, 1000, 1537, 2500, 4097, 6500, 8100]
+
+
+@pytest.mark.parametrize("n,share", [(n, 0.003) for n in SMALL_SIZES] + [(n, 0.2) for n in SMALL_SIZES if n <= 2500])
 @pytest.mark.parametrize("d", [20, 96, 130])
-@pytest.mark.parametrize("share", [0.003, 0.2])
 def test_small_problems_give_the_results_of_the_general_kernel(ej, n, d, share):
     """Tiles of 64 and of 128, one and several per workgroup, ragged edges, sparse and dense results: pairs, distances and
     counts of the general kernel, bit for bit."""
-    if share > 0.1 and n > 2500:
-        pytest.skip("dense results at the smaller sizes")
+    assert ej.join_work(n, d)[0] < 256
     print(f"small n={n} d={d} share={share}", flush=True)
     rng = np.random.default_rng(n + d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
@@ -758,9 +778,11 @@ def test_small_problems_overflow_status_and_captured_replays(ej):
 @pytest.mark.parametrize("share", [0.005, 0.03, 0.3])
 def test_counts_of_dense_tiles(ej, d, share):
     """Regions with candidates in a few, about twelve and all of their lanes, ragged edges and the diagonal, self-join and two
-    sets, at a size the general kernel works on: exactly the counts of the dense distance blocks."""
+    sets, at a size that goes to the general kernel's instance for dense tiles (up to 32,768 points), with and without a row panel
+    that stays in the LDS (d = 128): exactly the counts of the dense distance blocks."""
     print(f"dense counts d={d} share={share}", flush=True)
-    n, nq = 13007, 9001
+    n, nq = 14501, 9001
+    assert ej.join_work(n, d)[0] == ej.join_work(n, d, nq)[0] == 256 and n <= 32768
     rng = np.random.default_rng(d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
     P = orc.decode(X[:700])
@@ -794,6 +816,7 @@ def test_counts_of_dense_tiles_of_large_sets(ej, d, share):
     other fill tiles on the diagonal), all of them full, and an epsilon that reaches the marker of the rows past the end."""
     print(f"dense counts of a large set d={d} share={share}", flush=True)
     n, nq = 33001, 700
+    assert ej.join_work(n, d)[0] == ej.join_work(n, d, nq)[0] == ej.join_work(nq, d, n)[0] == 256 and n > 32768
     rng = np.random.default_rng(d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
     X[5000:5600] = X[5000]

@@ -13,9 +13,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.fixture(scope="module")
-def ej():
-    import paper_2508_21230_amd as pkg
-    e = pkg.EJoin(0)
+def ej(request):
+    e = parity.open_context(request)
     yield e
     e.close()
 
@@ -39,6 +38,7 @@ def draw_points(rng, n, d, ld):
     return out
 
 
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("seed", range(24))
 def test_random_self_join(ej, seed):
     rng = np.random.default_rng(50_000 + seed)

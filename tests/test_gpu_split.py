@@ -10,9 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.fixture(scope="module")
-def ej():
-    import paper_2508_21230_amd as pkg
-    e = pkg.EJoin(0)
+def ej(request):
+    e = parity.open_context(request)
     yield e
     e.close()
 
@@ -36,6 +35,7 @@ def data(kind, n, d, seed):
     raise ValueError(kind)
 
 
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("kind,n,d,ld_extra", [("uniform", 1500, 100, 0), ("offset", 1300, 64, 5), ("clustered", 2100, 257, 0),
                                                ("uniform", 1, 8, 0), ("uniform", 700, 1, 3), ("clustered", 6300, 48, 0)])
 def test_split_join_matches_fp64_on_the_fp32_data(ej, kind, n, d, ld_extra):
@@ -92,6 +92,7 @@ def test_split_join_is_more_accurate_than_the_fp16_join_where_conversion_hurts(e
     assert err.max() <= 2e-6 * s_max
 
 
+@parity.BOTH_KERNELS
 def test_split_join_duplicates_and_self_pairs(ej):
     rng = np.random.default_rng(9)
     X = rng.standard_normal((900, 70)).astype(np.float32)
@@ -121,6 +122,7 @@ def test_split_results_do_not_depend_on_the_kernel(ej, d):
     """A set large enough for the general kernel, and its first 1,000 and 2,600 points, which the kernel of small problems takes
     in tiles of 64 and of 128: the same pairs and counts among them, the same squared distances bit for bit."""
     n = 14500
+    assert [ej.join_work(m, d, split=True)[0] for m in (n, 2600, 1000)] == [256, 128, 64]
     print(f"split kernels d={d}", flush=True)
     X = data("uniform", n, d, seed=d)
     X[700] = X[3]
@@ -150,6 +152,7 @@ def test_split_counts_of_large_sets(ej, d, S):
     """More than 32,768 points, one, two and five k-blocks a part, wave tiles whose candidates fit the queue and ones that overflow it
     (the points are stored cluster by cluster): counts = histogram of the pairs."""
     n = 33100
+    assert ej.join_work(n, d, split=True)[0] == 256 and n > 32768
     print(f"split counts of a large set d={d} S={S}", flush=True)
     rng = np.random.default_rng(d)
     ids = np.sort(rng.integers(0, 33, size=n))

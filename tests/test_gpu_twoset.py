@@ -11,9 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.fixture(scope="module")
-def ej():
-    import paper_2508_21230_amd as pkg
-    e = pkg.EJoin(0)
+def ej(request):
+    e = parity.open_context(request)
     yield e
     e.close()
 
@@ -49,6 +48,7 @@ def check_two_set(P, Q, eps, gp, gd2, op, od2):
     return dict(gpu=len(kg), oracle=len(ko), only_gpu=int(only_g.size), only_oracle=int((~co).sum()))
 
 
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("w,n_p,n_q,S", [(2, 3000, 1700, 30), (3, 700, 2100, 12), (4, 257, 255, 40), (5, 1, 900, 5), (1, 4096, 256, 16)])
 def test_two_set_pairs_against_oracle(ej, w, n_p, n_q, S):
     print(f"two-set w={w} np={n_p} nq={n_q}", flush=True)
@@ -76,10 +76,14 @@ def test_two_set_pairs_against_oracle(ej, w, n_p, n_q, S):
     assert none is None and int(total2.cpu()[0]) == found and torch.equal(cp2, cp)
 
 
+@parity.BOTH_KERNELS
 @pytest.mark.parametrize("d,n_p,n_q", [(64, 4200, 4400), (128, 4200, 4400), (64, 9000, 7100), (128, 8000, 9100)])
 def test_two_set_more_tiles_than_workgroups(ej, d, n_p, n_q):
-    # 17 x 18 = 306 tiles on 256 workgroups, or 36 x 28 = 1008 (about four per workgroup); at d <= 64 a tile has fewer
-    # slices than the copies run ahead, and the copy cursor is two tiles ahead of the tile being computed
+    # general kernel: 17 x 18 = 306 tiles on 256 workgroups, or 36 x 28 = 1008 (about four per workgroup); at d <= 64 a tile has fewer
+    # slices than the copies run ahead, and the copy cursor is two tiles ahead of the tile being computed.  The smaller two
+    # problems go to the small kernel by size: 33 x 35 tiles of 128, up to two per workgroup
+    edge, _, tiles = ej.join_work(n_p, d, n_q)
+    assert tiles > (256 if edge == 256 else 768)
     rng = np.random.default_rng(900 + d)
     XP = rng.random((n_p, d), dtype=np.float32).astype(np.float16).view(np.uint16)
     XQ = rng.random((n_q, d), dtype=np.float32).astype(np.float16).view(np.uint16)
