@@ -2212,7 +2212,16 @@ int run_join(ejoin_ctx* ctx, const Workspace& w, bool own, const uint16_t* XA, i
   const int nkb = k_blocks(d);
   PrepSet SA{XA, nA, padA, ldA, w.s, w.Xp, 0}, SB{XB, nB, padB, ldB, w.s + padA, w.Xp + padA * (int64_t)(nkb + 1) * 4, 0};
   uint4 *XpA = SA.Xp, *XpB = SB.Xp;
-  if (const int tile = batch_rows ? 0 : small_tile(ctx, nA, self ? nA : nB, self, nkb)) return run_small<COUNT>(ctx, w, tile, SA, SB, nullptr, nkb, eps, r, st);
+  auto batch_done = [&](int b) -> int {
+    EJ_TRY(hipMemcpyAsync(ctx->batch_count + b, r.n_pairs, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+    EJ_TRY(hipEventRecord(ctx->batch_ev[b], st));
+    return EJOIN_OK;
+  };
+  // (one batch is the plain join: every self-join of up to 4,096 points, which one row of super-blocks covers)
+  if (const int tile = batch_rows && nbatches > 1 ? 0 : small_tile(ctx, nA, self ? nA : nB, self, nkb)) {
+    EJ_RC(run_small<COUNT>(ctx, w, tile, SA, SB, nullptr, nkb, eps, r, st));
+    return batch_rows ? batch_done(0) : EJOIN_OK;
+  }
   EJ_RC(begin_call(ctx, w, own, st));
   EJ_RC(prep_and_aux(ctx, w, SA, SB, nullptr, nkb, r.counter(COUNT), r, st));
   const Operand A{XpA, nA, padA}, B{self ? XpA : XpB, self ? nA : nB, self ? padA : padB};
@@ -2223,8 +2232,7 @@ int run_join(ejoin_ctx* ctx, const Workspace& w, bool own, const uint16_t* XA, i
       EJ_TRY(hipGetLastError());
     }
     EJ_RC(launch_join<COUNT>(ctx, w, own, A, B, self, nkb, eps, r, st, false, batch_rows[b], batch_rows[b + 1]));
-    EJ_TRY(hipMemcpyAsync(ctx->batch_count + b, r.n_pairs, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-    EJ_TRY(hipEventRecord(ctx->batch_ev[b], st));
+    EJ_RC(batch_done(b));
   }
   return EJOIN_OK;
 }

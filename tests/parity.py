@@ -34,9 +34,12 @@ BOTH_KERNELS = pytest.mark.parametrize("ej", ["by_size", "general"], indirect=Tr
 
 def open_context(request):
     import paper_2508_21230_amd as pkg
+    return pkg.EJoin(0) if getattr(request, "param", "by_size") == "by_size" else general_context()
+
+
+def general_context():
+    import paper_2508_21230_amd as pkg
     from paper_2508_21230_amd import build
-    if getattr(request, "param", "by_size") == "by_size":
-        return pkg.EJoin(0)
     sources = [os.path.join(os.path.dirname(build.SRC), f) for f in os.listdir(os.path.dirname(build.SRC)) if f.endswith((".hip", ".h"))]
     built = os.path.exists(build.GENERAL_KERNEL_LIB) and os.path.getmtime(build.GENERAL_KERNEL_LIB) >= max(map(os.path.getmtime, sources))
     assert built, "build the variants first: python -m paper_2508_21230_amd.build --ablations"

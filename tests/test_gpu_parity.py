@@ -562,15 +562,15 @@ def test_contexts_and_prepared_sets_release_their_device_memory():
     assert free0 - free1 < 64 << 20, f"device memory not returned: {free0 - free1} bytes"
 
 
-@pytest.mark.parametrize("batches", [1, 3, 32])
-def test_batched_return_to_host_gives_the_pairs_of_the_plain_join(ej, batches):
+@pytest.mark.parametrize("n,batches", [(21000, 1), (21000, 3), (21000, 32), (300, 4), (1500, 1), (4096, 2), (4097, 1), (4097, 2), (9000, 3)])
+def test_batched_return_to_host_gives_the_pairs_of_the_plain_join(ej, n, batches):
     """ejoin_selfjoin_pairs_to_host: the join cut into launches by rows of super-blocks, each batch copied to pinned host
     memory while the next computes -- same pair set and squared distances as ejoin_selfjoin_pairs, also when the
-    buffer overflows (exactly `capacity` pairs returned, the count still complete)."""
-    n = 21_000  # 83 tiles per side: six rows of super-blocks
+    buffer overflows (exactly `capacity` pairs returned, the count still complete).  21,000 points are 83 tiles a side, six rows
+    of super-blocks; up to 4,096 points are one row and hence one launch, which small problems do with their own kernel."""
     X = datagen.generate(2, n=n)
     Xd = torch.from_numpy(X.view(np.int16)).cuda()
-    eps = 0.78
+    eps = 0.78 if n > 10000 else 1.0
     want_pairs, want_d2, want_n = ej.selfjoin_pairs(Xd, eps, capacity=4_000_000)
     torch.cuda.synchronize()
     wp, wd, found = parity.to_host_pairs(want_pairs, want_d2, want_n)
@@ -689,14 +689,11 @@ def test_odd_numbers_of_slices(ej, d):
 
 
 # ------------------------------------------------------------------ the kernel of small problems against the general one
-def by_general_kernel(ej, Xd, eps, capacity, d):
-    """The pairs of the self-join by the launches of the batched return, which the general kernel does at every size."""
-    pairs = torch.zeros((capacity, 2), dtype=torch.int32, device="cuda")
-    d2 = torch.zeros(capacity, dtype=torch.float32, device="cuda")
-    hp, hd = torch.zeros((capacity, 2), dtype=torch.int32), torch.zeros(capacity, dtype=torch.float32)
-    found = ej.selfjoin_pairs_to_host(Xd, float(eps), 1, pairs, d2, hp, hd, d=d)
-    assert found <= capacity
-    return hp[:found].numpy().view(np.uint32), hd[:found].numpy()
+@pytest.fixture(scope="module")
+def general():
+    e = parity.general_context()
+    yield e
+    e.close()
 
 
 SMALL_SIZES = [1, 2, 63, 64, 65, 127, 129, 255, 257, 1000, 1537, 2500, 4097, 6500, 8100]
@@ -704,7 +701,7 @@ SMALL_SIZES = [1, 2, 63, 64, 65, 127, 129, 255, 257, 1000, 1537, 2500, 4097, 650
 
 @pytest.mark.parametrize("n,share", [(n, 0.003) for n in SMALL_SIZES] + [(n, 0.2) for n in SMALL_SIZES if n <= 2500])
 @pytest.mark.parametrize("d", [20, 96, 130])
-def test_small_problems_give_the_results_of_the_general_kernel(ej, n, d, share):
+def test_small_problems_give_the_results_of_the_general_kernel(ej, general, n, d, share):
     """Tiles of 64 and of 128, one and several per workgroup, ragged edges, sparse and dense results: pairs, distances and
     counts of the general kernel, bit for bit."""
     assert ej.join_work(n, d)[0] < 256
@@ -717,7 +714,7 @@ def test_small_problems_give_the_results_of_the_general_kernel(ej, n, d, share):
     P = orc.decode(X[np.sort(rng.choice(n, size=min(n, 900), replace=False))])
     eps = orc.eps_for_pair_rank(orc.all_pairs_dist2(P), max(1, int(share * P.shape[0] * (P.shape[0] - 1) / 2))) if n > 2 else np.float32(1.0)
     cap = int(n + 2 * share * n * n / 2 + 4096)
-    want, want_d2 = by_general_kernel(ej, Xd, eps, cap, d)
+    want, want_d2, _ = run_pairs(general, Xd, eps, capacity=cap, d=d)
     got, got_d2, found = run_pairs(ej, Xd, eps, capacity=cap, d=d)
     assert found == got.shape[0] == want.shape[0]
     kw, kg = orc.pair_keys(want), orc.pair_keys(got)
@@ -841,3 +838,31 @@ def test_counts_of_dense_tiles_of_large_sets(ej, d, share):
     for a, b, h in ((both[:n], both[n:].clone(), hit), (both[n:].clone(), both[:n], hit.T)):
         cp, cq, ct = ej.join_count(a, b, float(eps), d=d)
         assert torch.equal(cp.long(), h.sum(dim=1)) and torch.equal(cq.long(), h.sum(dim=0)) and int(ct.cpu()[0]) == int(hit.sum().cpu())
+
+
+@parity.BOTH_KERNELS
+@pytest.mark.parametrize("d", [50, 100, 200])
+@pytest.mark.parametrize("share", [0.004, 0.03, 0.1, 0.5])
+def test_pairs_of_dense_tiles(ej, d, share):
+    """Wave tiles whose candidates overflow the queue, with few and with nearly all lanes of a region holding one, with (d = 100) and
+    without a row panel kept in the LDS, whole tiles, the diagonal and ragged edges: exactly the pairs of the dense distance block."""
+    print(f"dense pairs d={d} share={share}", flush=True)
+    n = 1100
+    rng = np.random.default_rng(d)
+    X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    X[300:340] = X[300]  # (a region of duplicates among others)
+    P = orc.decode(X[:700])
+    eps = orc.eps_for_pair_rank(orc.all_pairs_dist2(P), int(share * 700 * 699 / 2))
+    Xd = dev(pad(X, (d + 63) // 64 * 64))
+    D = ej.dist2_tile(Xd, 0, 0, n, n, d=d).cpu().numpy()
+    hit = np.triu(D <= np.float32(eps) * np.float32(eps), 1)
+    pairs, d2, found = run_pairs(ej, Xd, eps, capacity=n * n, d=d)
+    want = np.argwhere(hit)
+    own = pairs[:, 0] == pairs[:, 1]
+    assert found == pairs.shape[0] == want.shape[0] + n and int(own.sum()) == n
+    assert np.array_equal(np.sort(orc.pair_keys(pairs[~own])), np.sort(orc.pair_keys(want.astype(np.uint32))))
+    assert np.array_equal(D[pairs[:, 0], pairs[:, 1]], d2)
+    # into less room than there are pairs
+    some, some_d2, again = run_pairs(ej, Xd, eps, capacity=found // 3, d=d)
+    assert again == found and np.unique(orc.pair_keys(some)).size == found // 3
+    assert np.all(hit[some[:, 0], some[:, 1]] | (some[:, 0] == some[:, 1])) and np.array_equal(D[some[:, 0], some[:, 1]], some_d2)

@@ -168,3 +168,22 @@ def test_split_counts_of_large_sets(ej, d, S):
     hist = torch.bincount(ns[:, 0], minlength=n) + torch.bincount(ns[:, 1], minlength=n)
     counts, total = ej.selfjoin_count_f32(Xd, float(eps))
     assert torch.equal(counts.long(), hist) and int(total.cpu()[0]) == ns.shape[0]
+
+
+@parity.BOTH_KERNELS
+@pytest.mark.parametrize("d,share", [(20, 0.05), (130, 0.05), (64, 0.6)])
+def test_split_pairs_of_dense_tiles(ej, d, share):
+    """Wave tiles whose candidates overflow the queue: pairs against the oracle, counts against the pairs."""
+    n = 900
+    print(f"split dense pairs d={d} share={share}", flush=True)
+    X = data("uniform", n, d, seed=n + d)
+    P = X.astype(np.float64)
+    eps = orc.select_eps_all_pairs(P, share * n)
+    ora_pairs, ora_d2 = orc.selfjoin_pairs(P, eps)
+    pairs, d2, found = run_f32(ej, X, eps, n * n)
+    assert found == pairs.shape[0]
+    parity.check_pair_sets(P, eps, pairs, d2, ora_pairs, ora_d2)
+    counts, total = ej.selfjoin_count_f32(torch.from_numpy(X).cuda(), float(eps))
+    ns = pairs[pairs[:, 0] != pairs[:, 1]]
+    hist = np.bincount(ns[:, 0], minlength=n) + np.bincount(ns[:, 1], minlength=n)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), hist) and int(total.cpu()[0]) == ns.shape[0]
