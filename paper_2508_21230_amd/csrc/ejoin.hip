@@ -788,7 +788,6 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 2, wn = wave & 3;
-  const int r16 = lane & 15, g = lane >> 4;
   const int nsl = a.nslices;       // slices per tile (at least 2)
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   // the constant chunks of the augmentation step (made visible by the barrier of the prologue)
