@@ -119,7 +119,8 @@ struct JoinArgs {
 // [2..3] the constant C = { c, c, c, 0 } of the call's augmentation step (FP16 bits, written by k_aux),
 // [8..15] alignment counters of the XCDs.  Between calls [1] and [8..15] are zero: k_aux clears the counters
 // (and the result counter of the call), k_join clears the maximum.  k_reset restores that state after a call
-// that did not get as far as its join kernel, and before every call on the shared static workspace.
+// that did not get as far as its join kernel, and before every call of k_join on the shared static workspace.
+// (Small problems and the dense-tile call use words [0] and [2..3] only.)
 __global__ void k_reset(uint32_t* status_and_max) {
   if (threadIdx.x < 8) status_and_max[8 + threadIdx.x] = 0;
   if (threadIdx.x == 0) {
@@ -919,19 +920,30 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   uint32_t fill = 0;               // wave-uniform
   unsigned long long hits = 0;     // count mode: pairs found by this wave
   bool dirty = false;              // stores/atomics issued by the rare path of the current tile (see there)
+  // What only storing results needs is read from the kernel's arguments again where it is needed (`a` lies at their start): kept
+  // across the main loop it costs scalar registers, whose spills are read back at every tile.  Together with the fillings
+  // of the queue after the first in code of their own (below): 10^6 points, d = 128, on operands that hardly toggle (no power
+  // limit) 86.7 ms, now 84.0; 10^5 points, d = 128, S = 64 1.5 % less.
+  auto arguments = []() {
+    auto ka = (const __attribute__((address_space(4))) JoinArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka));
+    return ka;
+  };
   auto store_staged = [&](unsigned long long base) {  // the staged entries to places base .. of the result
+    const auto ka = arguments();
     for (uint32_t e = lane; e < fill; e += 64) {
       const unsigned long long idx = base + e;
-      if (idx < a.capacity) {
-        reinterpret_cast<uint2*>(a.pairs)[idx] = make_uint2(stg[3 * e], stg[3 * e + 1]);
-        if (a.dist2) a.dist2[idx] = __uint_as_float(stg[3 * e + 2]);
+      if (idx < ka->capacity) {
+        reinterpret_cast<uint2*>(ka->pairs)[idx] = make_uint2(stg[3 * e], stg[3 * e + 1]);
+        if (ka->dist2) ka->dist2[idx] = __uint_as_float(stg[3 * e + 2]);
       }
     }
   };
   auto flush = [&]() {
     if (fill == 0) return;
     unsigned long long base = 0;
-    if (lane == 0) base = atomicAdd(a.n_pairs, (unsigned long long)fill);
+    const auto ka = arguments();
+    if (lane == 0) base = atomicAdd(ka->n_pairs, (unsigned long long)fill);
     const uint32_t blo = __builtin_amdgcn_readfirstlane((uint32_t)base);
     const uint32_t bhi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
     store_staged(((unsigned long long)bhi << 32) | blo);
@@ -1354,24 +1366,26 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       };
-      if constexpr (COUNT && !DENSE) {
+      if constexpr (!DENSE) {
         if (todo) {
           uint32_t qfill = fill_queue(F_{}, todo, taken);
           if (!todo) {
             drain_queue(qfill, F_{});
           } else {
-            // A dense wave tile: more candidates than the queue takes.  Its hits share rows and columns, and one global atomic per
-            // hit and side is what such counts are bound by (28 10^9 a second), so they are added up in the LDS first.  Against
+            // A dense wave tile: more candidates than the queue takes.  Counts: its hits share rows and columns, and one global atomic
+            // per hit and side is what such counts are bound by (28 10^9 a second), so they are added up in the LDS first.  Against
             // global atomics (and, in brackets, the ballot per register before the queue): 33,000 points, d = 128, S = 1,500
             // 2,230 (1,980) us, now 700; S = 4,000 5.4 (4.6) ms, now 1.0; 200,000 x 600, d = 384, S = 5,000 1,100 (750) us, now 290.
             // Wave tiles whose candidates fit the queue go on as they did: 10^6 points, d = 128, S = 64 109 ms on both.
             for (;;) {
-              drain_queue(qfill, T_{});
+              drain_queue(qfill, std::integral_constant<bool, COUNT>{});
               if (!todo) break;
               qfill = fill_queue(T_{}, todo, taken);
             }
-            send_region_counts(stg, l, a, I * TILE + wm * 128, J * TILE + wn * 64);
-            dirty = true;
+            if constexpr (COUNT) {
+              send_region_counts(stg, l, a, I * TILE + wm * 128, J * TILE + wn * 64);
+              dirty = true;
+            }
           }
         }
       } else {
@@ -1794,7 +1808,7 @@ namespace {
 struct Workspace {
   uint32_t* status;  // status block, 64 words (see k_reset)
   float* s;          // norms (4 B per point); the context's own: then one maximum per NORM_POINTS points (dense-tile call)
-  uint4* H;          // augmentation rows (16 B per point, padded to a multiple of TILE)
+  uint4* H;          // augmentation rows (16 B per point, padded to a multiple of TILE); small problems: the largest norms
   uint4* Xp;         // packed copy of X plus the augmentation k-block
 };
 
