@@ -37,6 +37,9 @@ ABLATION_DIR = os.path.join(PKG, "ablation")
 #: the library with problems of every size going to the general join kernel, for its tests on sizes that the small kernel takes
 GENERAL_KERNEL = {"general_kernel": ["-DEJOIN_ONLY_K_JOIN"]}
 GENERAL_KERNEL_LIB = os.path.join(ABLATION_DIR, "libejoin_general_kernel.so")
+#: ... and with all of them that can going to the kernel that keeps its rows in registers, likewise
+STRIP_KERNEL = {"strip_kernel": ["-DEJOIN_ONLY_K_JOIN_STRIP"]}
+STRIP_KERNEL_LIB = os.path.join(ABLATION_DIR, "libejoin_strip_kernel.so")
 
 
 def _compile(out: str, defines=(), verbose: bool = False) -> str:
@@ -64,7 +67,7 @@ def build_ablations(verbose: bool = False) -> dict:
     build of the general kernel -> ablation/libejoin_<name>.so."""
     os.makedirs(ABLATION_DIR, exist_ok=True)
     return {name: _compile(os.path.join(ABLATION_DIR, f"libejoin_{name}.so"), defs, verbose)
-            for name, defs in {**ABLATIONS, **EXPERIMENTS, **GENERAL_KERNEL}.items()}
+            for name, defs in {**ABLATIONS, **EXPERIMENTS, **GENERAL_KERNEL, **STRIP_KERNEL}.items()}
 
 
 if __name__ == "__main__":

@@ -12,6 +12,7 @@
 #include <math.h>
 #include <new>
 #include <type_traits>
+#include <utility>
 
 #include "ejoin.h"
 #include "ejoin_bench.h"
@@ -93,6 +94,7 @@ struct JoinArgs {
   const uint4* XpB;        // ... of the query points
   int64_t nA, nB;
   int self;                // 1: self-join (upper triangle, self pairs), 0: two different sets (full rectangle)
+  int swapped;             // k_join_strip: its rows are the query points, its columns the points (XpA, nA, counts: of the rows)
   uint32_t* status;        // status block of the workspace (see k_reset)
   int nslices;  // k-blocks of data per panel = slices per tile (the augmentation block follows them)
   float thr;    // pass <=> acc' >= thr, thr = -eps^2 / 2
@@ -1487,6 +1489,621 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
 }
 
 
+// ------------------------------------------------------------------------------------------
+// The join of points with few coordinates
+// ------------------------------------------------------------------------------------------
+// A workgroup holds a panel of 512 rows in registers for as long as its part of the schedule stays in them (StripCursor): a
+// wavefront all K k-blocks of its 64 rows (16 K registers).  Only the columns go through the LDS, 64 (32) of them with all their
+// k-blocks at a time, and a block of 64 rows x 32 columns per wavefront is complete after K steps, with 32 accumulators.
+// What bounds k_join at few coordinates is the boundary of a tile (a third of its time at four slices) and, in long launches, power.
+// Here a block's filter runs under the next block's MFMAs, there is no barrier (progress counters, below), the L2 -> LDS copies are a
+// quarter of k_join's (512 rows share them, and only columns are copied) and the LDS reads 57 B per clock and CU at MFMA peak instead
+// of 96.  Measured (join kernel): 10^6 points, d = 128, S = 64, counts 105.5 ms, now 91.5; 10^5 points, pairs 1383 us, now 1170 (output
+// left out 1160, now 900: MFMA pipe busy 0.76 of the cycles, at the clock that the power limit leaves); 40,000 points, d = 224,
+// pairs 296 us, now 276.  From nine k-blocks on there are no registers for two buffers of accumulators, and the filter is in the open:
+// 150,000 points, d = 320, 5.33 ms, now 5.08.
+// Tried: a barrier per stage (candidates of one wavefront hold up all: 10^5 x 128 1680 us); 256 rows and 64 columns a workgroup,
+// copies by four of the wavefronts (10^6 x 128 without candidates 94 ms, now 91); volatile progress counters (every LDS read
+// waited for: 110).
+template <class F, int... N>
+__device__ __forceinline__ void for_each_index(F&& f, std::integer_sequence<int, N...>) {
+  (f(std::integral_constant<int, N>{}), ...);
+}
+template <int K>
+struct Strip {
+  static constexpr bool TWO = K <= 7;             // two blocks of 32 columns a stage and two buffers of accumulators; else one of each
+  static constexpr int BLOCKS = TWO ? 2 : 1, COLS = 32 * BLOCKS;
+  static constexpr int KB = COLS * 64;            // bytes of a k-block of a stage
+  static constexpr int DATA = K * KB;             // bytes of coordinates ...
+  static constexpr int STAGE = DATA + COLS * 16;  // ... and of operands of the augmentation step
+  static constexpr bool ROWS_LDS = K >= 8;        // the rows' operands of that step: in the LDS, or in registers
+  static constexpr int DENSE = 5, FULL = 24;      // (counts) candidates in that many lanes of 32 x 32: each lane looks at its own, all at once
+  static constexpr int QUEUE = 16;                // entries of the candidate queue: 16 values and the place of the first
+  static constexpr int STG = 128;                 // staged results
+  static constexpr int WAVE = STG * 12 + QUEUE * 72;
+  static constexpr int TAIL = 640;                // constant chunks of the augmentation step (at 0 and 512), progress counters
+  static constexpr int ROWS = ROWS_LDS ? 8192 : 0;
+  static constexpr int FIT = (160 * 1024 - 8 * WAVE - TAIL - ROWS) / STAGE;
+  static constexpr int STAGES = FIT < 8 ? FIT : 8;
+  static constexpr int DEPTH = STAGES >= 8 ? 5 : (STAGES >= 5 ? 3 : 2);  // stages the copies are ahead
+  static constexpr int LAG = STAGES - DEPTH;      // a stage is refilled that many stages after its own
+  static constexpr int POST = DEPTH >= 4 ? 2 : 1; // at the start of stage g the copies of stage g + POST have landed
+  static constexpr int COPIES = TWO ? K + 1 : (K + 2) / 2;  // copy instructions per copying wavefront and stage
+  static constexpr int RING = K >= 10 ? 3 : (K == 4 || K == 8 ? 8 : (K == 3 || K == 6 || K == 9 ? 6 : 4));  // fragments of the columns in registers
+  static constexpr int CONST_OFF = STAGES * STAGE;
+  static constexpr int SYNC_OFF = CONST_OFF + 64;
+  static constexpr int ROWS_OFF = CONST_OFF + TAIL;
+  static constexpr int STG_OFF = ROWS_OFF + ROWS;
+  static constexpr int LDS = STG_OFF + 8 * WAVE;
+  static_assert(STAGES >= 3 && LAG >= 1 && DEPTH > POST && LDS <= 160 * 1024, "LDS budget of one CU");
+  static_assert(RING - 1 <= 2 * K, "what is read ahead belongs to this block or the next");
+};
+
+template <bool COUNT, int K>
+__global__ __launch_bounds__(THREADS) void k_join_strip(const JoinArgs a) {
+  using L = Strip<K>;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  // the largest norm of the call has been consumed by k_aux: cleared here for the next call
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.status[1] = 0;
+  if (*a.status != ST_OK) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t turn = (uint32_t)wave >> 2;  // who copies: wavefronts 0 .. 3 the even stages, 4 .. 7 the odd ones
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+  const int64_t panel_stride = (int64_t)(K + 1) * PANEL_BYTES;
+  const char* XbB = reinterpret_cast<const char*>(a.XpB);
+  if (tid < 4) {
+    const uint32_t c0 = a.status[2], c1 = a.status[3];
+    *reinterpret_cast<uint4*>(lds + L::CONST_OFF + 512 * (tid >> 1) + 16 * (tid & 1)) = tid & 1 ? make_uint4(0u, 0u, c0, c1) : make_uint4(c0, c1, 0u, 0u);
+  }
+
+  auto uniform_ptr = [](const char* p) -> const char* {
+    const uint64_t b = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
+  };
+
+  // ---- per-wavefront staging of results, and the queue of candidates (see k_join)
+  uint32_t* stg = reinterpret_cast<uint32_t*>(lds + L::STG_OFF + wave * L::WAVE);
+  float* queue_v = reinterpret_cast<float*>(lds + L::STG_OFF + wave * L::WAVE + L::STG * 12);
+  uint2* queue_t = reinterpret_cast<uint2*>(queue_v + 16 * L::QUEUE);  // the pair of the entry's first value
+  uint32_t fill = 0, qfill = 0;  // (uniform)
+  unsigned long long hits = 0;   // (uniform)
+  bool dirty = false;  // stores or atomics issued since the last wait for everything
+  auto arguments = []() {  // (read again where only the rare path needs them, see k_join)
+    auto ka = (const __attribute__((address_space(4))) JoinArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ka));
+    return ka;
+  };
+  // At the end of what runs now and then: nothing of it is outstanding on lgkmcnt (scalar loads return in any order: with one of them
+  // perhaps in flight, the compiler could only wait for everything at the next LDS read of the main loop, every time)
+  auto settle = []() { __builtin_amdgcn_s_waitcnt(0xC07F); };
+  auto store_staged = [&](unsigned long long base) __attribute__((always_inline)) {
+    const auto ka = arguments();
+    for (uint32_t e = lane; e < fill; e += 64) {
+      const unsigned long long idx = base + e;
+      if (idx < ka->capacity) {
+        reinterpret_cast<uint2*>(ka->pairs)[idx] = make_uint2(stg[3 * e], stg[3 * e + 1]);
+        if (ka->dist2) ka->dist2[idx] = __uint_as_float(stg[3 * e + 2]);
+      }
+    }
+  };
+  auto flush = [&]() __attribute__((always_inline)) {
+    unsigned long long base = 0;
+    const auto ka = arguments();
+    if (lane == 0) base = atomicAdd(ka->n_pairs, (unsigned long long)fill);
+    const uint32_t blo = __builtin_amdgcn_readfirstlane((uint32_t)base), bhi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+    store_staged(((unsigned long long)bhi << 32) | blo);
+    fill = 0;
+    dirty = true;
+  };
+  auto stage_entry = [&](unsigned long long mask, bool pass, uint32_t i, uint32_t j, uint32_t d2_bits) __attribute__((always_inline)) {
+    const bool swapped = a.swapped;
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    if (pass) {
+      const uint32_t e = fill + rank;
+      stg[3 * e] = swapped ? j : i;
+      stg[3 * e + 1] = swapped ? i : j;
+      stg[3 * e + 2] = d2_bits;
+    }
+    fill = __builtin_amdgcn_readfirstlane(fill + __popcll(mask));
+  };
+  // Count mode: the staging area holds counters instead, of the wavefront's 64 rows (kept until its row panel changes) and of the
+  // 32 columns of a block.
+  uint32_t* const row_counts = stg;
+  uint32_t* const col_counts = stg + 64;
+  uint32_t rows_at = 0;  // first row of the counters
+  if constexpr (COUNT) {
+    stg[lane] = 0;
+    if (lane < 32) col_counts[lane] = 0;
+  }
+  auto send_rows = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    const uint32_t c = row_counts[lane];
+    hits += wave_sum(c & 0xFFFFu) + ((unsigned long long)wave_sum(c >> 16) << 16);  // (every pair found is in one row's counter)
+    if (c) {
+      row_counts[lane] = 0;
+      uint32_t* to = arguments()->counts;
+      if (to) atomicAdd(to + rows_at + lane, c);
+    }
+    dirty = true;
+  };
+  auto drain = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    uint32_t l = lane;
+    asm volatile("" : "+v"(l));  // (nothing of this is kept across the main loop)
+    const uint32_t nnA = (uint32_t)a.nA, nnB = (uint32_t)a.nB, self = (uint32_t)a.self;
+    const uint32_t lr = l & 15u, roff = 16 * (lr >> 3) + (lr & 3), coff = 16 * ((lr >> 2) & 1);  // region_pair(0, lane % 16)
+    const float thr = a.thr;
+    // four entries a pass, one value per lane; with registers to spare the reads of all passes are in flight together
+    constexpr int AT_ONCE = K <= 6 ? L::QUEUE / 4 : 1;
+#pragma unroll 1
+    for (uint32_t p = 0; p < L::QUEUE / 4; p += AT_ONCE) {
+      float x[AT_ONCE];
+      uint2 at[AT_ONCE];
+#pragma unroll
+      for (int q = 0; q < AT_ONCE; ++q) {
+        x[q] = queue_v[64 * (p + q) + l];
+        at[q] = queue_t[4 * (p + q) + (l >> 4)];
+      }
+#pragma unroll
+      for (int q = 0; q < AT_ONCE; ++q) {
+        const uint32_t i = at[q].x + roff, j = at[q].y + coff;
+        const bool pass = x[q] >= thr && l + 64 * (p + q) < 16 * qfill && i < nnA && j < nnB && (!self || i < j);
+        const unsigned long long mask = __ballot(pass);
+        if (!mask) continue;
+        if constexpr (COUNT) {
+          if (pass) {
+            atomicAdd(row_counts + (i - rows_at), 1u);
+            const auto ka = arguments();
+            uint32_t* to = self ? ka->counts : ka->counts_b;
+            if (to) atomicAdd(to + j, 1u);
+          }
+          dirty = true;
+        } else {
+          if (fill + __popcll(mask) > (uint32_t)L::STG) flush();
+          stage_entry(mask, pass, i, j, __float_as_uint(fmaxf(-2.f * x[q], 0.f)));
+        }
+      }
+    }
+    settle();
+    qfill = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+
+  // ---- schedule.  The cursor is the copies', DEPTH stages ahead of what is computed; which stage a place of the ring holds (panel of
+  // rows, 64 columns) is kept in one lane of two registers per place.
+  StripCursor tc;
+  tc.init(blockIdx.x, gridDim.x, (uint32_t)a.self, (uint32_t)((a.nB + EJ_STRIP_COLS - 1) / EJ_STRIP_COLS), a.sb_row_begin, a.sb_row_end);
+  uint32_t run_i = 0, run_c = 0, run_end = 0;
+  auto next_run = [&]() __attribute__((always_inline)) -> bool {
+    constexpr uint32_t PER = EJ_STRIP_COLS / L::COLS;
+    const bool some = tc.next(run_i, run_c, run_end);
+    run_c *= PER;
+    run_end *= PER;
+    return some;
+  };
+  bool live = next_run();
+  auto xcd_leave = [&]() {
+    const auto ka = arguments();
+    if (ka->sync_mode >= 1 && tid == 0)
+      __hip_atomic_fetch_add(ka->xcd_bar + blockIdx.x % NUM_XCD, 1u << 24, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (!live) {
+    xcd_leave();
+    return;
+  }
+  uint32_t epoch = 0;
+  uint32_t sync_left = a.sync_mode >= 1 ? (uint32_t)a.sync_mode : 0xFFFFFFFFu;
+  if (a.sync_mode >= 1) xcd_align(a.xcd_bar + blockIdx.x % NUM_XCD, tc.step * ++epoch);
+  constexpr uint32_t NO_STAGE = 0xFFFFFFFFu;
+  uint32_t places = 0;             // lane p: the columns of place p, lane 32 + p: its panel of rows
+  uint32_t slot_in = 0, slot = 0;  // where the next stage goes; the stage being computed
+  uint32_t g = 0, g_in = 0;        // their numbers
+  const uint32_t quarter = wave & 3;
+  const uint32_t voff = lane * 16 + (L::TWO ? quarter * 1024 : (quarter & 1) * 1024 + (quarter >> 1) * PANEL_BYTES);
+  // The next stage.  64 columns: wavefront q of the four copies the q-th KB of every 4 KB (one k-block) and a quarter of the
+  // augmentation operands.  32 columns: the q-th KB of every two k-blocks, and what then lacks to the same number for all four.
+  auto issue = [&]() __attribute__((always_inline)) {
+    places = lane == (int)slot_in ? (live ? run_c : NO_STAGE) : places;
+    if (__builtin_expect(live, 1)) {
+      places = lane == (int)slot_in + 32 ? run_i : places;
+      if ((g_in & 1) == turn) {
+        constexpr uint32_t PER = TILE / L::COLS;  // stages of a panel of columns
+        const char* panel = uniform_ptr(XbB + (int64_t)(run_c / PER) * panel_stride);
+        const char* src = panel + (run_c % PER) * (uint32_t)(L::COLS * 64);
+        const uint32_t at = __builtin_amdgcn_readfirstlane(lds0 + slot_in * (uint32_t)L::STAGE);
+        const char* aug = panel + (int64_t)K * PANEL_BYTES + AUG_PART_BYTES + (run_c % PER) * (uint32_t)(L::COLS * 16);
+        for_each_index([&](auto n_c) {
+          constexpr int N = decltype(n_c)::value;
+          copy16_to_lds<N * 4096>(at + quarter * 1024, uniform_ptr(src + (int64_t)N * (L::TWO ? 1 : 2) * PANEL_BYTES), voff);
+        }, std::make_integer_sequence<int, L::TWO ? K : K / 2>{});
+        if constexpr (L::TWO || K % 2 == 0) {  // a quarter of the augmentation operands
+          if (lane < L::COLS / 4) copy16_to_lds<L::DATA>(at + quarter * (L::COLS * 4), uniform_ptr(aug + quarter * (L::COLS * 4)), lane * 16);
+        } else if (quarter < 2) {  // the last k-block
+          copy16_to_lds<K / 2 * 4096>(at + quarter * 1024, uniform_ptr(src + (int64_t)(K - 1) * PANEL_BYTES), voff);
+        } else {  // half of the augmentation operands
+          if (lane < L::COLS / 2) copy16_to_lds<L::DATA>(at + (quarter - 2) * (L::COLS * 8), uniform_ptr(aug + (quarter - 2) * (L::COLS * 8)), lane * 16);
+        }
+      }
+      if (__builtin_expect(++run_c == run_end, 0)) live = next_run();
+    }
+    slot_in = slot_in == L::STAGES - 1 ? 0 : slot_in + 1;
+    ++g_in;
+  };
+  // ---- Progress of the wavefronts, in the LDS: word w says that wavefront w's copies of all stages below it have landed, word
+  // 8 + w how many stages wavefront w has read.  A wavefront reads a stage when all of it has landed, and its place is refilled when
+  // all have read it.  (A barrier per stage instead makes all of them wait for the one that has candidates to look at.)
+  // (volatile accesses would make the compiler wait for every LDS read in flight)
+  typedef __attribute__((address_space(3))) uint32_t* lds_u32ptr;
+  const uint32_t sync0 = lds0 + L::SYNC_OFF;
+  uint32_t look_at = sync0 + 4 * (lane & 15);
+  if constexpr (L::TWO) asm volatile("" : "+v"(look_at));  // (kept in a register where there is one)
+  auto sync_word = [&](uint32_t w) { return (lds_u32ptr)(uintptr_t)(sync0 + 4 * w); };
+  if (tid < 16) *sync_word(tid) = tid < 8 ? L::POST + (((tid >> 2) & 1) != (L::POST & 1)) : 0;
+  // a lane's word plus `lead` must not lie below g + 2 when stage g + 1 is about to be read, and then the place of stage g + 1 - LAG refilled
+  const uint32_t lead = lane < 8 ? 0u : (lane < 16 ? (uint32_t)L::LAG : 0x40000000u);
+  uint32_t seen = 0;  // this lane's word, read a while ago
+  auto look = [&]() {
+    asm volatile("" ::: "memory");
+    seen = *(lds_u32ptr)(uintptr_t)look_at;
+  };
+  auto proceed = [&]() {
+    if (__builtin_expect(__ballot((int32_t)(seen + lead - (g + 2)) < 0) != 0, 0)) {
+      do look();
+      while (__ballot((int32_t)(seen + lead - (g + 2)) < 0));
+      settle();
+    }
+    asm volatile("" ::: "memory");
+  };
+  auto post_read = [&]() {  // every read of stage g has been issued, and the LDS serves a wavefront's instructions in order
+    asm volatile("" ::: "memory");
+    if (lane == 0) *sync_word(8 + wave) = g + 1;
+    asm volatile("" ::: "memory");
+  };
+  // Start of stage g: the copies of stage g + POST, if they were this wavefront's, have landed once only those of its younger stages are
+  // outstanding.
+  auto begin_stage = [&]() __attribute__((always_inline)) {
+    if (((g + L::POST) & 1) == turn) {
+      if (__builtin_expect(live, 1)) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::COPIES * ((L::DEPTH - 1 - L::POST) / 2)) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (lane == 0) *sync_word(wave) = g + L::POST + 2;
+    }
+    issue();  // stage g + DEPTH
+  };
+
+  // ---- operands.  Fragment h of the columns of a stage's block P, k-block kb: stage + kb * KB + 2048 P + fragment_offset(lane, h)
+  typedef const __attribute__((address_space(3))) char* lds_cptr;
+  typedef const __attribute__((address_space(3))) half8* lds_h8ptr;
+  auto at_lds = [&](uint32_t addr, int imm) -> half8 { return *reinterpret_cast<lds_h8ptr>((lds_cptr)(uintptr_t)addr + imm); };
+  const uint32_t off0 = lds0 + fragment_offset(lane, 0);  // (fragment_offset(lane, 1): bit 5 the other way)
+  // augmentation operand of the columns: their pieces in the stage (lanes 32 .. 63) or the constant chunk; of the rows: the
+  // wavefront's part of the rows' area (lanes 0 .. 31) or the constant chunk, 512 bytes further on for the second 32 rows
+  // (swapped: the two halves of the step the other way round, so that it adds the points' terms before the query points' as ever)
+  const bool upper = (lane >= 32) != (a.swapped != 0);
+  const uint32_t aug0 = lds0 + (upper ? L::DATA + 16 * (lane & 31) : L::CONST_OFF + 16 * ((lane >> 4) & 1));
+  const uint32_t aug_step = upper ? ~0u : 0u;
+  const uint32_t aug_rows = lds0 + (upper ? L::CONST_OFF + 16 * ((lane >> 3) & 1) : L::ROWS_OFF + 1024 * wave + 16 * (lane & 31));
+  constexpr int RING = L::RING, FRAGS = 2 * K;
+  half8 fa[K][4], ga[2], fb[RING];
+  float16v R[L::BLOCKS][2];  // [buffer][32 rows]: a region's four 16 x 16 blocks side by side
+  if constexpr (L::TWO)
+#pragma unroll
+  for (int r = 0; r < 2; ++r)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) R[L::BLOCKS - 1][r][q] = __uint_as_float(0xFFFFFFFFu);  // (above every threshold's pattern: nothing to look at before the first block)
+  const uint32_t thr_bits = __float_as_uint(a.thr) | 0x80000000u;  // (x >= thr on the bit patterns, see k_join)
+  uint32_t pend_i = 0, pend_j = 0;  // place of the block that the filter looks at next
+
+  // Rare path: candidates of the block in buffer P.  The lanes that hold one queue their sixteen values (see k_join); the queue is
+  // looked at when it is full.
+  auto rare = [&](auto p_c, uint32_t least0, uint32_t least1) __attribute__((always_inline)) {
+    constexpr int P = decltype(p_c)::value;
+    if constexpr (COUNT) {
+      if (rows_at != pend_i) {
+        if (qfill) drain();
+        send_rows();
+        rows_at = pend_i;
+        settle();
+      }
+    }
+    uint32_t l = lane;
+    asm volatile("" : "+v"(l));
+    const uint32_t in_i = 4 * (l >> 4), in_j = pend_j + (l & 15u);
+    uint32_t todo = 0;  // regions that did not fit
+    bool columns = false;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const float16v& v = R[P][r];
+      const bool has = (r ? least1 : least0) <= thr_bits;
+      const unsigned long long lanes = __ballot(has);
+      const uint32_t cnt = __popcll(lanes);
+      if (cnt == 0) continue;
+      if (COUNT && cnt >= (uint32_t)L::DENSE) {
+        // many candidates: every lane looks at its own, and the numbers are added up in the LDS
+        const uint32_t self = (uint32_t)a.self, i0 = pend_i + 32 * r + in_i;
+        uint32_t hit = 0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) hit |= v[q] >= a.thr ? 1u << q : 0u;
+        if ((self && pend_j < pend_i + 64) || pend_i + 64 > (uint32_t)a.nA || pend_j + 32 > (uint32_t)a.nB)
+          hit &= keep_mask(i0, in_j, (uint32_t)a.nA, (uint32_t)a.nB, self != 0);
+        if (cnt < (uint32_t)L::FULL) {  // a few hits a lane: one of each lane's per round
+          while (__ballot(hit != 0)) {
+            if (hit) {
+              const uint32_t q = (uint32_t)__builtin_ctz(hit);
+              atomicAdd(row_counts + 32 * r + in_i + 2 * (q & 8u) + (q & 3u), 1u);
+              atomicAdd(col_counts + (l & 15u) + 4 * (q & 4u), 1u);
+              hit &= hit - 1;
+            }
+          }
+          columns = true;
+          continue;
+        }
+        const uint32_t n0 = __popc(hit & 0x0F0Fu), n1 = __popc(hit & 0xF0F0u);
+        if (n0) atomicAdd(col_counts + (l & 15u), n0);
+        if (n1) atomicAdd(col_counts + 16 + (l & 15u), n1);
+        // Rows: a byte per row (two registers of a lane share one), added up over the sixteen lanes that share four of them twice.  (An
+        // atomic per lane and row, sixteen on one address: 32,000 points, d = 60, 500 neighbours, 342 us against 308.)
+        auto spread = [](uint32_t four) { return __umul24(four, 0x204081u) & 0x01010101u; };  // bit q to byte q
+        uint32_t rows[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          rows[h] = spread((hit >> (8 * h)) & 15u) + spread((hit >> (8 * h + 4)) & 15u);
+          rows[h] += __builtin_amdgcn_update_dpp(0, rows[h], 0x128, 0xF, 0xF, false);  // rotations by 8, 4, 2, 1 within sixteen lanes
+          rows[h] += __builtin_amdgcn_update_dpp(0, rows[h], 0x124, 0xF, 0xF, false);
+          rows[h] += __builtin_amdgcn_update_dpp(0, rows[h], 0x122, 0xF, 0xF, false);
+          rows[h] += __builtin_amdgcn_update_dpp(0, rows[h], 0x121, 0xF, 0xF, false);
+        }
+        const uint32_t mine = ((l & 4u ? rows[1] : rows[0]) >> (8 * (l & 3u))) & 0xFFu;
+        if ((l & 8u) == 0 && mine) atomicAdd(row_counts + 32 * r + in_i + 4 * (l & 4u) + (l & 3u), mine);
+        columns = true;
+      } else if (qfill + cnt <= (uint32_t)L::QUEUE) {
+        if (has) {
+          const uint32_t e = qfill + __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u));
+          float4v* q = reinterpret_cast<float4v*>(queue_v + 16 * e);
+          q[0] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+          q[1] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+          q[2] = __builtin_shufflevector(v, v, 8, 9, 10, 11);
+          q[3] = __builtin_shufflevector(v, v, 12, 13, 14, 15);
+          queue_t[e] = make_uint2(pend_i + 32 * r + in_i, in_j);
+        }
+        qfill = __builtin_amdgcn_readfirstlane(qfill + cnt);
+      } else {
+        todo |= 1u << r;
+      }
+    }
+    uint32_t taken = 0;
+#pragma unroll 1
+    while (todo) {
+      drain();
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        if (!(todo & (1u << r)) || qfill == (uint32_t)L::QUEUE) continue;
+        const float16v& v = R[P][r];
+        uint32_t least = r ? least1 : least0;
+        asm volatile("" : "+v"(least));
+        const bool has = least <= thr_bits;
+        const unsigned long long lanes = __ballot(has);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(lanes >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)lanes, 0u));
+        const uint32_t e = qfill + rank - taken;
+        if (has && rank >= taken && e < (uint32_t)L::QUEUE) {
+          float4v* q = reinterpret_cast<float4v*>(queue_v + 16 * e);
+          q[0] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+          q[1] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+          q[2] = __builtin_shufflevector(v, v, 8, 9, 10, 11);
+          q[3] = __builtin_shufflevector(v, v, 12, 13, 14, 15);
+          queue_t[e] = make_uint2(pend_i + 32 * r + in_i, in_j);
+        }
+        const uint32_t left = __popcll(lanes) - taken, room = L::QUEUE - qfill;
+        if (left <= room) {
+          qfill = __builtin_amdgcn_readfirstlane(qfill + left);
+          taken = 0;
+          todo &= ~(1u << r);
+        } else {
+          qfill = L::QUEUE;
+          taken += room;
+        }
+      }
+    }
+    if constexpr (COUNT) {
+      if (columns) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        if (l < 32) {
+          const uint32_t c = col_counts[l];
+          if (c) {
+            col_counts[l] = 0;
+            const auto ka = arguments();
+            if (ka->self) atomicAdd(&ka->counts[pend_j + l], c);
+            else if (ka->counts_b) atomicAdd(&ka->counts_b[pend_j + l], c);
+          }
+        }
+        dirty = true;
+        settle();
+      }
+    }
+    if (dirty) {  // (stores and atomics count on vmcnt like the copies, but complete in any order)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      dirty = false;
+    }
+  };
+  auto least_of = [&](const float16v& v) -> uint32_t {
+    auto u = [&](int r) { return __float_as_uint(v[r]); };
+    uint32_t m = min(min(u(0), u(1)), u(2));
+#pragma unroll
+    for (int r = 3; r < 15; r += 2) m = min(min(m, u(r)), u(r + 1));
+    return min(m, u(15));
+  };
+  // One block of a stage: 64 rows x 32 columns, k in ascending order, then the augmentation step.  P: which block, and its buffer;
+  // with two buffers the other one's block goes through the filter under the MFMAs of the second k-block.  cur, nxt: LDS offset of
+  // this and of the next stage.
+  auto block = [&](auto p_c, uint32_t cur, uint32_t nxt, uint32_t i, uint32_t j) __attribute__((always_inline)) {
+    constexpr int P = decltype(p_c)::value, Q = L::TWO ? 1 - P : 0;
+    constexpr bool LAST = P == L::BLOCKS - 1;
+    constexpr int TURN = FRAGS - (RING - 1);  // from this fragment on what is read belongs to the next block
+    float4v acc[4][2];
+    uint32_t least0 = 0, least1 = 0;
+    half8 gb;
+    for_each_index([&](auto f_c) __attribute__((always_inline)) {
+      constexpr int f = decltype(f_c)::value, kb = f / 2, c = f % 2;
+      constexpr int EARLY = L::TWO ? 0 : TURN - 2;  // what is needed at the end of the block is read here
+      if constexpr (LAST && f == TURN) {
+        post_read();
+        proceed();
+      }
+      if constexpr (f == EARLY) {
+        gb = at_lds(aug0 + ((cur + P * 512) & aug_step), 0);
+        if (LAST) look();
+      }
+      constexpr int read = f + RING - 1, then = read % FRAGS;
+      fb[(P * FRAGS + read) % RING] = at_lds((off0 + (LAST && read >= FRAGS ? nxt : cur)) ^ (then % 2 * 32),
+                                             then / 2 * L::KB + (read < FRAGS ? P : (LAST ? 0 : P + 1)) * 2048);
+      if constexpr (L::TWO && f == 2) {
+        least0 = least_of(R[Q][0]);
+        least1 = least_of(R[Q][1]);
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = c ? 3 - u : u;
+        const float4v z = {0.f, 0.f, 0.f, 0.f};
+        acc[t][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[kb][t], fb[(P * FRAGS + f) % RING], kb == 0 ? z : acc[t][c], 0, 0, 0);
+      }
+      // one LDS read, then four MFMAs, the filter's instructions between them
+      if constexpr (f == EARLY) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if constexpr (f == EARLY && LAST) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if constexpr (L::TWO && kb == 1) __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+      }
+      if constexpr (c) __builtin_amdgcn_sched_barrier(0);
+      if constexpr (L::TWO && f == 3) {
+        if (__ballot(min(least0, least1) <= thr_bits)) rare(std::integral_constant<int, Q>{}, least0, least1);
+      }
+    }, std::make_integer_sequence<int, FRAGS>{});
+#pragma unroll
+    for (int r = 1; r >= 0; --r)
+      R[P][r] = __builtin_amdgcn_mfma_f32_32x32x16_f16(L::ROWS_LDS ? at_lds(aug_rows, r * 512) : ga[r], gb,
+                                                       cat4(acc[2 * r][0], acc[2 * r][1], acc[2 * r + 1][0], acc[2 * r + 1][1]), 0, 0, 0);
+    pend_i = i;
+    pend_j = j;
+    if constexpr (!L::TWO) {
+      least0 = least_of(R[0][0]);
+      least1 = least_of(R[0][1]);
+      if (__ballot(min(least0, least1) <= thr_bits)) rare(std::integral_constant<int, 0>{}, least0, least1);
+    }
+  };
+
+  uint32_t held = run_i;  // the row panel in the registers
+  auto load_panel = [&](uint32_t I) __attribute__((always_inline)) {
+    held = I;
+    const auto ka = arguments();
+    uint32_t panel = 2 * I + (wave >> 2);
+    const bool none = panel >= ka->ntilesA;  // (an odd number of panels of 256)
+    if (none) panel = 2 * I;
+    const char* p = reinterpret_cast<const char*>(ka->XpA) + (int64_t)panel * panel_stride;
+#pragma unroll
+    for (int kb = 0; kb < K; ++kb)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        fa[kb][t] = *reinterpret_cast<const half8*>(p + kb * PANEL_BYTES + quarter * 4096 + (t >> 1) * 2048 + fragment_offset(lane, t & 1));
+    if constexpr (L::ROWS_LDS) {
+      uint4 own = *reinterpret_cast<const uint4*>(p + (int64_t)K * PANEL_BYTES + (quarter * 64 + lane) * 16);
+      if (none) own = make_uint4(P1_OUT_OF_RANGE, 0u, P1_OUT_OF_RANGE, 0u);
+      *reinterpret_cast<uint4*>(lds + L::ROWS_OFF + 1024 * wave + 16 * lane) = own;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    } else {
+      const uint32_t c0 = ka->status[2], c1 = ka->status[3];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        uint4 own = *reinterpret_cast<const uint4*>(p + (int64_t)K * PANEL_BYTES + (quarter * 64 + r * 32 + (lane & 31)) * 16);
+        if (none) own = make_uint4(P1_OUT_OF_RANGE, 0u, P1_OUT_OF_RANGE, 0u);
+        const uint4 con = (lane >> 3) & 1 ? make_uint4(0u, 0u, c0, c1) : make_uint4(c0, c1, 0u, 0u);
+        ga[r] = as_half8(upper ? con : own);
+      }
+    }
+    settle();
+  };
+
+  // ---------------- prologue
+  const uint32_t first_panel = run_i;
+  for (int q = 0; q < L::DEPTH; ++q) issue();
+  load_panel(first_panel);
+  // stages 0 .. POST - 1
+  if (live) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::COPIES * ((L::DEPTH - L::POST) / 2)) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+#pragma unroll
+  for (int f = 0; f < RING - 1; ++f) {  // (RING = 2 K + 1: the last of them are the second block's)
+    const int then = f % FRAGS;
+    fb[f] = at_lds(off0 ^ (then % 2 * 32), then / 2 * L::KB + (f < FRAGS ? 0 : 2048));
+  }
+  for (;;) {
+    const uint32_t c = __builtin_amdgcn_readlane(places, slot), I = __builtin_amdgcn_readlane(places, slot + 32);
+    if (__builtin_expect(c == NO_STAGE, 0)) break;
+    begin_stage();
+    if (__builtin_expect(I != held, 0)) load_panel(I);
+    if (!COUNT && __builtin_expect(a.self && c == I * (EJ_STRIP_ROWS / L::COLS) + wave * (64 / L::COLS), 0)) {  // (i, i) belongs to the result by definition, whatever the arithmetic says
+      const uint32_t i = c * L::COLS + lane;
+      if (fill + 64 > (uint32_t)L::STG) flush();
+      stage_entry(__ballot(i < (uint32_t)a.nA), i < (uint32_t)a.nA, i, i, 0u);
+      if (dirty) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        dirty = false;
+      }
+      settle();
+    }
+    const uint32_t cur = slot * (uint32_t)L::STAGE;
+    slot = slot == L::STAGES - 1 ? 0 : slot + 1;
+    const uint32_t nxt = slot * (uint32_t)L::STAGE;
+    const uint32_t i = I * EJ_STRIP_ROWS + wave * 64, j = c * L::COLS;
+    block(std::integral_constant<int, 0>{}, cur, nxt, i, j);
+    if constexpr (L::TWO) block(std::integral_constant<int, 1>{}, cur, nxt, i, j + 32);
+    if constexpr (L::BLOCKS * FRAGS % RING != 0) {  // the next block's first fragments to the places where it looks for them
+      half8 moved[RING - 1];
+#pragma unroll
+      for (int f = 0; f < RING - 1; ++f) moved[f] = fb[(L::BLOCKS * FRAGS + f) % RING];
+#pragma unroll
+      for (int f = 0; f < RING - 1; ++f) fb[f] = moved[f];
+    }
+    ++g;
+    if (__builtin_expect(--sync_left == 0, 0)) {
+      const auto ka = arguments();
+      sync_left = (uint32_t)ka->sync_mode;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      xcd_align(ka->xcd_bar + blockIdx.x % NUM_XCD, tc.step * ++epoch);
+      settle();
+    }
+  }
+  if constexpr (L::TWO) {
+    const uint32_t least0 = least_of(R[1][0]), least1 = least_of(R[1][1]);
+    if (__ballot(min(least0, least1) <= thr_bits)) rare(std::integral_constant<int, 1>{}, least0, least1);
+  }
+  if (qfill) drain();
+  if constexpr (COUNT) send_rows();
+  xcd_leave();
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // what is left, with one atomic for the workgroup (see k_join)
+  __syncthreads();
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(lds);
+  if (lane == 0) sums[wave] = COUNT ? hits : (unsigned long long)fill;
+  __syncthreads();
+  if (tid == 0) {
+    unsigned long long total = 0;
+    for (int w = 0; w < THREADS / 64; ++w) {
+      const unsigned long long v = sums[w];
+      sums[w] = total;
+      total += v;
+    }
+    if (COUNT && total) atomicAdd(a.total, total);
+    if (!COUNT) sums[THREADS / 64] = total ? atomicAdd(a.n_pairs, total) : 0ull;
+  }
+  if (!COUNT) {
+    __syncthreads();
+    store_staged(sums[THREADS / 64] + sums[wave]);
+  }
+}
+
 
 // ------------------------------------------------------------------------------------------
 // The join of small problems
@@ -2064,6 +2681,59 @@ JoinArgs join_args(const Workspace& w, const Operand& A, const Operand& B, bool 
   return a;
 }
 
+// k_join_strip of nkb k-blocks (2 .. STRIP_MAX), and its LDS
+constexpr int STRIP_MAX = 11;
+typedef void (*JoinKernel)(JoinArgs);
+template <bool COUNT, int... N>
+JoinKernel strip_kernel_of(int nkb, std::integer_sequence<int, N...>) {
+  static const JoinKernel k[] = {&k_join_strip<COUNT, N + 2>...};
+  return k[nkb - 2];
+}
+template <int... N>
+int strip_lds_of(int nkb, std::integer_sequence<int, N...>) {
+  static const int b[] = {Strip<N + 2>::LDS...};
+  return b[nkb - 2];
+}
+template <bool COUNT>
+JoinKernel strip_kernel(int nkb) { return strip_kernel_of<COUNT>(nkb, std::make_integer_sequence<int, STRIP_MAX - 1>{}); }
+int strip_lds(int nkb) { return strip_lds_of(nkb, std::make_integer_sequence<int, STRIP_MAX - 1>{}); }
+
+// Whether k_join_strip takes a problem, and with which set in its rows.  Two sets: the way round that has fewer stages, where a panel of
+// rows, which is read before its first stage starts, counts four (300,000 points x 300 queries, d = 128: 45 us with the queries in
+// the rows, 47 with the points; x 700 71 and 65; 100,000 x 2,000 56 and 61).  k_join computes a tile, twice a stage's pairs, in
+// 2 `gain` times the time of a stage (150,000 points, d = 64, 128, 224, 320: 2.14, 2.85, 4.02, 5.33 ms against 1.93, 2.48, 3.60,
+// 5.08), but needs no rows in place before it starts: where a workgroup has few stages it is the better one (18,000 points,
+// d = 128 / 224 / 320: 189 / 203 / 223 us against 187 / 206 / 235; 26,000: 266 / 300 / 339 against 253 / 293 / 342; 100,000 x 700 points,
+// d = 320: 54 against 62).  Counts of some 40,000 points of few coordinates with tens to hundreds of neighbours are full of candidates
+// and short of matrix work: d = 60, S = 100: 274 us by k_join, 302 here (20,000 points: 138, 113; 150,000: 2.35 ms, 2.28).
+int64_t strip_panels(int64_t n) { return (n + EJ_STRIP_ROWS - 1) / EJ_STRIP_ROWS; }
+int64_t strip_stages(int64_t n) { return (n + EJ_STRIP_COLS - 1) / EJ_STRIP_COLS; }
+struct StripPlan {
+  bool use, swapped;
+};
+StripPlan strip_plan(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nkb, bool count) {
+  StripPlan p{false, false};
+#ifdef EJOIN_ONLY_K_JOIN
+  return p;
+#endif
+  if (nkb > STRIP_MAX) return p;
+  const double cu = ctx->num_cu;
+  const int64_t a = strip_panels(nA), plain = a * strip_stages(nB), turned = strip_panels(nB) * strip_stages(nA);
+  p.swapped = !self && turned <= plain + 4 * a;
+#ifdef EJOIN_ONLY_K_JOIN_STRIP
+  p.use = true;
+  return p;
+#endif
+  const double load = nkb <= 4 ? 1. : (nkb <= 7 ? 1.5 : 2.), gain = nkb <= 2 ? 1.07 : (nkb <= 4 ? 1.13 : (nkb <= 7 ? 1.11 : 1.05));
+  const double cost = self ? ceil((double)a * (a + 1) * (EJ_STRIP_ROWS / EJ_STRIP_COLS / 2) / cu) + 1.5 * load
+                           : (p.swapped ? ceil(turned / cu) + 0.6 * load : ceil(plain / cu) + load * (1 + a / cu));
+  const int64_t ta = (nA + TILE - 1) / TILE, tb = (nB + TILE - 1) / TILE;
+  const double rounds = ceil((self ? (double)ta * (ta + 1) / 2 : (double)ta * tb) / cu);
+  const bool crowded = count && nkb == 2 && nA > 32768 && nA <= 65536;
+  p.use = cost < 2 * gain * rounds && !crowded;
+  return p;
+}
+
 // The join kernel on two packed operand sets whose augmentation blocks are in place.
 template <bool COUNT>
 int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, const Operand& B, bool self, int nslices, float eps,
@@ -2101,7 +2771,25 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
   void (*kernel)(JoinArgs) = split    ? (dense ? k_join<COUNT, false, COUNT, true> : k_join<COUNT, false, false, true>)
                              : keep_a ? (dense ? k_join<COUNT, true, COUNT, false> : k_join<COUNT, true, false, false>)
                                       : (dense ? k_join<COUNT, false, COUNT, false> : k_join<COUNT, false, false, false>);
-  hipLaunchKernelGGL(kernel, dim3(ctx->num_cu), dim3(THREADS), LDS_BYTES, st, a);
+  int lds_bytes = LDS_BYTES;
+  const StripPlan strip = split ? StripPlan{false, false} : strip_plan(ctx, A.n, B.n, self, a.nslices, COUNT);
+  if (strip.use) {
+    kernel = strip_kernel<COUNT>(a.nslices);
+    lds_bytes = strip_lds(a.nslices);
+    if (strip.swapped) {
+      a.swapped = 1;
+      std::swap(a.XpA, a.XpB);
+      std::swap(a.nA, a.nB);
+      std::swap(a.ntilesA, a.ntilesB);
+      std::swap(a.counts, a.counts_b);
+    }
+    const int64_t panels = strip_panels(a.nA), per = SB * TILE / EJ_STRIP_ROWS;
+    a.sb_row_begin = (uint32_t)(sb_row_begin * per);
+    a.sb_row_end = (uint32_t)(sb_row_end < (panels + per - 1) / per ? sb_row_end * per : panels);
+    a.sync_mode = 1024 / a.nslices;  // stages between two alignments: about as long as 512 slices of k_join
+    if (panels * strip_stages(a.nB) / (self ? 2 : 1) <= (int64_t)a.sync_mode * ctx->num_cu) a.sync_mode = 0;
+  }
+  hipLaunchKernelGGL(kernel, dim3(ctx->num_cu), dim3(THREADS), lds_bytes, st, a);
   EJ_TRY(hipGetLastError());
   if (own) ctx->ws_dirty = false;
   if (ctx->profiling) {
@@ -2123,7 +2811,7 @@ int small_tile(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nsli
     const int64_t a = (nA + t - 1) / t, b = (nB + t - 1) / t;
     return self ? a * (a + 1) / 2 : a * b;
   };
-#ifdef EJOIN_ONLY_K_JOIN
+#if defined(EJOIN_ONLY_K_JOIN) || defined(EJOIN_ONLY_K_JOIN_STRIP)
   return 0;
 #endif
   if (tiles(64) <= 300) return 64;
@@ -2369,6 +3057,9 @@ int ejoin_create(ejoin_ctx** out, int device) {
         &k_join<true, true, false, false>, &k_join<true, false, false, true>, &k_join<true, false, true, false>, &k_join<true, true, true, false>,
         &k_join<true, false, true, true>})
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+  for (int nkb = 2; nkb <= STRIP_MAX; ++nkb)
+    for (JoinKernel kernel : {strip_kernel<false>(nkb), strip_kernel<true>(nkb)})
+      if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, strip_lds(nkb));
   if (e != hipSuccess) {
     (void)hipGetLastError();
     ejoin_destroy(ctx);

@@ -139,4 +139,121 @@ struct TileCursor {
   }
 };
 
+// Work distribution of k_join_strip, whose workgroups hold a panel of 512 rows in registers and stream columns past it, 64 at a
+// time (a stage): what counts is that a workgroup changes its rows as seldom as possible, that the workgroups of an XCD stream the
+// same columns at the same time (through its L2), and that all have the same number of stages.
+//   * The panels are cut into bands of 32 (the rest into bands of 16, 8, 4, 2, 1).  A band is worked on along 32 lines: line w has
+//     panel w and goes through its columns from left to right (a band of h panels: 32 / h lines a panel, a part of its columns each).
+//   * XCD x works on the x-th eighth of all bands' lengths, its workgroup y on line y.
+//   * A self-join's band starts with the triangle on the diagonal, folded so that every line has (h + 1) / 2 of its squares of 512 x
+//     512: a line of the upper half gives the end of its row of the triangle to line h - 1 - w, which has that much less of its own.
+// So there are runs of consecutive stages in one panel, two for a band.
+constexpr uint32_t EJ_STRIP_ROWS = 512, EJ_STRIP_COLS = 64, EJ_STRIP_LINES = 32;
+struct StripCursor {
+  uint32_t self, stages, row_end;  // stages in a row (columns / 64); panels this launch covers
+  uint32_t line, step;             // this workgroup's line, workgroups of the XCD
+  uint32_t start_row, start_at, last_row, last_at;  // the XCD's part: from position start_at of the band that starts at start_row ...
+  uint32_t first, h_log2, reach, len;  // the current band: its first panel, log2 of its panels, stages of a panel, positions of a line
+  uint32_t at, piece;              // this line's position in it, and which of its two runs comes next
+
+  EJ_HD __attribute__((always_inline)) void enter(uint32_t f) {
+    first = f;
+    h_log2 = 0;
+    while ((2u << h_log2) <= EJ_STRIP_LINES && (2u << h_log2) <= row_end - f) ++h_log2;
+    const uint32_t h = 1u << h_log2, per = EJ_STRIP_ROWS / EJ_STRIP_COLS, diag_end = per * (f + h);
+    reach = self ? per / 2 * (h + 1) + (stages > diag_end ? stages - diag_end : 0u) : stages;
+    const uint32_t share = EJ_STRIP_LINES >> h_log2;  // lines of a panel
+    len = (reach + share - 1) / share;
+  }
+  // panels_begin .. panels_end - 1: the panels of rows of this launch
+  EJ_HD void init(uint32_t block, uint32_t nblocks, uint32_t self_join, uint32_t n_stages, uint32_t panels_begin, uint32_t panels_end) {
+    self = self_join;
+    stages = n_stages;
+    row_end = panels_end;
+    const uint32_t xcds = nblocks < EJ_NUM_XCD ? nblocks : EJ_NUM_XCD, xcd = block % xcds;
+    step = (nblocks - xcd + xcds - 1) / xcds;
+    line = block / xcds;
+    uint64_t total = 0;
+    for (uint32_t f = panels_begin; f < row_end; f += 1u << h_log2) {
+      enter(f);
+      total += len;
+    }
+    uint64_t from = total * xcd / xcds, to = total * (xcd + 1) / xcds;
+    start_row = last_row = row_end;
+    start_at = last_at = 0;
+    first = row_end;
+    at = piece = 0;
+    if (from == to || line >= EJ_STRIP_LINES) {
+      line = EJ_STRIP_LINES;
+      return;
+    }
+    uint32_t f = panels_begin;
+    for (enter(f); from >= len; enter(f)) {
+      from -= len;
+      to -= len;
+      f += 1u << h_log2;
+    }
+    start_row = f;
+    start_at = (uint32_t)from;
+    for (; to > len; enter(f)) {
+      to -= len;
+      f += 1u << h_log2;
+    }
+    last_row = f;
+    last_at = (uint32_t)to;
+    enter(start_row);
+    at = start_at;
+  }
+  // the next run: stages c .. c_end - 1 of panel I; false when the work is exhausted
+  EJ_HD __attribute__((always_inline)) bool next(uint32_t& I, uint32_t& c, uint32_t& c_end) {
+    while (line < EJ_STRIP_LINES) {
+      const uint32_t h = 1u << h_log2, w = line & (h - 1), offset = (line >> h_log2) * len;
+      const uint32_t per = EJ_STRIP_ROWS / EJ_STRIP_COLS;
+      // positions of this line in the band that belong to the XCD's part, as stages of the panel
+      const uint32_t lo = offset + at;
+      uint32_t hi = offset + (first == last_row ? last_at : len);
+      if (hi > reach) hi = reach;
+      // its runs: [0, turn) of panel r0 from column c0 on, [turn, reach) of panel w from column c1 on
+      uint32_t turn = 0, r0 = w, c0 = 0, c1 = 0;
+      if (self) {
+        if (w < h / 2) {
+          turn = per / 2 * (h + 1);
+          c0 = per * (first + w);
+          c1 = per * (first + h);
+        } else {
+          turn = per * w + per / 2 - per / 2 * h;
+          r0 = h - 1 - w;
+          c0 = per * (first + r0) + per / 2 * (h + 1);
+          c1 = per * (first + w);
+        }
+      }
+      while (piece < 2) {
+        const uint32_t a = piece ? (lo > turn ? lo : turn) : lo, b = piece ? hi : (hi < turn ? hi : turn);
+        const uint32_t row = first + (piece ? w : r0);
+        c = piece ? c1 + (a - turn) : c0 + a;
+        c_end = piece ? c1 + (b - turn) : c0 + b;
+        const bool some = a < b;
+        ++piece;
+        if (c_end > stages) c_end = stages;
+        if (some && c < c_end) {
+          I = EJ_UNIFORM(row);
+          c = EJ_UNIFORM(c);
+          c_end = EJ_UNIFORM(c_end);
+          return true;
+        }
+      }
+      piece = 0;
+      at = 0;
+      if (first != last_row) {
+        enter(first + h);
+      } else {  // (a grid of fewer workgroups than lines: the next of this one's lines)
+        line += step;
+        enter(start_row);
+        at = start_at;
+      }
+    }
+    return false;
+  }
+};
+
 #endif  // EJOIN_TILE_CURSOR_H

@@ -31,4 +31,25 @@ int64_t ejoin_test_schedule_rows(uint32_t nblocks, uint32_t self_join, uint32_t 
 int64_t ejoin_test_schedule(uint32_t nblocks, uint32_t self_join, uint32_t nt_a, uint32_t nt_b, uint32_t* out, int64_t cap) {
   return ejoin_test_schedule_rows(nblocks, self_join, nt_a, nt_b, 0, 0xFFFFFFFFu, out, cap);
 }
+
+// The same of the schedule in panels of 512 rows and stages of 64 columns: (block, panel, first stage, end) per run.
+int64_t ejoin_test_strips(uint32_t nblocks, uint32_t self_join, uint32_t stages, uint32_t panels_begin, uint32_t panels_end, uint32_t* out,
+                          int64_t cap) {
+  int64_t m = 0;
+  for (uint32_t b = 0; b < nblocks; ++b) {
+    StripCursor tc;
+    tc.init(b, nblocks, self_join, stages, panels_begin, panels_end);
+    uint32_t I = 0, c = 0, c_end = 0;
+    while (tc.next(I, c, c_end)) {
+      if (m < cap) {
+        out[4 * m] = b;
+        out[4 * m + 1] = I;
+        out[4 * m + 2] = c;
+        out[4 * m + 3] = c_end;
+      }
+      ++m;
+    }
+  }
+  return m;
+}
 }

@@ -36,8 +36,17 @@ def build_schedule(tmp_path_factory, kind):
         buf = np.zeros((want + 8, 4), dtype=np.uint32)
         m = lib.ejoin_test_schedule_rows(nblocks, int(self_join), nt_a, nt_b, row_begin, row_end, buf.ctypes.data, want + 8)
         return buf[:min(m, want + 8)], m
+    lib.ejoin_test_strips.restype = ctypes.c_int64
+    lib.ejoin_test_strips.argtypes = [ctypes.c_uint32] * 5 + [ctypes.c_void_p, ctypes.c_int64]
+
+    def run_strips(nblocks, self_join, stages, panels_begin, panels_end):
+        buf = np.zeros((400 * nblocks, 4), dtype=np.uint32)
+        m = lib.ejoin_test_strips(nblocks, int(self_join), stages, panels_begin, panels_end, buf.ctypes.data, len(buf))
+        assert m <= len(buf)
+        return buf[:m].astype(np.int64)
     run.kind = kind
     run.rows = run_rows
+    run.strips = run_strips
     return run
 
 
@@ -136,3 +145,25 @@ def test_every_workgroup_gets_the_same_number_of_tiles(sched, nblocks, self_join
     off_diagonal = J >= (I // 8 + 1) * 8 if self_join else np.ones(m, dtype=bool)
     on = (blk[1:] == blk[:-1]) & (I[1:] // 8 == I[:-1] // 8) & off_diagonal[1:] & off_diagonal[:-1] & ((I[1:] // 8 + 1) * 8 <= nt_a)
     assert (I[1:][on] == I[:-1][on]).all() and (J[1:][on] == J[:-1][on] + nblocks // 8).all()
+
+
+@pytest.mark.parametrize("nblocks,self_join,n_a,n_b", [(256, True, n, n) for n in (1, 64, 65, 512, 513, 5000, 20011, 100000)] +
+                         [(256, False, a, b) for a, b in ((1, 1), (500, 200000), (200000, 500), (7001, 30011), (513, 64), (70000, 900))] +
+                         [(7, True, 9000, 9000), (24, False, 30000, 5000), (300, True, 40000, 40000), (64, False, 100, 100000)])
+def test_strips_cover_every_stage_once_and_evenly(sched, nblocks, self_join, n_a, n_b):
+    """Runs of 64-column stages in panels of 512 rows: every stage right of the diagonal once, cut into launches or not, and (grids of
+    whole XCDs) no workgroup with more than a few stages over its share."""
+    panels, stages = (n_a + 511) // 512, (n_b + 63) // 64
+    for cuts in ([0, panels], [0, min(8, panels), panels] if self_join else [0, panels]):
+        seen = np.zeros((panels, stages), dtype=np.int64)
+        load = np.zeros(nblocks, dtype=np.int64)
+        for begin, end in zip(cuts[:-1], cuts[1:]):
+            runs = sched.strips(nblocks, self_join, stages, begin, end)
+            assert ((runs[:, 1] >= begin) & (runs[:, 1] < end) & (runs[:, 2] < runs[:, 3]) & (runs[:, 3] <= stages)).all()
+            for b, panel, c, c_end in runs:
+                seen[panel, c:c_end] += 1
+                load[b] += c_end - c
+        want = np.arange(stages)[None, :] >= 8 * np.arange(panels)[:, None] if self_join else np.ones_like(seen, dtype=bool)
+        assert np.array_equal(seen, want.astype(np.int64))
+        if nblocks == 256 and len(cuts) == 2:
+            assert load.max() <= -(-load.sum() // 256) + 2
