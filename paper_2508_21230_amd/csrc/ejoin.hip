@@ -269,12 +269,12 @@ constexpr uint32_t P1_OUT_OF_RANGE = 0xFB53u;  // -60000 in FP16
 // within -14 <= m <= 15 so that c = 2^m is a normal FP16 value (the matrix cores align the products
 // of a step by their exponent fields; a subnormal c would cost them low bits).  The split is exact
 // for every point with s >= max(2^-16 s_max, 2^-14): the 24 mantissa bits of s / 2^(m+1) then lie
-// above FP16's smallest subnormal.  A smaller norm is carried to 2^-25 2^m absolute.  Point i's
-// 16-byte row is  H_i = { P_i, C } = { p1, p2, p3, 0, c, c, c, 0 }; the extra step multiplies
+// above FP16's smallest subnormal.  A smaller norm is carried to 2^-25 2^m absolute.  With the pieces
+// P_i = { p1, p2, p3, 0 } and C = { c, c, c, 0 } the extra step multiplies
 // pieces by constants, c (p1 + p2 + p3)_i + c (q1 + q2 + q3)_j = -s_i/2 - s_j/2, every product exact in FP32.
-// H (npad rows) serves the dense-tile kernel only.  For the join the operands of the extra step are also
+// For the join the operands of the extra step are
 // written, ready made, into one more k-block behind the data k-blocks of each panel of the packed set (`Xp`,
-// may be null; k-block `aug_kb` of `blocks`): 16 bytes per row for the panel as the A operand (chunk 0 of
+// null: a set that is not there; k-block `aug_kb` of `blocks`): 16 bytes per row for the panel as the A operand (chunk 0 of
 // panel_layout.h, "the augmentation step": 256 x 16 B), then 16 bytes per row for the panel as the B operand
 // (chunk 1); the rest of the 16 KB is not used.  The join kernel copies the 4 KB + 4 KB of a tile's two panels
 // to the LDS once per tile; the constant chunks 2 and 3 it builds itself from C, which is left in the status block.
@@ -313,16 +313,13 @@ __device__ __forceinline__ uint2 norm_pieces(float s, int m) {
 struct AuxSet {
   const float* s;
   int64_t n, npad;
-  uint4* Xp;         // null: no augmentation block (dense-tile call)
+  uint4* Xp;
   uint32_t* counts;  // count mode: cleared on the way (n entries; may be null)
 };
 struct AuxArgs {
   AuxSet a, b;  // (b.npad = 0: one set)
   uint32_t* status_and_max;
   const uint32_t* set_max;  // largest norm of a prepared set, or null
-  const uint32_t* maxima;   // dense-tile call: largest norms, one per workgroup of k_norms (else the status block holds the largest)
-  uint32_t nmaxima;
-  uint4* H;                 // rows of set a for the dense-tile kernel, or null
   int aug_kb;               // k-block of the augmentation operands = data k-blocks of a panel
   unsigned long long* counter;
 };
@@ -332,16 +329,9 @@ __global__ __launch_bounds__(256) void k_aux(const AuxArgs args) {
   const AuxSet& set = second ? args.b : args.a;
   const int64_t i = (int64_t)(blockIdx.x - (second ? groups_a : 0u)) * 256 + threadIdx.x, n = set.n;
   const float* s = set.s;
-  uint32_t mb;
-  if (args.maxima) {
-    mb = 0;
-    for (uint32_t q = threadIdx.x; q < args.nmaxima; q += 256) mb = max(mb, args.maxima[q]);
-    mb = max_of_group(mb);
-  } else {
-    mb = args.status_and_max[1];
-    if (args.set_max) mb = max(mb, *args.set_max);
-  }
-  if (blockIdx.x == 0 && !args.maxima) {
+  uint32_t mb = args.status_and_max[1];
+  if (args.set_max) mb = max(mb, *args.set_max);
+  if (blockIdx.x == 0) {
     if (threadIdx.x < 8) args.status_and_max[8 + threadIdx.x] = 0;
     if (threadIdx.x == 8 && args.counter) *args.counter = 0;
   }
@@ -358,20 +348,13 @@ __global__ __launch_bounds__(256) void k_aux(const AuxArgs args) {
     if (st != ST_OK) return make_uint2(0u, 0u);
     return norm_pieces(s[x], ns.m);
   };
-  if (args.H) {
-    const uint2 cc = (i >= n || st == ST_OK) ? make_uint2(c | (c << 16), c) : make_uint2(0u, 0u);
-    const uint2 own = pieces(i);
-    args.H[i] = make_uint4(own.x, own.y, cc.x, cc.y);
-  }
-  if (set.Xp) {
-    const int r = (int)(i & 31);
-    const int64_t b = i - r;
-    const int64_t xa = b + aug_row_point(r), xb = b + aug_col_point(r);
-    const uint2 a0 = pieces(xa), a1 = pieces(xa + 4), b0 = pieces(xb), b1 = pieces(xb + 16);
-    uint4* blk = set.Xp + packed_index((i >> 8) << 10, args.aug_kb, args.aug_kb + 1);  // the panel's augmentation block
-    blk[aug_block_unit((int)(i & 255), 0)] = make_uint4(a0.x, a0.y, a1.x, a1.y);
-    blk[aug_block_unit((int)(i & 255), 1)] = make_uint4(b0.x, b0.y, b1.x, b1.y);
-  }
+  const int r = (int)(i & 31);
+  const int64_t b = i - r;
+  const int64_t xa = b + aug_row_point(r), xb = b + aug_col_point(r);
+  const uint2 a0 = pieces(xa), a1 = pieces(xa + 4), b0 = pieces(xb), b1 = pieces(xb + 16);
+  uint4* blk = set.Xp + packed_index((i >> 8) << 10, args.aug_kb, args.aug_kb + 1);  // the panel's augmentation block
+  blk[aug_block_unit((int)(i & 255), 0)] = make_uint4(a0.x, a0.y, a1.x, a1.y);
+  blk[aug_block_unit((int)(i & 255), 1)] = make_uint4(b0.x, b0.y, b1.x, b1.y);
 }
 
 __device__ __forceinline__ half8 as_half8(uint4 v) { return __builtin_bit_cast(half8, v); }
@@ -542,145 +525,6 @@ __global__ __launch_bounds__(512) void k_split_prep(const SplitArgs a) {
   }
 }
 
-// Dense block of squared distances with the join's arithmetic: a workgroup of 2 x 2 wavefronts per TS x TS tile of the block,
-// every 32 x 32 region of it computed the way the join kernel computes a region of its wave tile: four 16 x 16 blocks
-// accumulated with v_mfma_f32_16x16x32_f16, then one v_mfma_f32_32x32x16_f16 on the four blocks' registers side by side that
-// adds -s_i/2 - s_j/2 (operand layout: see the augmentation step of k_join).
-// Bound by writing the block and by how the operands reach the CUs: they are read from X as it is (64 coordinates of a row at a
-// time, whole lines), DEPTH slices ahead in registers, and go through two LDS stages in the arrangement of panel_layout.h, with
-// the 16-byte positions permuted further so that the stores too hit all banks (48 us without, for the block below).
-// With one wavefront per 32 x 32 region and its operands straight from memory, 4,000 x 5,000 at d = 384 took 119 us, now 44.
-// TS = 128 needs half the operand traffic of TS = 64, which gives four times the workgroups.  The line lies at three
-// workgroups of the larger kind for two CUs: at 1,280 of them (4,000 x 5,000, d = 384) 58 against 71 us a call, at 384
-// (3,000 x 2,000, d = 960) 48 against 50, at 144 (1,500 x 1,500, d = 384) 26 against 22.  DEPTH: one slice suffices where
-// two workgroups share a CU (TS = 128: 44 us, two slices 45), small blocks are latency and get four.
-template <int TS, int DEPTH>
-__global__ __launch_bounds__(256) void k_dist2_tile(const uint16_t* __restrict__ X, const uint4* __restrict__ H,
-                                                    const uint32_t* __restrict__ status, int64_t n, int64_t ld, int slices,
-                                                    int64_t i0, int64_t j0, int rows, int cols, float* __restrict__ out) {
-  constexpr int W = TS / 2, MT = W / 16;              // wave tile, 16 x 16 blocks along its edge
-  constexpr int LOADS = TS * 8 / 256;                 // 16-byte chunks per thread, operand and slice
-  constexpr int KB_BYTES = TS * 64, OP_BYTES = 2 * KB_BYTES, ST_BYTES = 2 * OP_BYTES;
-  __shared__ __attribute__((aligned(1024))) char lds[2 * ST_BYTES];
-  if (*status != ST_OK) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * W, wn = (wave & 1) * W;
-  // workgroup -> tile: a contiguous part of the tiles for every XCD, in bands of eight rows, column by column
-  const uint32_t tr = (uint32_t)(rows + TS - 1) / TS, tc = (uint32_t)(cols + TS - 1) / TS, tiles = tr * tc;
-  const uint32_t t = blockIdx.x % EJ_NUM_XCD * ((tiles + EJ_NUM_XCD - 1) / EJ_NUM_XCD) + blockIdx.x / EJ_NUM_XCD;
-  if (t >= tiles) return;
-  const uint32_t band = t / (EJ_BAND * tc), in_band = t - band * EJ_BAND * tc;
-  const uint32_t h = tr - band * EJ_BAND < EJ_BAND ? tr - band * EJ_BAND : EJ_BAND;
-  const int bi = (int)(band * EJ_BAND + in_band % h) * TS, bj = (int)(in_band / h) * TS;
-  auto row_a = [&](int local) { const int64_t r = i0 + bi + local; return r >= n ? n - 1 : r; };
-  auto row_b = [&](int local) { const int64_t r = j0 + bj + local; return r >= n ? n - 1 : r; };
-  auto lds_place = [](int row, int chunk, int kb) -> uint32_t {
-    return kb * KB_BYTES + (row ^ (kb << 1)) * 64 + ((chunk ^ swz(row) ^ ((row >> 3) & 2)) << 4);
-  };
-  const half8* ga[LOADS];
-  const half8* gb[LOADS];
-  uint32_t at[LOADS];
-#pragma unroll
-  for (int q = 0; q < LOADS; ++q) {
-    const int r = (tid + 256 * q) >> 3, c = tid & 7;  // eight lanes read a line of X
-    ga[q] = reinterpret_cast<const half8*>(X + row_a(r) * ld) + c;
-    gb[q] = reinterpret_cast<const half8*>(X + row_b(r) * ld) + c;
-    // the panel layout, with what eight lanes store for one row spread over all banks as well
-    const int64_t place = place_of(r, c & 3);
-    at[q] = lds_place((int)(place >> 2), (int)(place & 3) ^ swz((int)(place >> 2)), c >> 2);
-  }
-  half8 ra[DEPTH][LOADS], rb[DEPTH][LOADS];
-  auto load = [&](int slice, int set) {  // (past the last slice: the last one again, never used)
-    const int at_slice = (slice < slices ? slice : slices - 1) * 8;
-#pragma unroll
-    for (int q = 0; q < LOADS; ++q) {
-      ra[set][q] = ga[q][at_slice];
-      rb[set][q] = gb[q][at_slice];
-    }
-  };
-  auto store = [&](int slice, int set) {
-    char* st = lds + (slice & 1) * ST_BYTES;
-#pragma unroll
-    for (int q = 0; q < LOADS; ++q) {
-      *reinterpret_cast<half8*>(st + at[q]) = ra[set][q];
-      *reinterpret_cast<half8*>(st + OP_BYTES + at[q]) = rb[set][q];
-    }
-  };
-  uint32_t off[2][2];  // (as fragment_offset)
-#pragma unroll
-  for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-    for (int f = 0; f < 2; ++f) off[kb][f] = lds_place(lane & 31, 2 * f + (lane >> 5), kb);
-  float4v acc[MT][MT];
-#pragma unroll
-  for (int a = 0; a < MT; ++a)
-#pragma unroll
-    for (int c = 0; c < MT; ++c) acc[a][c] = float4v{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int slice) {
-    const char* st = lds + (slice & 1) * ST_BYTES;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      half8 fa[MT], fb[MT];
-#pragma unroll
-      for (int f = 0; f < MT; ++f) {
-        fa[f] = *reinterpret_cast<const half8*>(st + wm * 64 + (f >> 1) * 2048 + off[kb][f & 1]);
-        fb[f] = *reinterpret_cast<const half8*>(st + OP_BYTES + wn * 64 + (f >> 1) * 2048 + off[kb][f & 1]);
-      }
-#pragma unroll
-      for (int a = 0; a < MT; ++a)
-#pragma unroll
-        for (int c = 0; c < MT; ++c) acc[a][c] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[a], fb[c], acc[a][c], 0, 0, 0);
-    }
-  };
-  // slice s goes to LDS stage s % 2 and is loaded into register set s % DEPTH
-#pragma unroll
-  for (int u = 0; u < DEPTH; ++u) load(u, u);
-  store(0, 0);
-  load(DEPTH, 0);
-  __syncthreads();
-  for (int s0 = 0; s0 < slices; s0 += DEPTH) {
-#pragma unroll
-    for (int u = 0; u < DEPTH; ++u) {
-      const int s = s0 + u;
-      if (s < slices) {  // (uniform) the stage written here was last read for slice s - 1, before the barrier
-        store(s + 1, (u + 1) % DEPTH);
-        load(s + 1 + DEPTH, (u + 1) % DEPTH);
-        compute(s);
-        __syncthreads();
-      }
-    }
-  }
-  const int m = lane & 31;
-  const int ca = aug_chunk_a(lane), cb = aug_chunk_b(lane);
-  // augmentation operands: H_x = { p1, p2, p3, 0, c, c, c, 0 } (16 bytes): pieces in .x .y, constant in .z .w;
-  // the four chunks of the operand rows (panel_layout.h, "the augmentation step") are built here from the H rows
-  half8 ha[MT / 2], hb[MT / 2];
-#pragma unroll
-  for (int R = 0; R < MT / 2; ++R) {
-    const int xa = wm + 32 * R + aug_row_point(m), xb = wn + 32 * R + aug_col_point(m);
-    const uint4 h0 = H[row_a(xa)], h1 = H[row_a(xa + 4)], q0 = H[row_b(xb)], q1 = H[row_b(xb + 16)];
-    ha[R] = as_half8(ca == 0 ? make_uint4(h0.x, h0.y, h1.x, h1.y) : (ca == 2 ? make_uint4(h0.z, h0.w, 0, 0) : make_uint4(0, 0, h0.z, h0.w)));
-    hb[R] = as_half8(cb == 1 ? make_uint4(q0.x, q0.y, q1.x, q1.y) : (cb == 2 ? make_uint4(q0.z, q0.w, 0, 0) : make_uint4(0, 0, q0.z, q0.w)));
-  }
-#pragma unroll
-  for (int Ra = 0; Ra < MT / 2; ++Ra)
-#pragma unroll
-    for (int Rb = 0; Rb < MT / 2; ++Rb) {
-      const float16v res = __builtin_amdgcn_mfma_f32_32x32x16_f16(
-          ha[Ra], hb[Rb], cat4(acc[2 * Ra][2 * Rb], acc[2 * Ra][2 * Rb + 1], acc[2 * Ra + 1][2 * Rb], acc[2 * Ra + 1][2 * Rb + 1]), 0, 0, 0);
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        int pi, pj;
-        region_pair(lane, q, pi, pj);
-        const int rr = bi + wm + 32 * Ra + pi, cc = bj + wn + 32 * Rb + pj;
-        if (rr < rows && cc < cols) out[(int64_t)rr * cols + cc] = (i0 + rr == j0 + cc) ? 0.f : fmaxf(-2.f * res[q], 0.f);
-      }
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// The join kernel
-// ------------------------------------------------------------------------------------------
 // Workgroup barrier without the fences of __syncthreads(): those make the compiler wait for every
 // outstanding global->LDS copy (vmcnt(0)) at each barrier, which would serialise the copy pipeline.
 // The kernel orders its LDS traffic itself: copies are certified with counted vmcnt waits before the
@@ -702,7 +546,195 @@ __device__ __forceinline__ void copy16_to_lds(uint32_t lds_addr, const void* sba
       : "s"(lds_addr), "v"(voff), "s"(sbase), "n"(LDS_IMM)
       : "memory", "m0", "scc");
 }
+// The same from an address of each lane's own.
+template <int LDS_IMM>
+__device__ __forceinline__ void copy16_to_lds_from(uint32_t lds_addr, const void* p) {
+  asm volatile(
+      "s_add_u32 m0, %0, %2\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, off"
+      :
+      : "s"(lds_addr), "v"(p), "n"(LDS_IMM)
+      : "memory", "m0", "scc");
+}
 
+// Dense block of squared distances with the join's arithmetic: a workgroup of 2 x 2 wavefronts per TS x TS tile of the block,
+// every 32 x 32 region of it computed the way the join kernel computes a region of its wave tile: four 16 x 16 blocks
+// accumulated with v_mfma_f32_16x16x32_f16, then one v_mfma_f32_32x32x16_f16 on the four blocks' registers side by side that
+// adds -s_i/2 - s_j/2 (operand layout: see the augmentation step of k_join).
+// Bound by how the operands reach the CUs and then by writing the block (4,000 x 5,000 at d = 384, 80 MB: 39 us a call, of which the
+// norms of the 20,000 points take 6; 29 without the stores).  The operands come from X as it is, 64 coordinates of a row (a whole
+// line) at a time, straight to the LDS, STAGES - 1 slices ahead; the columns are the rows of the MFMAs, so that a lane stores sixteen
+// bytes of a row; the operands of the augmentation step are worked out here, from the norms.  With slices through registers, 4-byte
+// stores and a launch of their own for the augmentation rows: 57 us a call; 1,500 x 1,500 20, now 14; 3,000 x 2,000 at d = 960 42,
+// now 29; 6,000 x 6,000 at d = 128 54, now 40.  (Tried: rows of 256 bytes stored by way of the LDS: the same; stores that pass the
+// caches by: 68.)
+// TS = 128 needs half the operand traffic of TS = 64, which gives four times the workgroups: at 144 of the larger kind (1,500 x
+// 1,500, d = 384) 15.2 us a call against 13.6, at 225 (1,800 x 1,800) 15.6 against 16.9, at 240 (700 x 5,001, d = 100) 13.2 against
+// 14.6, at 289 the same, at 1,280 39 against 46: the line lies at three workgroups of the larger kind for four CUs.
+struct DenseArgs {
+  const uint16_t* X;
+  const float* s;
+  const uint32_t* maxima;  // largest norms, one per workgroup of k_norms
+  uint32_t nmaxima;
+  uint32_t* status;
+  int64_t n, ld;
+  int slices;  // of 64 coordinates
+  int64_t i0, j0;
+  int rows, cols;
+  float* out;
+};
+template <int TS>
+constexpr int dense_stages() { return TS == 64 ? 3 : 2; }
+template <int TS>
+constexpr int dense_lds_bytes() { return dense_stages<TS>() * 2 * TS * 128 + 2 * TS * 16 + 64; }
+template <int TS>
+__global__ __launch_bounds__(256, TS == 64 ? 3 : 2) void k_dist2_tile(const DenseArgs a) {
+  constexpr int W = TS / 2, MT = W / 16, NR = W / 32;     // wave tile, 16 x 16 blocks and 32 x 32 regions along its edge
+  constexpr int COPIES = TS / 32;                         // copy instructions per wavefront, operand and slice
+  constexpr int STAGES = dense_stages<TS>();
+  constexpr int OP_BYTES = TS * 128, ST_BYTES = 2 * OP_BYTES;
+  constexpr int AUG = STAGES * ST_BYTES, AUG_B = AUG + TS * 16, AUG_CONST = AUG_B + TS * 16;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave >> 1) * W, wn = (wave & 1) * W;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+  // workgroup -> tile: a contiguous part of the tiles for every XCD, in bands of eight rows, column by column
+  const uint32_t tr = (uint32_t)(a.rows + TS - 1) / TS, tc = (uint32_t)(a.cols + TS - 1) / TS, tiles = tr * tc;
+  const uint32_t t = blockIdx.x % EJ_NUM_XCD * ((tiles + EJ_NUM_XCD - 1) / EJ_NUM_XCD) + blockIdx.x / EJ_NUM_XCD;
+  if (t >= tiles) return;
+  const uint32_t band = t / (EJ_BAND * tc), in_band = t - band * EJ_BAND * tc;
+  const uint32_t h = tr - band * EJ_BAND < EJ_BAND ? tr - band * EJ_BAND : EJ_BAND;
+  const int bi = (int)(band * EJ_BAND + in_band % h) * TS, bj = (int)(in_band / h) * TS;
+  auto row_a = [&](int local) { const int64_t r = a.i0 + bi + local; return r >= a.n ? a.n - 1 : r; };
+  auto row_b = [&](int local) { const int64_t r = a.j0 + bj + local; return r >= a.n ? a.n - 1 : r; };
+  // A slice of an operand in the LDS: rows of 128 bytes (64 coordinates), chunk c of row r at position c ^ swizzle(r): the 16 lanes
+  // that an LDS read serves together, rows r .. r + 15 at one chunk or half of them at the chunk beside it, hit all banks.  A copy
+  // instruction fills eight rows.
+  auto swizzle = [](int row) { return (row >> 1) & 7; };
+  const char *ga[COPIES], *gb[COPIES];
+#pragma unroll
+  for (int q = 0; q < COPIES; ++q) {
+    const int r = 8 * (4 * q + wave) + (lane >> 3), c = (lane & 7) ^ swizzle(r);
+    ga[q] = reinterpret_cast<const char*>(a.X + row_a(r) * a.ld) + 16 * c;
+    gb[q] = reinterpret_cast<const char*>(a.X + row_b(r) * a.ld) + 16 * c;
+  }
+  auto issue = [&](int stage) {  // the next slice
+    const uint32_t at = __builtin_amdgcn_readfirstlane(lds0 + stage * ST_BYTES + wave * 1024);
+    copy16_to_lds_from<0>(at, ga[0]);
+    copy16_to_lds_from<4096>(at, ga[1]);
+    if constexpr (COPIES == 4) {
+      copy16_to_lds_from<8192>(at, ga[COPIES - 2]);
+      copy16_to_lds_from<12288>(at, ga[COPIES - 1]);
+    }
+    copy16_to_lds_from<OP_BYTES>(at, gb[0]);
+    copy16_to_lds_from<OP_BYTES + 4096>(at, gb[1]);
+    if constexpr (COPIES == 4) {
+      copy16_to_lds_from<OP_BYTES + 8192>(at, gb[COPIES - 2]);
+      copy16_to_lds_from<OP_BYTES + 12288>(at, gb[COPIES - 1]);
+    }
+#pragma unroll
+    for (int q = 0; q < COPIES; ++q) {
+      ga[q] += 128;
+      gb[q] += 128;
+    }
+  };
+#pragma unroll
+  for (int ks = 0; ks < STAGES - 1; ++ks)
+    if (ks < a.slices) issue(ks);
+  // ---- operands of the augmentation step from the norms: thread t row t of the tile's column points, then of its row points.  The
+  // wave tile is accumulated with the columns as rows of the MFMA (a lane then holds four consecutive columns of a row of the block);
+  // the step adds the rows' terms first all the same, as the joins do.
+  float sx = 0.f, sy = 0.f;
+  if (tid < 2 * TS) {
+    const bool row_part = tid >= TS;
+    const int r = tid & (TS - 1), in = r & 31;
+    const int x = (r & ~31) + (row_part ? aug_col_point(in) : aug_row_point(in)), y = x + (row_part ? 16 : 4);
+    sx = a.s[row_part ? row_a(x) : row_b(x)];
+    sy = a.s[row_part ? row_a(y) : row_b(y)];
+  }
+  uint32_t mb = 0;
+  for (uint32_t q = tid; q < a.nmaxima; q += 256) mb = max(mb, a.maxima[q]);
+  const NormScale ns = norm_scale(max_of_group(mb));
+  if (blockIdx.x == 0 && tid == 0) a.status[0] = ns.st;
+  if (ns.st != ST_OK) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the copies must land before the wave ends
+    return;
+  }
+  if (tid < 2 * TS) {
+    const uint2 p = norm_pieces(sx, ns.m), q = norm_pieces(sy, ns.m);
+    *reinterpret_cast<uint4*>(lds + AUG + tid * 16) = make_uint4(p.x, p.y, q.x, q.y);
+  }
+  if (tid < 4) {  // the constant chunks of the augmentation step (2 and 3)
+    const uint32_t c = fp16_bits(ns.c), c0 = c | (c << 16);
+    *reinterpret_cast<uint2*>(lds + AUG_CONST + tid * 8) = tid == 0 || tid == 3 ? make_uint2(c0, c) : make_uint2(0u, 0u);
+  }
+  uint32_t off[2];  // k-block kb of the slice: row lane % 16, chunk 4 kb + lane / 16
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb) off[kb] = (lane & 15) * 128 + (((4 * kb + (lane >> 4)) ^ swizzle(lane & 15)) << 4);
+  float4v acc[MT][MT];  // [columns][rows]
+#pragma unroll
+  for (int x = 0; x < MT; ++x)
+#pragma unroll
+    for (int y = 0; y < MT; ++y) acc[x][y] = float4v{0.f, 0.f, 0.f, 0.f};
+  int stage = 0;
+  for (int ks = 0; ks < a.slices; ++ks) {
+    // (as in k_join_small)
+    if (STAGES == 3 && ks + 1 < a.slices) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * COPIES) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    wg_barrier();  // slice ks is there for everybody, and everybody is done with slice ks - 1
+    if (ks + STAGES - 1 < a.slices) issue(stage == 0 ? STAGES - 1 : stage - 1);
+    const char* st = lds + stage * ST_BYTES;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      half8 fa[MT], fb[MT];
+#pragma unroll
+      for (int f = 0; f < MT; ++f) {
+        fa[f] = *reinterpret_cast<const half8*>(st + (wm + 16 * f) * 128 + off[kb]);
+        fb[f] = *reinterpret_cast<const half8*>(st + OP_BYTES + (wn + 16 * f) * 128 + off[kb]);
+      }
+#pragma unroll
+      for (int x = 0; x < MT; ++x)
+#pragma unroll
+        for (int y = 0; y < MT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[x], fa[y], acc[x][y], 0, 0, 0);
+    }
+    stage = stage == STAGES - 1 ? 0 : stage + 1;
+  }
+  const int m = lane & 31;
+  const char* aug_c = lds + (lane < 32 ? AUG_CONST + 16 * ((lane >> 3) & 1) : AUG + 16 * (wn + m));
+  const char* aug_r = lds + (lane < 32 ? AUG_B + 16 * (wm + m) : AUG_CONST + 16 * ((lane >> 4) & 1));
+  const int step_c = lane < 32 ? 0 : 512, step_r = lane < 32 ? 512 : 0;
+#pragma unroll
+  for (int Rr = 0; Rr < NR; ++Rr) {
+    const half8 hr = *reinterpret_cast<const half8*>(aug_r + Rr * step_r);
+#pragma unroll
+    for (int Rc = 0; Rc < NR; ++Rc) {
+      const half8 hc = *reinterpret_cast<const half8*>(aug_c + Rc * step_c);
+      const float16v res = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+          hc, hr, cat4(acc[2 * Rc][2 * Rr], acc[2 * Rc][2 * Rr + 1], acc[2 * Rc + 1][2 * Rr], acc[2 * Rc + 1][2 * Rr + 1]), 0, 0, 0);
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {  // (region_pair with rows and columns exchanged)
+          const int rr = bi + wm + 32 * Rr + 16 * c + (lane & 15), cc = bj + wn + 32 * Rc + 16 * b + 4 * (lane >> 4);
+          if (rr >= a.rows || cc >= a.cols) continue;
+          const int64_t self = a.i0 + rr - a.j0 - cc;  // column of the point itself, from cc
+          float4u v;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) v[q] = self == q ? 0.f : fmaxf(-2.f * res[8 * b + 4 * c + q], 0.f);
+          float* to = a.out + (int64_t)rr * a.cols + cc;
+          if (cc + 4 <= a.cols) *reinterpret_cast<float4u*>(to) = v;
+          else
+            for (int q = 0; q < a.cols - cc; ++q) to[q] = v[q];
+        }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// The join kernel
+// ------------------------------------------------------------------------------------------
 // Brings the workgroups of one XCD back in step: each adds one to its XCD's counter and waits until
 // the counter reaches `expect` (workgroups per XCD x number of alignments so far).  Workgroups that
 // share operand panels only hit each other's lines in the XCD's L2 while they are within a few slices
@@ -2425,7 +2457,7 @@ namespace {
 struct Workspace {
   uint32_t* status;  // status block, 64 words (see k_reset)
   float* s;          // norms (4 B per point); the context's own: then one maximum per NORM_POINTS points (dense-tile call)
-  uint4* H;          // augmentation rows (16 B per point, padded to a multiple of TILE); small problems: the largest norms
+  uint4* H;          // small problems: the largest norms of k_prep's workgroups (16 B per point, padded to a multiple of TILE)
   uint4* Xp;         // packed copy of X plus the augmentation k-block
 };
 
@@ -2504,7 +2536,7 @@ bool bad_eps(float eps) { return !(eps >= 0.f) || !isfinite(eps); }
 int64_t packed_bytes(int64_t rows, int64_t dpad) { return rows * (dpad + KSLICE) * 2; }
 
 // The context's own workspace for `rows` points in total (each set padded to a multiple of TILE).
-// dpad = 0: only the per-point arrays (norms, augmentation rows); dpad > 0: also the packed copies.
+// dpad = 0: only the per-point arrays (norms); dpad > 0: also the packed copies.
 // Growing frees the old arrays, which first waits for the device to be idle.
 int ensure_workspace(ejoin_ctx* ctx, int64_t rows, int64_t dpad) {
   Workspace& w = ctx->ws;
@@ -2605,7 +2637,7 @@ int launch_prep(ejoin_ctx* ctx, PrepSet& A, PrepSet& B, int nkb, PrepArgs& p, hi
 // the norms and the largest norm of all (in the status block; set_max: that of a prepared set), and what the call needs zero.
 int launch_aux(ejoin_ctx* ctx, uint32_t* status, const uint32_t* set_max, const AuxSet& A, const AuxSet& B, int data_blocks,
                unsigned long long* counter, hipStream_t st) {
-  const AuxArgs a{A, B, status, set_max, nullptr, 0, nullptr, data_blocks, counter};
+  const AuxArgs a{A, B, status, set_max, data_blocks, counter};
   hipLaunchKernelGGL(k_aux, dim3((unsigned)((A.npad + B.npad) / 256)), dim3(256), 0, st, a);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
@@ -3057,6 +3089,7 @@ int ejoin_create(ejoin_ctx** out, int device) {
         &k_join<true, true, false, false>, &k_join<true, false, false, true>, &k_join<true, false, true, false>, &k_join<true, true, true, false>,
         &k_join<true, false, true, true>})
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dist2_tile<128>), hipFuncAttributeMaxDynamicSharedMemorySize, dense_lds_bytes<128>());
   for (int nkb = 2; nkb <= STRIP_MAX; ++nkb)
     for (JoinKernel kernel : {strip_kernel<false>(nkb), strip_kernel<true>(nkb)})
       if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, strip_lds(nkb));
@@ -3322,25 +3355,22 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   ctx->last_stream = st;
   // (no atomics on the status block: its state between calls is left as it is)
   uint32_t* maxima = reinterpret_cast<uint32_t*>(w.s + ctx->s_cap);
-  AuxArgs aux{AuxSet{w.s, n, pad_rows(n), nullptr, nullptr}, AuxSet{}, w.status, nullptr, maxima, 0, w.H, 0, nullptr};
-  EJ_RC(launch_norms(ctx, X, n, d, ld, w.s, nullptr, nullptr, st, maxima, &aux.nmaxima));
-  // k_aux has a workgroup per 256 points and each reads all maxima, of which there are as many: from some 5 10^5 points on a launch
-  // that folds them first costs less (d = 16, block of 100 x 100: 500,000 points 23.2 us without, 23.7 with; 10^6 37.7 and 35.6;
-  // 5 10^6 248 and 168; 3 10^8 650 ms and 10)
+  DenseArgs a{X, w.s, maxima, 0, w.status, n, ld, (k_blocks(d) + 1) / 2 /* (rows are padded to a multiple of 64 coordinates) */, i0, j0, rows, cols, out};
+  EJ_RC(launch_norms(ctx, X, n, d, ld, w.s, nullptr, nullptr, st, maxima, &a.nmaxima));
+  // every workgroup of the dense kernel reads all maxima: from some 5 10^5 points on a launch that folds them first costs less
+  // (d = 16, block of 100 x 100: 200,000 points 14.3 us without, 17.7 with; 500,000 17.9 and 18.6; 10^6 28.2 and 27.8; 5 10^6 145 and
+  // 136; block of 4,000 x 4,000: 500,000 points 32.2 and 31.5; 10^6 44.7 and 41.4)
   constexpr uint32_t FOLD_MAXIMA = 2048;
-  if (aux.nmaxima > FOLD_MAXIMA) {
-    hipLaunchKernelGGL(k_fold_max, dim3(1), dim3(512), 0, st, maxima, aux.nmaxima);
+  if (a.nmaxima > FOLD_MAXIMA) {
+    hipLaunchKernelGGL(k_fold_max, dim3(1), dim3(512), 0, st, maxima, a.nmaxima);
     EJ_TRY(hipGetLastError());
-    aux.nmaxima = 1;
+    a.nmaxima = 1;
   }
-  hipLaunchKernelGGL(k_aux, dim3((unsigned)(aux.a.npad / 256)), dim3(256), 0, st, aux);
-  EJ_TRY(hipGetLastError());
-  const int slices = (k_blocks(d) + 1) / 2;  // (rows are padded to a multiple of 64 coordinates)
   auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
-  if (2 * blocks(128) >= 3 * ctx->num_cu)  // (see the kernel)
-    hipLaunchKernelGGL((k_dist2_tile<128, 1>), dim3((unsigned)blocks(128)), dim3(256), 0, st, X, w.H, w.status, n, ld, slices, i0, j0, rows, cols, out);
+  if (4 * blocks(128) >= 3 * ctx->num_cu)  // (see the kernel)
+    hipLaunchKernelGGL(k_dist2_tile<128>, dim3((unsigned)blocks(128)), dim3(256), dense_lds_bytes<128>(), st, a);
   else
-    hipLaunchKernelGGL((k_dist2_tile<64, 4>), dim3((unsigned)blocks(64)), dim3(256), 0, st, X, w.H, w.status, n, ld, slices, i0, j0, rows, cols, out);
+    hipLaunchKernelGGL(k_dist2_tile<64>, dim3((unsigned)blocks(64)), dim3(256), dense_lds_bytes<64>(), st, a);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }

@@ -151,6 +151,29 @@ def test_dist2_tile_sizes_agree_bit_for_bit(ej, d, rows, cols):
         assert np.all(np.abs(got[int(r)].cpu().numpy().astype(np.float64) - want[0]) <= tol[0])
 
 
+@pytest.mark.parametrize("d,rows,cols", [(1, 1, 3), (33, 65, 2), (64, 64, 66), (65, 130, 129), (96, 1535, 2048), (127, 1536, 2049), (129, 1537, 2047)])
+def test_dist2_tile_edges(ej, d, rows, cols):
+    """Columns that are no multiple of the four a lane stores, one and two slices, blocks on either side of the line between the
+    tile sizes (192 tiles of 128) that end at the last point and cross the diagonal: against the oracle, and nothing is written
+    past the block's end."""
+    print(f"dist2_tile edges d={d} {rows}x{cols}", flush=True)
+    n = 2100
+    rng = np.random.default_rng(100 * d + cols)
+    X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
+    i0, j0 = n - rows, n - cols
+    buf = torch.full((rows * cols + 64,), -7.0, dtype=torch.float32, device="cuda")
+    Xd = dev(pad(X, (d + 63) // 64 * 64))
+    ej._check(ej._lib.ejoin_dist2_tile(ej._h, Xd.data_ptr(), n, d, Xd.stride(0), i0, j0, rows, cols, buf.data_ptr(), ej._stream()), ej._h)
+    assert torch.all(buf[rows * cols:] == -7.0)
+    P = orc.decode(X)
+    s = orc.norms(P)
+    want = orc.dist2_block(P, i0, rows, j0, cols)
+    got = buf[:rows * cols].reshape(rows, cols).cpu().numpy().astype(np.float64)
+    assert np.all(np.abs(got - want) <= parity.value_tolerance(want, s[i0:, None] + s[None, j0:], s.max()))
+    same = np.arange(i0, n)[:, None] == np.arange(j0, n)[None, :]
+    assert np.all(got[same] == 0.0)
+
+
 @pytest.mark.parametrize("n", [524288, 524289, 800001])
 def test_dist2_tile_of_a_large_set_finds_its_largest_norm(ej, n):
     """One largest norm per 256 points, folded by a launch of its own from 524,289 points on: whichever point has the largest, the
