@@ -558,16 +558,17 @@ __device__ __forceinline__ void copy16_to_lds_from(uint32_t lds_addr, const void
       : "memory", "m0", "scc");
 }
 
-// Dense block of squared distances with the join's arithmetic: a workgroup of 2 x 2 wavefronts per TS x TS tile of the block,
+// Dense block of squared distances with the join's arithmetic: a workgroup of 2 x 2 or 2 x 4 wavefronts per TS x TS tile of the block,
 // every 32 x 32 region of it computed the way the join kernel computes a region of its wave tile: four 16 x 16 blocks
 // accumulated with v_mfma_f32_16x16x32_f16, then one v_mfma_f32_32x32x16_f16 on the four blocks' registers side by side that
 // adds -s_i/2 - s_j/2 (operand layout: see the augmentation step of k_join).
-// Bound by how the operands reach the CUs and then by writing the block (4,000 x 5,000 at d = 384, 80 MB: 39 us a call, of which the
-// norms of the 20,000 points take 6; 29 without the stores).  The operands come from X as it is, 64 coordinates of a row (a whole
+// Bound by how the operands reach the CUs and then by writing the block (4,000 x 5,000 at d = 384, 80 MB: 37 us a call, of which the
+// norms of the 20,000 points take 6; some 28 without the stores).  The operands come from X as it is, 64 coordinates of a row (a whole
 // line) at a time, straight to the LDS, STAGES - 1 slices ahead; the columns are the rows of the MFMAs, so that a lane stores sixteen
 // bytes of a row; the operands of the augmentation step are worked out here, from the norms.  With slices through registers, 4-byte
 // stores and a launch of their own for the augmentation rows: 57 us a call; 1,500 x 1,500 20, now 14; 3,000 x 2,000 at d = 960 42,
-// now 29; 6,000 x 6,000 at d = 128 54, now 40.  (Tried: rows of 256 bytes stored by way of the LDS: the same; stores that pass the
+// now 29; 6,000 x 6,000 at d = 128 54, now 37.  Eight wavefronts for TS = 128, of which two workgroups fit a CU: with four of
+// 64 x 64 each 41 us a call, with eight 37, with sixteen 38; 6,000 x 6,000 at d = 128 41, 37, 41.  (Tried: rows of 256 bytes stored by way of the LDS: the same; stores that pass the
 // caches by: 68.)
 // TS = 128 needs half the operand traffic of TS = 64, which gives four times the workgroups: at 144 of the larger kind (1,500 x
 // 1,500, d = 384) 15.2 us a call against 13.6, at 225 (1,800 x 1,800) 15.6 against 16.9, at 240 (700 x 5,001, d = 100) 13.2 against
@@ -587,18 +588,21 @@ struct DenseArgs {
 template <int TS>
 constexpr int dense_stages() { return TS == 64 ? 3 : 2; }
 template <int TS>
+constexpr int dense_waves() { return TS == 64 ? 4 : 8; }
+template <int TS>
 constexpr int dense_lds_bytes() { return dense_stages<TS>() * 2 * TS * 128 + 2 * TS * 16 + 64; }
 template <int TS>
-__global__ __launch_bounds__(256, TS == 64 ? 3 : 2) void k_dist2_tile(const DenseArgs a) {
-  constexpr int W = TS / 2, MT = W / 16, NR = W / 32;     // wave tile, 16 x 16 blocks and 32 x 32 regions along its edge
-  constexpr int COPIES = TS / 32;                         // copy instructions per wavefront, operand and slice
+__global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_dist2_tile(const DenseArgs a) {
+  constexpr int WAVES = dense_waves<TS>(), ACROSS = WAVES / 2;  // two rows of wavefronts
+  constexpr int WR = TS / 2, WC = TS / ACROSS, MR = WR / 16, MC = WC / 16;  // wave tile, and its 16 x 16 blocks: rows, columns
+  constexpr int COPIES = TS / 8 / WAVES;                  // copy instructions per wavefront, operand and slice
   constexpr int STAGES = dense_stages<TS>();
   constexpr int OP_BYTES = TS * 128, ST_BYTES = 2 * OP_BYTES;
   constexpr int AUG = STAGES * ST_BYTES, AUG_B = AUG + TS * 16, AUG_CONST = AUG_B + TS * 16;
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = (wave >> 1) * W, wn = (wave & 1) * W;
+  const int wm = wave / ACROSS * WR, wn = wave % ACROSS * WC;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   // workgroup -> tile: a contiguous part of the tiles for every XCD, in bands of eight rows, column by column
   const uint32_t tr = (uint32_t)(a.rows + TS - 1) / TS, tc = (uint32_t)(a.cols + TS - 1) / TS, tiles = tr * tc;
@@ -616,24 +620,17 @@ __global__ __launch_bounds__(256, TS == 64 ? 3 : 2) void k_dist2_tile(const Dens
   const char *ga[COPIES], *gb[COPIES];
 #pragma unroll
   for (int q = 0; q < COPIES; ++q) {
-    const int r = 8 * (4 * q + wave) + (lane >> 3), c = (lane & 7) ^ swizzle(r);
+    const int r = 8 * (WAVES * q + wave) + (lane >> 3), c = (lane & 7) ^ swizzle(r);
     ga[q] = reinterpret_cast<const char*>(a.X + row_a(r) * a.ld) + 16 * c;
     gb[q] = reinterpret_cast<const char*>(a.X + row_b(r) * a.ld) + 16 * c;
   }
   auto issue = [&](int stage) {  // the next slice
     const uint32_t at = __builtin_amdgcn_readfirstlane(lds0 + stage * ST_BYTES + wave * 1024);
+    static_assert(COPIES == 2, "two copy instructions per wavefront and operand");
     copy16_to_lds_from<0>(at, ga[0]);
-    copy16_to_lds_from<4096>(at, ga[1]);
-    if constexpr (COPIES == 4) {
-      copy16_to_lds_from<8192>(at, ga[COPIES - 2]);
-      copy16_to_lds_from<12288>(at, ga[COPIES - 1]);
-    }
+    copy16_to_lds_from<WAVES * 1024>(at, ga[1]);
     copy16_to_lds_from<OP_BYTES>(at, gb[0]);
-    copy16_to_lds_from<OP_BYTES + 4096>(at, gb[1]);
-    if constexpr (COPIES == 4) {
-      copy16_to_lds_from<OP_BYTES + 8192>(at, gb[COPIES - 2]);
-      copy16_to_lds_from<OP_BYTES + 12288>(at, gb[COPIES - 1]);
-    }
+    copy16_to_lds_from<OP_BYTES + WAVES * 1024>(at, gb[1]);
 #pragma unroll
     for (int q = 0; q < COPIES; ++q) {
       ga[q] += 128;
@@ -655,7 +652,7 @@ __global__ __launch_bounds__(256, TS == 64 ? 3 : 2) void k_dist2_tile(const Dens
     sy = a.s[row_part ? row_a(y) : row_b(y)];
   }
   uint32_t mb = 0;
-  for (uint32_t q = tid; q < a.nmaxima; q += 256) mb = max(mb, a.maxima[q]);
+  for (uint32_t q = tid; q < a.nmaxima; q += 64 * WAVES) mb = max(mb, a.maxima[q]);
   const NormScale ns = norm_scale(max_of_group(mb));
   if (blockIdx.x == 0 && tid == 0) a.status[0] = ns.st;
   if (ns.st != ST_OK) {
@@ -673,11 +670,11 @@ __global__ __launch_bounds__(256, TS == 64 ? 3 : 2) void k_dist2_tile(const Dens
   uint32_t off[2];  // k-block kb of the slice: row lane % 16, chunk 4 kb + lane / 16
 #pragma unroll
   for (int kb = 0; kb < 2; ++kb) off[kb] = (lane & 15) * 128 + (((4 * kb + (lane >> 4)) ^ swizzle(lane & 15)) << 4);
-  float4v acc[MT][MT];  // [columns][rows]
+  float4v acc[MC][MR];  // [columns][rows]
 #pragma unroll
-  for (int x = 0; x < MT; ++x)
+  for (int x = 0; x < MC; ++x)
 #pragma unroll
-    for (int y = 0; y < MT; ++y) acc[x][y] = float4v{0.f, 0.f, 0.f, 0.f};
+    for (int y = 0; y < MR; ++y) acc[x][y] = float4v{0.f, 0.f, 0.f, 0.f};
   int stage = 0;
   for (int ks = 0; ks < a.slices; ++ks) {
     // (as in k_join_small)
@@ -688,16 +685,15 @@ __global__ __launch_bounds__(256, TS == 64 ? 3 : 2) void k_dist2_tile(const Dens
     const char* st = lds + stage * ST_BYTES;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
-      half8 fa[MT], fb[MT];
+      half8 fa[MR], fb[MC];
 #pragma unroll
-      for (int f = 0; f < MT; ++f) {
-        fa[f] = *reinterpret_cast<const half8*>(st + (wm + 16 * f) * 128 + off[kb]);
-        fb[f] = *reinterpret_cast<const half8*>(st + OP_BYTES + (wn + 16 * f) * 128 + off[kb]);
-      }
+      for (int f = 0; f < MR; ++f) fa[f] = *reinterpret_cast<const half8*>(st + (wm + 16 * f) * 128 + off[kb]);
 #pragma unroll
-      for (int x = 0; x < MT; ++x)
+      for (int f = 0; f < MC; ++f) fb[f] = *reinterpret_cast<const half8*>(st + OP_BYTES + (wn + 16 * f) * 128 + off[kb]);
 #pragma unroll
-        for (int y = 0; y < MT; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[x], fa[y], acc[x][y], 0, 0, 0);
+      for (int x = 0; x < MC; ++x)
+#pragma unroll
+        for (int y = 0; y < MR; ++y) acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fb[x], fa[y], acc[x][y], 0, 0, 0);
     }
     stage = stage == STAGES - 1 ? 0 : stage + 1;
   }
@@ -706,10 +702,10 @@ __global__ __launch_bounds__(256, TS == 64 ? 3 : 2) void k_dist2_tile(const Dens
   const char* aug_r = lds + (lane < 32 ? AUG_B + 16 * (wm + m) : AUG_CONST + 16 * ((lane >> 4) & 1));
   const int step_c = lane < 32 ? 0 : 512, step_r = lane < 32 ? 512 : 0;
 #pragma unroll
-  for (int Rr = 0; Rr < NR; ++Rr) {
+  for (int Rr = 0; Rr < MR / 2; ++Rr) {
     const half8 hr = *reinterpret_cast<const half8*>(aug_r + Rr * step_r);
 #pragma unroll
-    for (int Rc = 0; Rc < NR; ++Rc) {
+    for (int Rc = 0; Rc < MC / 2; ++Rc) {
       const half8 hc = *reinterpret_cast<const half8*>(aug_c + Rc * step_c);
       const float16v res = __builtin_amdgcn_mfma_f32_32x32x16_f16(
           hc, hr, cat4(acc[2 * Rc][2 * Rr], acc[2 * Rc][2 * Rr + 1], acc[2 * Rc + 1][2 * Rr], acc[2 * Rc + 1][2 * Rr + 1]), 0, 0, 0);
@@ -3368,9 +3364,9 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   }
   auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
   if (4 * blocks(128) >= 3 * ctx->num_cu)  // (see the kernel)
-    hipLaunchKernelGGL(k_dist2_tile<128>, dim3((unsigned)blocks(128)), dim3(256), dense_lds_bytes<128>(), st, a);
+    hipLaunchKernelGGL(k_dist2_tile<128>, dim3((unsigned)blocks(128)), dim3(64 * dense_waves<128>()), dense_lds_bytes<128>(), st, a);
   else
-    hipLaunchKernelGGL(k_dist2_tile<64>, dim3((unsigned)blocks(64)), dim3(256), dense_lds_bytes<64>(), st, a);
+    hipLaunchKernelGGL(k_dist2_tile<64>, dim3((unsigned)blocks(64)), dim3(64 * dense_waves<64>()), dense_lds_bytes<64>(), st, a);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }
