@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import os
 import subprocess
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -66,8 +67,10 @@ def build_ablations(verbose: bool = False) -> dict:
     """Compile the ablation variants, the timing-only experiment builds (measurement only, see bench_ablation.py) and the tests'
     build of the general kernel -> ablation/libejoin_<name>.so."""
     os.makedirs(ABLATION_DIR, exist_ok=True)
-    return {name: _compile(os.path.join(ABLATION_DIR, f"libejoin_{name}.so"), defs, verbose)
-            for name, defs in {**ABLATIONS, **EXPERIMENTS, **GENERAL_KERNEL, **STRIP_KERNEL}.items()}
+    variants = {**ABLATIONS, **EXPERIMENTS, **GENERAL_KERNEL, **STRIP_KERNEL}
+    with ThreadPoolExecutor(min(4, os.cpu_count() or 1)) as pool:  # (one after the other they take six minutes)
+        libs = pool.map(lambda name: _compile(os.path.join(ABLATION_DIR, f"libejoin_{name}.so"), variants[name], verbose), variants)
+        return dict(zip(variants, libs))
 
 
 if __name__ == "__main__":
