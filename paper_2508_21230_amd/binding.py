@@ -131,8 +131,8 @@ class EJoin:
 
     @staticmethod
     def _stream():
-        # the handle of torch.cuda.current_stream(), without the object: 0.2 us a call where that takes 3.2, of the 13.3 that a
-        # count of 1,000 points costs the host (10.3 now; the GPU is done in 9)
+        # the handle of torch.cuda.current_stream(), without the object: 0.2 us a call where that takes 3.2, of the 12.7 to 13.9
+        # that a count of 1,000 points costs the host (10.3 to 11.9 now, over three machines; the GPU is done in 9)
         return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
     def _x(self, X: torch.Tensor, d):
