@@ -22,7 +22,7 @@ int ejoin_last_kernel_ms(ejoin_ctx* ctx, float* prep_ms, float* join_ms);
 /* What the join kernel of a call executes: *tiles output tiles of *edge x *edge points (256; 128 or 64 for small problems), *steps
  * matrix-core steps of 32 coordinates each, i.e. 2 * edge * edge * 32 * steps FLOP per tile (without the one step per tile that adds
  * the norms).  np points with themselves (nq = 0) or with nq query points; split != 0: the split-FP16 join of np FP32 rows.
- * (Points of two to eleven k-blocks of 32 coordinates are mostly joined in pieces of 512 x 64; they are counted as the tiles all the same.)
+ * (Points of two to ten k-blocks of 32 coordinates are mostly joined in pieces of 512 x 64; they are counted as the tiles all the same.)
  * (ejoin_selfjoin_pairs_to_host takes tiles of 256 where it cuts the join into several launches.)  Host pointers; no device work. */
 int ejoin_join_work(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int32_t split, int32_t* edge, int32_t* steps, int64_t* tiles);
 

@@ -2709,8 +2709,10 @@ JoinArgs join_args(const Workspace& w, const Operand& A, const Operand& B, bool 
   return a;
 }
 
-// k_join_strip of nkb k-blocks (2 .. STRIP_MAX), and its LDS
-constexpr int STRIP_MAX = 11;
+// k_join_strip of nkb k-blocks (2 .. STRIP_MAX), and its LDS.  At eleven k-blocks 12 (pairs) and 21 (counts) of its registers are spilled, and
+// what is read back at every stage waits for the copies just issued: d = 350, S = 16, 50,000 points 676 us of counts and 662 of pairs against
+// 650 and 653 by k_join, 100,000 points 2.47 and 2.43 ms against 2.49 and 2.49; 30,000 x 7,000 130 us of counts against 123.
+constexpr int STRIP_MAX = 10;
 typedef void (*JoinKernel)(JoinArgs);
 template <bool COUNT, int... N>
 JoinKernel strip_kernel_of(int nkb, std::integer_sequence<int, N...>) {
