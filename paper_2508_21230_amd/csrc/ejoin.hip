@@ -31,7 +31,7 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 // ------------------------------------------------------------------------------------------
 // Tiling constants
 // ------------------------------------------------------------------------------------------
-constexpr int TILE = 256;     // a workgroup computes a TILE x TILE block of the distance matrix
+constexpr int TILE = EJ_TILE;  // a workgroup computes a TILE x TILE block of the distance matrix
 constexpr int KPAD = 64;      // rows are padded with zeros to a multiple of KPAD coordinates (by the caller)
 constexpr int KSLICE = 32;    // coordinates per LDS stage (64 B per row)
 // Ablation builds (bench_ablation.py) take one design element out at a time; every variant computes the
@@ -1790,11 +1790,17 @@ __global__ __launch_bounds__(THREADS) void k_join_strip(const JoinArgs a) {
     asm volatile("" ::: "memory");
   };
   // Start of stage g: the copies of stage g + POST, if they were this wavefront's, have landed once only those of its younger stages are
-  // outstanding.
+  // outstanding.  (Stores and atomics count on vmcnt like the copies, but complete in any order: with some of them issued since, once
+  // nothing at all is.  Waiting for them where they are issued instead holds up every block that has candidates, in counts of many
+  // neighbours all of them: 33,000 points, d = 60, S = 100 225 us, now 200; 65,000, d = 96, S = 400 1.02 ms, now 0.88.)
   auto begin_stage = [&]() __attribute__((always_inline)) {
     if (((g + L::POST) & 1) == turn) {
-      if (__builtin_expect(live, 1)) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::COPIES * ((L::DEPTH - 1 - L::POST) / 2)) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if (__builtin_expect(live && !dirty, 1)) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(L::COPIES * ((L::DEPTH - 1 - L::POST) / 2)) : "memory");
+      } else {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        dirty = false;
+      }
       if (lane == 0) *sync_word(wave) = g + L::POST + 2;
     }
     issue();  // stage g + DEPTH
@@ -1949,10 +1955,6 @@ __global__ __launch_bounds__(THREADS) void k_join_strip(const JoinArgs a) {
         settle();
       }
     }
-    if (dirty) {  // (stores and atomics count on vmcnt like the copies, but complete in any order)
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      dirty = false;
-    }
   };
   auto least_of = [&](const float16v& v) -> uint32_t {
     auto u = [&](int r) { return __float_as_uint(v[r]); };
@@ -2075,10 +2077,6 @@ __global__ __launch_bounds__(THREADS) void k_join_strip(const JoinArgs a) {
       const uint32_t i = c * L::COLS + lane;
       if (fill + 64 > (uint32_t)L::STG) flush();
       stage_entry(__ballot(i < (uint32_t)a.nA), i < (uint32_t)a.nA, i, i, 0u);
-      if (dirty) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        dirty = false;
-      }
       settle();
     }
     const uint32_t cur = slot * (uint32_t)L::STAGE;
@@ -2709,10 +2707,7 @@ JoinArgs join_args(const Workspace& w, const Operand& A, const Operand& B, bool 
   return a;
 }
 
-// k_join_strip of nkb k-blocks (2 .. STRIP_MAX), and its LDS.  At eleven k-blocks 12 (pairs) and 21 (counts) of its registers are spilled, and
-// what is read back at every stage waits for the copies just issued: d = 350, S = 16, 50,000 points 676 us of counts and 662 of pairs against
-// 650 and 653 by k_join, 100,000 points 2.47 and 2.43 ms against 2.49 and 2.49; 30,000 x 7,000 130 us of counts against 123.
-constexpr int STRIP_MAX = 10;
+// k_join_strip of nkb k-blocks (2 .. EJ_STRIP_KB_MAX), and its LDS
 typedef void (*JoinKernel)(JoinArgs);
 template <bool COUNT, int... N>
 JoinKernel strip_kernel_of(int nkb, std::integer_sequence<int, N...>) {
@@ -2725,42 +2720,17 @@ int strip_lds_of(int nkb, std::integer_sequence<int, N...>) {
   return b[nkb - 2];
 }
 template <bool COUNT>
-JoinKernel strip_kernel(int nkb) { return strip_kernel_of<COUNT>(nkb, std::make_integer_sequence<int, STRIP_MAX - 1>{}); }
-int strip_lds(int nkb) { return strip_lds_of(nkb, std::make_integer_sequence<int, STRIP_MAX - 1>{}); }
+JoinKernel strip_kernel(int nkb) { return strip_kernel_of<COUNT>(nkb, std::make_integer_sequence<int, EJ_STRIP_KB_MAX - 1>{}); }
+int strip_lds(int nkb) { return strip_lds_of(nkb, std::make_integer_sequence<int, EJ_STRIP_KB_MAX - 1>{}); }
 
-// Whether k_join_strip takes a problem, and with which set in its rows.  Two sets: the way round that has fewer stages, where a panel of
-// rows, which is read before its first stage starts, counts four (300,000 points x 300 queries, d = 128: 45 us with the queries in
-// the rows, 47 with the points; x 700 71 and 65; 100,000 x 2,000 56 and 61).  k_join computes a tile, twice a stage's pairs, in
-// 2 `gain` times the time of a stage (150,000 points, d = 64, 128, 224, 320: 2.14, 2.85, 4.02, 5.33 ms against 1.93, 2.48, 3.60,
-// 5.08), but needs no rows in place before it starts: where a workgroup has few stages it is the better one (18,000 points,
-// d = 128 / 224 / 320: 189 / 203 / 223 us against 187 / 206 / 235; 26,000: 266 / 300 / 339 against 253 / 293 / 342; 100,000 x 700 points,
-// d = 320: 54 against 62).  Counts of some 40,000 points of few coordinates with tens to hundreds of neighbours are full of candidates
-// and short of matrix work: d = 60, S = 100: 274 us by k_join, 302 here (20,000 points: 138, 113; 150,000: 2.35 ms, 2.28).
-int64_t strip_panels(int64_t n) { return (n + EJ_STRIP_ROWS - 1) / EJ_STRIP_ROWS; }
-int64_t strip_stages(int64_t n) { return (n + EJ_STRIP_COLS - 1) / EJ_STRIP_COLS; }
-struct StripPlan {
-  bool use, swapped;
-};
-StripPlan strip_plan(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nkb, bool count) {
-  StripPlan p{false, false};
+StripPlan plan_strip(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nkb, bool count) {
+  StripPlan p = strip_plan(ctx->num_cu, nA, nB, self, nkb, count);
 #ifdef EJOIN_ONLY_K_JOIN
-  return p;
+  p.use = false;
 #endif
-  if (nkb > STRIP_MAX) return p;
-  const double cu = ctx->num_cu;
-  const int64_t a = strip_panels(nA), plain = a * strip_stages(nB), turned = strip_panels(nB) * strip_stages(nA);
-  p.swapped = !self && turned <= plain + 4 * a;
 #ifdef EJOIN_ONLY_K_JOIN_STRIP
-  p.use = true;
-  return p;
+  p.use = nkb <= EJ_STRIP_KB_MAX;
 #endif
-  const double load = nkb <= 4 ? 1. : (nkb <= 7 ? 1.5 : 2.), gain = nkb <= 2 ? 1.07 : (nkb <= 4 ? 1.13 : (nkb <= 7 ? 1.11 : 1.05));
-  const double cost = self ? ceil((double)a * (a + 1) * (EJ_STRIP_ROWS / EJ_STRIP_COLS / 2) / cu) + 1.5 * load
-                           : (p.swapped ? ceil(turned / cu) + 0.6 * load : ceil(plain / cu) + load * (1 + a / cu));
-  const int64_t ta = (nA + TILE - 1) / TILE, tb = (nB + TILE - 1) / TILE;
-  const double rounds = ceil((self ? (double)ta * (ta + 1) / 2 : (double)ta * tb) / cu);
-  const bool crowded = count && nkb == 2 && nA > 32768 && nA <= 65536;
-  p.use = cost < 2 * gain * rounds && !crowded;
   return p;
 }
 
@@ -2802,7 +2772,7 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
                              : keep_a ? (dense ? k_join<COUNT, true, COUNT, false> : k_join<COUNT, true, false, false>)
                                       : (dense ? k_join<COUNT, false, COUNT, false> : k_join<COUNT, false, false, false>);
   int lds_bytes = LDS_BYTES;
-  const StripPlan strip = split ? StripPlan{false, false} : strip_plan(ctx, A.n, B.n, self, a.nslices, COUNT);
+  const StripPlan strip = split ? StripPlan{false, false} : plan_strip(ctx, A.n, B.n, self, a.nslices, COUNT);
   if (strip.use) {
     kernel = strip_kernel<COUNT>(a.nslices);
     lds_bytes = strip_lds(a.nslices);
@@ -3088,7 +3058,7 @@ int ejoin_create(ejoin_ctx** out, int device) {
         &k_join<true, false, true, true>})
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dist2_tile<128>), hipFuncAttributeMaxDynamicSharedMemorySize, dense_lds_bytes<128>());
-  for (int nkb = 2; nkb <= STRIP_MAX; ++nkb)
+  for (int nkb = 2; nkb <= EJ_STRIP_KB_MAX; ++nkb)
     for (JoinKernel kernel : {strip_kernel<false>(nkb), strip_kernel<true>(nkb)})
       if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, strip_lds(nkb));
   if (e != hipSuccess) {

@@ -2,6 +2,7 @@
 #ifndef EJOIN_TILE_CURSOR_H
 #define EJOIN_TILE_CURSOR_H
 
+#include <math.h>
 #include <stdint.h>
 
 #if defined(__HIPCC__)
@@ -17,6 +18,7 @@
 #endif
 
 constexpr uint32_t EJ_NUM_XCD = 8;  // accelerator complex dies of the MI355X, each with its own L2
+constexpr int EJ_TILE = 256;        // edge of a tile
 constexpr uint32_t EJ_SB = 16;      // rows of tiles by which a launch can be cut (one super-block row = two bands)
 constexpr uint32_t EJ_BAND = 8;     // rows of tiles per band
 
@@ -255,5 +257,38 @@ struct StripCursor {
     return false;
   }
 };
+
+// Which joins k_join_strip takes, and with which set in its rows (`swapped`: the second of two).
+//
+// At eleven k-blocks 12 (pairs) and 21 (counts) of its registers are spilled, and what is read back at every stage waits for the copies
+// just issued: d = 350, S = 16, 50,000 points 676 us of counts and 662 of pairs against 650 and 653 by k_join, 100,000 points 2.47 and
+// 2.43 ms against 2.49 and 2.49; 30,000 x 7,000 130 us of counts against 123.
+//
+// Two sets: the way round that has fewer stages, where a panel of rows, which is read before its first stage starts, counts four
+// (300,000 points x 300 queries, d = 128: 45 us with the queries in the rows, 47 with the points; x 700 71 and 65; 100,000 x 2,000
+// 56 and 61).  k_join computes a tile, twice a stage's pairs, in 2 `gain` times the time of a stage (150,000 points, d = 64, 128, 224,
+// 320: 2.14, 2.85, 4.02, 5.33 ms against 1.93, 2.48, 3.60, 5.08), but needs no rows in place before it starts: where a workgroup has
+// few stages it is the better one (18,000 points, d = 128 / 224 / 320: 189 / 203 / 223 us against 187 / 206 / 235; 26,000:
+// 266 / 300 / 339 against 253 / 293 / 342; 100,000 x 700 points, d = 320: 54 against 62).
+constexpr int EJ_STRIP_KB_MAX = 10;
+struct StripPlan {
+  bool use, swapped;
+};
+inline int64_t strip_panels(int64_t n) { return (n + EJ_STRIP_ROWS - 1) / EJ_STRIP_ROWS; }
+inline int64_t strip_stages(int64_t n) { return (n + EJ_STRIP_COLS - 1) / EJ_STRIP_COLS; }
+inline StripPlan strip_plan(int num_cu, int64_t nA, int64_t nB, bool self, int nkb, bool count) {
+  (void)count;
+  const double cu = num_cu;
+  const int64_t a = strip_panels(nA), plain = a * strip_stages(nB), turned = strip_panels(nB) * strip_stages(nA);
+  StripPlan p{false, !self && turned <= plain + 4 * a};
+  if (nkb > EJ_STRIP_KB_MAX) return p;
+  const double load = nkb <= 4 ? 1. : (nkb <= 7 ? 1.5 : 2.), gain = nkb <= 2 ? 1.07 : (nkb <= 4 ? 1.13 : (nkb <= 7 ? 1.11 : 1.05));
+  const double cost = self ? ceil((double)a * (a + 1) * (EJ_STRIP_ROWS / EJ_STRIP_COLS / 2) / cu) + 1.5 * load
+                           : (p.swapped ? ceil(turned / cu) + 0.6 * load : ceil(plain / cu) + load * (1 + a / cu));
+  const int64_t ta = (nA + EJ_TILE - 1) / EJ_TILE, tb = (nB + EJ_TILE - 1) / EJ_TILE;
+  const double rounds = ceil((self ? (double)ta * (ta + 1) / 2 : (double)ta * tb) / cu);
+  p.use = cost < 2 * gain * rounds;
+  return p;
+}
 
 #endif  // EJOIN_TILE_CURSOR_H

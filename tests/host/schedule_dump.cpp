@@ -52,4 +52,10 @@ int64_t ejoin_test_strips(uint32_t nblocks, uint32_t self_join, uint32_t stages,
   }
   return m;
 }
+
+// Which joins go to the kernel of few coordinates: 0, or 1, or 3: with the second of the two sets in its rows.
+int32_t ejoin_test_strip_plan(int32_t num_cu, int64_t n_a, int64_t n_b, int32_t self_join, int32_t nkb, int32_t count) {
+  const StripPlan p = strip_plan(num_cu, n_a, n_b, self_join != 0, nkb, count != 0);
+  return p.use ? 1 + 2 * p.swapped : 0;
+}
 }

@@ -44,7 +44,10 @@ def build_schedule(tmp_path_factory, kind):
         m = lib.ejoin_test_strips(nblocks, int(self_join), stages, panels_begin, panels_end, buf.ctypes.data, len(buf))
         assert m <= len(buf)
         return buf[:m].astype(np.int64)
+    lib.ejoin_test_strip_plan.restype = ctypes.c_int32
+    lib.ejoin_test_strip_plan.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int64] + [ctypes.c_int32] * 3
     run.kind = kind
+    run.plan = lib.ejoin_test_strip_plan
     run.rows = run_rows
     run.strips = run_strips
     return run
@@ -167,3 +170,22 @@ def test_strips_cover_every_stage_once_and_evenly(sched, nblocks, self_join, n_a
         assert np.array_equal(seen, want.astype(np.int64))
         if nblocks == 256 and len(cuts) == 2:
             assert load.max() <= -(-load.sum() // 256) + 2
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    return build_schedule(tmp_path_factory, "xcd_rectangles").plan
+
+
+@pytest.mark.parametrize("nkb", range(2, 8))
+def test_larger_self_joins_of_few_coordinates_have_no_gap(plan, nkb):
+    """Lists and counts alike, from 27,000 points on."""
+    rng = np.random.default_rng(nkb)
+    for n in np.concatenate([np.arange(27000, 140000, 511), np.exp(rng.uniform(np.log(140000), np.log(5e8), 300)).astype(np.int64)]):
+        assert plan(256, int(n), int(n), 1, nkb, 0) == plan(256, int(n), int(n), 1, nkb, 1) == 1, n
+
+
+def test_counts_of_two_large_sets_of_few_coordinates_have_no_gap_either(plan):
+    for n in range(20000, 200000, 3001):
+        for nkb in range(2, 8):
+            assert all(plan(256, a, b, 0, nkb, count) for a, b in ((n, 500000), (500000, n)) for count in (0, 1)), (n, nkb)
