@@ -266,7 +266,16 @@ struct StripCursor {
 //
 // Two sets: the way round that has fewer stages, where a panel of rows, which is read before its first stage starts, counts four
 // (300,000 points x 300 queries, d = 128: 45 us with the queries in the rows, 47 with the points; x 700 71 and 65; 100,000 x 2,000
-// 56 and 61).  k_join computes a tile, twice a stage's pairs, in 2 `gain` times the time of a stage (150,000 points, d = 64, 128, 224,
+// 56 and 61).  More than two bands of panels are read anew by every XCD (the term of the cost: 50,000 x 600 lists, d = 200, 26 us by k_join,
+// 29 here).  None of it depends on which set is the first (so long as the second's panels counted nothing, 700 x 100,000 counts,
+// d = 320, took 82 us here, and 100,000 x 700 52 by k_join), but for counts, where hits in rows are added up in the LDS and hits in
+// columns are mostly one atomic each, those on one address served one after the other.  The points of a small set have the more hits
+// the more queries there are: they go into the rows where the queries are sixteen times as many (1,000 x 200,000, d = 60, four hits a
+// query: 74 us, 177 the other way round; 700 x 300,000, d = 128, two hits a query: 231 with the queries in the rows, 188 by k_join).  Else, up
+// to two bands, the queries do (3,000 x 20,000, d = 128, S = 32: 44 us, 62 the other way round); and columns of
+// at most two panels are met by rows of at least 1.5 panels a CU only (600 .. 700 columns, d = 128, S = 16 and 64: 90,000 points 32 and
+// 38 us by k_join, 32 and 44 here; 150,000 44 and 49, 42 and 50; 200,000 57 and 61, 51 and 58; 1,200 columns of 150,000: 64 and 70, 55 and 65).
+// k_join computes a tile, twice a stage's pairs, in 2 `gain` times the time of a stage (150,000 points, d = 64, 128, 224,
 // 320: 2.14, 2.85, 4.02, 5.33 ms against 1.93, 2.48, 3.60, 5.08), but needs no rows in place before it starts: where a workgroup has
 // few stages it is the better one (18,000 points, d = 128 / 224 / 320: 189 / 203 / 223 us against 187 / 206 / 235; 26,000:
 // 266 / 300 / 339 against 253 / 293 / 342; 100,000 x 700 points, d = 320: 54 against 62).
@@ -277,17 +286,21 @@ struct StripPlan {
 inline int64_t strip_panels(int64_t n) { return (n + EJ_STRIP_ROWS - 1) / EJ_STRIP_ROWS; }
 inline int64_t strip_stages(int64_t n) { return (n + EJ_STRIP_COLS - 1) / EJ_STRIP_COLS; }
 inline StripPlan strip_plan(int num_cu, int64_t nA, int64_t nB, bool self, int nkb, bool count) {
-  (void)count;
+  constexpr int64_t MANY = 2 * EJ_STRIP_LINES;
   const double cu = num_cu;
-  const int64_t a = strip_panels(nA), plain = a * strip_stages(nB), turned = strip_panels(nB) * strip_stages(nA);
-  StripPlan p{false, !self && turned <= plain + 4 * a};
+  const int64_t a = strip_panels(nA), b = strip_panels(nB), plain = a * strip_stages(nB), turned = b * strip_stages(nA);
+  const int64_t rows_a = plain + 4 * a, rows_b = turned + 4 * b;
+  StripPlan p{false, !self && (rows_b < rows_a || (rows_b == rows_a && b < a))};
+  if (!self && count) p.swapped = nB < 16 * nA && (b <= MANY ? turned : rows_b) <= rows_a;
   if (nkb > EJ_STRIP_KB_MAX) return p;
+  const double rows = p.swapped ? b : a, columns = p.swapped ? a : b;
   const double load = nkb <= 4 ? 1. : (nkb <= 7 ? 1.5 : 2.), gain = nkb <= 2 ? 1.07 : (nkb <= 4 ? 1.13 : (nkb <= 7 ? 1.11 : 1.05));
   const double cost = self ? ceil((double)a * (a + 1) * (EJ_STRIP_ROWS / EJ_STRIP_COLS / 2) / cu) + 1.5 * load
-                           : (p.swapped ? ceil(turned / cu) + 0.6 * load : ceil(plain / cu) + load * (1 + a / cu));
+                           : ceil((p.swapped ? turned : plain) / cu) + load * (rows <= MANY ? 0.6 : 1.6 + 0.7 * rows / cu);
   const int64_t ta = (nA + EJ_TILE - 1) / EJ_TILE, tb = (nB + EJ_TILE - 1) / EJ_TILE;
   const double rounds = ceil((self ? (double)ta * (ta + 1) / 2 : (double)ta * tb) / cu);
-  p.use = cost < 2 * gain * rounds;
+  const bool contended = !self && count && columns <= 2 && rows > MANY && rows < 1.5 * cu;
+  p.use = cost < 2 * gain * rounds && !contended;
   return p;
 }
 

@@ -189,3 +189,15 @@ def test_counts_of_two_large_sets_of_few_coordinates_have_no_gap_either(plan):
     for n in range(20000, 200000, 3001):
         for nkb in range(2, 8):
             assert all(plan(256, a, b, 0, nkb, count) for a, b in ((n, 500000), (500000, n)) for count in (0, 1)), (n, nkb)
+
+
+@pytest.mark.parametrize("nkb", range(2, 11))
+def test_two_sets_are_joined_alike_whichever_comes_first(plan, nkb):
+    """Lists: the same kernel, and the same set in its rows.  Counts: the points, each with more hits the more queries there are, in the
+    rows where the queries are many times as many."""
+    rng = np.random.default_rng(nkb)
+    for a, b in np.exp(rng.uniform(np.log(300), np.log(600000), (4000, 2))).astype(np.int64).tolist() + [(700, 100000), (300, 300000)]:
+        if (a + 63) // 64 == (b + 63) // 64:
+            continue
+        assert (plan(256, a, b, 0, nkb, 0), plan(256, b, a, 0, nkb, 0)) in ((0, 0), (1, 3), (3, 1)), (a, b)
+        assert 16 * min(a, b) > max(a, b) or plan(256, min(a, b), max(a, b), 0, nkb, 1) in (0, 1), (a, b)
