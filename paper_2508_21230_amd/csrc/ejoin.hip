@@ -1557,7 +1557,9 @@ struct Strip {
   static constexpr int LAG = STAGES - DEPTH;      // a stage is refilled that many stages after its own
   static constexpr int POST = DEPTH >= 4 ? 2 : 1; // at the start of stage g the copies of stage g + POST have landed
   static constexpr int COPIES = TWO ? K + 1 : (K + 2) / 2;  // copy instructions per copying wavefront and stage
-  static constexpr int RING = K >= 10 ? 3 : (K == 4 || K == 8 ? 8 : (K == 3 || K == 6 || K == 9 ? 6 : 4));  // fragments of the columns in registers
+  // fragments of the columns in registers (two at eight and nine k-blocks: 65,000 points, d = 240, S = 64 with eight 0.99 ms of counts and
+  // 0.95 of pairs, with three 0.96 and 0.93, now 0.95 and 0.92)
+  static constexpr int RING = K >= 10 ? 3 : (K >= 8 ? 2 : (K == 4 ? 8 : (K == 3 || K == 6 ? 6 : 4)));
   static constexpr int CONST_OFF = STAGES * STAGE;
   static constexpr int SYNC_OFF = CONST_OFF + 64;
   static constexpr int ROWS_OFF = CONST_OFF + TAIL;

@@ -278,7 +278,10 @@ struct StripCursor {
 // k_join computes a tile, twice a stage's pairs, in 2 `gain` times the time of a stage (150,000 points, d = 64, 128, 224,
 // 320: 2.14, 2.85, 4.02, 5.33 ms against 1.93, 2.48, 3.60, 5.08), but needs no rows in place before it starts: where a workgroup has
 // few stages it is the better one (18,000 points, d = 128 / 224 / 320: 189 / 203 / 223 us against 187 / 206 / 235; 26,000:
-// 266 / 300 / 339 against 253 / 293 / 342; 100,000 x 700 points, d = 320: 54 against 62).
+// 266 / 300 / 339 against 253 / 293 / 342; 100,000 x 700 points, d = 320: 54 against 62).  Counts of a set with itself, eight and nine
+// k-blocks: the gain is less, the filter of blocks full of candidates being in the open (d = 256, S = 16, 64 and 300: 65,000 points 0.81,
+// 0.90 and 1.19 ms by k_join, 0.81, 0.95 and 1.29 here; 100,000 1.88, 2.02 and 2.52, 1.81, 2.02 and 2.62; 200,000 7.37, 7.81 and 9.14,
+// 7.01, 7.47 and 8.82).
 constexpr int EJ_STRIP_KB_MAX = 10;
 struct StripPlan {
   bool use, swapped;
@@ -294,7 +297,9 @@ inline StripPlan strip_plan(int num_cu, int64_t nA, int64_t nB, bool self, int n
   if (!self && count) p.swapped = nB < 16 * nA && (b <= MANY ? turned : rows_b) <= rows_a;
   if (nkb > EJ_STRIP_KB_MAX) return p;
   const double rows = p.swapped ? b : a, columns = p.swapped ? a : b;
-  const double load = nkb <= 4 ? 1. : (nkb <= 7 ? 1.5 : 2.), gain = nkb <= 2 ? 1.07 : (nkb <= 4 ? 1.13 : (nkb <= 7 ? 1.11 : 1.05));
+  const double load = nkb <= 4 ? 1. : (nkb <= 7 ? 1.5 : 2.);
+  double gain = nkb <= 2 ? 1.07 : (nkb <= 4 ? 1.13 : (nkb <= 7 ? 1.11 : 1.05));
+  if (self && count && (nkb == 8 || nkb == 9)) gain -= 0.06 * fmin(1., 1e5 / (double)nA);
   const double cost = self ? ceil((double)a * (a + 1) * (EJ_STRIP_ROWS / EJ_STRIP_COLS / 2) / cu) + 1.5 * load
                            : ceil((p.swapped ? turned : plain) / cu) + load * (rows <= MANY ? 0.6 : 1.6 + 0.7 * rows / cu);
   const int64_t ta = (nA + EJ_TILE - 1) / EJ_TILE, tb = (nB + EJ_TILE - 1) / EJ_TILE;

@@ -201,3 +201,10 @@ def test_two_sets_are_joined_alike_whichever_comes_first(plan, nkb):
             continue
         assert (plan(256, a, b, 0, nkb, 0), plan(256, b, a, 0, nkb, 0)) in ((0, 0), (1, 3), (3, 1)), (a, b)
         assert 16 * min(a, b) > max(a, b) or plan(256, min(a, b), max(a, b), 0, nkb, 1) in (0, 1), (a, b)
+
+
+@pytest.mark.parametrize("nkb", [8, 9])
+def test_self_counts_with_the_filter_in_the_open_go_there_from_large_sets_on(plan, nkb):
+    rule = [plan(256, n, n, 1, nkb, 1) for n in range(20000, 400000, 997)]
+    assert not any(rule[:80]) and all(rule[160:])  # up to 99,000 points, from 179,000 on
+    assert all(plan(256, n, n, 1, nkb, 0) for n in range(60000, 400000, 997))  # lists
