@@ -806,11 +806,9 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
   return __builtin_amdgcn_readfirstlane(x);
 }
 
-// KEEP_A: the instance for tiles of exactly NSTAGE slices (96 < d <= 128), which leaves a row panel in the LDS across
-// the consecutive tiles that share it (see keep_a_cur); the other instance carries none of that logic.
 // DENSE (count mode): the instance whose rare path also handles regions with candidates in many lanes lane by lane.
 // SPLIT: the k-blocks of the slices are those of a split-FP16 set (see k_split_prep).
-template <bool COUNT, bool KEEP_A, bool DENSE, bool SPLIT>
+template <bool COUNT, bool DENSE, bool SPLIT>
 __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   // the largest norm of the call has been consumed by k_aux: cleared here for the next call
@@ -851,15 +849,13 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b), hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
     return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
   };
-  auto issue_slice = [&](const char* pa_, const char* pb_, uint32_t lds_stage /* LDS address of the stage + cw*1024 */, bool keep_a) {
+  auto issue_slice = [&](const char* pa_, const char* pb_, uint32_t lds_stage /* LDS address of the stage + cw*1024 */) {
     const char* pa = uniform_ptr(pa_);
     const char* pb = uniform_ptr(pb_);
-    if (!(KEEP_A && keep_a)) {
-      copy16_to_lds<0>(lds_stage, pa, voff0);
-      copy16_to_lds<4096>(lds_stage, pa, voff0 + 4096);
-      copy16_to_lds<8192>(lds_stage, pa, voff0 + 8192);
-      copy16_to_lds<12288>(lds_stage, pa, voff0 + 12288);
-    }
+    copy16_to_lds<0>(lds_stage, pa, voff0);
+    copy16_to_lds<4096>(lds_stage, pa, voff0 + 4096);
+    copy16_to_lds<8192>(lds_stage, pa, voff0 + 8192);
+    copy16_to_lds<12288>(lds_stage, pa, voff0 + 12288);
     copy16_to_lds<PANEL_BYTES>(lds_stage, pb, voff0);
     copy16_to_lds<PANEL_BYTES + 4096>(lds_stage, pb, voff0 + 4096);
     copy16_to_lds<PANEL_BYTES + 8192>(lds_stage, pb, voff0 + 8192);
@@ -868,15 +864,13 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   constexpr int NCOPY = 8;  // copy instructions per slice and copying wave
   // The operands of a tile's augmentation step: 4 KB of panel I's augmentation block and 4 KB of panel J's, into a
   // buffer of their own: eight copy instructions per tile, issued in the tile's first slice (every wave has then left the
-  // tile before and its reads of the buffer behind) and read in its last.  In the general instance they are the job of
+  // tile before and its reads of the buffer behind) and read in its last.  They are the job of
   // the four waves that do not copy slices, two each, behind their MFMAs of the first slice: they have nothing to do from
   // there to the next barrier, and their copies do not enter the counted waits of the copying waves; they wait for them
-  // (nothing else of theirs is outstanding) before the barrier of the tile's last slice.  In the KEEP_A instance, where
-  // the copying waves have half the copies and the others no time to spare, the copying waves issue them ahead of the
-  // slice's copies (NAUG each) and allow for them in the one counted wait where they are younger than what must have
-  // landed (a tile's second slice; from the third on they are older than everything that may be outstanding).
-  constexpr bool AUG_BY_IDLE_WAVES = !KEEP_A;
-  constexpr int NAUG = 2;
+  // (nothing else of theirs is outstanding) before the barrier of the tile's last slice.
+  // (Tried at four slices, where a slice always lands in the same stage: the row panel left in the LDS across the tiles that share
+  // it, its copies left out.  Since the copying waves then have the operands' copies too, it is the slower one: self-joins of 8,200 to
+  // 17,000 points, d = 128, S = 30, lists 31 .. 66 us, 30 .. 64 without; counts 38 .. 69, 37 .. 67.)
 #ifdef EJOIN_EXP_NO_COPIES
   bool aug_copied = false;
 #endif
@@ -1028,13 +1022,6 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   int iks = 0;
   int ahead = 0;
   bool issue_live = true;       // the issue cursor points at real work
-  // KEEP_A (a tile has exactly as many slices as the ring has stages, 96 < d <= 128): slice ks of every tile lands in
-  // stage ks.  The consecutive tiles of a workgroup in a band have the same row panel (tile_cursor.h): the A half of
-  // each stage then already holds what the next tile needs, and the copies of its A panel are left out (NCOPY / 2 per
-  // slice instead of NCOPY; the counted waits are told through the flags of the tile being issued, the tile being
-  // computed and the one after it).
-  uint32_t issue_I = I;
-  bool keep_a_issue = false, keep_a_cur = false, keep_a_next = false;
   const char* pa = XbA + (int64_t)EJ_PANEL_A(I) * panel_stride;
   const char* pb = XbB + (int64_t)EJ_PANEL_B(J) * panel_stride;
   const uint32_t lds_w = lds0 + cw * 1024;
@@ -1044,7 +1031,7 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
     if (Gissue >= (uint32_t)NSTAGE) return;
 #endif
     if (issue_live) {
-      issue_slice(pa, pb, lds_w + (Gissue % NSTAGE) * STAGE_BYTES, keep_a_issue);
+      issue_slice(pa, pb, lds_w + (Gissue % NSTAGE) * STAGE_BYTES);
     } else {
 #pragma unroll
       for (int q = 0; q < NCOPY; ++q) copy16_to_lds<0>(lds0 + DUMP_OFF, XbA, lane * 16);
@@ -1064,11 +1051,6 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
       const uint32_t ti = first_after ? In : In2, tj = first_after ? Jn : Jn2;
       pa = XbA + (int64_t)(issue_live ? EJ_PANEL_A(ti) : 0) * panel_stride;
       pb = XbB + (int64_t)(issue_live ? EJ_PANEL_B(tj) : 0) * panel_stride;
-      if constexpr (KEEP_A) {
-        keep_a_issue = issue_live && ti == issue_I;
-        keep_a_next = keep_a_issue;  // (with nsl == NSTAGE the cursor is one tile ahead at every wrap)
-        issue_I = ti;
-      }
     }
   };
   for (int q = 0; q < DIST; ++q) issue_one(q);
@@ -1159,38 +1141,24 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
   // One slice.  LAST: last slice of a tile (what is read ahead are the operands of the augmentation step).
   // COPIER: the instance the copying waves run; the other waves run one without any copy code in it
   // (the copy instructions are opaque to the scheduler and would break up the MFMA / LDS-read interleave for nothing).
-  // second: the slice after a tile's first.
-  auto data_slice = [&](auto first_c, auto last_c, auto copier_c, bool second) {
+  auto data_slice = [&](auto first_c, auto last_c, auto copier_c) {
     constexpr bool FIRST = decltype(first_c)::value;
     constexpr bool COPIER = decltype(copier_c)::value;
     const uint32_t st_cur = (G % NSTAGE) * STAGE_BYTES, st_nxt = ((G + 1) % NSTAGE) * STAGE_BYTES;
     // (a) this wave's copies of slice G+1 have landed once only those of slice G+2 are outstanding.
-    //     A tile whose A panel was kept has NCOPY / 2 copies per slice; the slice two ahead belongs to the tile being
-    //     computed in its first two slices and to the next one after that (KEEP_A: nsl == NSTAGE).
     //     The waves that do not copy slices have at most the tile's augmentation copies outstanding, which must have
     //     landed before the barrier of the last slice.
     constexpr bool LAST_ = decltype(last_c)::value;
-    if constexpr (!COPIER) {
-      if constexpr (AUG_BY_IDLE_WAVES && LAST_) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    } else if constexpr (AUG_BY_IDLE_WAVES) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCOPY * (DIST - 2)) : "memory");
-    } else if (KEEP_A && ((FIRST || second) ? keep_a_cur : keep_a_next)) {
-      if (DIST >= 3 && second) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCOPY / 2 * (DIST - 2) + NAUG) : "memory");
-      else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCOPY / 2 * (DIST - 2)) : "memory");
-    } else if (DIST >= 3 && second) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCOPY * (DIST - 2) + NAUG) : "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCOPY * (DIST - 2)) : "memory");
-    }
+    if constexpr (COPIER) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NCOPY * (DIST - 2)) : "memory");
+    else if constexpr (LAST_) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     // (b) after the barrier slice G+1 is complete in LDS for everybody, and everybody is done with slice G-1
     wg_barrier();
     // (c) the copying waves refill the stage slice G-1 occupied with slice G+DIST, while the other wave of
     //     their SIMD starts on the MFMAs of the slice
-    if constexpr (COPIER && FIRST && !AUG_BY_IDLE_WAVES) issue_aug(I, J);
     if constexpr (COPIER) issue_one(G + DIST);
     // (d) the MFMAs of slice G, overlapped with the LDS reads of what follows
     mma_slice(first_c, last_c, st_cur, st_nxt);
-    if constexpr (!COPIER && FIRST && AUG_BY_IDLE_WAVES) issue_aug(I, J);
+    if constexpr (!COPIER && FIRST) issue_aug(I, J);
     ++G;
   };
 
@@ -1213,17 +1181,17 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
     // ---------------- the nsl >= 2 slices of the tile
     EJ_MARK(0)
     if (copier) {
-      data_slice(T_{}, F_{}, T_{}, false);
+      data_slice(T_{}, F_{}, T_{});
       EJ_MARK(1)
-      for (int ks = 1; ks < nsl - 1; ++ks) data_slice(F_{}, F_{}, T_{}, ks == 1);
+      for (int ks = 1; ks < nsl - 1; ++ks) data_slice(F_{}, F_{}, T_{});
       EJ_MARK(2)
-      data_slice(F_{}, T_{}, T_{}, false);
+      data_slice(F_{}, T_{}, T_{});
     } else {
-      data_slice(T_{}, F_{}, F_{}, false);
+      data_slice(T_{}, F_{}, F_{});
       EJ_MARK(1)
-      for (int ks = 1; ks < nsl - 1; ++ks) data_slice(F_{}, F_{}, F_{}, false);
+      for (int ks = 1; ks < nsl - 1; ++ks) data_slice(F_{}, F_{}, F_{});
       EJ_MARK(2)
-      data_slice(F_{}, T_{}, F_{}, false);
+      data_slice(F_{}, T_{}, F_{});
     }
     EJ_MARK(3)
     // ---------------- the augmentation step, then the filter.
@@ -1472,7 +1440,6 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
     Jn = Jn2;
     have_next = have_next2;
     --ahead;  // (at least 1 before: the issue cursor has left the tile that was just finished)
-    if constexpr (KEEP_A) keep_a_cur = keep_a_next;
     if (have) {
       if (--sync_left == 0) {
         sync_left = (uint32_t)a.sync_mode;
@@ -2764,15 +2731,12 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
   }
   // Counts of sets of up to 32,768 points go to the instance for dense tiles.  Points in random order have 65,536 S / n hits a tile
   // at S neighbours: the smaller the set, the fuller its regions.  It is the better one from a few hundred neighbours on and the
-  // other one below (30,000 points, d = 128: S = 30 171 us against 163, S = 100 245 against 211, S = 512 318 against 364,
-  // S = 4,000 378 against 824); beyond 32,768 points few sets are that dense (10^6 points, S = 64: 109.2 ms against 107.4), and the
-  // other instance counts what dense tiles there are in the LDS, from its queue (100,000 points, d = 128, stored cluster by
-  // cluster, S = 900: 4.4 ms, now 1.4).
+  // other one below (30,000 points, d = 384: S = 30 280 us against 275, S = 100 332 against 305, S = 512 406 against 451; 15,000:
+  // 87 against 83, 122 against 96, 123 against 158); beyond 32,768 points few sets are that dense, and the other instance counts what
+  // dense tiles there are in the LDS, from its queue (100,000 points, d = 128, stored cluster by cluster, S = 900: 4.4 ms without).
   constexpr int64_t DENSE_POINTS = 32768;
-  const bool keep_a = a.nslices == NSTAGE, dense = COUNT && A.n <= DENSE_POINTS && B.n <= DENSE_POINTS;
-  void (*kernel)(JoinArgs) = split    ? (dense ? k_join<COUNT, false, COUNT, true> : k_join<COUNT, false, false, true>)
-                             : keep_a ? (dense ? k_join<COUNT, true, COUNT, false> : k_join<COUNT, true, false, false>)
-                                      : (dense ? k_join<COUNT, false, COUNT, false> : k_join<COUNT, false, false, false>);
+  const bool dense = COUNT && A.n <= DENSE_POINTS && B.n <= DENSE_POINTS;
+  JoinKernel kernel = split ? (dense ? &k_join<COUNT, COUNT, true> : &k_join<COUNT, false, true>) : (dense ? &k_join<COUNT, COUNT, false> : &k_join<COUNT, false, false>);
   int lds_bytes = LDS_BYTES;
   const StripPlan strip = split ? StripPlan{false, false} : plan_strip(ctx, A.n, B.n, self, a.nslices, COUNT);
   if (strip.use) {
@@ -3055,9 +3019,8 @@ int ejoin_create(ejoin_ctx** out, int device) {
   for (int i = 0; i < EJOIN_MAX_BATCHES && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&ctx->batch_ev[i], hipEventDisableTiming);
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&ctx->batch_count), EJOIN_MAX_BATCHES * sizeof(unsigned long long), hipHostMallocDefault);
   for (void (*kernel)(JoinArgs) :
-       {&k_join<false, false, false, false>, &k_join<false, true, false, false>, &k_join<false, false, false, true>, &k_join<true, false, false, false>,
-        &k_join<true, true, false, false>, &k_join<true, false, false, true>, &k_join<true, false, true, false>, &k_join<true, true, true, false>,
-        &k_join<true, false, true, true>})
+       {&k_join<false, false, false>, &k_join<false, false, true>, &k_join<true, false, false>, &k_join<true, false, true>, &k_join<true, true, false>,
+        &k_join<true, true, true>})
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dist2_tile<128>), hipFuncAttributeMaxDynamicSharedMemorySize, dense_lds_bytes<128>());
   for (int nkb = 2; nkb <= EJ_STRIP_KB_MAX; ++nkb)
