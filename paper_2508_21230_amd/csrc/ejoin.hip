@@ -122,7 +122,7 @@ struct JoinArgs {
 // [8..15] alignment counters of the XCDs.  Between calls [1] and [8..15] are zero: k_aux clears the counters
 // (and the result counter of the call), k_join clears the maximum.  k_reset restores that state after a call
 // that did not get as far as its join kernel, and before every call of k_join on the shared static workspace.
-// (Small problems and the dense-tile call use words [0] and [2..3] only.)
+// (Small problems and the dense-tile call use word [0] only.)
 __global__ void k_reset(uint32_t* status_and_max) {
   if (threadIdx.x < 8) status_and_max[8 + threadIdx.x] = 0;
   if (threadIdx.x == 0) {
@@ -2419,8 +2419,8 @@ namespace {
 // Device memory one call works in: either the context's own (grown on demand) or a carving of the static scratch.
 struct Workspace {
   uint32_t* status;  // status block, 64 words (see k_reset)
-  float* s;          // norms (4 B per point); the context's own: then one maximum per NORM_POINTS points (dense-tile call)
-  uint4* H;          // small problems: the largest norms of k_prep's workgroups (16 B per point, padded to a multiple of TILE)
+  float* s;          // norms (4 B per point)
+  uint32_t* maxima;  // behind them, small problems and the dense-tile call: largest norms of the norm kernels' workgroups (at most one per NORM_POINTS points)
   uint4* Xp;         // packed copy of X plus the augmentation k-block
 };
 
@@ -2430,7 +2430,7 @@ struct ejoin_ctx {
   int device;
   int num_cu;
   Workspace ws;      // owned by the context
-  int64_t s_cap;     // points ws.s and ws.H hold
+  int64_t s_cap;     // points ws.s holds
   int64_t xp_bytes;  // bytes of ws.Xp
   bool ws_dirty;     // a call on ws did not reach its join kernel: the status block may hold leftovers
   unsigned char* static_scratch;  // device address of `scratch` on this context's device
@@ -2504,23 +2504,20 @@ int64_t packed_bytes(int64_t rows, int64_t dpad) { return rows * (dpad + KSLICE)
 int ensure_workspace(ejoin_ctx* ctx, int64_t rows, int64_t dpad) {
   Workspace& w = ctx->ws;
   if (rows > ctx->s_cap) {
-    if (w.s || w.H) {
+    if (w.s) {
       EJ_TRY(hipDeviceSynchronize());
-      if (w.s) EJ_TRY(hipFree(w.s));
+      EJ_TRY(hipFree(w.s));
       w.s = nullptr;
-      if (w.H) EJ_TRY(hipFree(w.H));
-      w.H = nullptr;
       ctx->s_cap = 0;
     }
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&w.s), (size_t)(rows + rows / NORM_POINTS) * sizeof(float));  // (+ maxima)
-    if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&w.H), (size_t)rows * sizeof(uint4));
     if (e != hipSuccess) {
       (void)hipGetLastError();
-      if (w.s) (void)hipFree(w.s);
       w.s = nullptr;
       if (e == hipErrorOutOfMemory) return EJOIN_ENOMEM;
       return fail_hip(ctx, e, "hipMalloc(workspace)");
     }
+    w.maxima = reinterpret_cast<uint32_t*>(w.s + rows);
     ctx->s_cap = rows;
   }
   const int64_t need = dpad > 0 ? packed_bytes(rows, dpad) : 0;
@@ -2543,15 +2540,16 @@ int ensure_workspace(ejoin_ctx* ctx, int64_t rows, int64_t dpad) {
 }
 
 // The static scratch cut up for a self-join of `pad` (padded) points of dpad coordinates; false if it does not fit.
-// Every piece starts on a 256-byte boundary.
+// Every piece starts on a 256-byte boundary.  (The limit that ejoin.h states for it counts 20 bytes per point besides the packed copy:
+// 4 for the norms, 16 at whose start the maxima lie.)
 bool carve_static(unsigned char* base, int64_t pad, int64_t dpad, Workspace& w) {
   auto up = [](int64_t x) { return (x + 255) / 256 * 256; };
-  const int64_t off_s = 256, off_H = off_s + up(pad * 4), off_Xp = off_H + up(pad * 16);
+  const int64_t off_s = 256, off_max = off_s + up(pad * 4), off_Xp = off_max + up(pad * 16);
   const int64_t end = off_Xp + packed_bytes(pad, dpad);
   if (end > (int64_t)EJOIN_STATIC_SCRATCH_BYTES) return false;
   w.status = reinterpret_cast<uint32_t*>(base);
   w.s = reinterpret_cast<float*>(base + off_s);
-  w.H = reinterpret_cast<uint4*>(base + off_H);
+  w.maxima = reinterpret_cast<uint32_t*>(base + off_max);
   w.Xp = reinterpret_cast<uint4*>(base + off_Xp);
   return true;
 }
@@ -2816,7 +2814,7 @@ int run_small(ejoin_ctx* ctx, const Workspace& w, int tile, PrepSet A, PrepSet B
   if (ctx->profiling) EJ_TRY(hipEventRecord(ctx->ev[0], st));
   ctx->last_status = w.status;
   ctx->last_stream = st;
-  uint32_t* maxima = reinterpret_cast<uint32_t*>(w.H);
+  uint32_t* maxima = w.maxima;
   SmallArgs a;
   if (split) {
     split->maxima = maxima;
@@ -3041,7 +3039,6 @@ int ejoin_destroy(ejoin_ctx* ctx) {
   DeviceGuard guard(ctx->device);
   if (ctx->ws.status) (void)hipFree(ctx->ws.status);
   if (ctx->ws.s) (void)hipFree(ctx->ws.s);
-  if (ctx->ws.H) (void)hipFree(ctx->ws.H);
   if (ctx->ws.Xp) (void)hipFree(ctx->ws.Xp);
   for (int i = 0; i < 4; ++i)
     if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
@@ -3287,7 +3284,7 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   ctx->last_status = w.status;
   ctx->last_stream = st;
   // (no atomics on the status block: its state between calls is left as it is)
-  uint32_t* maxima = reinterpret_cast<uint32_t*>(w.s + ctx->s_cap);
+  uint32_t* maxima = w.maxima;
   DenseArgs a{X, w.s, maxima, 0, w.status, n, ld, (k_blocks(d) + 1) / 2 /* (rows are padded to a multiple of 64 coordinates) */, i0, j0, rows, cols, out};
   EJ_RC(launch_norms(ctx, X, n, d, ld, w.s, nullptr, nullptr, st, maxima, &a.nmaxima));
   // every workgroup of the dense kernel reads all maxima: from some 5 10^5 points on a launch that folds them first costs less

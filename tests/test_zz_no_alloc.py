@@ -70,3 +70,18 @@ def test_noalloc_entry_point_rejects_what_does_not_fit():
         assert int(n_pairs.cpu()[0]) == 7, "nothing may be enqueued on error"
     finally:
         ej.close()
+
+
+def test_reserve_takes_what_the_calls_need():
+    """Norms, one maximum per 32 points and the packed copy with its augmentation block: 4.125 + 2 (d + 32) bytes a point."""
+    import paper_2508_21230_amd as pkg
+    n, d = 4_000_000, 64
+    ej = pkg.EJoin(0)
+    try:
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        ej.reserve(n, d)
+        taken = before - torch.cuda.mem_get_info()[0]
+        assert n * (4 + 2 * (d + 32)) <= taken <= n * (4.125 + 2 * (d + 32)) + (8 << 20)  # (padding and the allocator's granularity)
+    finally:
+        ej.close()
