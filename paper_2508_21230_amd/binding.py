@@ -15,6 +15,7 @@ from . import build as _build
 
 EJOIN_OK = 0
 _libs: dict = {}
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (not part of torch's public interface)
 
 
 class EJoinError(RuntimeError):
@@ -133,7 +134,9 @@ class EJoin:
     def _stream():
         # the handle of torch.cuda.current_stream(), without the object: 0.2 us a call where that takes 3.2, of the 12.7 to 13.9
         # that a count of 1,000 points costs the host (10.3 to 11.9 now, over three machines; the GPU is done in 9)
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        if _raw_stream is not None:
+            return C.c_void_p(_raw_stream(torch.cuda.current_device()))
+        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
     def _x(self, X: torch.Tensor, d):
         if X.dtype not in (torch.float16, torch.int16, torch.uint16):

@@ -62,3 +62,20 @@ def test_header_is_plain_c(tmp_path):
         cpp = tmp_path / "use_header.cpp"
         cpp.write_text(src.read_text())
         subprocess.run(["g++", "-std=c++11", "-Wall", "-Werror", "-I", inc, "-c", str(cpp), "-o", str(tmp_path / "b.o")], check=True)
+
+
+def test_stream_handle_with_and_without_the_short_way():
+    """The current stream's handle comes from torch's raw getter where torch has it, else from the stream object."""
+    import subprocess
+    import sys
+    code = """
+import torch, types
+assert {have} or not hasattr(torch._C, "_cuda_getCurrentRawStream") or delattr(torch._C, "_cuda_getCurrentRawStream") is None
+torch.cuda.current_device = lambda: 3
+torch.cuda.current_stream = lambda: types.SimpleNamespace(cuda_stream=1234)
+if {have}: torch._C._cuda_getCurrentRawStream = lambda device: 70 + device
+from paper_2508_21230_amd import EJoin
+assert EJoin._stream().value == (73 if {have} else 1234)
+"""
+    for have in (True, False):
+        subprocess.run([sys.executable, "-c", code.format(have=have)], cwd=ROOT, check=True)
