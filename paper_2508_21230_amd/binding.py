@@ -83,6 +83,8 @@ def load_library(path: str | None = None) -> C.CDLL:
     lib.ejoin_last_kernel_ms.argtypes = [vp, C.POINTER(f32), C.POINTER(f32)]
     lib.ejoin_join_work.restype = C.c_int
     lib.ejoin_join_work.argtypes = [vp, i64, i64, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(i64)]
+    lib.ejoin_join_kernel.restype = C.c_int
+    lib.ejoin_join_kernel.argtypes = [vp, i64, i64, i32, i32, i32, C.POINTER(i32)]
     lib.ejoin_tiles_evaluated.restype = i64
     lib.ejoin_tiles_evaluated.argtypes = [i64]
     _libs[key] = lib
@@ -321,6 +323,12 @@ class EJoin:
         self._check(self._lib.ejoin_join_work(self._h, int(n), int(nq), int(d), int(split), C.byref(edge), C.byref(steps),
                                               C.byref(tiles)), self._h)
         return edge.value, steps.value, tiles.value
+
+    def join_kernel(self, n: int, d: int, nq: int = 0, split: bool = False, count: bool = False) -> str:
+        """Which kernel that is: "small", "tiles" or "strip" (ejoin_join_kernel)."""
+        kernel = C.c_int32()
+        self._check(self._lib.ejoin_join_kernel(self._h, int(n), int(nq), int(d), int(split), int(count), C.byref(kernel)), self._h)
+        return ("small", "tiles", "strip")[kernel.value]
 
     def set_profiling(self, on: bool):
         self._check(self._lib.ejoin_set_profiling(self._h, 1 if on else 0), self._h)

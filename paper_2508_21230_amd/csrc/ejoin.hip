@@ -3347,6 +3347,15 @@ int ejoin_join_work(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int
   return EJOIN_OK;
 }
 
+int ejoin_join_kernel(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int32_t split, int32_t count, int32_t* kernel) {
+  int32_t edge, steps;
+  int64_t tiles;
+  if (!kernel) return EJOIN_EINVAL;
+  EJ_RC(ejoin_join_work(ctx, np, nq, d, split, &edge, &steps, &tiles));
+  *kernel = edge < TILE ? EJOIN_KERNEL_SMALL : (!split && plan_strip(ctx, np, nq ? nq : np, nq == 0, steps, count != 0).use ? EJOIN_KERNEL_STRIP : EJOIN_KERNEL_TILES);
+  return EJOIN_OK;
+}
+
 int64_t ejoin_tiles_evaluated(int64_t n) {
   if (n < 1) return 0;
   const int64_t t = (n + TILE - 1) / TILE;

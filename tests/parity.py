@@ -37,14 +37,27 @@ def open_context(request):
     return pkg.EJoin(0) if getattr(request, "param", "by_size") == "by_size" else general_context()
 
 
-def general_context():
+def variant_context(path):
+    """A context of one of the tests' builds, which must be of the sources as they are."""
     import paper_2508_21230_amd as pkg
     from paper_2508_21230_amd import build
     sources = [os.path.join(os.path.dirname(build.SRC), f) for f in os.listdir(os.path.dirname(build.SRC)) if f.endswith((".hip", ".h"))]
-    built = os.path.exists(build.GENERAL_KERNEL_LIB) and os.path.getmtime(build.GENERAL_KERNEL_LIB) >= max(map(os.path.getmtime, sources))
+    built = os.path.exists(path) and os.path.getmtime(path) >= max(map(os.path.getmtime, sources))
     assert built, "build the variants first: python -m paper_2508_21230_amd.build --ablations"
-    e = pkg.EJoin(0, lib_path=build.GENERAL_KERNEL_LIB)
-    assert e.join_work(100, 64)[0] == 256
+    return pkg.EJoin(0, lib_path=path)
+
+
+def general_context():
+    from paper_2508_21230_amd import build
+    e = variant_context(build.GENERAL_KERNEL_LIB)
+    assert e.join_kernel(100, 64) == e.join_kernel(100000, 64) == "tiles"
+    return e
+
+
+def strip_context():
+    from paper_2508_21230_amd import build
+    e = variant_context(build.STRIP_KERNEL_LIB)
+    assert e.join_kernel(100, 64) == e.join_kernel(100, 320, 50, count=True) == "strip"
     return e
 
 

@@ -261,9 +261,7 @@ def test_more_tiles_than_workgroups_at_small_d(ej, n, d):
     """In the general kernel every workgroup walks several tiles (300 .. 406 tiles on 256 workgroups; 946 and 1128 in the last four
     cases, four to five per workgroup).  At d <= 64 a tile has two slices and the copy pipeline runs three ahead: the copy
     cursor works on the tile after the next one while the current one is still being computed.  At 96 < d <= 128 a tile
-    has as many slices as the LDS ring has stages, and a row panel stays in the LDS across the consecutive tiles of a
-    workgroup that share it (the last two cases: four to five tiles per workgroup, three of four with the row of the
-    tile before).  The small kernel, which the library's own rule takes for all of these but (7000, 40), walks tiles of 128, two to
+    has as many slices as the LDS ring has stages.  The small kernel, which the library's own rule takes for all of these but (7000, 40), walks tiles of 128, two to
     six per workgroup."""
     edge, _, tiles = ej.join_work(n, d)
     assert tiles > (256 if edge == 256 else 768)
@@ -794,15 +792,18 @@ def test_small_problems_overflow_status_and_captured_replays(ej):
 
 
 # ------------------------------------------------------------------ counts of dense tiles
-@pytest.mark.parametrize("d", [50, 128, 200])
+@parity.BOTH_KERNELS
+@pytest.mark.parametrize("d", [50, 128, 200, 384])
 @pytest.mark.parametrize("share", [0.005, 0.03, 0.3])
 def test_counts_of_dense_tiles(ej, d, share):
     """Regions with candidates in a few, about twelve and all of their lanes, ragged edges and the diagonal, self-join and two
-    sets, at a size that goes to the general kernel's instance for dense tiles (up to 32,768 points), with and without a row panel
-    that stays in the LDS (d = 128): exactly the counts of the dense distance blocks."""
+    sets, at a size that goes to the general kernel's instance for dense tiles (up to 32,768 points) in the build of that kernel and,
+    at d = 384, in the product's: exactly the counts of the dense distance blocks."""
     print(f"dense counts d={d} share={share}", flush=True)
     n, nq = 14501, 9001
     assert ej.join_work(n, d)[0] == ej.join_work(n, d, nq)[0] == 256 and n <= 32768
+    general = d > 320 or ej.join_kernel(100, d) != "small"
+    assert not general or ej.join_kernel(n, d, count=True) == ej.join_kernel(n, d, nq, count=True) == "tiles"
     rng = np.random.default_rng(d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
     P = orc.decode(X[:700])
@@ -829,14 +830,18 @@ def test_counts_of_dense_tiles(ej, d, share):
     assert torch.equal(cp[: n - nq].long(), full.sum(dim=1)[: n - nq]) and k.numel() == nq
 
 
-@pytest.mark.parametrize("d,share", [(50, 0.0005), (50, 0.02), (128, 0.0005), (128, 0.003), (128, 0.02), (128, 0.3), (128, 1.0), (200, 0.02)])
+@parity.BOTH_KERNELS
+@pytest.mark.parametrize("d,share", [(50, 0.0005), (50, 0.02), (128, 0.0005), (128, 0.003), (128, 0.02), (128, 0.3), (128, 1.0), (200, 0.02),
+                                     (384, 0.0005), (384, 0.003), (384, 0.3), (384, 1.0)])
 def test_counts_of_dense_tiles_of_large_sets(ej, d, share):
-    """More than 32,768 points: the instance whose wave tiles count from the queue, directly or, once their candidates overflow it,
+    """More than 32,768 points, in the build of the general kernel and, at d = 384, in the product's: the instance whose wave tiles count from the queue, directly or, once their candidates overflow it,
     in the LDS.  Some tiles of each kind (share 0.0005: about four candidates a wave tile; the near-duplicates stored next to each
     other fill tiles on the diagonal), all of them full, and an epsilon that reaches the marker of the rows past the end."""
     print(f"dense counts of a large set d={d} share={share}", flush=True)
     n, nq = 33001, 700
     assert ej.join_work(n, d)[0] == ej.join_work(n, d, nq)[0] == ej.join_work(nq, d, n)[0] == 256 and n > 32768
+    general = d > 320 or ej.join_kernel(100, d) != "small"
+    assert not general or ej.join_kernel(n, d, count=True) == ej.join_kernel(n, d, nq, count=True) == ej.join_kernel(nq, d, n, count=True) == "tiles"
     rng = np.random.default_rng(d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
     X[5000:5600] = X[5000]
@@ -867,8 +872,8 @@ def test_counts_of_dense_tiles_of_large_sets(ej, d, share):
 @pytest.mark.parametrize("d", [50, 100, 200])
 @pytest.mark.parametrize("share", [0.004, 0.03, 0.1, 0.5])
 def test_pairs_of_dense_tiles(ej, d, share):
-    """Wave tiles whose candidates overflow the queue, with few and with nearly all lanes of a region holding one, with (d = 100) and
-    without a row panel kept in the LDS, whole tiles, the diagonal and ragged edges: exactly the pairs of the dense distance block."""
+    """Wave tiles whose candidates overflow the queue, with few and with nearly all lanes of a region holding one, whole tiles, the
+    diagonal and ragged edges: exactly the pairs of the dense distance block."""
     print(f"dense pairs d={d} share={share}", flush=True)
     n = 1100
     rng = np.random.default_rng(d)

@@ -1,14 +1,9 @@
 """The join kernel that keeps its rows in registers, against the general kernel: pairs, squared distances bit for bit and counts, on a
 build that takes problems of every size there."""
-import os
-
-import numpy as np
 import pytest
 import torch
 
 import paper_2508_21230_amd as pkg
-from oracle import oracle as orc
-from paper_2508_21230_amd import build
 from tests import parity
 
 pytestmark = pytest.mark.gpu
@@ -16,8 +11,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.fixture(scope="module")
 def both():
-    assert os.path.getmtime(build.STRIP_KERNEL_LIB) >= os.path.getmtime(build.SRC), "build the variants first: python -m paper_2508_21230_amd.build --ablations"
-    g, s = parity.general_context(), pkg.EJoin(0, lib_path=build.STRIP_KERNEL_LIB)
+    g, s = parity.general_context(), parity.strip_context()
     yield g, s
     g.close()
     s.close()
@@ -52,7 +46,7 @@ def epsilon(X, d, share):
     return float(torch.quantile(D.flatten()[:100000], share))
 
 
-D_OF_BLOCKS = [20, 70, 128, 133, 190, 220, 256, 270, 300, 350, 384]  # two to twelve blocks of 32 coordinates
+D_OF_BLOCKS = [20, 70, 128, 133, 190, 220, 256, 270, 300, 350, 384]  # two to ten blocks of 32 coordinates, and two widths that go to the general kernel in either build
 
 
 @pytest.mark.parametrize("d", D_OF_BLOCKS)
@@ -139,3 +133,58 @@ def test_sets_of_many_norms_and_captured_replays(both):
         assert torch.equal(counts, want[0]) and torch.equal(total, want[1])
         both[1].selfjoin_count(Q, 1.0, d=d)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("n,nq,d", [(52000, 0, 256), (52000, 0, 270), (52000, 0, 320), (70000, 0, 150), (40000, 33000, 240), (33000, 40000, 300), (60000, 41000, 100),
+                                    (3500, 300000, 320)])
+def test_realignment(both, n, nq, d):
+    """Launches long enough that the workgroups of an XCD are re-aligned: stages of 64 and of 32 columns, two sets either way round."""
+    print(f"strip re-alignment n={n} nq={nq} d={d}", flush=True)
+    stages = (n + 511) // 512 * ((nq or n) // 64) // (1 if nq else 2)  # (either way round)
+    assert stages > 1.1 * 256 * (1024 // ((d + 31) // 32)) and both[1].join_kernel(n, d, nq) == "strip"
+    X = rows(n, d, seed=d)
+    eps = epsilon(X, d, 0.00002)
+    if nq:
+        Q = rows(nq, d, seed=d + 1)
+        calls = (lambda e: e.join_pairs(X, Q, eps, 4000000, d=d)), (lambda e: e.join_count(X, Q, eps, d=d))
+    else:
+        calls = (lambda e: e.selfjoin_pairs(X, eps, 8000000, d=d)), (lambda e: e.selfjoin_count(X, eps, d=d))
+    same_pairs(calls[0](both[0]), calls[0](both[1]))
+    for u, v in zip(calls[1](both[0]), calls[1](both[1])):
+        assert torch.equal(u, v)
+
+
+@pytest.fixture(scope="module")
+def product():
+    e = pkg.EJoin(0)
+    yield e
+    e.close()
+
+
+@pytest.mark.parametrize("n,d", [(14501, 128), (20011, 40), (33001, 60), (40000, 200), (65001, 96), (70000, 256), (52000, 310)])
+@pytest.mark.parametrize("share", [0.00001, 0.002])
+def test_self_joins_that_go_there(both, product, n, d, share):
+    """The product's own build at sizes that it sends there: few neighbours, and a hundred and more of them."""
+    print(f"strip product self n={n} d={d} share={share}", flush=True)
+    assert product.join_kernel(n, d) == "strip"
+    X = rows(n, d, seed=n)
+    X[n // 2:n // 2 + n // 20] = rows(n, d, seed=n + 1)[:n // 20]  # (other points in place of the duplicates)
+    eps = epsilon(X, d, share)
+    cap = int(4 * share * n * n) + 100000
+    same_pairs(both[0].selfjoin_pairs(X, eps, cap, d=d), product.selfjoin_pairs(X, eps, cap, d=d))
+    for u, v in zip(both[0].selfjoin_count(X, eps, d=d), product.selfjoin_count(X, eps, d=d)):
+        assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("n,nq,d,count", [(300000, 300, 128, True), (200000, 500, 300, True), (200000, 1000, 64, False), (1000, 200000, 60, True), (30011, 7001, 200, False),
+                                          (7001, 30011, 200, True), (500000, 700, 100, True), (2500, 100000, 256, False)])
+def test_two_sets_that_go_there(both, product, n, nq, d, count):
+    print(f"strip product two sets n={n} nq={nq} d={d} count={count}", flush=True)
+    assert product.join_kernel(n, d, nq, count=count) == "strip"
+    P, Q = rows(n, d, seed=d), rows(nq, d, seed=d + 1)
+    eps = epsilon(Q, d, 0.0002)
+    if count:
+        for u, v in zip(both[0].join_count(P, Q, eps, d=d), product.join_count(P, Q, eps, d=d)):
+            assert torch.equal(u, v)
+    else:
+        same_pairs(both[0].join_pairs(P, Q, eps, n * nq // 500, d=d), product.join_pairs(P, Q, eps, n * nq // 500, d=d))
