@@ -3,7 +3,8 @@
 Table "leave-one-out", Section 4.3, for this kernel's own optimisations).
 
 Each variant is the same source built with one element taken out (paper_2508_21230_amd/build.py:
-ABLATIONS; build them first with `python -m paper_2508_21230_amd.build --ablations`); all variants
+ABLATIONS; build them first with `python -m paper_2508_21230_amd.build --ablations`), beside the build that
+sends problems of every size and width to that kernel ("full"; the product sends few coordinates elsewhere); all variants
 compute the same pairs, which this script checks by comparing the number of pairs found.  "no
 symmetry" runs the full library's two-set join of the data with itself (every tile of the square).
 Prints one JSON line per (variant, workload) and a markdown table.
@@ -52,13 +53,13 @@ def main():
 
     with open(os.path.join(ROOT, "paper_2508_21230_amd", "workloads_eps.json")) as f:
         eps_all = json.load(f)
-    variants = [("full", None)]
+    variants = [("full", build.GENERAL_KERNEL_LIB)]
     for name in build.ABLATIONS:
         path = os.path.join(build.ABLATION_DIR, f"libejoin_{name}.so")
         if not os.path.exists(path):
             sys.exit(f"{path} is missing: run `python -m paper_2508_21230_amd.build --ablations` first")
         variants.append((name, path))
-    variants.append(("no_symmetry", None))
+    variants.append(("no_symmetry", build.GENERAL_KERNEL_LIB))
     if args.variant:
         variants = [v for v in variants if v[0] == args.variant]
         if not variants:
@@ -160,7 +161,7 @@ def experiments(args):
         # (no_copies computes every tile on the first tile's operands: compared output-free, epsilon = 0, so that the
         # rare path sees no more than the duplicates in either build)
         for name in ("full", "hot_panels", "full eps=0", "no_copies", "full", "hot_panels", "full eps=0", "no_copies"):
-            ej = pkg.EJoin(0, lib_path=None if name.startswith("full") else os.path.join(build.ABLATION_DIR, f"libejoin_{name}.so"))
+            ej = pkg.EJoin(0, lib_path=build.GENERAL_KERNEL_LIB if name.startswith("full") else os.path.join(build.ABLATION_DIR, f"libejoin_{name}.so"))
             eps_run = 0.0 if name in ("full eps=0", "no_copies") else eps
             step = lambda: ej.selfjoin_pairs(Xd, eps_run, cap, pairs=pairs, dist2=d2, n_pairs=npairs)
             step()

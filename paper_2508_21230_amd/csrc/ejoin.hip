@@ -562,14 +562,14 @@ __device__ __forceinline__ void copy16_to_lds_from(uint32_t lds_addr, const void
 // every 32 x 32 region of it computed the way the join kernel computes a region of its wave tile: four 16 x 16 blocks
 // accumulated with v_mfma_f32_16x16x32_f16, then one v_mfma_f32_32x32x16_f16 on the four blocks' registers side by side that
 // adds -s_i/2 - s_j/2 (operand layout: see the augmentation step of k_join).
-// Bound by how the operands reach the CUs and then by writing the block (4,000 x 5,000 at d = 384, 80 MB: 37 us a call, of which the
-// norms of the 20,000 points take 6; some 28 without the stores).  The operands come from X as it is, 64 coordinates of a row (a whole
+// Bound by how the operands reach the CUs and then by writing the block (4,000 x 5,000 at d = 384, 80 MB: 33.5 to 38 us a call over
+// the cards, of which the norms of the 20,000 points take 6; some 28 without the stores).  The operands come from X as it is, 64 coordinates of a row (a whole
 // line) at a time, straight to the LDS, STAGES - 1 slices ahead; the columns are the rows of the MFMAs, so that a lane stores sixteen
-// bytes of a row; the operands of the augmentation step are worked out here, from the norms.  With slices through registers, 4-byte
-// stores and a launch of their own for the augmentation rows: 57 us a call; 1,500 x 1,500 20, now 14; 3,000 x 2,000 at d = 960 42,
-// now 29; 6,000 x 6,000 at d = 128 54, now 37.  Eight wavefronts for TS = 128, of which two workgroups fit a CU: with four of
-// 64 x 64 each 41 us a call, with eight 37, with sixteen 38; 6,000 x 6,000 at d = 128 41, 37, 41.  (Tried: rows of 256 bytes stored by way of the LDS: the same; stores that pass the
-// caches by: 68.)
+// bytes of a row; the operands of the augmentation step are worked out here, from the norms.  With slices through registers, four
+// wavefronts, 4-byte stores and a launch of their own for the augmentation rows, both on one card: 53.8 us a call, now 37.8;
+// 1,500 x 1,500 20.5, now 17.2; 2,000 x 3,000 at d = 960 47.2, now 33.7; 6,000 x 6,000 at d = 128 56.2, now 40.6.  Eight wavefronts for TS = 128, of which two workgroups fit a CU: with four of
+// 64 x 64 each (another card) 41 us a call, with eight 37, with sixteen 38; 6,000 x 6,000 at d = 128 41, 37, 41.  (Tried: rows of
+// 256 bytes stored by way of the LDS: the same; stores that pass the caches by: 68.)
 // TS = 128 needs half the operand traffic of TS = 64, which gives four times the workgroups: at 144 of the larger kind (1,500 x
 // 1,500, d = 384) 15.2 us a call against 13.6, at 225 (1,800 x 1,800) 15.6 against 16.9, at 240 (700 x 5,001, d = 100) 13.2 against
 // 14.6, at 289 the same, at 1,280 39 against 46: the line lies at three workgroups of the larger kind for four CUs.
@@ -1492,10 +1492,10 @@ __global__ __launch_bounds__(THREADS) void k_join(const JoinArgs a) {
 // k-blocks at a time, and a block of 64 rows x 32 columns per wavefront is complete after K steps, with 32 accumulators.
 // What bounds k_join at few coordinates is the boundary of a tile (a third of its time at four slices) and, in long launches, power.
 // Here a block's filter runs under the next block's MFMAs, there is no barrier (progress counters, below), the L2 -> LDS copies are a
-// quarter of k_join's (512 rows share them, and only columns are copied) and the LDS reads 57 B per clock and CU at MFMA peak instead
-// of 96.  Measured (join kernel): 10^6 points, d = 128, S = 64, counts 105.5 ms, now 91.5; 10^5 points, pairs 1383 us, now 1170 (output
+// quarter of k_join's (512 rows share them, and only columns are copied) and the LDS reads 64 B per clock and CU at MFMA peak instead
+// of 96 (d = 128).  Measured (join kernel): 10^6 points, d = 128, S = 64, counts 105.5 ms, now 91.5; 10^5 points, pairs 1383 us, now 1170 (output
 // left out 1160, now 900: MFMA pipe busy 0.76 of the cycles, at the clock that the power limit leaves); 40,000 points, d = 224,
-// pairs 296 us, now 276.  From nine k-blocks on there are no registers for two buffers of accumulators, and the filter is in the open:
+// pairs 296 us, now 276.  From eight k-blocks on there are no registers for two buffers of accumulators, and the filter is in the open:
 // 150,000 points, d = 320, 5.33 ms, now 5.08.
 // Tried: a barrier per stage (candidates of one wavefront hold up all: 10^5 x 128 1680 us); 256 rows and 64 columns a workgroup,
 // copies by four of the wavefronts (10^6 x 128 without candidates 94 ms, now 91); volatile progress counters (every LDS read
@@ -1533,7 +1533,7 @@ struct Strip {
   static constexpr int STG_OFF = ROWS_OFF + ROWS;
   static constexpr int LDS = STG_OFF + 8 * WAVE;
   static_assert(STAGES >= 3 && LAG >= 1 && DEPTH > POST && LDS <= 160 * 1024, "LDS budget of one CU");
-  static_assert(RING - 1 <= 2 * K, "what is read ahead belongs to this block or the next");
+  static_assert(RING <= 2 * K, "what is read ahead belongs to this block or the next");
 };
 
 template <bool COUNT, int K>
@@ -2033,10 +2033,7 @@ __global__ __launch_bounds__(THREADS) void k_join_strip(const JoinArgs a) {
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 #pragma unroll
-  for (int f = 0; f < RING - 1; ++f) {  // (RING = 2 K + 1: the last of them are the second block's)
-    const int then = f % FRAGS;
-    fb[f] = at_lds(off0 ^ (then % 2 * 32), then / 2 * L::KB + (f < FRAGS ? 0 : 2048));
-  }
+  for (int f = 0; f < RING - 1; ++f) fb[f] = at_lds(off0 ^ (f % 2 * 32), f / 2 * L::KB);
   for (;;) {
     const uint32_t c = __builtin_amdgcn_readlane(places, slot), I = __builtin_amdgcn_readlane(places, slot + 32);
     if (__builtin_expect(c == NO_STAGE, 0)) break;
