@@ -246,7 +246,10 @@ __global__ __launch_bounds__(512) void k_norms(const uint16_t* __restrict__ X, i
                                                float* __restrict__ s, uint32_t* __restrict__ max_bits, uint4* __restrict__ Xp,
                                                int blocks /* k-blocks per panel of Xp: k32steps + 1 */,
                                                uint32_t* __restrict__ maxima /* one per workgroup (may be null) */) {
-  const int64_t row0 = ((int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (16 * HALVES);
+  // Norms alone, from the last point on: of rows that have just been written, more than the memory-side cache holds, those are still in
+  // it (10^6 x 200 converted, then normed: 331 us, now 309)
+  const uint32_t group = HALVES == 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+  const int64_t row0 = ((int64_t)group * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (16 * HALVES);
   uint32_t most = 0;
   if (row0 < (PACK ? npad : n)) most = norms_of_wave<PACK, HALVES>(row0, X, n, ld, k32steps, s, Xp, blocks);
   if (max_bits) merge_max(most, max_bits);
@@ -368,53 +371,63 @@ typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Ingestion: FP32 rows -> FP16 rows in the layout the join expects (row stride ld16, a multiple of 64,
 // columns d .. ld16-1 zero).  y = fp16_rne(fl32(scale * fl32(x - center_k))).
-// Bound by memory.  A thread makes 8 output columns of CONVERT_ROWS rows: two 16-byte loads and one 16-byte store each, the
+// Bound by memory.  A thread makes COLS output columns of CONVERT_ROWS rows: 16-byte loads, and one store per row, the
 // loads of all its rows in flight together; `wide` consecutive threads (a power of two that divides the chunks of a row, 8 to 64)
 // take consecutive chunks of a row: at least a full line of the result.  With one row per thread, eight 4-byte loads 32 bytes
-// apart and a 64-bit division per chunk it took 346 us on 5 10^5 x 200 (1.9 TB/s), now 105 (6.2 TB/s; two rows per thread 111,
-// eight 117).
+// apart and a 64-bit division per chunk it took 346 us on 5 10^5 x 200 (1.9 TB/s), with eight columns and four rows 105 to 115 (two rows
+// per thread 111, eight 117).
+// Input that the memory-side cache (256 MB) cannot hold is read past the caches (NT), which leaves them to the result: what comes next,
+// norms or a join, reads that.  Then it has to be four columns a thread, whose loads are whole lines: 5 10^5 x 200 100 us, with the
+// norms after it 161 us, now 135; 10^6 x 128 176, now 148; eight columns (half lines) 151.  Smaller input may well be in that cache
+// already (10^5 x 128 again and again, with the norms: 19.7 us, 20.3 past the caches; 2 10^5 x 200 57, 60), and keeps eight columns.  Rows that
+// are not 16-byte aligned have lines that two loads share: 4 10^5 x 333 158 us with eight columns, 184 past the caches with four,
+// 146 through them.
 constexpr int CONVERT_ROWS = 4;
+constexpr int64_t CONVERT_CACHED = 256ll << 20;  // bytes of input
+template <int COLS, bool NT>
 __global__ __launch_bounds__(256) void k_convert_f32(const float* __restrict__ X32, int64_t n, int32_t d, int64_t ld32,
                                                      const float* __restrict__ center, float scale, uint16_t* __restrict__ X16, int64_t ld16,
                                                      uint32_t wide_log2, uint32_t blocks_per_row) {
+  typedef _Float16 halves __attribute__((ext_vector_type(COLS)));
   const uint32_t wide = 1u << wide_log2, step = 256u >> wide_log2;  // chunks side by side, rows at a time
   const uint32_t rows_block = blockIdx.x / blocks_per_row;
   const int64_t chunk = ((int64_t)(blockIdx.x - rows_block * blocks_per_row) << wide_log2) + (threadIdx.x & (wide - 1));
   const int64_t row0 = (int64_t)rows_block * (step * CONVERT_ROWS) + (threadIdx.x >> wide_log2);
-  const int64_t k0 = chunk * 8;
-  float c[8];
+  const int64_t k0 = chunk * COLS;
+  float c[COLS];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) c[k] = center && k0 + k < d ? center[k0 + k] : 0.f;
-  float x[CONVERT_ROWS][8];
+  for (int k = 0; k < COLS; ++k) c[k] = center && k0 + k < d ? center[k0 + k] : 0.f;
+  float x[CONVERT_ROWS][COLS];
 #pragma unroll
   for (int r = 0; r < CONVERT_ROWS; ++r) {
     const int64_t i = row0 + r * step;
     const float* p = X32 + (i < n ? i : n - 1) * ld32 + k0;
-    if (k0 + 8 <= d) {
-      const float4u lo = *reinterpret_cast<const float4u*>(p), hi = *reinterpret_cast<const float4u*>(p + 4);
+    if (k0 + COLS <= d) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        x[r][k] = lo[k];
-        x[r][4 + k] = hi[k];
+      for (int q = 0; q < COLS; q += 4) {
+        const float4u* at = reinterpret_cast<const float4u*>(p + q);
+        const float4u four = NT ? __builtin_nontemporal_load(at) : *at;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) x[r][q + k] = four[k];
       }
     } else {
 #pragma unroll
-      for (int k = 0; k < 8; ++k) x[r][k] = k0 + k < d ? p[k] : 0.f;
+      for (int k = 0; k < COLS; ++k) x[r][k] = k0 + k < d ? p[k] : 0.f;
     }
   }
 #pragma unroll
   for (int r = 0; r < CONVERT_ROWS; ++r) {
     const int64_t i = row0 + r * step;
-    half8 h;
+    halves h;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < COLS; ++k) {
       float t = x[r][k] - c[k];
       asm volatile("" : "+v"(t));  // keep the FP32 rounding of every step: no fused subtract-multiply-convert
       float y = k0 + k < d ? scale * t : 0.f;
       asm volatile("" : "+v"(y));
       h[k] = (_Float16)y;
     }
-    if (i < n) *reinterpret_cast<half8*>(X16 + i * ld16 + k0) = h;
+    if (i < n) *reinterpret_cast<halves*>(X16 + i * ld16 + k0) = h;
   }
 }
 
@@ -3259,11 +3272,16 @@ int ejoin_convert_f32(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, in
   if (!guard.ok) return EJOIN_EHIP;
   const int64_t per_row = ld16 / 8;
   if ((n * per_row + 255) / 256 > 0x7FFFFFFFll) return EJOIN_EUNSUPPORTED;
+  // (a grid has fewer than 2^32 threads; at few coordinates most of a row of the result is padding, and eight columns are the better ones)
+  const bool large = n * d * (int64_t)sizeof(float) > CONVERT_CACHED && d > 32 && n * per_row < (1ll << 32);
+  const bool past = large && ld32 % 4 == 0 && (reinterpret_cast<uintptr_t>(X32) & 15) == 0;
+  const int64_t chunks = large ? ld16 / 4 : per_row;  // of a row
   uint32_t wide_log2 = 3;  // (a row is a multiple of 64 columns)
-  while (wide_log2 < 6 && per_row % (2ll << wide_log2) == 0) ++wide_log2;
+  while (wide_log2 < 6 && chunks % (2ll << wide_log2) == 0) ++wide_log2;
   const int64_t rows = (256 >> wide_log2) * CONVERT_ROWS;
-  hipLaunchKernelGGL(k_convert_f32, dim3((unsigned)((n + rows - 1) / rows * (per_row >> wide_log2))), dim3(256), 0, static_cast<hipStream_t>(stream), X32,
-                     n, d, ld32, center, scale, X16, ld16, wide_log2, (uint32_t)(per_row >> wide_log2));
+  hipLaunchKernelGGL((past ? k_convert_f32<4, true> : large ? k_convert_f32<4, false> : k_convert_f32<8, false>),
+                     dim3((unsigned)((n + rows - 1) / rows * (chunks >> wide_log2))), dim3(256), 0, static_cast<hipStream_t>(stream), X32,
+                     n, d, ld32, center, scale, X16, ld16, wide_log2, (uint32_t)(chunks >> wide_log2));
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }
