@@ -19,7 +19,8 @@ extern "C" {
 int ejoin_set_profiling(ejoin_ctx* ctx, int on);
 int ejoin_last_kernel_ms(ejoin_ctx* ctx, float* prep_ms, float* join_ms);
 
-/* What the join kernel of a call executes: *tiles output tiles of *edge x *edge points (256; 128 or 64 for small problems), *steps
+/* What the join kernel of a call executes: *tiles output tiles of *edge x *edge points (256; 128 or 64 for small problems, of a pair list of
+ * rows: counts and prepared sets of a few thousand points may have the other of the two), *steps
  * matrix-core steps of 32 coordinates each, i.e. 2 * edge * edge * 32 * steps FLOP per tile (without the one step per tile that adds
  * the norms).  np points with themselves (nq = 0) or with nq query points; split != 0: the split-FP16 join of np FP32 rows.
  * (EJOIN_KERNEL_STRIP works in pieces of 512 x 64 points; they are counted as tiles of 256 all the same, which for 10^5 points with

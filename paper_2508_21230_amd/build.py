@@ -42,6 +42,10 @@ GENERAL_KERNEL_LIB = os.path.join(ABLATION_DIR, "libejoin_general_kernel.so")
 STRIP_KERNEL = {"strip_kernel": ["-DEJOIN_ONLY_K_JOIN_STRIP"]}
 STRIP_KERNEL_LIB = os.path.join(ABLATION_DIR, "libejoin_strip_kernel.so")
 
+#: ... and the one whose one-launch joins wait for none of their workgroups, so that (nearly) all are late
+LATE = {"once_late": ["-DEJOIN_ONCE_SPINS=0"]}
+LATE_LIB = os.path.join(ABLATION_DIR, "libejoin_once_late.so")
+
 
 def _compile(out: str, defines=(), verbose: bool = False) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -67,7 +71,7 @@ def build_ablations(verbose: bool = False) -> dict:
     """Compile the ablation variants, the timing-only experiment builds (measurement only, see bench_ablation.py) and the tests'
     build of the general kernel -> ablation/libejoin_<name>.so."""
     os.makedirs(ABLATION_DIR, exist_ok=True)
-    variants = {**ABLATIONS, **EXPERIMENTS, **GENERAL_KERNEL, **STRIP_KERNEL}
+    variants = {**ABLATIONS, **EXPERIMENTS, **GENERAL_KERNEL, **STRIP_KERNEL, **LATE}
     with ThreadPoolExecutor(min(4, os.cpu_count() or 1)) as pool:  # (one after the other they take six minutes)
         libs = pool.map(lambda name: _compile(os.path.join(ABLATION_DIR, f"libejoin_{name}.so"), variants[name], verbose), variants)
         return dict(zip(variants, libs))

@@ -2413,6 +2413,363 @@ __global__ __launch_bounds__(256, small_groups_per_cu<TS>()) void k_join_small(c
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// The join of the smallest problems, in one launch
+// ------------------------------------------------------------------------------------------
+// Problems whose tiles all fit the CUs at once: a workgroup of k_join_once computes one tile from the rows of X as they are, and the
+// norms of the tile's points beside it (two more MFMA chains per wavefront, the diagonals of 16 points' Gram blocks as in
+// norms_of_wave).  What bounds them is launches and latency, on the host as much as on the GPU; by k_prep and k_join_small, a call
+// (all on one card): counts of 1,000 x 96 11.5 us, now 8.3; 2,400 x 128 14.3, now 9.3; lists of 4,096 x 128 18.1, now 15.5 (counts
+// 17.8, 11.6), of 2,800 x 384 20.9, now 14.7, 4,096 x 960 39.9, now 38.4; 25,000 points x 60 queries, d = 384, 26.5, now 15.1.
+//   * The scale of the norm terms comes from the largest norm of all points.  The workgroups on the diagonal (two sets: of the first
+//     row and column of tiles) put the largest norm of every 64 of their points into a slot each, and every workgroup reads all the
+//     slots before its augmentation step.  It waits for them a bounded number of times only: workgroups that the GPU has not started
+//     yet may be behind others that wait for this kernel's.  Past that it works the largest norm out by itself (`late`).
+//     The slots are there once for every XCD, so that no line has more than an eighth of the readers (4,096 x 128: one copy 18.3 us,
+//     eight 16.4, thirty-two 16.9, without the wait 14.8).
+//   * Counts are cleared by the workgroups that fill those rows' slots, before they do, so whoever has seen all slots may add to them.  A late
+//     workgroup adds to counters of the context's instead, which the last workgroup of all adds to the result.
+//   * The result's counter is the context's, with a ticket in its upper bits: one atomic per workgroup says where its pairs go and
+//     which workgroup is the last; that one stores the total and leaves everything as it was found, all zero.  Those atomics are served
+//     one after the other, 6 to 13 ns each: counts take theirs XCD by XCD from ONCE_STEPS tiles on (4,096 x 128 16.3 us, then 13.0).
+//   * Eight wavefronts to a tile of 128: with four of 64 x 64 each 16.2 us for the lists of 4,096 x 128 and 13.0 for the counts, with
+//     eight 15.5 and 11.6.  Three workgroups fit a CU.  Its slices are of 32 coordinates (half lines, two-way bank conflicts), so that three stages do.
+// The arithmetic is k_join's, step by step, and the results its bits.
+struct OnceArgs {
+  JoinArgs j;  // (ntilesA, ntilesB in tiles of TS; no packed copies)
+  const uint16_t* XA;
+  const uint16_t* XB;
+  int64_t ldA, ldB;
+  float* sA;  // for the norms that a late workgroup works out (nobody reads them)
+  float* sB;
+  uint32_t tiles, slots_a, slots;  // slots: one per 64 points of the first set, then of the second
+  // of the context, all zero between calls
+  unsigned long long* state;  // [0], and [16 (1 + x)] of XCD x.  Bits 0 .. 39: pairs found; 40 .. 51: late workgroups; 52 .. 63: tickets
+  uint32_t* slot;             // ONCE_SLOTS for each XCD
+  uint32_t* late_counts;      // of the points, then of the query points
+};
+constexpr int ONCE_SLOTS = 2048, ONCE_COUNTS = 1 << 17;  // capacities
+constexpr uint32_t ONCE_STEPS = 256;                     // tiles from which on counts take their tickets XCD by XCD
+constexpr size_t ONCE_STATE_BYTES = 16 * 8 * (1 + EJ_NUM_XCD);
+#ifndef EJOIN_ONCE_SPINS
+#define EJOIN_ONCE_SPINS 2048  // (a build for the tests waits for nothing)
+#endif
+constexpr int ONCE_GROUPS_PER_CU = 3;
+template <int TS>
+struct Once {
+  static constexpr int WR = TS / 32, WC = 2, WAVES = WR * WC, THREADS = 64 * WAVES;  // wavefronts: of the rows, of the columns; 32 x TS / 2 each
+  static constexpr int SC = TS == 64 ? 64 : 32;  // coordinates of a slice
+  static constexpr int ROW = 2 * SC;             // bytes of a row of it
+  static constexpr int OP = TS * ROW, STAGE = 2 * OP;
+  static constexpr int STAGES = 3;
+  static constexpr int COPIES = OP / (WAVES * 1024);  // copy instructions per wavefront, operand and slice
+  // after the last slice, where the stages were: the norms, staged results or counters, the operands of the augmentation step
+  static constexpr int TAIL = 2 * TS * 4, AUG = TAIL + WAVES * SMALL_STG_CAP * 12, AUG_B = AUG + TS * 16, AUG_CONST = AUG_B + TS * 16;
+  static constexpr int SUMS = STAGES * STAGE, LDS = SUMS + 128;
+  static_assert(AUG_CONST + 64 <= SUMS && LDS * ONCE_GROUPS_PER_CU <= 152 * 1024, "LDS budget");
+};
+template <bool COUNT, int TS>
+__global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::WAVES / 4) void k_join_once(const OnceArgs args) {
+  using L = Once<TS>;
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  constexpr int MR = 2, MC = TS / 32, NC = MC / 2, KBS = L::SC / KSLICE;  // a wavefront's blocks of rows and columns, its regions
+  const JoinArgs& a = args.j;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * (TS / 2);
+  const int r16 = lane & 15, g = lane >> 4;
+  const int nkb = a.nslices, nsl = (nkb + KBS - 1) / KBS;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lds, nnA = (uint32_t)a.nA, nnB = (uint32_t)a.nB;
+  // The tiles whose workgroups fill slots come first.
+  uint32_t I, J;
+  once_tile(blockIdx.x, (uint32_t)a.self, a.ntilesA, a.ntilesB, I, J);
+  const uint32_t i_tile = I * TS, j_tile = J * TS;
+  const bool diag = a.self && I == J;
+
+  // ---- this thread's point of the tile: row tid of its rows, then of its columns
+  const bool col = tid >= TS;
+  const uint32_t own = (col ? j_tile : i_tile) + (tid & (TS - 1));
+  const bool exists = tid < 2 * TS && own < (col ? nnB : nnA);
+  const bool fills = col ? !a.self && I == 0 : (a.self ? I == J : J == 0);  // (uniform over a wavefront)
+  if (COUNT && fills && exists) {
+    uint32_t* to = col ? a.counts_b : a.counts;
+    if (to) __hip_atomic_store(to + own, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  // ---- copies.  Rows of 128 bytes: chunk c of row r at position c ^ (r / 2 % 8), as in the dense block; of 64 bytes: c ^ (r / 4 % 4).
+  // Rows past the end are the last one's again (they carry the marker in the norm term).
+  constexpr int PER = 1024 / L::ROW, CH = L::ROW / 16;  // rows and chunks a row of a copy instruction
+  auto swizzle = [](int r) { return TS == 64 ? (r >> 1) & 7 : (r >> 2) & 3; };
+  const char *ga[L::COPIES], *gb[L::COPIES];
+#pragma unroll
+  for (int q = 0; q < L::COPIES; ++q) {
+    const int r = PER * (L::WAVES * q + wave) + lane / CH, c = (lane % CH) ^ swizzle(r);
+    ga[q] = reinterpret_cast<const char*>(args.XA + (int64_t)min(i_tile + r, nnA - 1) * args.ldA) + 16 * c;
+    gb[q] = reinterpret_cast<const char*>(args.XB + (int64_t)min(j_tile + r, nnB - 1) * args.ldB) + 16 * c;
+  }
+  auto issue = [&](int stage) {  // the next slice
+    const uint32_t at = __builtin_amdgcn_readfirstlane(lds0 + stage * L::STAGE + wave * 1024);
+    copy16_to_lds_from<0>(at, ga[0]);
+    if constexpr (L::COPIES == 2) copy16_to_lds_from<4096>(at, ga[1]);
+    copy16_to_lds_from<L::OP>(at, gb[0]);
+    if constexpr (L::COPIES == 2) copy16_to_lds_from<L::OP + 4096>(at, gb[1]);
+#pragma unroll
+    for (int q = 0; q < L::COPIES; ++q) {
+      ga[q] += L::ROW;
+      gb[q] += L::ROW;
+    }
+  };
+#pragma unroll
+  for (int ks = 0; ks < L::STAGES - 1; ++ks)
+    if (ks < nsl) issue(ks);
+  uint32_t off[KBS];  // k-block kb of a slice: row lane % 16, chunk 4 kb + lane / 16
+#pragma unroll
+  for (int kb = 0; kb < KBS; ++kb) off[kb] = r16 * L::ROW + (((4 * kb + g) ^ swizzle(r16)) << 4);
+
+  // ---- the Gram products and the norms: every wavefront's one of its two blocks of rows and one of its WR blocks of columns, so that
+  // the wavefronts that share them have them all
+  const int norm_r = wm + 16 * (wave & 1), norm_c = wn + 16 * (wave >> 1);
+  float4v acc[MR][MC], norm[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int x = 0; x < MR; ++x)
+#pragma unroll
+    for (int y = 0; y < MC; ++y) acc[x][y] = float4v{0.f, 0.f, 0.f, 0.f};
+  int stage = 0;
+  for (int ks = 0; ks < nsl; ++ks) {
+    if (ks + 1 < nsl) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * L::COPIES) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    wg_barrier();  // slice ks is there for everybody, and everybody is done with slice ks - 1
+    if (ks + L::STAGES - 1 < nsl) issue(stage == 0 ? L::STAGES - 1 : stage - 1);
+    const char* st = lds + stage * L::STAGE;
+#pragma unroll
+    for (int kb = 0; kb < KBS; ++kb) {
+      if (KBS > 1 && ks * KBS + kb >= nkb) break;
+      half8 fa[MR], fb[MC];
+#pragma unroll
+      for (int f = 0; f < MR; ++f) fa[f] = *reinterpret_cast<const half8*>(st + (wm + 16 * f) * L::ROW + off[kb]);
+#pragma unroll
+      for (int f = 0; f < MC; ++f) fb[f] = *reinterpret_cast<const half8*>(st + L::OP + (wn + 16 * f) * L::ROW + off[kb]);
+      const half8 nr = *reinterpret_cast<const half8*>(st + norm_r * L::ROW + off[kb]), nc = *reinterpret_cast<const half8*>(st + L::OP + norm_c * L::ROW + off[kb]);
+#pragma unroll
+      for (int y = 0; y < MC; ++y)
+#pragma unroll
+        for (int u = 0; u < MR; ++u) {
+          const int x = (y & 1) ? MR - 1 - u : u;
+          acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[x], fb[y], acc[x][y], 0, 0, 0);
+        }
+      norm[0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(nr, nr, norm[0], 0, 0, 0);
+      norm[1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(nc, nc, norm[1], 0, 0, 0);
+    }
+    stage = stage == L::STAGES - 1 ? 0 : stage + 1;
+  }
+  __syncthreads();  // everybody has read the last slice
+  float* norms = reinterpret_cast<float*>(lds);  // of the rows, then of the columns
+  store_diagonal(norm[0], norm_r, 2 * TS, norms);
+  store_diagonal(norm[1], TS + norm_c, 2 * TS, norms);
+  if (COUNT) {
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(lds + L::TAIL);
+    if (tid < 2 * TS) cnt[tid] = 0;
+  }
+  __syncthreads();
+
+  // ---- the largest norm of all
+  constexpr uint32_t FILLED = 0x80000000u;  // (a norm has no sign)
+  if (fills && tid < 2 * TS) {
+    uint32_t most = exists ? __float_as_uint(norms[tid]) : 0u;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, o));
+    if (COUNT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the counts are cleared
+    const uint32_t first = own - lane;
+    if (lane < NUM_XCD && first < (col ? nnB : nnA))
+      __hip_atomic_store(args.slot + lane * ONCE_SLOTS + (col ? args.slots_a : 0u) + first / 64, most | FILLED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  uint32_t mb = 0;
+  bool missing = false;
+  const uint32_t* slot = args.slot + blockIdx.x % NUM_XCD * ONCE_SLOTS;
+  for (uint32_t q = tid; q < args.slots; q += L::THREADS) {
+    uint32_t v = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int spin = 0; v == 0 && spin < EJOIN_ONCE_SPINS; ++spin) {
+      __builtin_amdgcn_s_sleep(1);
+      v = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    missing |= v == 0;
+    mb = max(mb, v & ~FILLED);
+  }
+  const bool late = __syncthreads_or(missing);
+  if (late) {
+    mb = 0;
+    for (int64_t row0 = wave * 32; row0 < a.nA; row0 += L::WAVES * 32)
+      mb = max(mb, norms_of_wave<false>(row0, args.XA, a.nA, args.ldA, nkb, args.sA, nullptr, 0));
+    if (!a.self)
+      for (int64_t row0 = wave * 32; row0 < a.nB; row0 += L::WAVES * 32)
+        mb = max(mb, norms_of_wave<false>(row0, args.XB, a.nB, args.ldB, nkb, args.sB, nullptr, 0));
+  }
+  const NormScale ns = norm_scale(max_of_group(mb));
+  if (blockIdx.x == 0 && tid == 0) a.status[0] = ns.st;
+
+  // ---- the augmentation step and the filter.  Bit r of hit: register r of this lane's part of a region passes.
+  float16v v[NC];
+  uint32_t hit[NC] = {};
+  if (ns.st == ST_OK) {
+    if (tid < 2 * TS) {  // (as in k_join_small)
+      const int row = tid & (TS - 1), in = row & 31;
+      const uint32_t first = (uint32_t)((row & ~31) + (col ? aug_col_point(in) : aug_row_point(in)));
+      const uint32_t x = (col ? j_tile : i_tile) + first, y = x + (col ? 16u : 4u), nn = col ? nnB : nnA;
+      const float* s = norms + (col ? TS : 0) + first;
+      uint2 p = make_uint2(P1_OUT_OF_RANGE, 0u), q = p;
+      if (x < nn) p = norm_pieces(s[0], ns.m);
+      if (y < nn) q = norm_pieces(s[col ? 16 : 4], ns.m);
+      *reinterpret_cast<uint4*>(lds + (col ? L::AUG_B : L::AUG) + row * 16) = make_uint4(p.x, p.y, q.x, q.y);
+    }
+    if (tid < 4) {  // the constant chunks of the augmentation step (2 and 3)
+      const uint32_t c = fp16_bits(ns.c), c0 = c | (c << 16);
+      *reinterpret_cast<uint2*>(lds + L::AUG_CONST + tid * 8) = tid == 0 || tid == 3 ? make_uint2(c0, c) : make_uint2(0u, 0u);
+    }
+    __syncthreads();
+    const int ca = aug_chunk_a(lane), cb = aug_chunk_b(lane);
+    const char* aug_a = lds + (ca == 0 ? L::AUG + 16 * (wm + (lane & 31)) : L::AUG_CONST + 16 * (ca - 2));
+    const char* aug_b = lds + (cb == 1 ? L::AUG_B + 16 * (wn + (lane & 31)) : L::AUG_CONST + 16 * (cb - 2));
+    const int step_b = cb == 1 ? 512 : 0;
+    const bool partial = diag || i_tile + TS > nnA || j_tile + TS > nnB;
+    const half8 ha = *reinterpret_cast<const half8*>(aug_a);
+#pragma unroll
+    for (int R = 0; R < NC; ++R) {
+      const half8 hb = *reinterpret_cast<const half8*>(aug_b + R * step_b);
+      v[R] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ha, hb, cat4(acc[0][2 * R], acc[0][2 * R + 1], acc[1][2 * R], acc[1][2 * R + 1]), 0, 0, 0);
+    }
+#pragma unroll
+    for (int R = 0; R < NC; ++R) {
+      uint32_t h = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) h |= v[R][r] >= a.thr ? 1u << r : 0u;
+      if (partial && __ballot(h != 0)) h &= keep_mask(i_tile + wm + 4 * g, j_tile + wn + 32 * R + r16, nnA, nnB, diag);
+      hit[R] = h;
+    }
+  }
+
+  // ---- results.  One atomic for the workgroup, with its ticket.
+  unsigned long long* sums = reinterpret_cast<unsigned long long*>(lds + L::SUMS);
+  constexpr unsigned long long FOUND = (1ull << 40) - 1, TICKET = 1ull << 52;
+  const bool own_pairs = diag && !COUNT && wave < TS / 64 && ns.st == ST_OK;  // (i, i) belongs to the result by definition
+  uint32_t found = own_pairs && i_tile + tid < nnA ? 1u : 0u;
+#pragma unroll
+  for (int R = 0; R < NC; ++R) found += __popc(hit[R]);
+  found = wave_sum(found);
+  if (lane == 0) sums[wave] = found;
+  if constexpr (COUNT) {
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(lds + L::TAIL);
+#pragma unroll
+    for (int R = 0; R < NC; ++R)
+      if (__ballot(hit[R] != 0)) add_region_counts(hit[R], cnt + wm + 4 * g, cnt + TS + wn + 32 * R + r16);
+    __syncthreads();
+    if (tid < 2 * TS) {
+      const uint32_t c = cnt[tid];
+      uint32_t* to = !col || a.self ? a.counts : a.counts_b;
+      if (late) to = args.late_counts + (!col || a.self ? 0 : a.nA);
+      if (c && to) atomicAdd(to + own, c);
+      if (late) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // before the ticket
+    }
+    if (late) __syncthreads();
+  } else {
+    __syncthreads();
+  }
+  unsigned long long old = 0, total = 0;  // (of thread 0)
+  uint32_t lates = late;
+  if (tid == 0) {
+    for (int w = 0; w < L::WAVES; ++w) total += sums[w];
+    const unsigned long long add = TICKET | ((unsigned long long)late << 40) | total;
+    if (COUNT && args.tiles > ONCE_STEPS) {
+      unsigned long long* own_xcd = args.state + 16 * (1 + blockIdx.x % NUM_XCD);
+      const unsigned long long in_xcd = atomicAdd(own_xcd, add) + add;
+      old = ~0ull;
+      if (in_xcd >> 52 == (args.tiles - blockIdx.x % NUM_XCD + NUM_XCD - 1) / NUM_XCD) {  // its last
+        *own_xcd = 0;
+        old = atomicAdd(args.state, TICKET | (in_xcd & (TICKET - 1)));
+        total = in_xcd & FOUND;
+        lates = (uint32_t)(in_xcd >> 40) & 0xFFFu;
+      }
+    } else {
+      old = atomicAdd(args.state, add);
+    }
+  }
+  auto close = [&]() {  // (thread 0) the workgroup's place in the result, and whether it is the last of all
+    const unsigned long long all = COUNT && args.tiles > ONCE_STEPS ? (unsigned long long)NUM_XCD : args.tiles;
+    const bool last = old != ~0ull && (old >> 52) + 1 == all;
+    sums[8] = old & FOUND;
+    sums[9] = last ? 1 + ((old >> 40) & 0xFFFu) + lates : 0;  // 1 + late workgroups
+    if (last) {
+      *(COUNT ? a.total : a.n_pairs) = (old & FOUND) + total;
+      *args.state = 0;
+    }
+  };
+  if constexpr (COUNT) {
+    if (tid == 0) close();
+    __syncthreads();
+  } else {
+    // The hits are sorted out while the atomic is under way, unless there are more than fit the LDS.
+    uint32_t* stg = reinterpret_cast<uint32_t*>(lds + L::TAIL + wave * (SMALL_STG_CAP * 12));
+    uint32_t fill = 0;            // entries staged, wave-uniform
+    unsigned long long base = 0;  // where they go
+    bool many = false;
+    for (int w = 0; w < L::WAVES; ++w) many |= sums[w] > SMALL_STG_CAP;
+    auto place = [&]() {
+      if (tid == 0) close();
+      __syncthreads();
+      base = sums[8];
+      for (int w = 0; w < wave; ++w) base += sums[w];
+    };
+    auto store_staged = [&]() {
+      for (uint32_t e = lane; e < fill; e += 64) {
+        const unsigned long long idx = base + e;
+        if (idx < a.capacity) {
+          reinterpret_cast<uint2*>(a.pairs)[idx] = make_uint2(stg[3 * e], stg[3 * e + 1]);
+          if (a.dist2) a.dist2[idx] = __uint_as_float(stg[3 * e + 2]);
+        }
+      }
+      base += fill;
+      fill = 0;
+    };
+    auto append = [&](unsigned long long mask, bool pass, uint32_t i, uint32_t j, uint32_t d2_bits) {
+      const uint32_t more = __popcll(mask);
+      if (fill + more > SMALL_STG_CAP) store_staged();
+      const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+      if (pass) {
+        const uint32_t e = fill + rank;
+        stg[3 * e] = i;
+        stg[3 * e + 1] = j;
+        stg[3 * e + 2] = d2_bits;
+      }
+      fill += more;
+    };
+    if (many) place();
+    if (own_pairs) {
+      const uint32_t i = i_tile + tid;
+      append(__ballot(i < nnA), i < nnA, i, i, 0u);
+    }
+#pragma unroll
+    for (int R = 0; R < NC; ++R) {
+      uint32_t h = hit[R];
+      // every round takes one hit of each lane that has any left
+      for (unsigned long long mask = __ballot(h != 0); mask; mask = __ballot(h != 0)) {
+        const uint32_t r = (uint32_t)__builtin_ctz(h | 0x10000u);
+        append(mask, h != 0, i_tile + wm + 4 * g + 2 * (r & 8u) + (r & 3u), j_tile + wn + 32 * R + r16 + 4 * (r & 4u),
+               __float_as_uint(fmaxf(-2.f * pick(v[R], r), 0.f)));
+        h &= h - 1;
+      }
+    }
+    if (!many) place();
+    store_staged();
+  }
+  if (sums[9]) {
+    for (uint32_t q = tid; q < args.slots * NUM_XCD; q += L::THREADS) args.slot[q % NUM_XCD * ONCE_SLOTS + q / NUM_XCD] = 0;
+    if (COUNT && sums[9] > 1)
+      for (uint32_t q = tid; q < nnA + (a.self ? 0u : nnB); q += L::THREADS) {
+        const uint32_t c = __hip_atomic_exchange(args.late_counts + q, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t* to = q < nnA ? a.counts + q : (a.counts_b ? a.counts_b + (q - nnA) : nullptr);
+        if (c && to) atomicAdd(to, c);
+      }
+  }
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------------------------------
@@ -2443,6 +2800,7 @@ struct ejoin_ctx {
   int64_t s_cap;     // points ws.s holds
   int64_t xp_bytes;  // bytes of ws.Xp
   bool ws_dirty;     // a call on ws did not reach its join kernel: the status block may hold leftovers
+  unsigned char* once;            // device: k_join_once's state, slots and late counts, all zero between calls
   unsigned char* static_scratch;  // device address of `scratch` on this context's device
   uint32_t* last_status;          // status block of the last join or dense-tile call, and the stream it ran on
   hipStream_t last_stream;
@@ -2773,7 +3131,7 @@ int launch_join(ejoin_ctx* ctx, const Workspace& w, bool own, const Operand& A, 
   return EJOIN_OK;
 }
 
-// Which tile k_join_small should work a problem in, or 0: k_join.  In tiles of 64 up to 300 of them (1,000 points, 136 tiles:
+// Which tile k_join_small should work a problem in that k_join_once does not take (or a prepared or split set), or 0: k_join.  In tiles of 64 up to 300 of them (1,000 points, 136 tiles:
 // 13.0 us a call against 14.0 in tiles of 128 and 23.7 by k_join; 2,000 points, 528 tiles: 15.5, 14.2, 21.8).  In tiles of 128
 // where the CUs, which hold 768 of them, need no more rounds for them than k_join for its 256 at a time (at d = 64, 384 and
 // 960: one round 10 + 4.5, 7 + 10.5, 0 + 24 us, further ones 4.5, 10.5, 24; k_join 10.5 + 5, 11 + 11, 11 + 22), or one more
@@ -2864,6 +3222,56 @@ int run_small(ejoin_ctx* ctx, const Workspace& w, int tile, PrepSet A, PrepSet B
   return EJOIN_OK;
 }
 
+// Which tile k_join_once works a join of FP16 rows in, or 0: its tiles do not all fit the CUs at once.
+// Counts: tiles of 64 while they do (1,984 points, d = 64, 384 and 960: 8.3, 10.1 and 14.0 us, in tiles of 128 9.1, 12.4 and 18.7; 2,400
+// points 9.0, 11.4 and 17.5 against 9.3, 12.9 and 20.0; 3,000 x 1,000, d = 128, 10.4 against 10.6).  Lists pay some 13 ns a tile for their place in the result, tiles of 128 1.6 us and 0.19 us a
+// k-block for their longer chain (tiles of 64 and of 128: 1,000 x 64 8.0 and 9.2 us; 1,984 points, d = 64, 384 and 960, 12.7, 14.6 and 18.4,
+// 9.9, 13.4 and 20.0); with three of them on a CU tiles of 64 lose more (2,400 x 960 23.4 against 21.2).
+int once_edge(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nkb, bool count) {
+#if defined(EJOIN_ONLY_K_JOIN) || defined(EJOIN_ONLY_K_JOIN_STRIP)
+  return 0;
+#endif
+  auto tiles = [&](int64_t t) {
+    const int64_t a = (nA + t - 1) / t, b = (nB + t - 1) / t;
+    return self ? a * (a + 1) / 2 : a * b;
+  };
+  const int64_t held = (int64_t)ctx->num_cu * ONCE_GROUPS_PER_CU, t64 = tiles(64), t128 = tiles(128);
+  if (held >= 4096 || nA + (self ? 0 : nB) > ONCE_COUNTS || (nA + 63) / 64 + (self ? 0 : (nB + 63) / 64) > ONCE_SLOTS) return 0;
+  if (count ? t64 <= held : t64 <= 2 * ctx->num_cu && t64 - t128 <= 123 + 15 * nkb) return 64;
+  return t128 <= held ? 128 : 0;
+}
+// A join by k_join_once.  XB == nullptr: self-join of XA.
+template <bool COUNT>
+int run_once(ejoin_ctx* ctx, const Workspace& w, int tile, const uint16_t* XA, int64_t nA, int64_t ldA, const uint16_t* XB, int64_t nB, int64_t ldB,
+             int nkb, float eps, const Results& r, hipStream_t st) {
+  const bool self = XB == nullptr;
+  for (int e = 0; ctx->profiling && e < 3; ++e) EJ_TRY(hipEventRecord(ctx->ev[e], st));
+  ctx->last_status = w.status;
+  ctx->last_stream = st;
+  OnceArgs a;
+  a.j = join_args(w, Operand{nullptr, nA, 0}, Operand{nullptr, self ? nA : nB, 0}, self, nkb, eps, r, tile);
+  a.XA = XA;
+  a.XB = self ? XA : XB;
+  a.ldA = ldA;
+  a.ldB = self ? ldA : ldB;
+  a.sA = w.s;
+  a.sB = w.s + pad_rows(nA);
+  a.tiles = self ? a.j.ntilesA * (a.j.ntilesA + 1) / 2 : a.j.ntilesA * a.j.ntilesB;
+  a.slots_a = (uint32_t)((nA + 63) / 64);
+  a.slots = a.slots_a + (self ? 0u : (uint32_t)((nB + 63) / 64));
+  a.state = reinterpret_cast<unsigned long long*>(ctx->once);
+  a.slot = reinterpret_cast<uint32_t*>(ctx->once + ONCE_STATE_BYTES);
+  a.late_counts = a.slot + NUM_XCD * ONCE_SLOTS;
+  hipLaunchKernelGGL((tile == 64 ? k_join_once<COUNT, 64> : k_join_once<COUNT, 128>), dim3(a.tiles), dim3(tile == 64 ? Once<64>::THREADS : Once<128>::THREADS),
+                     (tile == 64 ? Once<64>::LDS : Once<128>::LDS), st, a);
+  EJ_TRY(hipGetLastError());
+  if (ctx->profiling) {
+    EJ_TRY(hipEventRecord(ctx->ev[3], st));
+    ctx->ev_valid = 1;
+  }
+  return EJOIN_OK;
+}
+
 // Norms, packed copies and augmentation operands of the sets of a k_join call, and its results cleared.
 int prep_and_aux(ejoin_ctx* ctx, const Workspace& w, PrepSet A, PrepSet B, const uint32_t* set_max, int nkb, unsigned long long* counter, const Results& r,
                  hipStream_t st) {
@@ -2893,8 +3301,11 @@ int run_join(ejoin_ctx* ctx, const Workspace& w, bool own, const uint16_t* XA, i
     return EJOIN_OK;
   };
   // (one batch is the plain join: every self-join of up to 4,096 points, which one row of super-blocks covers)
-  if (const int tile = batch_rows && nbatches > 1 ? 0 : small_tile(ctx, nA, self ? nA : nB, self, nkb)) {
-    EJ_RC(run_small<COUNT>(ctx, w, tile, SA, SB, nullptr, nkb, eps, r, st));
+  const bool plain = !batch_rows || nbatches == 1;
+  const int once = plain ? once_edge(ctx, nA, self ? nA : nB, self, nkb, COUNT) : 0;
+  const int small = plain && !once ? small_tile(ctx, nA, self ? nA : nB, self, nkb) : 0;
+  if (once || small) {
+    EJ_RC(once ? run_once<COUNT>(ctx, w, once, XA, nA, ldA, XB, nB, ldB, nkb, eps, r, st) : run_small<COUNT>(ctx, w, small, SA, SB, nullptr, nkb, eps, r, st));
     return batch_rows ? batch_done(0) : EJOIN_OK;
   }
   EJ_RC(begin_call(ctx, w, own, st));
@@ -3020,6 +3431,9 @@ int ejoin_create(ejoin_ctx** out, int device) {
   }
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&ctx->ws.status), 256);
   if (e == hipSuccess) e = hipMemset(ctx->ws.status, 0, 256);
+  constexpr size_t ONCE_BYTES = ONCE_STATE_BYTES + (NUM_XCD * ONCE_SLOTS + ONCE_COUNTS) * sizeof(uint32_t);
+  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->once), ONCE_BYTES);
+  if (e == hipSuccess) e = hipMemset(ctx->once, 0, ONCE_BYTES);
   // this device's copy of the static scratch (the device is current here)
   if (e == hipSuccess) e = hipGetSymbolAddress(reinterpret_cast<void**>(&ctx->static_scratch), HIP_SYMBOL(scratch));
   for (int i = 0; i < 4 && e == hipSuccess; ++i) e = hipEventCreate(&ctx->ev[i]);
@@ -3048,6 +3462,7 @@ int ejoin_destroy(ejoin_ctx* ctx) {
   if (!ctx) return EJOIN_EINVAL;
   DeviceGuard guard(ctx->device);
   if (ctx->ws.status) (void)hipFree(ctx->ws.status);
+  if (ctx->once) (void)hipFree(ctx->once);
   if (ctx->ws.s) (void)hipFree(ctx->ws.s);
   if (ctx->ws.Xp) (void)hipFree(ctx->ws.Xp);
   for (int i = 0; i < 4; ++i)
@@ -3355,7 +3770,8 @@ int ejoin_last_kernel_ms(ejoin_ctx* ctx, float* prep_ms, float* join_ms) {
 int ejoin_join_work(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int32_t split, int32_t* edge, int32_t* steps, int64_t* tiles) {
   if (!ctx || !edge || !steps || !tiles || np < 1 || nq < 0 || d < 1 || d > 65536 || (split && nq)) return EJOIN_EINVAL;
   *steps = split ? 3 * ((d + KSLICE - 1) / KSLICE) : k_blocks(d);
-  const int small = small_tile(ctx, np, nq ? nq : np, nq == 0, *steps);
+  const int once = split ? 0 : once_edge(ctx, np, nq ? nq : np, nq == 0, *steps, false);
+  const int small = once ? once : small_tile(ctx, np, nq ? nq : np, nq == 0, *steps);
   *edge = small ? small : TILE;
   const int64_t a = (np + *edge - 1) / *edge, b = (nq + *edge - 1) / *edge;
   *tiles = nq ? a * b : a * (a + 1) / 2;

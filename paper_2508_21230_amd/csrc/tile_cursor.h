@@ -141,6 +141,29 @@ struct TileCursor {
   }
 };
 
+// The one tile of a workgroup of k_join_once: first the tiles on the diagonal (two sets: of the first column, then of the first row),
+// whose workgroups others wait for, then the rest, column by column (row by row).
+EJ_HD inline void once_tile(uint32_t block, uint32_t self_join, uint32_t nt_a, uint32_t nt_b, uint32_t& I, uint32_t& J) {
+  if (block < nt_a) {
+    I = block;
+    J = self_join ? block : 0;
+    return;
+  }
+  uint32_t r = block - nt_a;
+  if (self_join) {
+    J = 1;
+    while (r >= J) r -= J++;  // column J has rows 0 .. J - 1 above the diagonal
+    I = r;
+  } else if (r < nt_b - 1) {
+    I = 0;
+    J = r + 1;
+  } else {
+    r -= nt_b - 1;
+    I = 1 + r / (nt_b - 1);
+    J = 1 + r % (nt_b - 1);
+  }
+}
+
 // Work distribution of k_join_strip, whose workgroups hold a panel of 512 rows in registers and stream columns past it, 64 at a
 // time (a stage): what counts is that a workgroup changes its rows as seldom as possible, that the workgroups of an XCD stream the
 // same columns at the same time (through its L2), and that all have the same number of stages.

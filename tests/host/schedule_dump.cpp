@@ -53,6 +53,11 @@ int64_t ejoin_test_strips(uint32_t nblocks, uint32_t self_join, uint32_t stages,
   return m;
 }
 
+// The tiles of the one-launch join, two numbers each.
+void ejoin_test_once(uint32_t blocks, uint32_t self_join, uint32_t nt_a, uint32_t nt_b, uint32_t* out) {
+  for (uint32_t b = 0; b < blocks; ++b) once_tile(b, self_join, nt_a, nt_b, out[2 * b], out[2 * b + 1]);
+}
+
 // Which joins go to the kernel of few coordinates: 0, or 1, or 3: with the second of the two sets in its rows.
 int32_t ejoin_test_strip_plan(int32_t num_cu, int64_t n_a, int64_t n_b, int32_t self_join, int32_t nkb, int32_t count) {
   const StripPlan p = strip_plan(num_cu, n_a, n_b, self_join != 0, nkb, count != 0);

@@ -1,0 +1,134 @@
+"""The join of the smallest problems, in one launch, against the general kernel: pairs, squared distances bit for bit, counts and status;
+each by a workgroup that waits for the others' norms, and by one that does not and works the largest norm out by itself."""
+import pytest
+import torch
+
+import paper_2508_21230_amd as pkg
+from paper_2508_21230_amd import build
+from tests import parity
+from tests.test_gpu_strip import epsilon, rows, same_pairs, sorted_pairs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def general():
+    e = parity.general_context()
+    yield e
+    e.close()
+
+
+@pytest.fixture(scope="module", params=["waits", "late"])
+def once(request):
+    e = pkg.EJoin(0) if request.param == "waits" else parity.variant_context(build.LATE_LIB)
+    yield e
+    e.close()
+
+
+# one tile; edges of tiles; the last list in tiles of 64 and the first of 128 (d = 96: 1,216 and 1,217 points); the last counts in tiles of 64
+# (2,432) and the first of 128; the last problem of all (4,864), and one of the kernel after it
+@pytest.mark.parametrize("d", [1, 64, 96, 130, 960])
+@pytest.mark.parametrize("n,share", [(1, 0.5), (63, 0.3), (65, 0.3), (129, 1.0), (1216, 0.01), (1217, 0.01), (2432, 0.003), (2433, 0.003), (4864, 0.0005), (4865, 0.0005)])
+def test_self_join(general, once, n, d, share):
+    print(f"once self n={n} d={d} share={share}", flush=True)
+    X = rows(n, d, seed=n + d)
+    eps = epsilon(X, d, share)
+    cap = n + int(general.selfjoin_count(X, eps, d=d)[1])
+    for _ in range(2):  # (the first call leaves the context as it found it)
+        same_pairs(general.selfjoin_pairs(X, eps, cap, d=d), once.selfjoin_pairs(X, eps, cap, d=d))
+        for u, v in zip(general.selfjoin_count(X, eps, d=d), once.selfjoin_count(X, eps, d=d)):
+            assert torch.equal(u, v)
+        assert once.status() == 0
+
+
+@pytest.mark.parametrize("d", [40, 200])
+@pytest.mark.parametrize("n,nq", [(1, 1), (64, 1), (65, 63), (1000, 10), (10, 1000), (4000, 500), (20000, 60), (700, 7000), (3000, 1900), (300, 90000)])
+def test_two_sets(general, once, n, nq, d):
+    print(f"once two sets n={n} nq={nq} d={d}", flush=True)
+    P, Q = rows(n, d, seed=d), rows(nq, d, seed=d + 1)
+    Q[:min(n, nq) // 3] = P[:min(n, nq) // 3]
+    eps = epsilon(Q, d, 0.01)
+    cap = int(general.join_count(P, Q, eps, d=d)[2])
+    same_pairs(general.join_pairs(P, Q, eps, cap, d=d), once.join_pairs(P, Q, eps, cap, d=d))
+    for wanted in (True, False):
+        for u, v in zip(general.join_count(P, Q, eps, d=d, want_counts_q=wanted), once.join_count(P, Q, eps, d=d, want_counts_q=wanted)):
+            assert u is v is None or torch.equal(u, v)
+
+
+@pytest.mark.parametrize("n", [1500, 3000])
+@pytest.mark.parametrize("value,row", [(float("nan"), 0), (float("inf"), 1499), (60000.0, 700)])
+def test_data_out_of_range_reports_nothing(once, n, value, row):
+    X = rows(n, 96, seed=1)
+    X[row, :90] = value
+    pairs, _, found = once.selfjoin_pairs(X, 100.0, 1000, d=96)
+    assert once.status() == (1 if value == 60000.0 else 2) and int(found) == 0
+    counts, total = once.selfjoin_count(X, 100.0, d=96)
+    assert once.status() != 0 and int(total) == 0 and not counts.any()
+    X[row] = 0
+    assert int(once.selfjoin_count(X, 100.0, d=96)[1]) == n * (n - 1) // 2 and once.status() == 0  # (zero, and all within epsilon)
+
+
+def test_norms_of_very_different_sizes(general, once):
+    """The scale of the norm terms is that of all points, not of a tile's."""
+    X = rows(1400, 96, seed=2)
+    X[:600] *= 0.004
+    X[9] *= 250
+    for eps in (0.01, 0.05, 4.0):
+        cap = 1400 + int(general.selfjoin_count(X, eps, d=96)[1])
+        same_pairs(general.selfjoin_pairs(X, eps, cap, d=96), once.selfjoin_pairs(X, eps, cap, d=96))
+
+
+@pytest.mark.parametrize("n", [300, 3000])
+def test_a_list_that_is_cut_off(once, n):
+    X = rows(n, 64, seed=3)
+    whole, d2 = sorted_pairs(once.selfjoin_pairs(X, 100.0, n * (n + 1) // 2, d=64))
+    assert whole.numel() == n * (n + 1) // 2  # (more than a wavefront stages in the LDS)
+    pairs, dist2, found = once.selfjoin_pairs(X, 100.0, 1000, d=64)
+    keys, order = torch.sort(pairs.reshape(-1).view(torch.int64))
+    at = torch.searchsorted(whole, keys)
+    assert int(found) == whole.numel() and torch.equal(whole[at], keys) and torch.equal(d2[at], dist2[order]) and bool((keys[1:] != keys[:-1]).all())
+
+
+def test_captured_and_replayed_on_new_data(once):
+    X = rows(2000, 96, seed=4)
+    other = [rows(2000, 96, seed=s) * f for s, f in ((5, 1.0), (6, 3.0), (7, 0.2))]
+    side = torch.cuda.Stream()
+    counts, total = torch.empty(2000, dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int64, device="cuda")
+    call = lambda: once.selfjoin_count(X, 2.5, d=96, counts=counts, total=total)
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for Y in other * 2:
+        X.copy_(Y)
+        g.replay()
+        torch.cuda.synchronize()
+        got = counts.clone(), total.clone()
+        call()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], counts) and torch.equal(got[1], total)
+
+
+def test_several_contexts_on_streams_of_their_own():
+    """Their workgroups share the CUs: some may be started only when others' have ended."""
+    X = [rows(4800, 64, seed=20 + k) for k in range(4)]
+    want = [general_count(x) for x in X]
+    each = [(pkg.EJoin(0), torch.cuda.Stream()) for _ in X]
+    torch.cuda.synchronize()
+    got = [[] for _ in X]
+    for _ in range(20):
+        for k, (e, stream) in enumerate(each):
+            with torch.cuda.stream(stream):
+                got[k].append(e.selfjoin_count(X[k], 1.2, d=64))
+    torch.cuda.synchronize()
+    for k in range(4):
+        assert all(torch.equal(c, want[k][0]) and torch.equal(t, want[k][1]) for c, t in got[k])
+
+
+def general_count(X):
+    e = parity.general_context()
+    counts = e.selfjoin_count(X, 1.2, d=64)
+    torch.cuda.synchronize()
+    return counts

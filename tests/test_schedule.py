@@ -46,6 +46,8 @@ def build_schedule(tmp_path_factory, kind):
         return buf[:m].astype(np.int64)
     lib.ejoin_test_strip_plan.restype = ctypes.c_int32
     lib.ejoin_test_strip_plan.argtypes = [ctypes.c_int32, ctypes.c_int64, ctypes.c_int64] + [ctypes.c_int32] * 3
+    lib.ejoin_test_once.argtypes = [ctypes.c_uint32] * 4 + [ctypes.c_void_p]
+    run.once = lib.ejoin_test_once
     run.kind = kind
     run.plan = lib.ejoin_test_strip_plan
     run.rows = run_rows
@@ -208,3 +210,14 @@ def test_self_counts_with_the_filter_in_the_open_go_there_from_large_sets_on(pla
     rule = [plan(256, n, n, 1, nkb, 1) for n in range(20000, 400000, 997)]
     assert not any(rule[:80]) and all(rule[160:])  # up to 99,000 points, from 179,000 on
     assert all(plan(256, n, n, 1, nkb, 0) for n in range(60000, 400000, 997))  # lists
+
+
+@pytest.mark.parametrize("self_join,nt_a,nt_b", [(True, n, n) for n in (1, 2, 5, 38)] + [(False, a, b) for a, b in ((1, 1), (1, 9), (9, 1), (2, 2), (7, 30), (30, 7))])
+def test_the_one_launch_join_has_every_tile_once_and_those_that_others_wait_for_first(sched, self_join, nt_a, nt_b):
+    tiles = nt_a * (nt_a + 1) // 2 if self_join else nt_a * nt_b
+    out = np.zeros((tiles, 2), dtype=np.uint32)
+    sched.once(tiles, int(self_join), nt_a, nt_b, out.ctypes.data)
+    want = {(i, j) for i in range(nt_a) for j in range(i if self_join else 0, nt_b)}
+    assert {tuple(t) for t in out.tolist()} == want
+    first = nt_a if self_join else nt_a + nt_b - 1
+    assert all(i == j if self_join else i == 0 or j == 0 for i, j in out[:first].tolist())
