@@ -2451,6 +2451,22 @@ struct OnceArgs {
 constexpr int ONCE_SLOTS = 2048, ONCE_COUNTS = 1 << 17;  // capacities
 constexpr uint32_t ONCE_STEPS = 256;                     // tiles from which on counts take their tickets XCD by XCD
 constexpr size_t ONCE_STATE_BYTES = 16 * 8 * (1 + EJ_NUM_XCD);
+constexpr unsigned long long ONCE_FOUND = (1ull << 40) - 1, ONCE_TICKET = 1ull << 52;
+// A workgroup's ticket, with what it adds to the fields below, XCD by XCD: an eighth of the atomics on each of the XCDs' words, then
+// one each on [0].  (One thread.)  True for the last workgroup of all, whose `all` are the fields' sums; the state is zero again.
+__device__ __forceinline__ bool close_by_xcd(unsigned long long* state, uint32_t workgroups, unsigned long long add, unsigned long long& all) {
+  const uint32_t xcd = blockIdx.x % EJ_NUM_XCD, xcds = min(workgroups, EJ_NUM_XCD);
+  unsigned long long* own = state + 16 * (1 + xcd);
+  add |= ONCE_TICKET;
+  const unsigned long long in_xcd = atomicAdd(own, add) + add;
+  if (in_xcd >> 52 != (workgroups - xcd + xcds - 1) / xcds) return false;
+  *own = 0;
+  const unsigned long long sum = ONCE_TICKET | (in_xcd & (ONCE_TICKET - 1));
+  all = atomicAdd(state, sum) + sum;
+  if (all >> 52 != xcds) return false;
+  *state = 0;
+  return true;
+}
 #ifndef EJOIN_ONCE_SPINS
 #define EJOIN_ONCE_SPINS 2048  // (a build for the tests waits for nothing)
 #endif
@@ -2648,7 +2664,6 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
 
   // ---- results.  One atomic for the workgroup, with its ticket.
   unsigned long long* sums = reinterpret_cast<unsigned long long*>(lds + L::SUMS);
-  constexpr unsigned long long FOUND = (1ull << 40) - 1, TICKET = 1ull << 52;
   const bool own_pairs = diag && !COUNT && wave < TS / 64 && ns.st == ST_OK;  // (i, i) belongs to the result by definition
   uint32_t found = own_pairs && i_tile + tid < nnA ? 1u : 0u;
 #pragma unroll
@@ -2672,34 +2687,22 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
   } else {
     __syncthreads();
   }
-  unsigned long long old = 0, total = 0;  // (of thread 0)
-  uint32_t lates = late;
+  unsigned long long all = 0, total = 0;  // (of thread 0) the state with this workgroup's ticket; its pairs
+  bool last = false;
   if (tid == 0) {
     for (int w = 0; w < L::WAVES; ++w) total += sums[w];
-    const unsigned long long add = TICKET | ((unsigned long long)late << 40) | total;
-    if (COUNT && args.tiles > ONCE_STEPS) {
-      unsigned long long* own_xcd = args.state + 16 * (1 + blockIdx.x % NUM_XCD);
-      const unsigned long long in_xcd = atomicAdd(own_xcd, add) + add;
-      old = ~0ull;
-      if (in_xcd >> 52 == (args.tiles - blockIdx.x % NUM_XCD + NUM_XCD - 1) / NUM_XCD) {  // its last
-        *own_xcd = 0;
-        old = atomicAdd(args.state, TICKET | (in_xcd & (TICKET - 1)));
-        total = in_xcd & FOUND;
-        lates = (uint32_t)(in_xcd >> 40) & 0xFFFu;
-      }
-    } else {
-      old = atomicAdd(args.state, add);
-    }
+    const unsigned long long add = ONCE_TICKET | ((unsigned long long)late << 40) | total;
+    if (COUNT && args.tiles > ONCE_STEPS) last = close_by_xcd(args.state, args.tiles, add, all);
+    else all = atomicAdd(args.state, add) + add;
   }
   auto close = [&]() {  // (thread 0) the workgroup's place in the result, and whether it is the last of all
-    const unsigned long long all = COUNT && args.tiles > ONCE_STEPS ? (unsigned long long)NUM_XCD : args.tiles;
-    const bool last = old != ~0ull && (old >> 52) + 1 == all;
-    sums[8] = old & FOUND;
-    sums[9] = last ? 1 + ((old >> 40) & 0xFFFu) + lates : 0;  // 1 + late workgroups
-    if (last) {
-      *(COUNT ? a.total : a.n_pairs) = (old & FOUND) + total;
-      *args.state = 0;
+    if (!(COUNT && args.tiles > ONCE_STEPS)) {
+      last = all >> 52 == args.tiles;
+      if (last) *args.state = 0;
     }
+    sums[8] = (all & ONCE_FOUND) - total;
+    sums[9] = last ? 1 + ((all >> 40) & 0xFFFu) : 0;  // 1 + late workgroups
+    if (last) *(COUNT ? a.total : a.n_pairs) = all & ONCE_FOUND;
   };
   if constexpr (COUNT) {
     if (tid == 0) close();
@@ -2768,6 +2771,278 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
         if (c && to) atomicAdd(to, c);
       }
   }
+}
+
+// ------------------------------------------------------------------------------------------
+// The join of a prepared set with few query points
+// ------------------------------------------------------------------------------------------
+// A batch of up to 16 RF query points against a prepared set, in one launch.  Bound by reading the set's packed copy and, where that is
+// little, by the launch.  The query points are the rows of the MFMAs, in the LDS of every workgroup; a wavefront streams 32 points
+// with all their k-blocks through its registers at a time, as MFMA operands the way they lie in the packed copy, a chunk of
+// few_chunk k-blocks ahead, with no barrier and no copy to the LDS.  Every workgroup works out the norms of the query points, the largest with that of the
+// set, and the points' part of the augmentation step from their norms: nothing is waited for, and the set's augmentation block is neither
+// read nor written.  A point's count is complete in its wavefront; those of the query points go through the context's counters, which
+// the last workgroup copies (see k_join_once).
+// A call (counts) in us, by k_prep, k_aux and k_join or k_join_strip, or by k_prep and k_join_small, and now: 8, 60, 120 and 250 queries against 100,000
+// points of 128 coordinates 28.0, 29.7, 30.9 and 26.9, now 10.0, 11.6, 14.6 and 19.1 (floor 5.3); 60 against 20,000 x 32 15.5, now 10.0; 60 against
+// 400,000 x 384 104.9, now 60.5 (floor 63); 8 against 400,000 x 960 194, now 133; 60 201, now 189.
+// Up to 64 query points two workgroups a CU and chunks of two k-blocks (60 against 400,000 x 384: one workgroup and chunks of four 78, of eight 77); more take
+// the registers of one.
+// The arithmetic is k_join_strip's with the sets exchanged, step by step, and the results its bits.
+struct FewArgs {
+  const uint4* Xp;
+  const float* s;
+  const uint32_t* set_max;
+  int64_t n;
+  int nkb;
+  const uint16_t* Q;
+  int64_t nq, ldq;
+  float thr;
+  uint32_t* status;
+  uint32_t* pairs;
+  float* dist2;
+  unsigned long long capacity;
+  unsigned long long* n_pairs;
+  uint32_t* counts_p;
+  uint32_t* counts_q;  // may be null
+  unsigned long long* total;
+  // of the context, all zero between calls (see OnceArgs)
+  unsigned long long* state;
+  uint32_t* counters;
+};
+constexpr int FEW_LDS = 159 * 1024;  // (a little is the compiler's)
+template <int RF>
+constexpr int few_chunk() { return RF == 8 ? 4 : 2; }
+constexpr int few_groups_per_cu(int rf, int lds_bytes) { return rf <= 4 && lds_bytes <= 79 * 1024 ? 2 : 1; }
+constexpr int FEW_STG = 128, FEW_WAVES = 8;
+// the query points, their norms, part of the augmentation step and counters, the constants of that step, staged results
+template <bool COUNT>
+constexpr int few_lds_bytes(int rows, int nkb) { return rows * (nkb * 64 + 4 + 16 + 4) + 64 + 64 + (COUNT ? 0 : FEW_WAVES * FEW_STG * 12); }
+template <bool COUNT, int RF>
+__global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(const FewArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char lds[];
+  constexpr int ROWS = 16 * RF, NR = RF / 2, CHUNK = few_chunk<RF>();
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nkb = a.nkb;
+  const uint32_t n = (uint32_t)a.n, nq = (uint32_t)a.nq;
+  char* const aug = lds + ROWS * nkb * 64;
+  char* const constants = aug + ROWS * 16;
+  float* const norms = reinterpret_cast<float*>(constants + 64);
+  uint32_t* const row_counts = reinterpret_cast<uint32_t*>(norms + ROWS);
+  unsigned long long* const sums = reinterpret_cast<unsigned long long*>(row_counts + ROWS);
+  uint32_t* const stg = reinterpret_cast<uint32_t*>(sums + 8) + wave * FEW_STG * 3;
+
+  // ---- the points: a workgroup a panel of 256, each of its wavefronts 32 of them, and so on through the panels
+  const uint32_t panels = (n + TILE - 1) / TILE, chunks = (uint32_t)(nkb + CHUNK - 1) / CHUNK;
+  const int64_t panel_stride = (int64_t)(nkb + 1) * PANEL_BYTES;
+  const char* const mine = reinterpret_cast<const char*>(a.Xp) + wave * 2048;
+  const uint32_t at0 = fragment_offset(lane, 0), at1 = fragment_offset(lane, 1);
+  half8 buf[2][CHUNK][2];
+  float point_norm[2][2];
+  auto load = [&](auto b_c, uint32_t panel, uint32_t chunk) __attribute__((always_inline)) {
+    constexpr int B = decltype(b_c)::value;
+    if (panel >= panels) return;
+    const char* p = mine + panel * panel_stride + (int64_t)chunk * (CHUNK * PANEL_BYTES);
+#pragma unroll
+    for (int k = 0; k < CHUNK; ++k)
+      if ((int)chunk * CHUNK + k < nkb) {
+        buf[B][k][0] = *reinterpret_cast<const half8*>(p + k * PANEL_BYTES + at0);
+        buf[B][k][1] = *reinterpret_cast<const half8*>(p + k * PANEL_BYTES + at1);
+      }
+    if (chunk + 1 == chunks) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) point_norm[B][h] = a.s[min(panel * TILE + wave * 32 + 16 * h + r16, n - 1)];
+    }
+  };
+  uint32_t panel = blockIdx.x, chunk = 0;  // what is computed next
+  load(std::integral_constant<int, 0>{}, panel, chunk);
+
+  // ---- the query points, as operands: k-block k of rows 16 f .. 16 f + 15 at (f nkb + k) KB.  (Rows past the last are that one again.)
+  for (int q = wave; q < RF * nkb; q += FEW_WAVES) {
+    const int f = q / nkb, k = q - f * nkb;
+    const uint32_t row = min((uint32_t)(16 * f + r16), nq - 1);
+    *reinterpret_cast<half8*>(lds + q * 1024 + lane * 16) = *reinterpret_cast<const half8*>(a.Q + row * a.ldq + k * KSLICE + 8 * g);
+  }
+  if (tid < ROWS) row_counts[tid] = 0;
+  __syncthreads();
+  for (int f = wave; f < RF; f += FEW_WAVES) {
+    float4v sq = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < nkb; ++k) {
+      const half8 x = *reinterpret_cast<const half8*>(lds + (f * nkb + k) * 1024 + lane * 16);
+      sq = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, x, sq, 0, 0, 0);
+    }
+    store_diagonal(sq, 16 * f, ROWS, norms);
+  }
+  __syncthreads();
+  const NormScale ns = norm_scale(max_of_group(max(*a.set_max, (uint32_t)tid < nq ? __float_as_uint(norms[tid]) : 0u)));
+  if (blockIdx.x == 0 && tid == 0) a.status[0] = ns.st;
+  if (tid < ROWS) {
+    const uint32_t x = (uint32_t)((tid & ~31) + aug_row_point(tid & 31)), y = x + 4;
+    uint2 p = make_uint2(P1_OUT_OF_RANGE, 0u), q = p;
+    if (x < nq) p = norm_pieces(norms[x], ns.m);
+    if (y < nq) q = norm_pieces(norms[y], ns.m);
+    *reinterpret_cast<uint4*>(aug + tid * 16) = make_uint4(p.x, p.y, q.x, q.y);
+  }
+  if (tid < 4) {  // the constant chunks of the augmentation step (2 and 3)
+    const uint32_t c = fp16_bits(ns.c), c0 = c | (c << 16);
+    *reinterpret_cast<uint2*>(constants + tid * 8) = tid == 0 || tid == 3 ? make_uint2(c0, c) : make_uint2(0u, 0u);
+  }
+  __syncthreads();
+  // operands of that step, the halves exchanged as in k_join_strip with the sets exchanged
+  const char* const row_operand = lane < 32 ? constants + 16 * ((lane >> 3) & 1) : aug + 16 * (lane & 31);
+  const int row_step = lane < 32 ? 0 : 512;
+  const uint32_t edge_mask = keep_mask(4 * g, 0, nq % 32, 0xFFFFFFFFu, false);  // registers of the last region whose query point exists
+  const uint4 column_constant = *reinterpret_cast<const uint4*>(constants + 16 * ((lane >> 4) & 1));
+
+  uint32_t fill = 0;             // (pairs) staged, uniform
+  unsigned long long found = 0;  // (counts) of this lane
+  const uint32_t thr_bits = __float_as_uint(a.thr) | 0x80000000u;  // (x >= thr on the bit patterns, see k_join)
+  auto store_staged = [&](unsigned long long base) {
+    for (uint32_t e = lane; e < fill; e += 64) {
+      const unsigned long long idx = base + e;
+      if (idx < a.capacity) {
+        reinterpret_cast<uint2*>(a.pairs)[idx] = make_uint2(stg[3 * e], stg[3 * e + 1]);
+        if (a.dist2) a.dist2[idx] = __uint_as_float(stg[3 * e + 2]);
+      }
+    }
+    fill = 0;
+  };
+  auto append = [&](unsigned long long mask, bool pass, uint32_t i, uint32_t j, uint32_t d2_bits) {
+    const uint32_t more = __popcll(mask);
+    if (fill + more > FEW_STG) {
+      unsigned long long base = 0;
+      if (lane == 0) base = atomicAdd(a.state, (unsigned long long)fill) & ONCE_FOUND;
+      const uint32_t blo = __builtin_amdgcn_readfirstlane((uint32_t)base), bhi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
+      store_staged(((unsigned long long)bhi << 32) | blo);
+    }
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    if (pass) {
+      const uint32_t e = fill + rank;
+      stg[3 * e] = i;
+      stg[3 * e + 1] = j;
+      stg[3 * e + 2] = d2_bits;
+    }
+    fill += more;
+  };
+  float4v acc[RF][2];
+  auto clear = [&]() {
+#pragma unroll
+    for (int f = 0; f < RF; ++f)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) acc[f][c] = float4v{0.f, 0.f, 0.f, 0.f};
+  };
+  clear();
+  // the products of 32 points from j0 on are complete: the norm terms, the filter, the results
+  auto finish = [&](uint32_t j0, float s0, float s1) __attribute__((always_inline)) {
+    const uint32_t j = j0 + r16;
+    uint2 p = make_uint2(P1_OUT_OF_RANGE, 0u), q = p;
+    if (j < n) p = norm_pieces(s0, ns.m);
+    if (j + 16 < n) q = norm_pieces(s1, ns.m);
+    const half8 gb = as_half8(lane < 32 ? make_uint4(p.x, p.y, q.x, q.y) : column_constant);
+    uint32_t first = 0, second = 0;  // (counts) of points j and j + 16
+#pragma unroll
+    for (int R = 0; R < NR; ++R) {
+      const half8 ga = *reinterpret_cast<const half8*>(row_operand + R * row_step);
+      const float16v v = __builtin_amdgcn_mfma_f32_32x32x16_f16(ga, gb, cat4(acc[2 * R][0], acc[2 * R][1], acc[2 * R + 1][0], acc[2 * R + 1][1]), 0, 0, 0);
+      auto u = [&](int r) { return __float_as_uint(v[r]); };
+      uint32_t least = min(min(u(0), u(1)), u(2));
+#pragma unroll
+      for (int r = 3; r < 15; r += 2) least = min(min(least, u(r)), u(r + 1));
+      if (__ballot(min(least, u(15)) <= thr_bits) == 0) continue;
+      uint32_t hit = 0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) hit |= v[r] >= a.thr ? 1u << r : 0u;
+      hit &= (32 * R + 32 <= nq ? 0xFFFFu : (32 * R < nq ? edge_mask : 0u)) & ((j < n ? 0x0F0Fu : 0u) | (j + 16 < n ? 0xF0F0u : 0u));
+      if constexpr (COUNT) {
+        first += __popc(hit & 0x0F0Fu);
+        second += __popc(hit & 0xF0F0u);
+        while (__ballot(hit != 0)) {
+          if (hit) {
+            const uint32_t r = (uint32_t)__builtin_ctz(hit);
+            atomicAdd(row_counts + 32 * R + 4 * g + 2 * (r & 8u) + (r & 3u), 1u);
+            hit &= hit - 1;
+          }
+        }
+      } else {
+        for (unsigned long long mask = __ballot(hit != 0); mask; mask = __ballot(hit != 0)) {
+          const uint32_t r = (uint32_t)__builtin_ctz(hit | 0x10000u);
+          append(mask, hit != 0, j + 4 * (r & 4u), 32 * R + 4 * g + 2 * (r & 8u) + (r & 3u), __float_as_uint(fmaxf(-2.f * pick(v, r), 0.f)));
+          hit &= hit - 1;
+        }
+      }
+    }
+    if constexpr (COUNT) {
+      found += first + second;
+      if (__ballot(first + second != 0)) {  // the four lanes of a point
+        first += __shfl_xor(first, 16);
+        first += __shfl_xor(first, 32);
+        second += __shfl_xor(second, 16);
+        second += __shfl_xor(second, 32);
+      }
+      if (lane < 32 && j0 + lane < n) a.counts_p[j0 + lane] = lane < 16 ? first : second;
+    }
+  };
+  auto step = [&](auto b_c) __attribute__((always_inline)) -> bool {
+    constexpr int B = decltype(b_c)::value;
+    const bool ends = chunk + 1 == chunks;
+    const uint32_t next_panel = ends ? panel + gridDim.x : panel, next_chunk = ends ? 0 : chunk + 1;
+    load(std::integral_constant<int, 1 - B>{}, next_panel, next_chunk);
+#pragma unroll
+    for (int k = 0; k < CHUNK; ++k) {
+      const int kb = (int)chunk * CHUNK + k;
+      if (kb >= nkb) break;
+#pragma unroll
+      for (int f = 0; f < RF; ++f) {
+        const half8 x = *reinterpret_cast<const half8*>(lds + (f * nkb + kb) * 1024 + lane * 16);
+        acc[f][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, buf[B][k][0], acc[f][0], 0, 0, 0);
+        acc[f][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(x, buf[B][k][1], acc[f][1], 0, 0, 0);
+      }
+    }
+    if (ends) {
+      if (panel * TILE + wave * 32 < n) finish(panel * TILE + wave * 32, point_norm[B][0], point_norm[B][1]);
+      clear();
+    }
+    panel = next_panel;
+    chunk = next_chunk;
+    return panel < panels;
+  };
+  if (ns.st == ST_OK) {
+    while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{})) {}
+  } else if (COUNT) {  // data out of range: nothing is found
+    for (; panel < panels; panel += gridDim.x)
+      if (tid < TILE && panel * TILE + tid < n) a.counts_p[panel * TILE + tid] = 0;
+  }
+
+  // ---- what is left, and the workgroup's ticket
+  if constexpr (COUNT) {
+    found = wave_sum((uint32_t)found) + ((unsigned long long)wave_sum((uint32_t)(found >> 32)) << 32);
+  }
+  if (lane == 0) sums[wave] = COUNT ? found : fill;
+  __syncthreads();
+  if constexpr (COUNT) {
+    if ((uint32_t)tid < nq && tid < ROWS && row_counts[tid] && a.counts_q) atomicAdd(a.counters + tid, row_counts[tid]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // before the ticket
+  }
+  __syncthreads();
+  __shared__ unsigned long long base;
+  __shared__ bool last;
+  if (tid == 0) {
+    unsigned long long sum = 0, all = 0;
+    for (int w = 0; w < FEW_WAVES; ++w) {
+      const unsigned long long v = sums[w];
+      sums[w] = sum;
+      sum += v;
+    }
+    if (!COUNT) base = sum ? atomicAdd(a.state, sum) & ONCE_FOUND : 0;
+    if (!COUNT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    last = close_by_xcd(a.state, gridDim.x, COUNT ? sum : 0, all);
+    if (last) *(COUNT ? a.total : a.n_pairs) = all & ONCE_FOUND;
+  }
+  __syncthreads();
+  if (!COUNT) store_staged(base + sums[wave]);
+  if (COUNT && last && a.counts_q && (uint32_t)tid < nq)
+    a.counts_q[tid] = __hip_atomic_exchange(a.counters + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace
@@ -3342,6 +3617,42 @@ int run_join_split(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, int64
   return launch_join<COUNT>(ctx, w, true, A, A, true, 3 * nkb, eps, r, st, true);
 }
 
+typedef void (*FewKernel)(FewArgs);
+template <bool COUNT>
+FewKernel few_kernel(int rf) { return rf == 2 ? &k_join_few<COUNT, 2> : rf == 4 ? &k_join_few<COUNT, 4> : rf == 8 ? &k_join_few<COUNT, 8> : &k_join_few<COUNT, 16>; }
+// Groups of 16 query points that k_join_few should hold for nQ of them against a prepared set of n, or 0: another kernel.  They have to fit
+// the LDS, and every workgroup fills it anew, 1 KB a group and k-block: the more of them, the more points it takes (start of the call to
+// its end, here and by k_prep and k_join_small, in us: 64 KB 5,000 points 13.2 and 13.2, 1,000 13.7 and 11.9; 120 KB 20,000 points 27.0 and 31.9, 5,000 19.2 and 19.3;
+// 128 KB 20,000 18.8 and 19.5, 5,000 18.7 and 17.0; 48 KB 5,000 12.2 and 14.1, 1,000 12.4 and 12.7; 16 KB 1,000 10.8 and 12.7).
+int few_groups(int64_t n, int64_t nQ, int nkb) {
+#if defined(EJOIN_ONLY_K_JOIN) || defined(EJOIN_ONLY_K_JOIN_STRIP)
+  return 0;
+#endif
+  if (nQ > 256) return 0;
+  const int rf = nQ <= 32 ? 2 : (nQ <= 64 ? 4 : (nQ <= 128 ? 8 : 16));
+  return few_lds_bytes<false>(16 * rf, nkb) <= FEW_LDS && n >= 150ll * (rf * nkb - 24) ? rf : 0;
+}
+template <bool COUNT>
+int run_few(ejoin_ctx* ctx, const Workspace& w, const ejoin_set* P, int rf, int nkb, const uint16_t* XQ, int64_t nQ, int64_t ldQ, float eps, const Results& r,
+            hipStream_t st) {
+  for (int e = 0; ctx->profiling && e < 3; ++e) EJ_TRY(hipEventRecord(ctx->ev[e], st));
+  ctx->last_status = w.status;
+  ctx->last_stream = st;
+  const int lds_bytes = few_lds_bytes<COUNT>(16 * rf, nkb);
+  const int64_t panels = P->pad / TILE, most = (int64_t)ctx->num_cu * few_groups_per_cu(rf, lds_bytes);
+  const int64_t rounds = (panels + most - 1) / most, groups = (panels + rounds - 1) / rounds;
+  const FewArgs a{P->Xp, P->s, P->max_bits, P->n, nkb, XQ, nQ, ldQ, -0.5f * (eps * eps), w.status, r.pairs, r.dist2, r.capacity,
+                  reinterpret_cast<unsigned long long*>(r.n_pairs), r.counts, r.counts_b, reinterpret_cast<unsigned long long*>(r.total),
+                  reinterpret_cast<unsigned long long*>(ctx->once), reinterpret_cast<uint32_t*>(ctx->once + ONCE_STATE_BYTES) + NUM_XCD * ONCE_SLOTS};
+  hipLaunchKernelGGL(few_kernel<COUNT>(rf), dim3((unsigned)groups), dim3(64 * FEW_WAVES), lds_bytes, st, a);
+  EJ_TRY(hipGetLastError());
+  if (ctx->profiling) {
+    EJ_TRY(hipEventRecord(ctx->ev[3], st));
+    ctx->ev_valid = 1;
+  }
+  return EJOIN_OK;
+}
+
 // Two-set join of a prepared point set with query points given as FP16 rows.
 template <bool COUNT>
 int run_join_prepared(ejoin_ctx* ctx, const ejoin_set* P, const uint16_t* XQ, int64_t nQ, int64_t ldQ, float eps, const Results& r,
@@ -3351,6 +3662,7 @@ int run_join_prepared(ejoin_ctx* ctx, const ejoin_set* P, const uint16_t* XQ, in
   EJ_RC(ensure_workspace(ctx, padQ, pad_dims(d)));
   const Workspace& w = ctx->ws;
   const int nkb = k_blocks(d);
+  if (const int rf = few_groups(P->n, nQ, nkb)) return run_few<COUNT>(ctx, w, P, rf, nkb, XQ, nQ, ldQ, eps, r, st);
   PrepSet SP{nullptr, P->n, P->pad, 0, P->s, P->Xp, 0}, SQ{XQ, nQ, padQ, ldQ, w.s, w.Xp, 0};
   if (const int tile = small_tile(ctx, P->n, nQ, false, nkb)) return run_small<COUNT>(ctx, w, tile, SP, SQ, P->max_bits, nkb, eps, r, st);
   EJ_RC(begin_call(ctx, w, true, st));
@@ -3431,6 +3743,9 @@ int ejoin_create(ejoin_ctx** out, int device) {
   }
   hipError_t e = hipMalloc(reinterpret_cast<void**>(&ctx->ws.status), 256);
   if (e == hipSuccess) e = hipMemset(ctx->ws.status, 0, 256);
+  for (int rf : {2, 4, 8, 16})
+    for (FewKernel kernel : {few_kernel<false>(rf), few_kernel<true>(rf)})
+      if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, FEW_LDS);
   constexpr size_t ONCE_BYTES = ONCE_STATE_BYTES + (NUM_XCD * ONCE_SLOTS + ONCE_COUNTS) * sizeof(uint32_t);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&ctx->once), ONCE_BYTES);
   if (e == hipSuccess) e = hipMemset(ctx->once, 0, ONCE_BYTES);
