@@ -160,14 +160,58 @@ __global__ __launch_bounds__(512) void k_fold_max(uint32_t* values, uint32_t n) 
   if (threadIdx.x == 0) values[0] = most;
 }
 
+// ---- What the workgroups of the one-launch kernels tell each other, in memory of the context's that is all zero between calls:
+// 64-bit words, [0] and [16 (1 + x)] of XCD x (bits 0 .. 39: pairs found; 40 .. 51: workgroups that were late; 52 .. 63: tickets), slots for the largest norms of
+// parts of the points, once for each XCD, and counters.  A slot that has been filled has its top bit set (a norm has no sign).
+constexpr int ONCE_SLOTS = 2048, ONCE_COUNTS = 1 << 17;  // capacities
+constexpr size_t ONCE_STATE_BYTES = 16 * 8 * (1 + EJ_NUM_XCD);
+constexpr unsigned long long ONCE_FOUND = (1ull << 40) - 1, ONCE_TICKET = 1ull << 52;
+// A workgroup's ticket, with what it adds to the fields below, XCD by XCD: an eighth of the atomics on each of the XCDs' words, then
+// one each on [0].  (One thread.)  True for the last workgroup of all, whose `all` are the fields' sums; the state is zero again.
+__device__ __forceinline__ unsigned long long* state_of_xcd(unsigned long long* state) { return state + 16 * (1 + blockIdx.x % EJ_NUM_XCD); }
+__device__ __forceinline__ bool close_by_xcd(unsigned long long* state, uint32_t workgroups, unsigned long long in_xcd /* with the ticket */, unsigned long long& all) {
+  const uint32_t xcd = blockIdx.x % EJ_NUM_XCD, xcds = min(workgroups, EJ_NUM_XCD);
+  unsigned long long* own = state_of_xcd(state);
+  if (in_xcd >> 52 != (workgroups - xcd + xcds - 1) / xcds) return false;
+  *own = 0;
+  const unsigned long long sum = ONCE_TICKET | (in_xcd & (ONCE_TICKET - 1));
+  all = atomicAdd(state, sum) + sum;
+  if (all >> 52 != xcds) return false;
+  *state = 0;
+  return true;
+}
+#ifndef EJOIN_ONCE_SPINS
+#define EJOIN_ONCE_SPINS 2048  // (a build for the tests waits for nothing)
+#endif
+constexpr uint32_t ONCE_FILLED = 0x80000000u;
+// The largest norm in the slots, of what this thread reads of them, for threads of `threads`; missing: one of them is still empty
+// after `spins` more looks.
+__device__ __forceinline__ uint32_t look_at_slots(const uint32_t* slot, uint32_t slots, uint32_t threads, int spins, bool& missing) {
+  uint32_t most = 0;
+  missing = false;
+  slot += blockIdx.x % EJ_NUM_XCD * ONCE_SLOTS;
+  for (uint32_t q = threadIdx.x; q < slots; q += threads) {
+    uint32_t v = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int spin = 0; v == 0 && spin < spins; ++spin) {
+      __builtin_amdgcn_s_sleep(1);
+      v = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    missing |= v == 0;
+    most = max(most, v & ~ONCE_FILLED);
+  }
+  return most;
+}
+
 // Diagonal of the 16 x 16 Gram block of points row0 .. row0 + 15, whose element (row, col) sits in lane col + 16 * (row / 4),
 // register row % 4: stored to s for points below n.  Returns this lane's norm (0 in a lane that holds none).
+template <bool SHARED = false>  // SHARED: for other workgroups of the launch
 __device__ __forceinline__ float store_diagonal(const float4v& acc, int64_t row0, int64_t n, float* __restrict__ s) {
   const int lane = threadIdx.x & 63, c = lane & 15;
   if ((c >> 2) != (lane >> 4) || row0 + c >= n) return 0.f;
   const float lo = (c & 1) ? acc[1] : acc[0], hi = (c & 1) ? acc[3] : acc[2];
   const float v = (c & 2) ? hi : lo;
-  s[row0 + c] = v;
+  if (SHARED) __hip_atomic_store(s + row0 + c, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else s[row0 + c] = v;
   return v;
 }
 
@@ -195,7 +239,7 @@ __device__ __forceinline__ float store_diagonal(const float4v& acc, int64_t row0
 // one k-block after the other: 10^6 x 64 26.5 us, now 19.6 (16 points, workgroups of 256, one k-block after the other, as
 // before: 23.8); 10^5 x 512 18.4, now 16.1 (17.9).
 constexpr int NORM_POINTS = 32;  // points per wavefront
-template <bool PACK, int HALVES = 2>  // returns the pattern of this lane's largest norm
+template <bool PACK, int HALVES = 2, bool SHARED = false>  // returns the pattern of this lane's largest norm
 __device__ __forceinline__ uint32_t norms_of_wave(int64_t row0, const uint16_t* __restrict__ X, int64_t n, int64_t ld, int k32steps,
                                                   float* __restrict__ s, uint4* __restrict__ Xp, int blocks) {
   const int lane = threadIdx.x & 63;
@@ -237,7 +281,7 @@ __device__ __forceinline__ uint32_t norms_of_wave(int64_t row0, const uint16_t* 
   if (k < k32steps) steps(k, std::integral_constant<int, 1>{});
   uint32_t most = 0;
 #pragma unroll
-  for (int h = 0; h < HALVES; ++h) most = max(most, __float_as_uint(store_diagonal(acc[h], row0 + 16 * h, n, s)));
+  for (int h = 0; h < HALVES; ++h) most = max(most, __float_as_uint(store_diagonal<SHARED>(acc[h], row0 + 16 * h, n, s)));
   return most;
 }
 
@@ -583,12 +627,14 @@ __device__ __forceinline__ void copy16_to_lds_from(uint32_t lds_addr, const void
 // 1,500 x 1,500 20.5, now 17.2; 2,000 x 3,000 at d = 960 47.2, now 33.7; 6,000 x 6,000 at d = 128 56.2, now 40.6.  Eight wavefronts for TS = 128, of which two workgroups fit a CU: with four of
 // 64 x 64 each (another card) 41 us a call, with eight 37, with sixteen 38; 6,000 x 6,000 at d = 128 41, 37, 41.  (Tried: rows of
 // 256 bytes stored by way of the LDS: the same; stores that pass the caches by: 68.)
+// ONE: the norms are worked out in this launch, by workgroups that come before those of the tiles, which look for them before their
+// first slice and, where they are not there yet, after the last (see k_join_once: slots, a bounded wait, tickets).
 // TS = 128 needs half the operand traffic of TS = 64, which gives four times the workgroups: at 144 of the larger kind (1,500 x
 // 1,500, d = 384) 15.2 us a call against 13.6, at 225 (1,800 x 1,800) 15.6 against 16.9, at 240 (700 x 5,001, d = 100) 13.2 against
 // 14.6, at 289 the same, at 1,280 39 against 46: the line lies at three workgroups of the larger kind for four CUs.
 struct DenseArgs {
   const uint16_t* X;
-  const float* s;
+  float* s;
   const uint32_t* maxima;  // largest norms, one per workgroup of k_norms
   uint32_t nmaxima;
   uint32_t* status;
@@ -597,6 +643,11 @@ struct DenseArgs {
   int64_t i0, j0;
   int rows, cols;
   float* out;
+  // ONE: workgroups that work out the norms (a multiple of 8), their k-blocks, and of the context, all zero between calls:
+  uint32_t norm_groups;
+  int nkb;
+  unsigned long long* state;
+  uint32_t* slot;
 };
 template <int TS>
 constexpr int dense_stages() { return TS == 64 ? 3 : 2; }
@@ -604,7 +655,7 @@ template <int TS>
 constexpr int dense_waves() { return TS == 64 ? 4 : 8; }
 template <int TS>
 constexpr int dense_lds_bytes() { return dense_stages<TS>() * 2 * TS * 128 + 2 * TS * 16 + 64; }
-template <int TS>
+template <int TS, bool ONE>
 __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_dist2_tile(const DenseArgs a) {
   constexpr int WAVES = dense_waves<TS>(), ACROSS = WAVES / 2;  // two rows of wavefronts
   constexpr int WR = TS / 2, WC = TS / ACROSS, MR = WR / 16, MC = WC / 16;  // wave tile, and its 16 x 16 blocks: rows, columns
@@ -619,8 +670,39 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   // workgroup -> tile: a contiguous part of the tiles for every XCD, in bands of eight rows, column by column
   const uint32_t tr = (uint32_t)(a.rows + TS - 1) / TS, tc = (uint32_t)(a.cols + TS - 1) / TS, tiles = tr * tc;
-  const uint32_t t = blockIdx.x % EJ_NUM_XCD * ((tiles + EJ_NUM_XCD - 1) / EJ_NUM_XCD) + blockIdx.x / EJ_NUM_XCD;
-  if (t >= tiles) return;
+  const uint32_t block = blockIdx.x - (ONE ? a.norm_groups : 0u);
+  const uint32_t t = block % EJ_NUM_XCD * ((tiles + EJ_NUM_XCD - 1) / EJ_NUM_XCD) + block / EJ_NUM_XCD;
+  unsigned long long in_xcd = 0;
+  auto ticket = [&]() {  // (ONE) the slots are no longer needed
+    if (ONE && tid == 0) in_xcd = atomicAdd(state_of_xcd(a.state), ONCE_TICKET);
+  };
+  auto leave = [&]() {  // the last workgroup of all clears them
+    if (!ONE || wave != 0) return;
+    unsigned long long all;
+    const bool last = lane == 0 && close_by_xcd(a.state, gridDim.x, in_xcd + ONCE_TICKET, all);
+    if (__ballot(last))
+      for (uint32_t q = lane; q < a.norm_groups * EJ_NUM_XCD; q += 64) a.slot[q % EJ_NUM_XCD * ONCE_SLOTS + q / EJ_NUM_XCD] = 0;
+  };
+  auto norms_from = [&](int64_t row0) -> uint32_t {
+    return row0 < a.n ? norms_of_wave<false, 1, true>(row0, a.X, a.n, a.ld, a.nkb, a.s, nullptr, 0) : 0u;
+  };
+  if constexpr (ONE) {
+    if (blockIdx.x < a.norm_groups) {
+      const uint32_t own = norms_from(((int64_t)blockIdx.x * WAVES + wave) * 16);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the norms are there before the slot says so
+      const uint32_t most = max_of_group(own);
+      if (tid < (int)EJ_NUM_XCD) __hip_atomic_store(a.slot + tid * ONCE_SLOTS + blockIdx.x, most | ONCE_FILLED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      ticket();
+      leave();
+      return;
+    }
+  }
+  if (t >= tiles) {
+    ticket();
+    leave();
+    return;
+  }
   const uint32_t band = t / (EJ_BAND * tc), in_band = t - band * EJ_BAND * tc;
   const uint32_t h = tr - band * EJ_BAND < EJ_BAND ? tr - band * EJ_BAND : EJ_BAND;
   const int bi = (int)(band * EJ_BAND + in_band % h) * TS, bj = (int)(in_band / h) * TS;
@@ -656,29 +738,51 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
   // ---- operands of the augmentation step from the norms: thread t row t of the tile's column points, then of its row points.  The
   // wave tile is accumulated with the columns as rows of the MFMA (a lane then holds four consecutive columns of a row of the block);
   // the step adds the rows' terms first all the same, as the joins do.
-  float sx = 0.f, sy = 0.f;
-  if (tid < 2 * TS) {
-    const bool row_part = tid >= TS;
-    const int r = tid & (TS - 1), in = r & 31;
-    const int x = (r & ~31) + (row_part ? aug_col_point(in) : aug_row_point(in)), y = x + (row_part ? 16 : 4);
-    sx = a.s[row_part ? row_a(x) : row_b(x)];
-    sy = a.s[row_part ? row_a(y) : row_b(y)];
-  }
   uint32_t mb = 0;
-  for (uint32_t q = tid; q < a.nmaxima; q += 64 * WAVES) mb = max(mb, a.maxima[q]);
-  const NormScale ns = norm_scale(max_of_group(mb));
-  if (blockIdx.x == 0 && tid == 0) a.status[0] = ns.st;
-  if (ns.st != ST_OK) {
+  bool usable = true;
+  float sx = 0.f, sy = 0.f;
+  auto read_norms = [&]() {
+    if (tid < 2 * TS) {
+      const bool row_part = tid >= TS;
+      const int r = tid & (TS - 1), in = r & 31;
+      const int x = (r & ~31) + (row_part ? aug_col_point(in) : aug_row_point(in)), y = x + (row_part ? 16 : 4);
+      const float *px = a.s + (row_part ? row_a(x) : row_b(x)), *py = a.s + (row_part ? row_a(y) : row_b(y));
+      sx = ONE ? __hip_atomic_load(px, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *px;
+      sy = ONE ? __hip_atomic_load(py, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *py;
+    }
+  };
+  auto norm_operands = [&]() {
+    if (!ONE)
+      for (uint32_t q = tid; q < a.nmaxima; q += 64 * WAVES) mb = max(mb, a.maxima[q]);
+    const NormScale ns = norm_scale(max_of_group(mb));
+    if (block == 0 && tid == 0) a.status[0] = ns.st;
+    usable = ns.st == ST_OK;
+    if (!usable) return;
+    if (tid < 2 * TS) {
+      const uint2 p = norm_pieces(sx, ns.m), q = norm_pieces(sy, ns.m);
+      *reinterpret_cast<uint4*>(lds + AUG + tid * 16) = make_uint4(p.x, p.y, q.x, q.y);
+    }
+    if (tid < 4) {  // the constant chunks of the augmentation step (2 and 3)
+      const uint32_t c = fp16_bits(ns.c), c0 = c | (c << 16);
+      *reinterpret_cast<uint2*>(lds + AUG_CONST + tid * 8) = tid == 0 || tid == 3 ? make_uint2(c0, c) : make_uint2(0u, 0u);
+    }
+  };
+  bool there = true;  // the norms and their largest
+  if (!ONE) read_norms();
+  if constexpr (ONE) {
+    bool missing;
+    mb = look_at_slots(a.slot, a.norm_groups, 64 * WAVES, 0, missing);
+    there = !__syncthreads_or(missing);
+    if (there) {
+      read_norms();
+      ticket();
+    }
+  }
+  if (there) norm_operands();
+  if (!usable) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the copies must land before the wave ends
+    leave();
     return;
-  }
-  if (tid < 2 * TS) {
-    const uint2 p = norm_pieces(sx, ns.m), q = norm_pieces(sy, ns.m);
-    *reinterpret_cast<uint4*>(lds + AUG + tid * 16) = make_uint4(p.x, p.y, q.x, q.y);
-  }
-  if (tid < 4) {  // the constant chunks of the augmentation step (2 and 3)
-    const uint32_t c = fp16_bits(ns.c), c0 = c | (c << 16);
-    *reinterpret_cast<uint2*>(lds + AUG_CONST + tid * 8) = tid == 0 || tid == 3 ? make_uint2(c0, c) : make_uint2(0u, 0u);
   }
   uint32_t off[2];  // k-block kb of the slice: row lane % 16, chunk 4 kb + lane / 16
 #pragma unroll
@@ -710,6 +814,26 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
     }
     stage = stage == STAGES - 1 ? 0 : stage + 1;
   }
+  if constexpr (ONE) {
+    if (!there) {
+      bool missing;
+      mb = look_at_slots(a.slot, a.norm_groups, 64 * WAVES, EJOIN_ONCE_SPINS, missing);
+      if (__syncthreads_or(missing)) {  // workgroups that have not been started: all norms by this one
+        mb = 0;
+        for (int64_t row0 = wave * 16; row0 < a.n; row0 += WAVES * 16) mb = max(mb, norms_from(row0));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+      }
+      read_norms();
+      ticket();
+      norm_operands();
+      if (!usable) {
+        leave();
+        return;
+      }
+      __syncthreads();
+    }
+  }
   const int m = lane & 31;
   const char* aug_c = lds + (lane < 32 ? AUG_CONST + 16 * ((lane >> 3) & 1) : AUG + 16 * (wn + m));
   const char* aug_r = lds + (lane < 32 ? AUG_B + 16 * (wm + m) : AUG_CONST + 16 * ((lane >> 4) & 1));
@@ -739,6 +863,7 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
         }
     }
   }
+  leave();
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2444,33 +2569,12 @@ struct OnceArgs {
   float* sB;
   uint32_t tiles, slots_a, slots;  // slots: one per 64 points of the first set, then of the second
   // of the context, all zero between calls
-  unsigned long long* state;  // [0], and [16 (1 + x)] of XCD x.  Bits 0 .. 39: pairs found; 40 .. 51: late workgroups; 52 .. 63: tickets
-  uint32_t* slot;             // ONCE_SLOTS for each XCD
-  uint32_t* late_counts;      // of the points, then of the query points
+  unsigned long long* state;
+  uint32_t* slot;
+  uint32_t* late_counts;  // of the points, then of the query points
 };
-constexpr int ONCE_SLOTS = 2048, ONCE_COUNTS = 1 << 17;  // capacities
-constexpr uint32_t ONCE_STEPS = 256;                     // tiles from which on counts take their tickets XCD by XCD
-constexpr size_t ONCE_STATE_BYTES = 16 * 8 * (1 + EJ_NUM_XCD);
-constexpr unsigned long long ONCE_FOUND = (1ull << 40) - 1, ONCE_TICKET = 1ull << 52;
-// A workgroup's ticket, with what it adds to the fields below, XCD by XCD: an eighth of the atomics on each of the XCDs' words, then
-// one each on [0].  (One thread.)  True for the last workgroup of all, whose `all` are the fields' sums; the state is zero again.
-__device__ __forceinline__ bool close_by_xcd(unsigned long long* state, uint32_t workgroups, unsigned long long add, unsigned long long& all) {
-  const uint32_t xcd = blockIdx.x % EJ_NUM_XCD, xcds = min(workgroups, EJ_NUM_XCD);
-  unsigned long long* own = state + 16 * (1 + xcd);
-  add |= ONCE_TICKET;
-  const unsigned long long in_xcd = atomicAdd(own, add) + add;
-  if (in_xcd >> 52 != (workgroups - xcd + xcds - 1) / xcds) return false;
-  *own = 0;
-  const unsigned long long sum = ONCE_TICKET | (in_xcd & (ONCE_TICKET - 1));
-  all = atomicAdd(state, sum) + sum;
-  if (all >> 52 != xcds) return false;
-  *state = 0;
-  return true;
-}
-#ifndef EJOIN_ONCE_SPINS
-#define EJOIN_ONCE_SPINS 2048  // (a build for the tests waits for nothing)
-#endif
 constexpr int ONCE_GROUPS_PER_CU = 3;
+constexpr uint32_t ONCE_STEPS = 256; // tiles from which on counts take their tickets XCD by XCD
 template <int TS>
 struct Once {
   static constexpr int WR = TS / 32, WC = 2, WAVES = WR * WC, THREADS = 64 * WAVES;  // wavefronts: of the rows, of the columns; 32 x TS / 2 each
@@ -2588,7 +2692,6 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
   __syncthreads();
 
   // ---- the largest norm of all
-  constexpr uint32_t FILLED = 0x80000000u;  // (a norm has no sign)
   if (fills && tid < 2 * TS) {
     uint32_t most = exists ? __float_as_uint(norms[tid]) : 0u;
 #pragma unroll
@@ -2596,20 +2699,10 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
     if (COUNT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the counts are cleared
     const uint32_t first = own - lane;
     if (lane < NUM_XCD && first < (col ? nnB : nnA))
-      __hip_atomic_store(args.slot + lane * ONCE_SLOTS + (col ? args.slots_a : 0u) + first / 64, most | FILLED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(args.slot + lane * ONCE_SLOTS + (col ? args.slots_a : 0u) + first / 64, most | ONCE_FILLED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  uint32_t mb = 0;
-  bool missing = false;
-  const uint32_t* slot = args.slot + blockIdx.x % NUM_XCD * ONCE_SLOTS;
-  for (uint32_t q = tid; q < args.slots; q += L::THREADS) {
-    uint32_t v = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int spin = 0; v == 0 && spin < EJOIN_ONCE_SPINS; ++spin) {
-      __builtin_amdgcn_s_sleep(1);
-      v = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    missing |= v == 0;
-    mb = max(mb, v & ~FILLED);
-  }
+  bool missing;
+  uint32_t mb = look_at_slots(args.slot, args.slots, L::THREADS, EJOIN_ONCE_SPINS, missing);
   const bool late = __syncthreads_or(missing);
   if (late) {
     mb = 0;
@@ -2692,7 +2785,7 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
   if (tid == 0) {
     for (int w = 0; w < L::WAVES; ++w) total += sums[w];
     const unsigned long long add = ONCE_TICKET | ((unsigned long long)late << 40) | total;
-    if (COUNT && args.tiles > ONCE_STEPS) last = close_by_xcd(args.state, args.tiles, add, all);
+    if (COUNT && args.tiles > ONCE_STEPS) last = close_by_xcd(args.state, args.tiles, atomicAdd(state_of_xcd(args.state), add) + add, all);
     else all = atomicAdd(args.state, add) + add;
   }
   auto close = [&]() {  // (thread 0) the workgroup's place in the result, and whether it is the last of all
@@ -3036,7 +3129,8 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
     }
     if (!COUNT) base = sum ? atomicAdd(a.state, sum) & ONCE_FOUND : 0;
     if (!COUNT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    last = close_by_xcd(a.state, gridDim.x, COUNT ? sum : 0, all);
+    const unsigned long long add = ONCE_TICKET | (COUNT ? sum : 0);
+    last = close_by_xcd(a.state, gridDim.x, atomicAdd(state_of_xcd(a.state), add) + add, all);
     if (last) *(COUNT ? a.total : a.n_pairs) = all & ONCE_FOUND;
   }
   __syncthreads();
@@ -3759,7 +3853,8 @@ int ejoin_create(ejoin_ctx** out, int device) {
        {&k_join<false, false, false>, &k_join<false, false, true>, &k_join<true, false, false>, &k_join<true, false, true>, &k_join<true, true, false>,
         &k_join<true, true, true>})
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_dist2_tile<128>), hipFuncAttributeMaxDynamicSharedMemorySize, dense_lds_bytes<128>());
+  for (void (*kernel)(DenseArgs) : {&k_dist2_tile<128, false>, &k_dist2_tile<128, true>})
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, dense_lds_bytes<128>());
   for (int nkb = 2; nkb <= EJ_STRIP_KB_MAX; ++nkb)
     for (JoinKernel kernel : {strip_kernel<false>(nkb), strip_kernel<true>(nkb)})
       if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, strip_lds(nkb));
@@ -4030,7 +4125,22 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   ctx->last_stream = st;
   // (no atomics on the status block: its state between calls is left as it is)
   uint32_t* maxima = w.maxima;
-  DenseArgs a{X, w.s, maxima, 0, w.status, n, ld, (k_blocks(d) + 1) / 2 /* (rows are padded to a multiple of 64 coordinates) */, i0, j0, rows, cols, out};
+  DenseArgs a{X, w.s, maxima, 0, w.status, n, ld, (k_blocks(d) + 1) / 2 /* (rows are padded to a multiple of 64 coordinates) */, i0, j0, rows, cols, out,
+              0, k_blocks(d), reinterpret_cast<unsigned long long*>(ctx->once), reinterpret_cast<uint32_t*>(ctx->once + ONCE_STATE_BYTES)};
+  auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
+  const bool wide = 4 * blocks(128) >= 3 * ctx->num_cu;  // (see the kernel)
+  const int64_t groups = wide ? blocks(128) : blocks(64), per = 16 * (wide ? dense_waves<128>() : dense_waves<64>());
+  const int64_t norm_groups = ((n + per - 1) / per + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD;
+  // One launch, the norms by the first of its workgroups, where there is about one workgroup a CU in all (two launches and now, in us: 300 x 300 of
+  // 8,000 x 64 11.5, 9.6; 600 x 600 of 8,000 x 384 11.9, 9.6; 1,000 x 1,000 of 1,000 x 96 11.1, 8.9).  Beyond, it is the slots that take long to
+  // read and what waits for them (300 x 300 of 20,000 x 384 11.6 both ways, of 120,000 x 64 11.1 and 21.4; 2,500 x 700 of 12,000 x 200 11.3, 12.3).
+  if (norm_groups <= ONCE_SLOTS && 4 * (groups + norm_groups) <= 5 * ctx->num_cu) {
+    a.norm_groups = (uint32_t)norm_groups;
+    hipLaunchKernelGGL((wide ? k_dist2_tile<128, true> : k_dist2_tile<64, true>), dim3((unsigned)(groups + norm_groups)),
+                       dim3(64 * (wide ? dense_waves<128>() : dense_waves<64>())), (wide ? dense_lds_bytes<128>() : dense_lds_bytes<64>()), st, a);
+    EJ_TRY(hipGetLastError());
+    return EJOIN_OK;
+  }
   EJ_RC(launch_norms(ctx, X, n, d, ld, w.s, nullptr, nullptr, st, maxima, &a.nmaxima));
   // every workgroup of the dense kernel reads all maxima: from some 5 10^5 points on a launch that folds them first costs less
   // (d = 16, block of 100 x 100: 200,000 points 14.3 us without, 17.7 with; 500,000 17.9 and 18.6; 10^6 28.2 and 27.8; 5 10^6 145 and
@@ -4041,11 +4151,8 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
     EJ_TRY(hipGetLastError());
     a.nmaxima = 1;
   }
-  auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
-  if (4 * blocks(128) >= 3 * ctx->num_cu)  // (see the kernel)
-    hipLaunchKernelGGL(k_dist2_tile<128>, dim3((unsigned)blocks(128)), dim3(64 * dense_waves<128>()), dense_lds_bytes<128>(), st, a);
-  else
-    hipLaunchKernelGGL(k_dist2_tile<64>, dim3((unsigned)blocks(64)), dim3(64 * dense_waves<64>()), dense_lds_bytes<64>(), st, a);
+  hipLaunchKernelGGL((wide ? k_dist2_tile<128, false> : k_dist2_tile<64, false>), dim3((unsigned)groups),
+                     dim3(64 * (wide ? dense_waves<128>() : dense_waves<64>())), (wide ? dense_lds_bytes<128>() : dense_lds_bytes<64>()), st, a);
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }

@@ -132,3 +132,34 @@ def general_count(X):
     counts = e.selfjoin_count(X, 1.2, d=64)
     torch.cuda.synchronize()
     return counts
+
+
+# the norms by workgroups of the launch: one tile; tiles of 64, ragged; of 128; the last block and set in one launch (320 workgroups) and the first in two
+@pytest.mark.parametrize("n,d,i0,j0,rows_,cols", [(1, 20, 0, 0, 1, 1), (300, 70, 7, 100, 3, 200), (2000, 384, 1, 700, 501, 499), (8000, 100, 1000, 3000, 1800, 1750),
+                                                  (20480, 64, 0, 20000, 20, 300), (20481, 64, 0, 20000, 20, 300)])
+def test_dense_block(general, once, n, d, i0, j0, rows_, cols):
+    """The distances of the joins, zero on the diagonal; and data out of range is reported."""
+    print(f"once dense n={n} d={d} rows={rows_} cols={cols}", flush=True)
+    X = rows(n, d, seed=n)
+    X[:n // 3] *= 0.01
+    for _ in range(2):
+        D = once.dist2_tile(X, i0, j0, rows_, cols, d=d)
+        assert once.status() == 0
+    pairs, d2, _ = sorted_triples(general.join_pairs(X[i0:i0 + rows_].clone(), X[j0:j0 + cols].clone(), 1e3, rows_ * cols, d=d))
+    i, j = pairs[:, 0].long(), pairs[:, 1].long()
+    off = i0 + i != j0 + j
+    scale = torch.sqrt((X.float() ** 2).sum(1).max())  # (the scale of the norm terms of a part of the points may be another)
+    assert i.numel() == rows_ * cols and bool(((D[i, j] - d2)[off].abs() <= 2e-6 * scale ** 2).all()) and not D[i, j][~off].any()
+    if 1 < n < 9000:  # (bit for bit, of the same set)
+        keys, dist2 = sorted_pairs(general.selfjoin_pairs(X, epsilon(X, d, 0.01), n * (n + 1) // 2, d=d))
+        p = keys.view(torch.int32).view(-1, 2).long()
+        inside = (p[:, 0] >= i0) & (p[:, 0] < i0 + rows_) & (p[:, 1] >= j0) & (p[:, 1] < j0 + cols)
+        assert torch.equal(D[p[inside, 0] - i0, p[inside, 1] - j0], dist2[inside])
+    X[n - 1, 0] = float("nan")
+    once.dist2_tile(X, 0, 0, 1, 1, d=d)
+    assert once.status() == 2
+
+
+def sorted_triples(call):
+    pairs, d2, found = call
+    return pairs[:int(found)], d2[:int(found)], int(found)
