@@ -634,7 +634,7 @@ __device__ __forceinline__ void copy16_to_lds_from(uint32_t lds_addr, const void
 // 14.6, at 289 the same, at 1,280 39 against 46: the line lies at three workgroups of the larger kind for four CUs.
 struct DenseArgs {
   const uint16_t* X;
-  float* s;
+  const float* s;
   const uint32_t* maxima;  // largest norms, one per workgroup of k_norms
   uint32_t nmaxima;
   uint32_t* status;
@@ -643,7 +643,11 @@ struct DenseArgs {
   int64_t i0, j0;
   int rows, cols;
   float* out;
-  // ONE: workgroups that work out the norms (a multiple of 8), their k-blocks, and of the context, all zero between calls:
+};
+struct NoArgs {};
+struct DenseOneArgs {  // (ONE)
+  // workgroups that work out the norms (a multiple of 8), their k-blocks, and of the context, all zero between calls:
+  float* s_out;  // (s)
   uint32_t norm_groups;
   int nkb;
   unsigned long long* state;
@@ -656,7 +660,7 @@ constexpr int dense_waves() { return TS == 64 ? 4 : 8; }
 template <int TS>
 constexpr int dense_lds_bytes() { return dense_stages<TS>() * 2 * TS * 128 + 2 * TS * 16 + 64; }
 template <int TS, bool ONE>
-__global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_dist2_tile(const DenseArgs a) {
+__global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_dist2_tile(const DenseArgs a, const std::conditional_t<ONE, DenseOneArgs, NoArgs> one) {
   constexpr int WAVES = dense_waves<TS>(), ACROSS = WAVES / 2;  // two rows of wavefronts
   constexpr int WR = TS / 2, WC = TS / ACROSS, MR = WR / 16, MC = WC / 16;  // wave tile, and its 16 x 16 blocks: rows, columns
   constexpr int COPIES = TS / 8 / WAVES;                  // copy instructions per wavefront, operand and slice
@@ -670,28 +674,34 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
   // workgroup -> tile: a contiguous part of the tiles for every XCD, in bands of eight rows, column by column
   const uint32_t tr = (uint32_t)(a.rows + TS - 1) / TS, tc = (uint32_t)(a.cols + TS - 1) / TS, tiles = tr * tc;
-  const uint32_t block = blockIdx.x - (ONE ? a.norm_groups : 0u);
+  uint32_t block = blockIdx.x;
+  if constexpr (ONE) block -= one.norm_groups;
   const uint32_t t = block % EJ_NUM_XCD * ((tiles + EJ_NUM_XCD - 1) / EJ_NUM_XCD) + block / EJ_NUM_XCD;
   unsigned long long in_xcd = 0;
-  auto ticket = [&]() {  // (ONE) the slots are no longer needed
-    if (ONE && tid == 0) in_xcd = atomicAdd(state_of_xcd(a.state), ONCE_TICKET);
+  auto ticket = [&]() __attribute__((always_inline)) {  // (ONE) the slots are no longer needed
+    if constexpr (ONE) {
+      if (tid == 0) in_xcd = atomicAdd(state_of_xcd(one.state), ONCE_TICKET);
+    }
   };
-  auto leave = [&]() {  // the last workgroup of all clears them
-    if (!ONE || wave != 0) return;
-    unsigned long long all;
-    const bool last = lane == 0 && close_by_xcd(a.state, gridDim.x, in_xcd + ONCE_TICKET, all);
-    if (__ballot(last))
-      for (uint32_t q = lane; q < a.norm_groups * EJ_NUM_XCD; q += 64) a.slot[q % EJ_NUM_XCD * ONCE_SLOTS + q / EJ_NUM_XCD] = 0;
+  auto leave = [&]() __attribute__((always_inline)) {  // the last workgroup of all clears them
+    if constexpr (ONE) {
+      if (wave != 0) return;
+      unsigned long long all;
+      const bool last = lane == 0 && close_by_xcd(one.state, gridDim.x, in_xcd + ONCE_TICKET, all);
+      if (__ballot(last))
+        for (uint32_t q = lane; q < one.norm_groups * EJ_NUM_XCD; q += 64) one.slot[q % EJ_NUM_XCD * ONCE_SLOTS + q / EJ_NUM_XCD] = 0;
+    }
   };
-  auto norms_from = [&](int64_t row0) -> uint32_t {
-    return row0 < a.n ? norms_of_wave<false, 1, true>(row0, a.X, a.n, a.ld, a.nkb, a.s, nullptr, 0) : 0u;
+  auto norms_from = [&](int64_t row0) __attribute__((always_inline)) -> uint32_t {
+    if constexpr (!ONE) return 0u;
+    else return row0 < a.n ? norms_of_wave<false, 1, true>(row0, a.X, a.n, a.ld, one.nkb, one.s_out, nullptr, 0) : 0u;
   };
   if constexpr (ONE) {
-    if (blockIdx.x < a.norm_groups) {
+    if (blockIdx.x < one.norm_groups) {
       const uint32_t own = norms_from(((int64_t)blockIdx.x * WAVES + wave) * 16);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the norms are there before the slot says so
       const uint32_t most = max_of_group(own);
-      if (tid < (int)EJ_NUM_XCD) __hip_atomic_store(a.slot + tid * ONCE_SLOTS + blockIdx.x, most | ONCE_FILLED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid < (int)EJ_NUM_XCD) __hip_atomic_store(one.slot + tid * ONCE_SLOTS + blockIdx.x, most | ONCE_FILLED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       ticket();
       leave();
@@ -699,8 +709,10 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
     }
   }
   if (t >= tiles) {
-    ticket();
-    leave();
+    if constexpr (ONE) {
+      ticket();
+      leave();
+    }
     return;
   }
   const uint32_t band = t / (EJ_BAND * tc), in_band = t - band * EJ_BAND * tc;
@@ -738,26 +750,27 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
   // ---- operands of the augmentation step from the norms: thread t row t of the tile's column points, then of its row points.  The
   // wave tile is accumulated with the columns as rows of the MFMA (a lane then holds four consecutive columns of a row of the block);
   // the step adds the rows' terms first all the same, as the joins do.
-  uint32_t mb = 0;
-  bool usable = true;
   float sx = 0.f, sy = 0.f;
-  auto read_norms = [&]() {
+  uint32_t mb = 0;
+  auto read_norms = [&]() __attribute__((always_inline)) {
     if (tid < 2 * TS) {
       const bool row_part = tid >= TS;
       const int r = tid & (TS - 1), in = r & 31;
       const int x = (r & ~31) + (row_part ? aug_col_point(in) : aug_row_point(in)), y = x + (row_part ? 16 : 4);
-      const float *px = a.s + (row_part ? row_a(x) : row_b(x)), *py = a.s + (row_part ? row_a(y) : row_b(y));
-      sx = ONE ? __hip_atomic_load(px, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *px;
-      sy = ONE ? __hip_atomic_load(py, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *py;
+      if constexpr (ONE) {
+        const int64_t ax = row_a(x), bx = row_b(x), ay = row_a(y), by = row_b(y);  // (a choice between the two before they are worked out puts the arguments into scratch memory)
+        sx = __hip_atomic_load(a.s + (row_part ? ax : bx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sy = __hip_atomic_load(a.s + (row_part ? ay : by), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      } else {
+        sx = a.s[row_part ? row_a(x) : row_b(x)];
+        sy = a.s[row_part ? row_a(y) : row_b(y)];
+      }
     }
   };
-  auto norm_operands = [&]() {
-    if (!ONE)
-      for (uint32_t q = tid; q < a.nmaxima; q += 64 * WAVES) mb = max(mb, a.maxima[q]);
+  auto norm_operands = [&]() __attribute__((always_inline)) -> bool {  // false: data out of range
     const NormScale ns = norm_scale(max_of_group(mb));
     if (block == 0 && tid == 0) a.status[0] = ns.st;
-    usable = ns.st == ST_OK;
-    if (!usable) return;
+    if (ns.st != ST_OK) return false;
     if (tid < 2 * TS) {
       const uint2 p = norm_pieces(sx, ns.m), q = norm_pieces(sy, ns.m);
       *reinterpret_cast<uint4*>(lds + AUG + tid * 16) = make_uint4(p.x, p.y, q.x, q.y);
@@ -766,20 +779,22 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
       const uint32_t c = fp16_bits(ns.c), c0 = c | (c << 16);
       *reinterpret_cast<uint2*>(lds + AUG_CONST + tid * 8) = tid == 0 || tid == 3 ? make_uint2(c0, c) : make_uint2(0u, 0u);
     }
+    return true;
   };
   bool there = true;  // the norms and their largest
-  if (!ONE) read_norms();
   if constexpr (ONE) {
     bool missing;
-    mb = look_at_slots(a.slot, a.norm_groups, 64 * WAVES, 0, missing);
+    mb = look_at_slots(one.slot, one.norm_groups, 64 * WAVES, 0, missing);
     there = !__syncthreads_or(missing);
     if (there) {
       read_norms();
       ticket();
     }
+  } else {
+    read_norms();
+    for (uint32_t q = tid; q < a.nmaxima; q += 64 * WAVES) mb = max(mb, a.maxima[q]);
   }
-  if (there) norm_operands();
-  if (!usable) {
+  if (there && !norm_operands()) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the copies must land before the wave ends
     leave();
     return;
@@ -817,7 +832,7 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
   if constexpr (ONE) {
     if (!there) {
       bool missing;
-      mb = look_at_slots(a.slot, a.norm_groups, 64 * WAVES, EJOIN_ONCE_SPINS, missing);
+      mb = look_at_slots(one.slot, one.norm_groups, 64 * WAVES, EJOIN_ONCE_SPINS, missing);
       if (__syncthreads_or(missing)) {  // workgroups that have not been started: all norms by this one
         mb = 0;
         for (int64_t row0 = wave * 16; row0 < a.n; row0 += WAVES * 16) mb = max(mb, norms_from(row0));
@@ -826,8 +841,7 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
       }
       read_norms();
       ticket();
-      norm_operands();
-      if (!usable) {
+      if (!norm_operands()) {
         leave();
         return;
       }
@@ -3853,8 +3867,8 @@ int ejoin_create(ejoin_ctx** out, int device) {
        {&k_join<false, false, false>, &k_join<false, false, true>, &k_join<true, false, false>, &k_join<true, false, true>, &k_join<true, true, false>,
         &k_join<true, true, true>})
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES);
-  for (void (*kernel)(DenseArgs) : {&k_dist2_tile<128, false>, &k_dist2_tile<128, true>})
-    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, dense_lds_bytes<128>());
+  for (const void* kernel : {reinterpret_cast<const void*>(&k_dist2_tile<128, false>), reinterpret_cast<const void*>(&k_dist2_tile<128, true>)})
+    if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, dense_lds_bytes<128>());
   for (int nkb = 2; nkb <= EJ_STRIP_KB_MAX; ++nkb)
     for (JoinKernel kernel : {strip_kernel<false>(nkb), strip_kernel<true>(nkb)})
       if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, strip_lds(nkb));
@@ -4125,8 +4139,7 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   ctx->last_stream = st;
   // (no atomics on the status block: its state between calls is left as it is)
   uint32_t* maxima = w.maxima;
-  DenseArgs a{X, w.s, maxima, 0, w.status, n, ld, (k_blocks(d) + 1) / 2 /* (rows are padded to a multiple of 64 coordinates) */, i0, j0, rows, cols, out,
-              0, k_blocks(d), reinterpret_cast<unsigned long long*>(ctx->once), reinterpret_cast<uint32_t*>(ctx->once + ONCE_STATE_BYTES)};
+  DenseArgs a{X, w.s, maxima, 0, w.status, n, ld, (k_blocks(d) + 1) / 2 /* (rows are padded to a multiple of 64 coordinates) */, i0, j0, rows, cols, out};
   auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
   const bool wide = 4 * blocks(128) >= 3 * ctx->num_cu;  // (see the kernel)
   const int64_t groups = wide ? blocks(128) : blocks(64), per = 16 * (wide ? dense_waves<128>() : dense_waves<64>());
@@ -4135,9 +4148,9 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   // 8,000 x 64 11.5, 9.6; 600 x 600 of 8,000 x 384 11.9, 9.6; 1,000 x 1,000 of 1,000 x 96 11.1, 8.9).  Beyond, it is the slots that take long to
   // read and what waits for them (300 x 300 of 20,000 x 384 11.6 both ways, of 120,000 x 64 11.1 and 21.4; 2,500 x 700 of 12,000 x 200 11.3, 12.3).
   if (norm_groups <= ONCE_SLOTS && 4 * (groups + norm_groups) <= 5 * ctx->num_cu) {
-    a.norm_groups = (uint32_t)norm_groups;
+    const DenseOneArgs one{w.s, (uint32_t)norm_groups, k_blocks(d), reinterpret_cast<unsigned long long*>(ctx->once), reinterpret_cast<uint32_t*>(ctx->once + ONCE_STATE_BYTES)};
     hipLaunchKernelGGL((wide ? k_dist2_tile<128, true> : k_dist2_tile<64, true>), dim3((unsigned)(groups + norm_groups)),
-                       dim3(64 * (wide ? dense_waves<128>() : dense_waves<64>())), (wide ? dense_lds_bytes<128>() : dense_lds_bytes<64>()), st, a);
+                       dim3(64 * (wide ? dense_waves<128>() : dense_waves<64>())), (wide ? dense_lds_bytes<128>() : dense_lds_bytes<64>()), st, a, one);
     EJ_TRY(hipGetLastError());
     return EJOIN_OK;
   }
@@ -4152,7 +4165,7 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
     a.nmaxima = 1;
   }
   hipLaunchKernelGGL((wide ? k_dist2_tile<128, false> : k_dist2_tile<64, false>), dim3((unsigned)groups),
-                     dim3(64 * (wide ? dense_waves<128>() : dense_waves<64>())), (wide ? dense_lds_bytes<128>() : dense_lds_bytes<64>()), st, a);
+                     dim3(64 * (wide ? dense_waves<128>() : dense_waves<64>())), (wide ? dense_lds_bytes<128>() : dense_lds_bytes<64>()), st, a, NoArgs{});
   EJ_TRY(hipGetLastError());
   return EJOIN_OK;
 }
