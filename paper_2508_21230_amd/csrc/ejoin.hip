@@ -3610,6 +3610,10 @@ int run_small(ejoin_ctx* ctx, const Workspace& w, int tile, PrepSet A, PrepSet B
 // points 9.0, 11.4 and 17.5 against 9.3, 12.9 and 20.0; 3,000 x 1,000, d = 128, 10.4 against 10.6).  Lists pay some 13 ns a tile for their place in the result, tiles of 128 1.6 us and 0.19 us a
 // k-block for their longer chain (tiles of 64 and of 128: 1,000 x 64 8.0 and 9.2 us; 1,984 points, d = 64, 384 and 960, 12.7, 14.6 and 18.4,
 // 9.9, 13.4 and 20.0); with three of them on a CU tiles of 64 lose more (2,400 x 960 23.4 against 21.2).
+// Tiles of 128 are copied in half lines and their norms multiplied once a tile: with three of them on a CU and many k-blocks k_prep and k_join_small are
+// the better ones (4,300 points, d = 384, 768, 960, 2,048 and 4,096: lists 25.5, 35.6, 40.9, 66.5 and 110 us by those, 25.3, 36.6, 41.7, 71.7 and
+// 133 here, counts 24.7, 35.3, 40.7, 64.9 and 110, 21.8, 33.8, 39.4, 70.0 and 133), with
+// two up to 128 k-blocks not (3,900 points, d = 2,048 and 4,096: 59.8 and 97.7, 52.3 and 95.4; counts of 4,000 x 2,000, d = 4,096, 99 and 98).
 int once_edge(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nkb, bool count) {
 #if defined(EJOIN_ONLY_K_JOIN) || defined(EJOIN_ONLY_K_JOIN_STRIP)
   return 0;
@@ -3621,7 +3625,7 @@ int once_edge(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nkb, 
   const int64_t held = (int64_t)ctx->num_cu * ONCE_GROUPS_PER_CU, t64 = tiles(64), t128 = tiles(128);
   if (held >= 4096 || nA + (self ? 0 : nB) > ONCE_COUNTS || (nA + 63) / 64 + (self ? 0 : (nB + 63) / 64) > ONCE_SLOTS) return 0;
   if (count ? t64 <= held : t64 <= 2 * ctx->num_cu && t64 - t128 <= 123 + 15 * nkb) return 64;
-  return t128 <= held ? 128 : 0;
+  return t128 <= (nkb <= (count ? 24 : 12) ? held : nkb <= 128 ? 2 * ctx->num_cu : 0) ? 128 : 0;
 }
 // A join by k_join_once.  XB == nullptr: self-join of XA.
 template <bool COUNT>

@@ -26,9 +26,9 @@ def once(request):
 
 
 # one tile; edges of tiles; the last list in tiles of 64 and the first of 128 (d = 96: 1,216 and 1,217 points); the last counts in tiles of 64
-# (2,432) and the first of 128; the last problem of all (4,864), and one of the kernel after it
+# (2,432) and the first of 128; the last problem of all (4,864; of many coordinates 3,968, two tiles a CU), and one of the kernel after it
 @pytest.mark.parametrize("d", [1, 64, 96, 130, 960])
-@pytest.mark.parametrize("n,share", [(1, 0.5), (63, 0.3), (65, 0.3), (129, 1.0), (1216, 0.01), (1217, 0.01), (2432, 0.003), (2433, 0.003), (4864, 0.0005), (4865, 0.0005)])
+@pytest.mark.parametrize("n,share", [(1, 0.5), (63, 0.3), (65, 0.3), (129, 1.0), (1216, 0.01), (1217, 0.01), (2432, 0.003), (2433, 0.003), (3968, 0.0005), (3969, 0.0005), (4864, 0.0005), (4865, 0.0005)])
 def test_self_join(general, once, n, d, share):
     print(f"once self n={n} d={d} share={share}", flush=True)
     X = rows(n, d, seed=n + d)
