@@ -2921,7 +2921,9 @@ constexpr int FEW_LDS = 159 * 1024;  // (a little is the compiler's)
 template <int RF>
 constexpr int few_chunk() { return RF == 8 ? 4 : 2; }
 constexpr int few_groups_per_cu(int rf, int lds_bytes) { return rf <= 4 && lds_bytes <= 79 * 1024 ? 2 : 1; }
-constexpr int FEW_STG = 128, FEW_WAVES = 8;
+// Staged results a wavefront: one atomic for as many (20,000 points x 250 queries, d = 64, 2.6 % of all pairs, with 128 22.3 us, now 17.1, by k_join_small 18.6;
+// 76 % of 20,000 x 30 52, 28 and 38).
+constexpr int FEW_STG = 256, FEW_WAVES = 8;
 // the query points, their norms, part of the augmentation step and counters, the constants of that step, staged results
 template <bool COUNT>
 constexpr int few_lds_bytes(int rows, int nkb) { return rows * (nkb * 64 + 4 + 16 + 4) + 64 + 64 + (COUNT ? 0 : FEW_WAVES * FEW_STG * 12); }
