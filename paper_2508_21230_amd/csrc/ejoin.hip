@@ -2910,6 +2910,7 @@ struct FewArgs {
   float* dist2;
   unsigned long long capacity;
   unsigned long long* n_pairs;
+  uint32_t staged;  // (pairs) results a wavefront stages
   uint32_t* counts_p;
   uint32_t* counts_q;  // may be null
   unsigned long long* total;
@@ -2921,12 +2922,17 @@ constexpr int FEW_LDS = 159 * 1024;  // (a little is the compiler's)
 template <int RF>
 constexpr int few_chunk() { return RF == 8 ? 4 : 2; }
 constexpr int few_groups_per_cu(int rf, int lds_bytes) { return rf <= 4 && lds_bytes <= 79 * 1024 ? 2 : 1; }
-// Staged results a wavefront: one atomic for as many (20,000 points x 250 queries, d = 64, 2.6 % of all pairs, with 128 22.3 us, now 17.1, by k_join_small 18.6;
-// 76 % of 20,000 x 30 52, 28 and 38).
-constexpr int FEW_STG = 256, FEW_WAVES = 8;
+constexpr int FEW_WAVES = 8;
 // the query points, their norms, part of the augmentation step and counters, the constants of that step, staged results
 template <bool COUNT>
-constexpr int few_lds_bytes(int rows, int nkb) { return rows * (nkb * 64 + 4 + 16 + 4) + 64 + 64 + (COUNT ? 0 : FEW_WAVES * FEW_STG * 12); }
+constexpr int few_lds_bytes(int rows, int nkb, int staged) { return rows * (nkb * 64 + 4 + 16 + 4) + 64 + 64 + (COUNT ? 0 : FEW_WAVES * staged * 12); }
+// Results that a wavefront stages, one atomic for as many: 256, or 128 (at least 64, what one append adds) where the 12 KB more would cost a workgroup of the CU
+// or the place in LDS.  Lists with 128 and with 256, us: 20,000 points x 250 queries, d = 64, 2.6 % of all pairs 22.1 and 17.2 (k_join_small 18.3), 20,000 x 30, d = 300,
+// 76 % 52.0 and 28.4 (39.2); with a workgroup less 300,000 x 60, d = 512 57.6 and 71.4; by other kernels for want of place 100,000 x 60, d = 1080 47.3 and 61.7.
+constexpr int few_staged(int rf, int nkb) {
+  const int more = few_lds_bytes<false>(16 * rf, nkb, 256), less = few_lds_bytes<false>(16 * rf, nkb, 128);
+  return more <= FEW_LDS && few_groups_per_cu(rf, more) == few_groups_per_cu(rf, less) ? 256 : 128;
+}
 template <bool COUNT, int RF>
 __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(const FewArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
@@ -2940,7 +2946,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
   float* const norms = reinterpret_cast<float*>(constants + 64);
   uint32_t* const row_counts = reinterpret_cast<uint32_t*>(norms + ROWS);
   unsigned long long* const sums = reinterpret_cast<unsigned long long*>(row_counts + ROWS);
-  uint32_t* const stg = reinterpret_cast<uint32_t*>(sums + 8) + wave * FEW_STG * 3;
+  uint32_t* const stg = reinterpret_cast<uint32_t*>(sums + 8) + wave * a.staged * 3;
 
   // ---- the points: a workgroup a panel of 256, each of its wavefronts 32 of them, and so on through the panels
   const uint32_t panels = (n + TILE - 1) / TILE, chunks = (uint32_t)(nkb + CHUNK - 1) / CHUNK;
@@ -3019,7 +3025,7 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
   };
   auto append = [&](unsigned long long mask, bool pass, uint32_t i, uint32_t j, uint32_t d2_bits) {
     const uint32_t more = __popcll(mask);
-    if (fill + more > FEW_STG) {
+    if (fill + more > a.staged) {
       unsigned long long base = 0;
       if (lane == 0) base = atomicAdd(a.state, (unsigned long long)fill) & ONCE_FOUND;
       const uint32_t blo = __builtin_amdgcn_readfirstlane((uint32_t)base), bhi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
@@ -3744,7 +3750,7 @@ int few_groups(int64_t n, int64_t nQ, int nkb) {
 #endif
   if (nQ > 256) return 0;
   const int rf = nQ <= 32 ? 2 : (nQ <= 64 ? 4 : (nQ <= 128 ? 8 : 16));
-  return few_lds_bytes<false>(16 * rf, nkb) <= FEW_LDS && n >= 150ll * (rf * nkb - 24) ? rf : 0;
+  return few_lds_bytes<false>(16 * rf, nkb, few_staged(rf, nkb)) <= FEW_LDS && n >= 150ll * (rf * nkb - 24) ? rf : 0;
 }
 template <bool COUNT>
 int run_few(ejoin_ctx* ctx, const Workspace& w, const ejoin_set* P, int rf, int nkb, const uint16_t* XQ, int64_t nQ, int64_t ldQ, float eps, const Results& r,
@@ -3752,11 +3758,11 @@ int run_few(ejoin_ctx* ctx, const Workspace& w, const ejoin_set* P, int rf, int 
   for (int e = 0; ctx->profiling && e < 3; ++e) EJ_TRY(hipEventRecord(ctx->ev[e], st));
   ctx->last_status = w.status;
   ctx->last_stream = st;
-  const int lds_bytes = few_lds_bytes<COUNT>(16 * rf, nkb);
+  const int staged = few_staged(rf, nkb), lds_bytes = few_lds_bytes<COUNT>(16 * rf, nkb, staged);
   const int64_t panels = P->pad / TILE, most = (int64_t)ctx->num_cu * few_groups_per_cu(rf, lds_bytes);
   const int64_t rounds = (panels + most - 1) / most, groups = (panels + rounds - 1) / rounds;
   const FewArgs a{P->Xp, P->s, P->max_bits, P->n, nkb, XQ, nQ, ldQ, -0.5f * (eps * eps), w.status, r.pairs, r.dist2, r.capacity,
-                  reinterpret_cast<unsigned long long*>(r.n_pairs), r.counts, r.counts_b, reinterpret_cast<unsigned long long*>(r.total),
+                  reinterpret_cast<unsigned long long*>(r.n_pairs), (uint32_t)staged, r.counts, r.counts_b, reinterpret_cast<unsigned long long*>(r.total),
                   reinterpret_cast<unsigned long long*>(ctx->once), reinterpret_cast<uint32_t*>(ctx->once + ONCE_STATE_BYTES) + NUM_XCD * ONCE_SLOTS};
   hipLaunchKernelGGL(few_kernel<COUNT>(rf), dim3((unsigned)groups), dim3(64 * FEW_WAVES), lds_bytes, st, a);
   EJ_TRY(hipGetLastError());
