@@ -3744,13 +3744,23 @@ FewKernel few_kernel(int rf) { return rf == 2 ? &k_join_few<COUNT, 2> : rf == 4 
 // the LDS, and every workgroup fills it anew, 1 KB a group and k-block: the more of them, the more points it takes (start of the call to
 // its end, here and by k_prep and k_join_small, in us: 64 KB 5,000 points 13.2 and 13.2, 1,000 13.7 and 11.9; 120 KB 20,000 points 27.0 and 31.9, 5,000 19.2 and 19.3;
 // 128 KB 20,000 18.8 and 19.5, 5,000 18.7 and 17.0; 48 KB 5,000 12.2 and 14.1, 1,000 12.4 and 12.7; 16 KB 1,000 10.8 and 12.7).
-int few_groups(int64_t n, int64_t nQ, int nkb) {
+// Lists of which a wavefront stages only 128 results: up to a capacity that they can stage; past it the atomics, one after the other at one address, are longer
+// than what is saved (before and here, us: 100,000 x 120, d = 530, 69 results a wavefront 45.4 and 37.4, 200 49.9 and 56.3, 1,107 122 and 211; 20,000 x 60, d = 512,
+// 82 25.3 and 15.7, 358 33.3 and 35.5, 1,393 64.7 and 102.9).
+int few_workgroups(const ejoin_ctx* ctx, int64_t n, int rf, int lds_bytes) {
+  const int64_t panels = (n + TILE - 1) / TILE, most = (int64_t)ctx->num_cu * few_groups_per_cu(rf, lds_bytes), rounds = (panels + most - 1) / most;
+  return (int)((panels + rounds - 1) / rounds);
+}
+template <bool COUNT>
+int few_groups(const ejoin_ctx* ctx, int64_t n, int64_t nQ, int nkb, unsigned long long capacity) {
 #if defined(EJOIN_ONLY_K_JOIN) || defined(EJOIN_ONLY_K_JOIN_STRIP)
   return 0;
 #endif
   if (nQ > 256) return 0;
   const int rf = nQ <= 32 ? 2 : (nQ <= 64 ? 4 : (nQ <= 128 ? 8 : 16));
-  return few_lds_bytes<false>(16 * rf, nkb, few_staged(rf, nkb)) <= FEW_LDS && n >= 150ll * (rf * nkb - 24) ? rf : 0;
+  const int staged = few_staged(rf, nkb), lds_bytes = few_lds_bytes<false>(16 * rf, nkb, staged);
+  if (lds_bytes > FEW_LDS || n < 150ll * (rf * nkb - 24)) return 0;
+  return !COUNT && staged == 128 && capacity > 128ull * FEW_WAVES * few_workgroups(ctx, n, rf, lds_bytes) ? 0 : rf;
 }
 template <bool COUNT>
 int run_few(ejoin_ctx* ctx, const Workspace& w, const ejoin_set* P, int rf, int nkb, const uint16_t* XQ, int64_t nQ, int64_t ldQ, float eps, const Results& r,
@@ -3759,8 +3769,7 @@ int run_few(ejoin_ctx* ctx, const Workspace& w, const ejoin_set* P, int rf, int 
   ctx->last_status = w.status;
   ctx->last_stream = st;
   const int staged = few_staged(rf, nkb), lds_bytes = few_lds_bytes<COUNT>(16 * rf, nkb, staged);
-  const int64_t panels = P->pad / TILE, most = (int64_t)ctx->num_cu * few_groups_per_cu(rf, lds_bytes);
-  const int64_t rounds = (panels + most - 1) / most, groups = (panels + rounds - 1) / rounds;
+  const int groups = few_workgroups(ctx, P->n, rf, lds_bytes);
   const FewArgs a{P->Xp, P->s, P->max_bits, P->n, nkb, XQ, nQ, ldQ, -0.5f * (eps * eps), w.status, r.pairs, r.dist2, r.capacity,
                   reinterpret_cast<unsigned long long*>(r.n_pairs), (uint32_t)staged, r.counts, r.counts_b, reinterpret_cast<unsigned long long*>(r.total),
                   reinterpret_cast<unsigned long long*>(ctx->once), reinterpret_cast<uint32_t*>(ctx->once + ONCE_STATE_BYTES) + NUM_XCD * ONCE_SLOTS};
@@ -3782,7 +3791,7 @@ int run_join_prepared(ejoin_ctx* ctx, const ejoin_set* P, const uint16_t* XQ, in
   EJ_RC(ensure_workspace(ctx, padQ, pad_dims(d)));
   const Workspace& w = ctx->ws;
   const int nkb = k_blocks(d);
-  if (const int rf = few_groups(P->n, nQ, nkb)) return run_few<COUNT>(ctx, w, P, rf, nkb, XQ, nQ, ldQ, eps, r, st);
+  if (const int rf = few_groups<COUNT>(ctx, P->n, nQ, nkb, r.capacity)) return run_few<COUNT>(ctx, w, P, rf, nkb, XQ, nQ, ldQ, eps, r, st);
   PrepSet SP{nullptr, P->n, P->pad, 0, P->s, P->Xp, 0}, SQ{XQ, nQ, padQ, ldQ, w.s, w.Xp, 0};
   if (const int tile = small_tile(ctx, P->n, nQ, false, nkb)) return run_small<COUNT>(ctx, w, tile, SP, SQ, P->max_bits, nkb, eps, r, st);
   EJ_RC(begin_call(ctx, w, true, st));

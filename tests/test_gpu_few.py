@@ -41,12 +41,13 @@ def test_number_of_query_points(both, nq, d):
     compare(both, P, Q, epsilon(P, d, 0.002), d)
 
 
+@pytest.mark.parametrize("share", [0.03, 0.3])
 @pytest.mark.parametrize("nq, d", [(60, 416), (60, 448), (60, 512), (60, 544), (60, 1056), (60, 1152), (120, 512), (120, 544)])
-def test_staged_results(both, nq, d):
-    """The dimensions where a wavefront stages half as many results, or the LDS is full; more results than either holds."""
-    print(f"few staged nq={nq} d={d}", flush=True)
+def test_staged_results(both, nq, d, share):
+    """The dimensions where a wavefront stages half as many results, or the LDS is full; capacities to either side of what they stage."""
+    print(f"few staged nq={nq} d={d} share={share}", flush=True)
     P, Q = rows(20011, d, seed=d), rows(nq, d, seed=d + nq)
-    compare(both, P, Q, epsilon(P, d, 0.3), d)
+    compare(both, P, Q, epsilon(P, d, share), d)
 
 
 @pytest.mark.parametrize("share", [0.02, 1.0])
