@@ -2714,6 +2714,8 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
     const uint32_t first = own - lane;
     if (lane < NUM_XCD && first < (col ? nnB : nnA))
       __hip_atomic_store(args.slot + lane * ONCE_SLOTS + (col ? args.slots_a : 0u) + first / 64, most | ONCE_FILLED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // before the ticket, after which the slots are cleared (not every copy has a reader, and barriers do not wait for stores)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   bool missing;
   uint32_t mb = look_at_slots(args.slot, args.slots, L::THREADS, EJOIN_ONCE_SPINS, missing);

@@ -78,6 +78,22 @@ def test_norms_of_very_different_sizes(general, once):
         same_pairs(general.selfjoin_pairs(X, eps, cap, d=96), once.selfjoin_pairs(X, eps, cap, d=96))
 
 
+def test_joins_of_two_sets_in_a_few_tiles_leave_nothing_for_the_next(general, once):
+    """Two to seven tiles fill slots in copies that no workgroup of theirs reads; the next join has more workgroups and far smaller norms."""
+    X = rows(1500, 96, seed=8) * 0.004
+    eps = 0.01
+    cap = 1500 + int(general.selfjoin_count(X, eps, d=96)[1])
+    want = general.selfjoin_pairs(X, eps, cap, d=96), general.selfjoin_count(X, eps, d=96)
+    for n, nq in ((60, 100), (60, 200), (100, 200), (30, 300), (300, 30), (180, 100), (1, 440)) * 5:
+        P, Q = rows(n, 96, seed=n), rows(nq, 96, seed=nq) * 50
+        for u, v in zip(general.join_count(P, Q, 200.0, d=96), once.join_count(P, Q, 200.0, d=96)):
+            assert torch.equal(u, v)
+        same_pairs(want[0], once.selfjoin_pairs(X, eps, cap, d=96))
+        once.join_pairs(P, Q, 200.0, n * nq, d=96)
+        for u, v in zip(want[1], once.selfjoin_count(X, eps, d=96)):
+            assert torch.equal(u, v)
+
+
 @pytest.mark.parametrize("n", [300, 3000])
 def test_a_list_that_is_cut_off(once, n):
     X = rows(n, 64, seed=3)
