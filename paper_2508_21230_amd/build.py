@@ -42,9 +42,10 @@ GENERAL_KERNEL_LIB = os.path.join(ABLATION_DIR, "libejoin_general_kernel.so")
 STRIP_KERNEL = {"strip_kernel": ["-DEJOIN_ONLY_K_JOIN_STRIP"]}
 STRIP_KERNEL_LIB = os.path.join(ABLATION_DIR, "libejoin_strip_kernel.so")
 
-#: ... and the one whose one-launch joins wait for none of their workgroups, so that (nearly) all are late
-LATE = {"once_late": ["-DEJOIN_ONCE_SPINS=0"]}
+#: ... and the ones whose one-launch kernels wait for none of their workgroups, so that (nearly) all are late, and miss every third of their norms
+LATE = {"once_late": ["-DEJOIN_ONCE_SPINS=0"], "once_blind": ["-DEJOIN_ONCE_BLIND=3"]}
 LATE_LIB = os.path.join(ABLATION_DIR, "libejoin_once_late.so")
+BLIND_LIB = os.path.join(ABLATION_DIR, "libejoin_once_blind.so")
 
 
 def _compile(out: str, defines=(), verbose: bool = False) -> str:

@@ -180,26 +180,43 @@ __device__ __forceinline__ bool close_by_xcd(unsigned long long* state, uint32_t
   *state = 0;
   return true;
 }
+// Looks at empty slots, of a thread at all of its own together, before it gives up; each is a load past the L2.  Where the GPU is shared the slots may be filled
+// only once others' work has ended, and a workgroup that waits keeps its LDS from them; what it does instead, the norms of the points of the empty slots, is not
+// much longer (every workgroup without waiting, and with a third of the slots empty to it: 1,000 x 96 15 and 13 us a call, 3,900 x 960 228 and 158, 3,900 x 4,096 919 and
+// 633; 95.8 with all slots seen).  (Builds for the tests: EJOIN_ONCE_SPINS=0 waits for nothing, EJOIN_ONCE_BLIND=m takes every m-th slot for empty.)
 #ifndef EJOIN_ONCE_SPINS
-#define EJOIN_ONCE_SPINS 2048  // (a build for the tests waits for nothing)
+#define EJOIN_ONCE_SPINS 256
 #endif
 constexpr uint32_t ONCE_FILLED = 0x80000000u;
+constexpr int ONCE_EMPTY_WORDS = ONCE_SLOTS / 32;
 // The largest norm in the slots, of what this thread reads of them, for threads of `threads`; missing: one of them is still empty
-// after `spins` more looks.
-__device__ __forceinline__ uint32_t look_at_slots(const uint32_t* slot, uint32_t slots, uint32_t threads, int spins, bool& missing) {
+// after `spins` more looks.  empty (LDS, ONCE_EMPTY_WORDS words that are zero, may be null): a bit for each of those.
+__device__ __forceinline__ uint32_t look_at_slots(const uint32_t* slot, uint32_t slots, uint32_t threads, int spins, bool& missing, uint32_t* empty = nullptr) {
   uint32_t most = 0;
   missing = false;
   slot += blockIdx.x % EJ_NUM_XCD * ONCE_SLOTS;
   for (uint32_t q = threadIdx.x; q < slots; q += threads) {
     uint32_t v = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int spin = 0; v == 0 && spin < spins; ++spin) {
+    for (; v == 0 && spins > 0; --spins) {
       __builtin_amdgcn_s_sleep(1);
       v = __hip_atomic_load(slot + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    missing |= v == 0;
+#ifdef EJOIN_ONCE_BLIND
+    if (empty && q % EJOIN_ONCE_BLIND == 1) v = 0;
+#endif
+    if (v == 0) {
+      missing = true;
+      if (empty) atomicOr(empty + q / 32, 1u << (q % 32));
+    }
     most = max(most, v & ~ONCE_FILLED);
   }
   return most;
+}
+// f(q) for every empty slot q, by all threads of the workgroup.  (Behind a barrier.)
+template <typename F>
+__device__ __forceinline__ void for_empty_slots(const uint32_t* empty, uint32_t slots, F f) {
+  for (uint32_t word = 0; word * 32 < slots; ++word)
+    for (uint32_t bits = __builtin_amdgcn_readfirstlane(empty[word]); bits; bits &= bits - 1) f(word * 32 + (uint32_t)__builtin_ctz(bits));
 }
 
 // Diagonal of the 16 x 16 Gram block of points row0 .. row0 + 15, whose element (row, col) sits in lane col + 16 * (row / 4),
@@ -831,11 +848,13 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
   }
   if constexpr (ONE) {
     if (!there) {
+      uint32_t* empty = reinterpret_cast<uint32_t*>(lds + AUG);
+      if (tid < ONCE_EMPTY_WORDS) empty[tid] = 0;
+      __syncthreads();
       bool missing;
-      mb = look_at_slots(one.slot, one.norm_groups, 64 * WAVES, EJOIN_ONCE_SPINS, missing);
-      if (__syncthreads_or(missing)) {  // workgroups that have not been started: all norms by this one
-        mb = 0;
-        for (int64_t row0 = wave * 16; row0 < a.n; row0 += WAVES * 16) mb = max(mb, norms_from(row0));
+      mb = look_at_slots(one.slot, one.norm_groups, 64 * WAVES, EJOIN_ONCE_SPINS, missing, empty);
+      if (__syncthreads_or(missing)) {  // workgroups that have not been started: their norms by this one
+        for_empty_slots(empty, one.norm_groups, [&](uint32_t q) { mb = max(mb, norms_from(((int64_t)q * WAVES + wave) * 16)); });
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
       }
@@ -2563,7 +2582,7 @@ __global__ __launch_bounds__(256, small_groups_per_cu<TS>()) void k_join_small(c
 //   * The scale of the norm terms comes from the largest norm of all points.  The workgroups on the diagonal (two sets: of the first
 //     row and column of tiles) put the largest norm of every 64 of their points into a slot each, and every workgroup reads all the
 //     slots before its augmentation step.  It waits for them a bounded number of times only: workgroups that the GPU has not started
-//     yet may be behind others that wait for this kernel's.  Past that it works the largest norm out by itself (`late`).
+//     yet may be behind others that wait for this kernel's.  Past that it works out by itself what is missing (`late`).
 //     The slots are there once for every XCD, so that no line has more than an eighth of the readers (4,096 x 128: one copy 18.3 us,
 //     eight 16.4, thirty-two 16.9, without the wait 14.8).
 //   * Counts are cleared by the workgroups that fill those rows' slots, before they do, so whoever has seen all slots may add to them.  A late
@@ -2600,7 +2619,7 @@ struct Once {
   // after the last slice, where the stages were: the norms, staged results or counters, the operands of the augmentation step
   static constexpr int TAIL = 2 * TS * 4, AUG = TAIL + WAVES * SMALL_STG_CAP * 12, AUG_B = AUG + TS * 16, AUG_CONST = AUG_B + TS * 16;
   static constexpr int SUMS = STAGES * STAGE, LDS = SUMS + 128;
-  static_assert(AUG_CONST + 64 <= SUMS && LDS * ONCE_GROUPS_PER_CU <= 152 * 1024, "LDS budget");
+  static_assert(ONCE_EMPTY_WORDS * 4 <= TS * 16 && ONCE_EMPTY_WORDS <= THREADS && AUG_CONST + 64 <= SUMS && LDS * ONCE_GROUPS_PER_CU <= 152 * 1024, "LDS budget");
 };
 template <bool COUNT, int TS>
 __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::WAVES / 4) void k_join_once(const OnceArgs args) {
@@ -2703,6 +2722,8 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
     uint32_t* cnt = reinterpret_cast<uint32_t*>(lds + L::TAIL);
     if (tid < 2 * TS) cnt[tid] = 0;
   }
+  uint32_t* empty = reinterpret_cast<uint32_t*>(lds + L::AUG);
+  if (tid < ONCE_EMPTY_WORDS) empty[tid] = 0;
   __syncthreads();
 
   // ---- the largest norm of all
@@ -2718,15 +2739,18 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   bool missing;
-  uint32_t mb = look_at_slots(args.slot, args.slots, L::THREADS, EJOIN_ONCE_SPINS, missing);
+  uint32_t mb = look_at_slots(args.slot, args.slots, L::THREADS, EJOIN_ONCE_SPINS, missing, empty);
   const bool late = __syncthreads_or(missing);
   if (late) {
-    mb = 0;
-    for (int64_t row0 = wave * 32; row0 < a.nA; row0 += L::WAVES * 32)
-      mb = max(mb, norms_of_wave<false>(row0, args.XA, a.nA, args.ldA, nkb, args.sA, nullptr, 0));
-    if (!a.self)
-      for (int64_t row0 = wave * 32; row0 < a.nB; row0 += L::WAVES * 32)
-        mb = max(mb, norms_of_wave<false>(row0, args.XB, a.nB, args.ldB, nkb, args.sB, nullptr, 0));
+    uint32_t half = 0;  // 32 points a wavefront, in turn
+    for_empty_slots(empty, args.slots, [&](uint32_t q) {
+      const bool second = q >= args.slots_a;
+      const int64_t row0 = (int64_t)(second ? q - args.slots_a : q) * 64;
+      for (int h = 0; h < 2; ++h)
+        if (half++ % L::WAVES == (uint32_t)wave && row0 + 32 * h < (second ? a.nB : a.nA))
+          mb = max(mb, norms_of_wave<false>(row0 + 32 * h, second ? args.XB : args.XA, second ? a.nB : a.nA, second ? args.ldB : args.ldA, nkb,
+                                            second ? args.sB : args.sA, nullptr, 0));
+    });
   }
   const NormScale ns = norm_scale(max_of_group(mb));
   if (blockIdx.x == 0 && tid == 0) a.status[0] = ns.st;

@@ -1,5 +1,5 @@
 """The join of the smallest problems, in one launch, against the general kernel: pairs, squared distances bit for bit, counts and status;
-each by a workgroup that waits for the others' norms, and by one that does not and works the largest norm out by itself."""
+each by workgroups that wait for the others' norms, by ones that do not and work (nearly) all of them out, and by ones that miss every third."""
 import pytest
 import torch
 
@@ -18,9 +18,9 @@ def general():
     e.close()
 
 
-@pytest.fixture(scope="module", params=["waits", "late"])
+@pytest.fixture(scope="module", params=["waits", "late", "blind"])
 def once(request):
-    e = pkg.EJoin(0) if request.param == "waits" else parity.variant_context(build.LATE_LIB)
+    e = pkg.EJoin(0) if request.param == "waits" else parity.variant_context({"late": build.LATE_LIB, "blind": build.BLIND_LIB}[request.param])
     yield e
     e.close()
 
