@@ -17,6 +17,7 @@
 #include "ejoin.h"
 #include "ejoin_bench.h"
 #include "panel_layout.h"
+#include "rules.h"
 #include "tile_cursor.h"
 
 namespace {
@@ -302,14 +303,12 @@ __device__ __forceinline__ uint32_t norms_of_wave(int64_t row0, const uint16_t* 
   return most;
 }
 
-template <bool PACK, int HALVES = 2>
+template <bool PACK, int HALVES = 2, bool FROM_THE_END = false>
 __global__ __launch_bounds__(512) void k_norms(const uint16_t* __restrict__ X, int64_t n, int64_t npad, int64_t ld, int k32steps,
                                                float* __restrict__ s, uint32_t* __restrict__ max_bits, uint4* __restrict__ Xp,
                                                int blocks /* k-blocks per panel of Xp: k32steps + 1 */,
                                                uint32_t* __restrict__ maxima /* one per workgroup (may be null) */) {
-  // Norms alone, from the last point on: of rows that have just been written, more than the memory-side cache holds, those are still in
-  // it (10^6 x 200 converted, then normed: 331 us, now 309)
-  const uint32_t group = HALVES == 1 ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+  const uint32_t group = FROM_THE_END ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
   const int64_t row0 = ((int64_t)group * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (16 * HALVES);
   uint32_t most = 0;
   if (row0 < (PACK ? npad : n)) most = norms_of_wave<PACK, HALVES>(row0, X, n, ld, k32steps, s, Xp, blocks);
@@ -3348,7 +3347,8 @@ int launch_norms(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, int64_
                  hipStream_t st, uint32_t* maxima = nullptr, uint32_t* nmaxima = nullptr) {
   const int64_t npad = pad_rows(n);
   if (!Xp && !max_bits && !maxima && n < (1ll << 30)) {  // norms alone (a grid has fewer than 2^32 threads)
-    hipLaunchKernelGGL((k_norms<false, 1>), dim3((unsigned)((n + 15) / 16)), dim3(64), 0, st, X, n, npad, ld, k_blocks(d), s, max_bits, Xp, 0, maxima);
+    hipLaunchKernelGGL((norms_from_the_end(n, ld) ? k_norms<false, 1, true> : k_norms<false, 1>), dim3((unsigned)((n + 15) / 16)), dim3(64), 0, st, X, n, npad, ld,
+                       k_blocks(d), s, max_bits, Xp, 0, maxima);
     EJ_TRY(hipGetLastError());
     return EJOIN_OK;
   }

@@ -32,3 +32,16 @@ def test_conversion_by_size_and_alignment(n, d, ld, offset):
     for r in range(0, n, 1 << 18):
         want = ((X[r:r + (1 << 18)] - center) * 1.7).half()
         assert torch.equal(got[r:r + (1 << 18), :d].view(torch.int16), want.view(torch.int16))
+
+
+# the last set normed from its first point on and the first normed from its last (240 MB of rows), ragged
+@pytest.mark.parametrize("n,d", [(1966080, 20), (1966081, 20), (2200003, 64), (300001, 400)])
+def test_norms_in_either_order_of_the_points(n, d):
+    """Those of parts of the set, to the bit."""
+    print(f"norms n={n} d={d}", flush=True)
+    e = pkg.EJoin(0)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    X = e.convert_f32(torch.randn(n, d, generator=gen, device="cuda"))
+    s = e.norms(X, d=d)
+    for r in range(0, n, 99991):
+        assert torch.equal(s[r:r + 99991], e.norms(X[r:r + 99991], d=d))
