@@ -2920,6 +2920,11 @@ __global__ __launch_bounds__(Once<TS>::THREADS, ONCE_GROUPS_PER_CU * Once<TS>::W
 // 400,000 x 384 104.9, now 60.5 (floor 63); 8 against 400,000 x 960 194, now 133; 60 201, now 189.
 // Up to 64 query points two workgroups a CU and chunks of two k-blocks (60 against 400,000 x 384: one workgroup and chunks of four 78, of eight 77); more take
 // the registers of one.
+// Lists: a wavefront stages its results.  Those of a panel that do not fit stay in registers, as hits and distances, until their place in the result is known, by one
+// atomic for them and what is staged; of a wavefront's last panel that is the workgroup's, with its ticket.  One atomic for every 256 results cost dense
+// lists more than the rest (they are served one after the other; all wavefronts are full at the same time).  Before that, with an atomic for as many as are
+// staged, and now, us: 100,000 x 120, d = 300, 4, 14 and 76 % of all pairs 46.4, 43.7 and 38.0; 108, 96 and 61; 482, 467 and 89; 60,000 x 200, d = 128,
+// 66, 31 and 24; 184, 95 and 33; 1,110, 461 and 55; 400,000 x 60, d = 384, 235, 95 and 88; 456, 222 and 159; 2,263, 958 and 197.
 // The arithmetic is k_join_strip's with the sets exchanged, step by step, and the results its bits.
 struct FewArgs {
   const uint4* Xp;
@@ -2951,15 +2956,18 @@ constexpr int FEW_WAVES = 8;
 // the query points, their norms, part of the augmentation step and counters, the constants of that step, staged results
 template <bool COUNT>
 constexpr int few_lds_bytes(int rows, int nkb, int staged) { return rows * (nkb * 64 + 4 + 16 + 4) + 64 + 64 + (COUNT ? 0 : FEW_WAVES * staged * 12); }
-// Results that a wavefront stages, one atomic for as many: 256, or 128 (at least 64, what one append adds) where the 12 KB more would cost a workgroup of the CU
-// or the place in LDS.  Lists with 128 and with 256, us: 20,000 points x 250 queries, d = 64, 2.6 % of all pairs 22.1 and 17.2 (k_join_small 18.3), 20,000 x 30, d = 300,
-// 76 % 52.0 and 28.4 (39.2); with a workgroup less 300,000 x 60, d = 512 57.6 and 71.4; by other kernels for want of place 100,000 x 60, d = 1080 47.3 and 61.7.
+// Results that a wavefront stages: 256, or 64 or 128 fewer where the LDS for them would cost a workgroup of the CU or the place in LDS (at least 64, what one append
+// adds).  Lists with 128 and with 256, us: 100,000 points x 120 queries, d = 300, 4 % of all pairs 47.0 and 38.0, 20,000 x 30, d = 300, 14 % 14.1 and 13.4; with a
+// workgroup less 300,000 x 60, d = 512 61.3 and 72.3.
 constexpr int few_staged(int rf, int nkb) {
-  const int more = few_lds_bytes<false>(16 * rf, nkb, 256), less = few_lds_bytes<false>(16 * rf, nkb, 128);
-  return more <= FEW_LDS && few_groups_per_cu(rf, more) == few_groups_per_cu(rf, less) ? 256 : 128;
+  const int groups = few_groups_per_cu(rf, few_lds_bytes<false>(16 * rf, nkb, 128));
+  int staged = 256;
+  while (staged > 128 && (few_lds_bytes<false>(16 * rf, nkb, staged) > FEW_LDS || few_groups_per_cu(rf, few_lds_bytes<false>(16 * rf, nkb, staged)) < groups)) staged -= 64;
+  return staged;
 }
+// (waves_per_eu: without the upper bound the instances of up to 64 query points save registers for a fifth wavefront, one operand in flight at a time: + 0.3 us)
 template <bool COUNT, int RF>
-__global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(const FewArgs a) {
+__global__ __launch_bounds__(64 * FEW_WAVES) __attribute__((amdgpu_waves_per_eu(RF <= 4 ? 4 : 2, RF <= 4 ? 4 : 2))) void k_join_few(const FewArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char lds[];
   constexpr int ROWS = 16 * RF, NR = RF / 2, CHUNK = few_chunk<RF>();
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, g = lane >> 4;
@@ -3036,9 +3044,15 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
   const uint4 column_constant = *reinterpret_cast<const uint4*>(constants + 16 * ((lane >> 4) & 1));
 
   uint32_t fill = 0;             // (pairs) staged, uniform
+  unsigned long long base = 0;   // (pairs) where what is staged goes, once that is known
+  uint32_t hits[(NR + 1) / 2];   // (pairs) of the last 32 points, those that are not staged: two regions a word
+  uint32_t left = 0, left_j0 = 0;  // (pairs) how many of those wait for the workgroup's atomic, and the first of the points
   unsigned long long found = 0;  // (counts) of this lane
   const uint32_t thr_bits = __float_as_uint(a.thr) | 0x80000000u;  // (x >= thr on the bit patterns, see k_join)
-  auto store_staged = [&](unsigned long long base) {
+  auto uniform = [](unsigned long long x) {
+    return ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(x >> 32)) << 32) | __builtin_amdgcn_readfirstlane((uint32_t)x);
+  };
+  auto store_staged = [&]() {
     for (uint32_t e = lane; e < fill; e += 64) {
       const unsigned long long idx = base + e;
       if (idx < a.capacity) {
@@ -3046,16 +3060,10 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
         if (a.dist2) a.dist2[idx] = __uint_as_float(stg[3 * e + 2]);
       }
     }
+    base += fill;
     fill = 0;
   };
   auto append = [&](unsigned long long mask, bool pass, uint32_t i, uint32_t j, uint32_t d2_bits) {
-    const uint32_t more = __popcll(mask);
-    if (fill + more > a.staged) {
-      unsigned long long base = 0;
-      if (lane == 0) base = atomicAdd(a.state, (unsigned long long)fill) & ONCE_FOUND;
-      const uint32_t blo = __builtin_amdgcn_readfirstlane((uint32_t)base), bhi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-      store_staged(((unsigned long long)bhi << 32) | blo);
-    }
     const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
     if (pass) {
       const uint32_t e = fill + rank;
@@ -3063,8 +3071,11 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
       stg[3 * e + 1] = j;
       stg[3 * e + 2] = d2_bits;
     }
-    fill += more;
+    fill += __popcll(mask);
   };
+  // Data out of range: nothing is found.  (Lists: by the same code, in the first panel; a branch past it would have acc cleared twice, 0.3 us of a call.)
+  const bool none = !COUNT && __builtin_amdgcn_readfirstlane(ns.st) != ST_OK;
+  const uint32_t end = none ? 0u : panels, reach = none ? 0u : n;
   float4v acc[RF][2];
   auto clear = [&]() {
 #pragma unroll
@@ -3073,44 +3084,88 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
       for (int c = 0; c < 2; ++c) acc[f][c] = float4v{0.f, 0.f, 0.f, 0.f};
   };
   clear();
+  // (pairs) the results in `hits` and acc, of 32 points from j0 on; their place is known
+  auto emit = [&](uint32_t j0) __attribute__((always_inline)) {
+    uint32_t l = lane;
+    asm volatile("" : "+v"(l));  // (nothing of this is worked out before the loop over the points)
+    const uint32_t r16 = l & 15, g = l >> 4;
+#pragma unroll
+    for (int R = 0; R < NR; ++R) {
+      uint32_t h = R & 1 ? hits[R / 2] >> 16 : hits[R / 2] & 0xFFFFu;
+      for (unsigned long long mask = __ballot(h != 0); mask; mask = __ballot(h != 0)) {
+        if (fill + __popcll(mask) > a.staged) store_staged();
+        const uint32_t r = (uint32_t)__builtin_ctz(h | 0x10000u);
+        append(mask, h != 0, j0 + r16 + 4 * (r & 4u), 32 * R + 4 * g + 2 * (r & 8u) + (r & 3u),
+               __float_as_uint(fmaxf(-2.f * pick(cat4(acc[2 * R][0], acc[2 * R][1], acc[2 * R + 1][0], acc[2 * R + 1][1]), r), 0.f)));
+        h &= h - 1;
+      }
+    }
+  };
   // the products of 32 points from j0 on are complete: the norm terms, the filter, the results
-  auto finish = [&](uint32_t j0, float s0, float s1) __attribute__((always_inline)) {
+  auto finish = [&](uint32_t j0, float s0, float s1, bool last) __attribute__((always_inline)) {
     const uint32_t j = j0 + r16;
     uint2 p = make_uint2(P1_OUT_OF_RANGE, 0u), q = p;
     if (j < n) p = norm_pieces(s0, ns.m);
     if (j + 16 < n) q = norm_pieces(s1, ns.m);
     const half8 gb = as_half8(lane < 32 ? make_uint4(p.x, p.y, q.x, q.y) : column_constant);
     uint32_t first = 0, second = 0;  // (counts) of points j and j + 16
+    bool full = false;               // (pairs) the rest have to wait for their place
 #pragma unroll
     for (int R = 0; R < NR; ++R) {
+      if (!COUNT && R % 2 == 0) hits[R / 2] = 0;
       const half8 ga = *reinterpret_cast<const half8*>(row_operand + R * row_step);
       const float16v v = __builtin_amdgcn_mfma_f32_32x32x16_f16(ga, gb, cat4(acc[2 * R][0], acc[2 * R][1], acc[2 * R + 1][0], acc[2 * R + 1][1]), 0, 0, 0);
+      if constexpr (!COUNT) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[2 * R + q / 2][q % 2] = float4v{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+      }
       auto u = [&](int r) { return __float_as_uint(v[r]); };
       uint32_t least = min(min(u(0), u(1)), u(2));
 #pragma unroll
       for (int r = 3; r < 15; r += 2) least = min(min(least, u(r)), u(r + 1));
       if (__ballot(min(least, u(15)) <= thr_bits) == 0) continue;
-      uint32_t hit = 0;
+      uint32_t h = 0;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) hit |= v[r] >= a.thr ? 1u << r : 0u;
-      hit &= (32 * R + 32 <= nq ? 0xFFFFu : (32 * R < nq ? edge_mask : 0u)) & ((j < n ? 0x0F0Fu : 0u) | (j + 16 < n ? 0xF0F0u : 0u));
+      for (int r = 0; r < 16; ++r) h |= v[r] >= a.thr ? 1u << r : 0u;
+      h &= (32 * R + 32 <= nq ? 0xFFFFu : (32 * R < nq ? edge_mask : 0u)) & ((j < reach ? 0x0F0Fu : 0u) | (j + 16 < reach ? 0xF0F0u : 0u));
       if constexpr (COUNT) {
-        first += __popc(hit & 0x0F0Fu);
-        second += __popc(hit & 0xF0F0u);
-        while (__ballot(hit != 0)) {
-          if (hit) {
-            const uint32_t r = (uint32_t)__builtin_ctz(hit);
+        first += __popc(h & 0x0F0Fu);
+        second += __popc(h & 0xF0F0u);
+        while (__ballot(h != 0)) {
+          if (h) {
+            const uint32_t r = (uint32_t)__builtin_ctz(h);
             atomicAdd(row_counts + 32 * R + 4 * g + 2 * (r & 8u) + (r & 3u), 1u);
-            hit &= hit - 1;
+            h &= h - 1;
           }
         }
       } else {
-        for (unsigned long long mask = __ballot(hit != 0); mask; mask = __ballot(hit != 0)) {
-          const uint32_t r = (uint32_t)__builtin_ctz(hit | 0x10000u);
-          append(mask, hit != 0, j + 4 * (r & 4u), 32 * R + 4 * g + 2 * (r & 8u) + (r & 3u), __float_as_uint(fmaxf(-2.f * pick(v, r), 0.f)));
-          hit &= hit - 1;
+        for (unsigned long long mask = __ballot(h != 0); mask && !full; mask = __ballot(h != 0)) {
+          full = fill + __popcll(mask) > a.staged;
+          if (full) break;
+          const uint32_t r = (uint32_t)__builtin_ctz(h | 0x10000u);
+          append(mask, h != 0, j + 4 * (r & 4u), 32 * R + 4 * g + 2 * (r & 8u) + (r & 3u), __float_as_uint(fmaxf(-2.f * pick(v, r), 0.f)));
+          h &= h - 1;
         }
+        hits[R / 2] |= R & 1 ? h << 16 : h;
       }
+    }
+    if constexpr (!COUNT) {
+      if (!full) return;
+      uint32_t own = 0, more = 0;  // of this lane (at most 16 a region), of the wavefront
+#pragma unroll
+      for (int q = 0; q < (NR + 1) / 2; ++q) own += __popc(hits[q]);
+#pragma unroll
+      for (int bit = 1; bit <= 16 * NR; bit *= 2) more += bit * __popcll(__ballot(own & bit));
+      if (last) {  // the workgroup's one atomic is next
+        left = more;
+        left_j0 = j0;
+        return;
+      }
+      unsigned long long place = 0;
+      if (lane == 0) place = atomicAdd(a.state, (unsigned long long)(fill + more)) & ONCE_FOUND;
+      base = uniform(place);
+      emit(j0);
+      store_staged();
     }
     if constexpr (COUNT) {
       found += first + second;
@@ -3140,16 +3195,17 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
       }
     }
     if (ends) {
-      if (panel * TILE + wave * 32 < n) finish(panel * TILE + wave * 32, point_norm[B][0], point_norm[B][1]);
-      clear();
+      const bool last = next_panel >= end;
+      if (panel * TILE + wave * 32 < n) finish(panel * TILE + wave * 32, point_norm[B][0], point_norm[B][1], last);
+      if (COUNT || !last) clear();
     }
     panel = next_panel;
     chunk = next_chunk;
-    return panel < panels;
+    return panel < end;
   };
-  if (ns.st == ST_OK) {
+  if (!COUNT || ns.st == ST_OK) {
     while (step(std::integral_constant<int, 0>{}) && step(std::integral_constant<int, 1>{})) {}
-  } else if (COUNT) {  // data out of range: nothing is found
+  } else {  // data out of range: nothing is found
     for (; panel < panels; panel += gridDim.x)
       if (tid < TILE && panel * TILE + tid < n) a.counts_p[panel * TILE + tid] = 0;
   }
@@ -3158,14 +3214,14 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
   if constexpr (COUNT) {
     found = wave_sum((uint32_t)found) + ((unsigned long long)wave_sum((uint32_t)(found >> 32)) << 32);
   }
-  if (lane == 0) sums[wave] = COUNT ? found : fill;
+  if (lane == 0) sums[wave] = COUNT ? found : fill + left;
   __syncthreads();
   if constexpr (COUNT) {
     if ((uint32_t)tid < nq && tid < ROWS && row_counts[tid] && a.counts_q) atomicAdd(a.counters + tid, row_counts[tid]);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // before the ticket
   }
   __syncthreads();
-  __shared__ unsigned long long base;
+  __shared__ unsigned long long group_base;
   __shared__ bool last;
   if (tid == 0) {
     unsigned long long sum = 0, all = 0;
@@ -3174,14 +3230,18 @@ __global__ __launch_bounds__(64 * FEW_WAVES, RF <= 4 ? 4 : 2) void k_join_few(co
       sums[w] = sum;
       sum += v;
     }
-    if (!COUNT) base = sum ? atomicAdd(a.state, sum) & ONCE_FOUND : 0;
+    if (!COUNT) group_base = sum ? atomicAdd(a.state, sum) & ONCE_FOUND : 0;
     if (!COUNT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const unsigned long long add = ONCE_TICKET | (COUNT ? sum : 0);
     last = close_by_xcd(a.state, gridDim.x, atomicAdd(state_of_xcd(a.state), add) + add, all);
     if (last) *(COUNT ? a.total : a.n_pairs) = all & ONCE_FOUND;
   }
   __syncthreads();
-  if (!COUNT) store_staged(base + sums[wave]);
+  if constexpr (!COUNT) {
+    base = uniform(group_base + sums[wave]);
+    if (left) emit(left_j0);
+    store_staged();
+  }
   if (COUNT && last && a.counts_q && (uint32_t)tid < nq)
     a.counts_q[tid] = __hip_atomic_exchange(a.counters + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -3770,23 +3830,18 @@ FewKernel few_kernel(int rf) { return rf == 2 ? &k_join_few<COUNT, 2> : rf == 4 
 // the LDS, and every workgroup fills it anew, 1 KB a group and k-block: the more of them, the more points it takes (start of the call to
 // its end, here and by k_prep and k_join_small, in us: 64 KB 5,000 points 13.2 and 13.2, 1,000 13.7 and 11.9; 120 KB 20,000 points 27.0 and 31.9, 5,000 19.2 and 19.3;
 // 128 KB 20,000 18.8 and 19.5, 5,000 18.7 and 17.0; 48 KB 5,000 12.2 and 14.1, 1,000 12.4 and 12.7; 16 KB 1,000 10.8 and 12.7).
-// Lists of which a wavefront stages only 128 results: up to a capacity that they can stage; past it the atomics, one after the other at one address, are longer
-// than what is saved (before and here, us: 100,000 x 120, d = 530, 69 results a wavefront 45.4 and 37.4, 200 49.9 and 56.3, 1,107 122 and 211; 20,000 x 60, d = 512,
-// 82 25.3 and 15.7, 358 33.3 and 35.5, 1,393 64.7 and 102.9).
 int few_workgroups(const ejoin_ctx* ctx, int64_t n, int rf, int lds_bytes) {
   const int64_t panels = (n + TILE - 1) / TILE, most = (int64_t)ctx->num_cu * few_groups_per_cu(rf, lds_bytes), rounds = (panels + most - 1) / most;
   return (int)((panels + rounds - 1) / rounds);
 }
-template <bool COUNT>
-int few_groups(const ejoin_ctx* ctx, int64_t n, int64_t nQ, int nkb, unsigned long long capacity) {
+int few_groups(int64_t n, int64_t nQ, int nkb) {
 #if defined(EJOIN_ONLY_K_JOIN) || defined(EJOIN_ONLY_K_JOIN_STRIP)
   return 0;
 #endif
   if (nQ > 256) return 0;
   const int rf = nQ <= 32 ? 2 : (nQ <= 64 ? 4 : (nQ <= 128 ? 8 : 16));
-  const int staged = few_staged(rf, nkb), lds_bytes = few_lds_bytes<false>(16 * rf, nkb, staged);
-  if (lds_bytes > FEW_LDS || n < 150ll * (rf * nkb - 24)) return 0;
-  return !COUNT && staged == 128 && capacity > 128ull * FEW_WAVES * few_workgroups(ctx, n, rf, lds_bytes) ? 0 : rf;
+  if (few_lds_bytes<false>(16 * rf, nkb, few_staged(rf, nkb)) > FEW_LDS || n < 150ll * (rf * nkb - 24)) return 0;
+  return rf;
 }
 template <bool COUNT>
 int run_few(ejoin_ctx* ctx, const Workspace& w, const ejoin_set* P, int rf, int nkb, const uint16_t* XQ, int64_t nQ, int64_t ldQ, float eps, const Results& r,
@@ -3817,7 +3872,7 @@ int run_join_prepared(ejoin_ctx* ctx, const ejoin_set* P, const uint16_t* XQ, in
   EJ_RC(ensure_workspace(ctx, padQ, pad_dims(d)));
   const Workspace& w = ctx->ws;
   const int nkb = k_blocks(d);
-  if (const int rf = few_groups<COUNT>(ctx, P->n, nQ, nkb, r.capacity)) return run_few<COUNT>(ctx, w, P, rf, nkb, XQ, nQ, ldQ, eps, r, st);
+  if (const int rf = few_groups(P->n, nQ, nkb)) return run_few<COUNT>(ctx, w, P, rf, nkb, XQ, nQ, ldQ, eps, r, st);
   PrepSet SP{nullptr, P->n, P->pad, 0, P->s, P->Xp, 0}, SQ{XQ, nQ, padQ, ldQ, w.s, w.Xp, 0};
   if (const int tile = small_tile(ctx, P->n, nQ, false, nkb)) return run_small<COUNT>(ctx, w, tile, SP, SQ, P->max_bits, nkb, eps, r, st);
   EJ_RC(begin_call(ctx, w, true, st));

@@ -44,7 +44,7 @@ def test_number_of_query_points(both, nq, d):
 @pytest.mark.parametrize("share", [0.03, 0.3])
 @pytest.mark.parametrize("nq, d", [(60, 416), (60, 448), (60, 512), (60, 544), (60, 1056), (60, 1152), (120, 512), (120, 544)])
 def test_staged_results(both, nq, d, share):
-    """The dimensions where a wavefront stages half as many results, or the LDS is full; capacities to either side of what they stage."""
+    """The dimensions where a wavefront stages fewer results, or the LDS is full."""
     print(f"few staged nq={nq} d={d} share={share}", flush=True)
     P, Q = rows(20011, d, seed=d), rows(nq, d, seed=d + nq)
     compare(both, P, Q, epsilon(P, d, share), d)
@@ -58,6 +58,25 @@ def test_number_of_points(both, n, share):
     d, nq = 70, 50 if share < 1 else 20
     P, Q = rows(n, d, seed=n), rows(nq, d, seed=n + 1)
     compare(both, P, Q, epsilon(torch.cat([P[:500], Q]), d, share) * (1.0 if share < 1 else 3.0), d)
+
+
+@pytest.mark.parametrize("share", [0.04, 0.14, 0.76])
+@pytest.mark.parametrize("n, nq, d", [(140001, 20, 40), (140001, 60, 40), (140001, 120, 40), (70001, 250, 64), (20011, 250, 64), (70001, 120, 530)])
+def test_lists_of_more_than_is_staged(both, n, nq, d, share):
+    """Two and three panels a wavefront: results that wait for an atomic of their own, and, in its last panel, for the workgroup's; whole, cut off and not wanted."""
+    print(f"few dense n={n} nq={nq} d={d} share={share}", flush=True)
+    P, Q = rows(n, d, seed=d + 1), rows(nq, d, seed=nq)
+    eps = epsilon(torch.cat([P[:2000], Q]), d, share)
+    compare(both, P, Q, eps, d)
+    s = both[1].prepare(P, d=d)
+    total = int(s.join_count(Q, eps)[2])
+    whole, d2 = sorted_pairs(s.join_pairs(Q, eps, total))
+    pairs, dist2, found = s.join_pairs(Q, eps, total // 2)
+    keys, order = torch.sort(pairs.reshape(-1).view(torch.int64))
+    at = torch.searchsorted(whole, keys)
+    assert int(found) == total and torch.equal(whole[at], keys) and torch.equal(d2[at], dist2[order]) and bool((keys[1:] != keys[:-1]).all())
+    assert int(s.join_pairs(Q, eps, 0)[2]) == total
+    s.close()
 
 
 def test_query_norms_far_above_the_sets_and_out_of_range(both):
