@@ -3826,22 +3826,17 @@ int run_join_split(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, int64
 typedef void (*FewKernel)(FewArgs);
 template <bool COUNT>
 FewKernel few_kernel(int rf) { return rf == 2 ? &k_join_few<COUNT, 2> : rf == 4 ? &k_join_few<COUNT, 4> : rf == 8 ? &k_join_few<COUNT, 8> : &k_join_few<COUNT, 16>; }
-// Groups of 16 query points that k_join_few should hold for nQ of them against a prepared set of n, or 0: another kernel.  They have to fit
-// the LDS, and every workgroup fills it anew, 1 KB a group and k-block: the more of them, the more points it takes (start of the call to
-// its end, here and by k_prep and k_join_small, in us: 64 KB 5,000 points 13.2 and 13.2, 1,000 13.7 and 11.9; 120 KB 20,000 points 27.0 and 31.9, 5,000 19.2 and 19.3;
-// 128 KB 20,000 18.8 and 19.5, 5,000 18.7 and 17.0; 48 KB 5,000 12.2 and 14.1, 1,000 12.4 and 12.7; 16 KB 1,000 10.8 and 12.7).
 int few_workgroups(const ejoin_ctx* ctx, int64_t n, int rf, int lds_bytes) {
   const int64_t panels = (n + TILE - 1) / TILE, most = (int64_t)ctx->num_cu * few_groups_per_cu(rf, lds_bytes), rounds = (panels + most - 1) / most;
   return (int)((panels + rounds - 1) / rounds);
 }
-int few_groups(int64_t n, int64_t nQ, int nkb) {
+// Groups of 16 query points that k_join_few should hold for nQ of them against a prepared set of n, or 0: another kernel.
+int few_groups(int64_t n, int64_t nQ, int nkb, bool count) {
 #if defined(EJOIN_ONLY_K_JOIN) || defined(EJOIN_ONLY_K_JOIN_STRIP)
   return 0;
 #endif
-  if (nQ > 256) return 0;
-  const int rf = nQ <= 32 ? 2 : (nQ <= 64 ? 4 : (nQ <= 128 ? 8 : 16));
-  if (few_lds_bytes<false>(16 * rf, nkb, few_staged(rf, nkb)) > FEW_LDS || n < 150ll * (rf * nkb - 24)) return 0;
-  return rf;
+  const int rf = few_groups_of(nQ);
+  return rf && few_lds_bytes<false>(16 * rf, nkb, few_staged(rf, nkb)) <= FEW_LDS && few_pays(n, nQ, rf, nkb, count) ? rf : 0;
 }
 template <bool COUNT>
 int run_few(ejoin_ctx* ctx, const Workspace& w, const ejoin_set* P, int rf, int nkb, const uint16_t* XQ, int64_t nQ, int64_t ldQ, float eps, const Results& r,
@@ -3872,7 +3867,7 @@ int run_join_prepared(ejoin_ctx* ctx, const ejoin_set* P, const uint16_t* XQ, in
   EJ_RC(ensure_workspace(ctx, padQ, pad_dims(d)));
   const Workspace& w = ctx->ws;
   const int nkb = k_blocks(d);
-  if (const int rf = few_groups(P->n, nQ, nkb)) return run_few<COUNT>(ctx, w, P, rf, nkb, XQ, nQ, ldQ, eps, r, st);
+  if (const int rf = few_groups(P->n, nQ, nkb, COUNT)) return run_few<COUNT>(ctx, w, P, rf, nkb, XQ, nQ, ldQ, eps, r, st);
   PrepSet SP{nullptr, P->n, P->pad, 0, P->s, P->Xp, 0}, SQ{XQ, nQ, padQ, ldQ, w.s, w.Xp, 0};
   if (const int tile = small_tile(ctx, P->n, nQ, false, nkb)) return run_small<COUNT>(ctx, w, tile, SP, SQ, P->max_bits, nkb, eps, r, st);
   EJ_RC(begin_call(ctx, w, true, st));

@@ -16,4 +16,23 @@ inline bool norms_from_the_end(int64_t n, int64_t ld) {
   return bytes > EJ_MEMORY_SIDE_CACHE / 16 * 15 && bytes <= EJ_MEMORY_SIDE_CACHE * 3;
 }
 
+// A prepared set of n points against few query points: groups of 16 of them that k_join_few is built for (0: too many) ...
+inline int few_groups_of(int64_t nq) { return nq <= 32 ? 2 : (nq <= 64 ? 4 : (nq <= 128 ? 8 : (nq <= 256 ? 16 : 0))); }
+// ... and whether it is the better kernel, where the LDS holds them.  Every workgroup fills its LDS with them, 1 KB a group and k-block, and has one panel of 256
+// points or a few: the more there is to fill, the more points it takes to have the CUs at work.  What it is measured against (time here over time there, sparse results, 4 and
+// 14 % of all pairs; counts, lists) is k_prep and k_join_small.  Up to 300 tiles of 64 that works in those, on up to 300 workgroups: 60 queries, 6,000 points,
+// d = 256 0.83, 0.82, 0.85; 0.78, 0.90, 1.04; d = 512 1.09, 1.06, 1.07; 1.09, 1.14, 1.24; 13,000 points 1.01, 0.90, 0.91; 1.01, 1.01, 1.11; d = 768, 18,500 points 1.14, 1.05, 1.07;
+// 1.14, 1.17, 1.23; 30 queries, d = 512, 6,000 points 0.92, 0.91, 0.91; 0.93, 0.94, 0.96; d = 1,024, 13,000 1.17, 1.13, 1.13; 1.17, 1.15, 1.17; 120 queries, 6,000 points, d = 128
+// 0.78, 0.89, 0.95; 0.78, 1.01, 1.37; d = 256 1.03, 1.04, 1.10; 1.01, 1.22, 1.46.  From there on in tiles of 128, and up to 128 queries it is the slower one: 60, 19,500 points,
+// d = 768 0.91, 0.84, 0.84; 0.89, 0.83, 0.79; 120, 13,000 points, d = 480 0.97, 0.92, 0.93; 0.98, 0.98, 0.95; 30, 19,500 points, d = 2,100 0.80, 0.79, 0.79; 0.79, 0.78, 0.77.
+// More than 128 queries it has in two columns of tiles and their registers leave k_join_few one workgroup a CU.  250 queries, counts: d = 64, 3,000 points 0.83, 1.08, 1.22; d = 128, 13,000 0.99,
+// 0.96, 1.04; 16 neighbours a query, d = 180, 16,000 and 20,000 0.98, 0.92; d = 220, 16,000, 20,000 and 24,000 1.10, 1.02, 0.96; d = 250, 24,000, 33,000 and 38,000 1.08, 1.03, 0.90; lists, which every wavefront sorts out
+// by itself: d = 64, 13,000 0.80, 1.16, 0.86; 24,000 0.75, 1.01, 0.57; d = 128 0.90, 1.13, 0.59; 4 %, 30,000 and 40,000 1.09, 0.94; d = 256 1.21, 1.06.
+inline bool few_pays(int64_t n, int64_t nq, int groups, int nkb, bool count) {
+  const int kb = groups * nkb;
+  if (groups == 16) return n >= (count ? 9ll * kb * kb / 5 : 14000 + 300ll * kb);
+  const bool other_in_64 = (n + 63) / 64 * ((nq + 63) / 64) <= 300;
+  return !other_in_64 || n >= (groups == 4 ? 300ll : 600ll) * (kb - 32);
+}
+
 #endif  // EJOIN_RULES_H

@@ -15,6 +15,8 @@ def rules(tmp_path_factory):
                     os.path.join(ROOT, "tests", "host", "rules_dump.cpp"), "-o", str(out)], check=True)
     lib = ctypes.CDLL(str(out))
     lib.ejoin_test_norms_from_the_end.argtypes = [ctypes.c_int64] * 2
+    lib.ejoin_test_few_pays.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2
+    lib.ejoin_test_few_groups_of.argtypes = [ctypes.c_int64]
     return lib
 
 
@@ -23,3 +25,18 @@ def test_norms_start_at_the_end_only_of_rows_that_the_memory_side_cache_does_not
         assert not rules.ejoin_test_norms_from_the_end(n, ld)
     for n, ld in ((2_000_000, 64), (500000, 256), (10**6, 256), (6_290_000, 64)):  # from 256 MB on
         assert rules.ejoin_test_norms_from_the_end(n, ld)
+
+
+def test_few_query_points_against_sets_where_that_is_the_better_kernel(rules):
+    assert [rules.ejoin_test_few_groups_of(nq) for nq in (1, 32, 33, 64, 65, 128, 129, 256, 257)] == [2, 2, 4, 4, 8, 8, 16, 16, 0]
+    # (n, nq, d): measured as slower by a tenth or more, counts and lists; and as faster
+    for n, nq, d in ((16000, 60, 960), (18500, 60, 768), (6000, 120, 384), (9000, 120, 480), (13000, 30, 1024), (3000, 60, 512), (20000, 140, 250), (28000, 250, 250), (16000, 250, 200)):
+        assert not rules.ejoin_test_few_pays(n, nq, d, 0) and not rules.ejoin_test_few_pays(n, nq, d, 1)
+    for n, nq, d in ((100000, 120, 530), (20000, 60, 960), (20000, 30, 1500), (12000, 120, 480), (1500, 30, 512), (1500, 60, 256), (6000, 120, 128), (24000, 250, 64), (60000, 250, 250)):
+        assert rules.ejoin_test_few_pays(n, nq, d, 0) and rules.ejoin_test_few_pays(n, nq, d, 1)
+    # lists of more than 128 query points take more points than counts
+    for n, nq, d, count, there in ((13000, 250, 64, 1, 1), (13000, 250, 64, 0, 0), (23599, 250, 64, 0, 0), (23600, 250, 64, 0, 1), (24000, 250, 220, 0, 0), (7371, 250, 128, 1, 0), (7372, 250, 128, 1, 1)):
+        assert rules.ejoin_test_few_pays(n, nq, d, count) == there
+    # the other kernel's tiles of 64: up to 300 of them
+    for n, nq, d, there in ((19200, 64, 960, 0), (19201, 64, 960, 1), (9600, 128, 480, 0), (9601, 128, 480, 1), (9599, 64, 512, 0), (9600, 64, 512, 1)):
+        assert rules.ejoin_test_few_pays(n, nq, d, 1) == there
