@@ -773,14 +773,9 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
       const bool row_part = tid >= TS;
       const int r = tid & (TS - 1), in = r & 31;
       const int x = (r & ~31) + (row_part ? aug_col_point(in) : aug_row_point(in)), y = x + (row_part ? 16 : 4);
-      if constexpr (ONE) {
-        const int64_t ax = row_a(x), bx = row_b(x), ay = row_a(y), by = row_b(y);  // (a choice between the two before they are worked out puts the arguments into scratch memory)
-        sx = __hip_atomic_load(a.s + (row_part ? ax : bx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sy = __hip_atomic_load(a.s + (row_part ? ay : by), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      } else {
-        sx = a.s[row_part ? row_a(x) : row_b(x)];
-        sy = a.s[row_part ? row_a(y) : row_b(y)];
-      }
+      const int64_t ax = row_a(x), bx = row_b(x), ay = row_a(y), by = row_b(y);  // (a choice between the two before they are worked out puts the arguments into scratch memory)
+      sx = __hip_atomic_load(a.s + (row_part ? ax : bx), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sy = __hip_atomic_load(a.s + (row_part ? ay : by), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   };
   auto norm_operands = [&]() __attribute__((always_inline)) -> bool {  // false: data out of range
@@ -806,8 +801,14 @@ __global__ __launch_bounds__(64 * dense_waves<TS>(), TS == 64 ? 3 : 4) void k_di
       read_norms();
       ticket();
     }
-  } else {
-    read_norms();
+  } else {  // (as in read_norms, which by itself makes these instances 20 instructions longer)
+    if (tid < 2 * TS) {
+      const bool row_part = tid >= TS;
+      const int r = tid & (TS - 1), in = r & 31;
+      const int x = (r & ~31) + (row_part ? aug_col_point(in) : aug_row_point(in)), y = x + (row_part ? 16 : 4);
+      sx = a.s[row_part ? row_a(x) : row_b(x)];
+      sy = a.s[row_part ? row_a(y) : row_b(y)];
+    }
     for (uint32_t q = tid; q < a.nmaxima; q += 64 * WAVES) mb = max(mb, a.maxima[q]);
   }
   if (there && !norm_operands()) {
