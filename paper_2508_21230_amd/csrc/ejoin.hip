@@ -164,7 +164,7 @@ __global__ __launch_bounds__(512) void k_fold_max(uint32_t* values, uint32_t n) 
 // ---- What the workgroups of the one-launch kernels tell each other, in memory of the context's that is all zero between calls:
 // 64-bit words, [0] and [16 (1 + x)] of XCD x (bits 0 .. 39: pairs found; 40 .. 51: workgroups that were late; 52 .. 63: tickets), slots for the largest norms of
 // parts of the points, once for each XCD, and counters.  A slot that has been filled has its top bit set (a norm has no sign).
-constexpr int ONCE_SLOTS = 2048, ONCE_COUNTS = 1 << 17;  // capacities
+// (ONCE_SLOTS, ONCE_COUNTS: capacities)
 constexpr size_t ONCE_STATE_BYTES = 16 * 8 * (1 + EJ_NUM_XCD);
 constexpr unsigned long long ONCE_FOUND = (1ull << 40) - 1, ONCE_TICKET = 1ull << 52;
 // A workgroup's ticket, with what it adds to the fields below, XCD by XCD: an eighth of the atomics on each of the XCDs' words, then
@@ -2606,7 +2606,6 @@ struct OnceArgs {
   uint32_t* slot;
   uint32_t* late_counts;  // of the points, then of the query points
 };
-constexpr int ONCE_GROUPS_PER_CU = 3;
 constexpr uint32_t ONCE_STEPS = 256; // tiles from which on counts take their tickets XCD by XCD
 template <int TS>
 struct Once {
@@ -3700,27 +3699,12 @@ int run_small(ejoin_ctx* ctx, const Workspace& w, int tile, PrepSet A, PrepSet B
   return EJOIN_OK;
 }
 
-// Which tile k_join_once works a join of FP16 rows in, or 0: its tiles do not all fit the CUs at once.
-// Counts: tiles of 64 while they do (1,984 points, d = 64, 384 and 960: 8.3, 10.1 and 14.0 us, in tiles of 128 9.1, 12.4 and 18.7; 2,400
-// points 9.0, 11.4 and 17.5 against 9.3, 12.9 and 20.0; 3,000 x 1,000, d = 128, 10.4 against 10.6).  Lists pay some 13 ns a tile for their place in the result, tiles of 128 1.6 us and 0.19 us a
-// k-block for their longer chain (tiles of 64 and of 128: 1,000 x 64 8.0 and 9.2 us; 1,984 points, d = 64, 384 and 960, 12.7, 14.6 and 18.4,
-// 9.9, 13.4 and 20.0); with three of them on a CU tiles of 64 lose more (2,400 x 960 23.4 against 21.2).
-// Tiles of 128 are copied in half lines and their norms multiplied once a tile: with three of them on a CU and many k-blocks k_prep and k_join_small are
-// the better ones (4,300 points, d = 384, 768, 960, 2,048 and 4,096: lists 25.5, 35.6, 40.9, 66.5 and 110 us by those, 25.3, 36.6, 41.7, 71.7 and
-// 133 here, counts 24.7, 35.3, 40.7, 64.9 and 110, 21.8, 33.8, 39.4, 70.0 and 133), with
-// two up to 128 k-blocks not (3,900 points, d = 2,048 and 4,096: 59.8 and 97.7, 52.3 and 95.4; counts of 4,000 x 2,000, d = 4,096, 99 and 98).
+// Which tile k_join_once works a join of FP16 rows in, or 0: another kernel.
 int once_edge(const ejoin_ctx* ctx, int64_t nA, int64_t nB, bool self, int nkb, bool count) {
 #if defined(EJOIN_ONLY_K_JOIN) || defined(EJOIN_ONLY_K_JOIN_STRIP)
   return 0;
 #endif
-  auto tiles = [&](int64_t t) {
-    const int64_t a = (nA + t - 1) / t, b = (nB + t - 1) / t;
-    return self ? a * (a + 1) / 2 : a * b;
-  };
-  const int64_t held = (int64_t)ctx->num_cu * ONCE_GROUPS_PER_CU, t64 = tiles(64), t128 = tiles(128);
-  if (held >= 4096 || nA + (self ? 0 : nB) > ONCE_COUNTS || (nA + 63) / 64 + (self ? 0 : (nB + 63) / 64) > ONCE_SLOTS) return 0;
-  if (count ? t64 <= held : t64 <= 2 * ctx->num_cu && t64 - t128 <= 123 + 15 * nkb) return 64;
-  return t128 <= (nkb <= (count ? 24 : 12) ? held : nkb <= 128 ? 2 * ctx->num_cu : 0) ? 128 : 0;
+  return once_tile_edge(ctx->num_cu, nA, nB, self, nkb, count);
 }
 // A join by k_join_once.  XB == nullptr: self-join of XA.
 template <bool COUNT>

@@ -16,6 +16,31 @@ inline bool norms_from_the_end(int64_t n, int64_t ld) {
   return bytes > EJ_MEMORY_SIDE_CACHE / 16 * 15 && bytes <= EJ_MEMORY_SIDE_CACHE * 3;
 }
 
+// Tiles of edge x edge points of a self-join of a points, or of a and b points.
+inline int64_t tiles_of(int64_t edge, int64_t a, int64_t b, bool self) {
+  const int64_t ta = (a + edge - 1) / edge, tb = (b + edge - 1) / edge;
+  return self ? ta * (ta + 1) / 2 : ta * tb;
+}
+
+// Which tile k_join_once works a join of FP16 rows in, or 0: another kernel, its tiles do not all fit the CUs at once (three workgroups a CU).
+// Counts: tiles of 64 while they do (1,984 points, d = 64, 384 and 960: 8.3, 10.1 and 14.0 us, in tiles of 128 9.1, 12.4 and 18.7; 2,400
+// points 9.0, 11.4 and 17.5 against 9.3, 12.9 and 20.0; 3,000 x 1,000, d = 128, 10.4 against 10.6).  Lists pay some 13 ns a tile for their place in the result, tiles of 128 1.6 us and 0.19 us a
+// k-block for their longer chain (tiles of 64 and of 128: 1,000 x 64 8.0 and 9.2 us; 1,984 points, d = 64, 384 and 960, 12.7, 14.6 and 18.4,
+// 9.9, 13.4 and 20.0); with three of them on a CU tiles of 64 lose more (2,400 x 960 23.4 against 21.2).
+// Tiles of 128 are copied in half lines and their norms multiplied once a tile: with three of them on a CU and many k-blocks k_prep and k_join_small are the better
+// ones (time here over time there).  Counts, 30, 36, 40 and 48 k-blocks: 4,100 points 0.92, 0.97, 0.99, 1.03, 4,400 0.96, 0.97, 1.03, 1.07, 4,800 0.93, 0.96, 1.00, 1.06; of two sets, 24, 26, 30 and 36:
+// 8,000 x 1,400 0.99, 1.00, 1.02, 1.03, 4,000 x 3,000 0.92, 0.97, 0.98, 1.02, 2,500 x 4,300 0.97, 1.01, 1.03.  Lists, 12, 16, 20, 24 and 30: 4,100 0.95, 0.94, 0.96, 0.96, 0.97, 4,400 0.98, 0.96, 0.98, 1.00, 1.00,
+// 4,300 at 20 and 24 1.02, 1.04, 8,000 x 1,400 0.98, 0.97, 1.00, 1.03, 1.04.  With two up to 128 k-blocks not (3,900 points,
+// d = 2,048 and 4,096: 59.8 and 97.7, 52.3 and 95.4; counts of 4,000 x 2,000, d = 4,096, 99 and 98).
+constexpr int ONCE_SLOTS = 2048, ONCE_COUNTS = 1 << 17, ONCE_GROUPS_PER_CU = 3;
+inline int once_tile_edge(int num_cu, int64_t a, int64_t b, bool self, int nkb, bool count) {
+  const int64_t held = (int64_t)num_cu * ONCE_GROUPS_PER_CU, t64 = tiles_of(64, a, b, self), t128 = tiles_of(128, a, b, self);
+  if (held >= 4096 || a + (self ? 0 : b) > ONCE_COUNTS || (a + 63) / 64 + (self ? 0 : (b + 63) / 64) > ONCE_SLOTS) return 0;
+  if (count ? t64 <= held : t64 <= 2 * num_cu && t64 - t128 <= 123 + 15 * nkb) return 64;
+  const int most_kb = count ? (self ? 36 : 24) : 16;
+  return t128 <= (nkb <= most_kb ? held : nkb <= 128 ? 2 * num_cu : 0) ? 128 : 0;
+}
+
 // A prepared set of n points against few query points: groups of 16 of them that k_join_few is built for (0: too many) ...
 inline int few_groups_of(int64_t nq) { return nq <= 32 ? 2 : (nq <= 64 ? 4 : (nq <= 128 ? 8 : (nq <= 256 ? 16 : 0))); }
 // ... and whether it is the better kernel, where the LDS holds them.  Every workgroup fills its LDS with them, 1 KB a group and k-block, and has one panel of 256
@@ -31,7 +56,7 @@ inline int few_groups_of(int64_t nq) { return nq <= 32 ? 2 : (nq <= 64 ? 4 : (nq
 inline bool few_pays(int64_t n, int64_t nq, int groups, int nkb, bool count) {
   const int kb = groups * nkb;
   if (groups == 16) return n >= (count ? 9ll * kb * kb / 5 : 14000 + 300ll * kb);
-  const bool other_in_64 = (n + 63) / 64 * ((nq + 63) / 64) <= 300;
+  const bool other_in_64 = tiles_of(64, n, nq, false) <= 300;
   return !other_in_64 || n >= (groups == 4 ? 300ll : 600ll) * (kb - 32);
 }
 

@@ -16,6 +16,7 @@ def rules(tmp_path_factory):
     lib = ctypes.CDLL(str(out))
     lib.ejoin_test_norms_from_the_end.argtypes = [ctypes.c_int64] * 2
     lib.ejoin_test_few_pays.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2
+    lib.ejoin_test_once_edge.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2
     lib.ejoin_test_few_groups_of.argtypes = [ctypes.c_int64]
     return lib
 
@@ -40,3 +41,13 @@ def test_few_query_points_against_sets_where_that_is_the_better_kernel(rules):
     # the other kernel's tiles of 64: up to 300 of them
     for n, nq, d, there in ((19200, 64, 960, 0), (19201, 64, 960, 1), (9600, 128, 480, 0), (9601, 128, 480, 1), (9599, 64, 512, 0), (9600, 64, 512, 1)):
         assert rules.ejoin_test_few_pays(n, nq, d, 1) == there
+
+
+def test_tiles_of_the_one_launch_join(rules):
+    """(n, nq or 0, d, counts): the last problem in tiles of 64 and the first of 128, the last of all and the first of another kernel."""
+    for n, nq, d, count, edge in ((1216, 0, 64, 0, 64), (1217, 0, 64, 0, 128), (1344, 0, 96, 0, 64), (1345, 0, 96, 0, 128), (1472, 0, 130, 0, 64), (1473, 0, 130, 0, 128),
+                                  (2432, 0, 96, 1, 64), (2433, 0, 96, 1, 128), (4864, 0, 96, 0, 128), (4865, 0, 96, 0, 0), (4864, 0, 96, 1, 128), (4865, 0, 96, 1, 0),
+                                  (3968, 0, 960, 0, 128), (3969, 0, 960, 0, 0), (4864, 0, 512, 0, 128), (4864, 0, 513, 0, 0), (4864, 0, 1152, 1, 128), (4864, 0, 1153, 1, 0),
+                                  (3968, 0, 1153, 1, 128), (3968, 0, 4096, 0, 128), (3968, 0, 4097, 0, 0), (4000, 3000, 768, 1, 128), (4000, 3000, 769, 1, 0), (4000, 3000, 512, 0, 128),
+                                  (4000, 3000, 513, 0, 0), (300, 90000, 40, 0, 0), (300, 20000, 40, 0, 128), (100, 60000, 40, 1, 128), (10, 131062, 40, 1, 0)):
+        assert rules.ejoin_test_once_edge(n, nq, d, count) == edge, (n, nq, d, count)
