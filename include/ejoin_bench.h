@@ -19,8 +19,8 @@ extern "C" {
 int ejoin_set_profiling(ejoin_ctx* ctx, int on);
 int ejoin_last_kernel_ms(ejoin_ctx* ctx, float* prep_ms, float* join_ms);
 
-/* What the join kernel of a call executes: *tiles output tiles of *edge x *edge points (256; 128 or 64 for small problems, of a pair list of
- * rows: counts and prepared sets of a few thousand points may have the other of the two), *steps
+/* What the join kernel of a call executes: *tiles output tiles of *edge x *edge points (256; 128 or 64 for small problems), of a pair list of
+ * rows (counts of a few thousand points may have the other of the two; for prepared sets see ejoin_join_kernel), *steps
  * matrix-core steps of 32 coordinates each, i.e. 2 * edge * edge * 32 * steps FLOP per tile (without the one step per tile that adds
  * the norms).  np points with themselves (nq = 0) or with nq query points; split != 0: the split-FP16 join of np FP32 rows.
  * (EJOIN_KERNEL_STRIP works in pieces of 512 x 64 points; they are counted as tiles of 256 all the same, which for 10^5 points with
@@ -28,11 +28,14 @@ int ejoin_last_kernel_ms(ejoin_ctx* ctx, float* prep_ms, float* join_ms);
  * (ejoin_selfjoin_pairs_to_host takes tiles of 256 where it cuts the join into several launches.)  Host pointers; no device work. */
 int ejoin_join_work(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int32_t split, int32_t* edge, int32_t* steps, int64_t* tiles);
 
-/* Which kernel that is, for a list (count = 0) or counts: the one of small problems, the general one in tiles of 256, or the one that
- * keeps 512 rows of few coordinates in registers. */
+/* Which kernel a call goes to, for a list (count = 0) or counts, of rows (split = 0), the split-FP16 join (1) or a prepared set of np points with nq query
+ * points (2): the one of small problems, the general one in tiles of 256, the one that keeps 512 rows of few coordinates in registers, the join of rows in one launch, or
+ * the one that holds the few query points of a prepared set in the LDS. */
 #define EJOIN_KERNEL_SMALL 0
 #define EJOIN_KERNEL_TILES 1
 #define EJOIN_KERNEL_STRIP 2
+#define EJOIN_KERNEL_ONCE 3
+#define EJOIN_KERNEL_FEW 4
 int ejoin_join_kernel(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int32_t split, int32_t count, int32_t* kernel);
 
 #ifdef __cplusplus

@@ -324,11 +324,11 @@ class EJoin:
                                               C.byref(tiles)), self._h)
         return edge.value, steps.value, tiles.value
 
-    def join_kernel(self, n: int, d: int, nq: int = 0, split: bool = False, count: bool = False) -> str:
-        """Which kernel that is: "small", "tiles" or "strip" (ejoin_join_kernel)."""
+    def join_kernel(self, n: int, d: int, nq: int = 0, split: bool = False, count: bool = False, prepared: bool = False) -> str:
+        """Which kernel a call goes to (prepared: nq query points against a prepared set): "small", "tiles", "strip", "once" or "few" (ejoin_join_kernel)."""
         kernel = C.c_int32()
-        self._check(self._lib.ejoin_join_kernel(self._h, int(n), int(nq), int(d), int(split), int(count), C.byref(kernel)), self._h)
-        return ("small", "tiles", "strip")[kernel.value]
+        self._check(self._lib.ejoin_join_kernel(self._h, int(n), int(nq), int(d), 2 if prepared else int(split), int(count), C.byref(kernel)), self._h)
+        return ("small", "tiles", "strip", "once", "few")[kernel.value]
 
     def set_profiling(self, on: bool):
         self._check(self._lib.ejoin_set_profiling(self._h, 1 if on else 0), self._h)

@@ -4222,14 +4222,10 @@ int ejoin_dist2_tile(ejoin_ctx* ctx, const uint16_t* X, int64_t n, int32_t d, in
   // (no atomics on the status block: its state between calls is left as it is)
   uint32_t* maxima = w.maxima;
   DenseArgs a{X, w.s, maxima, 0, w.status, n, ld, (k_blocks(d) + 1) / 2 /* (rows are padded to a multiple of 64 coordinates) */, i0, j0, rows, cols, out};
-  auto blocks = [&](int ts) { return (((int64_t)rows + ts - 1) / ts * (((int64_t)cols + ts - 1) / ts) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; };
-  const bool wide = 4 * blocks(128) >= 3 * ctx->num_cu;  // (see the kernel)
-  const int64_t groups = wide ? blocks(128) : blocks(64), per = 16 * (wide ? dense_waves<128>() : dense_waves<64>());
-  const int64_t norm_groups = ((n + per - 1) / per + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD;
-  // One launch, the norms by the first of its workgroups, where there is about one workgroup a CU in all (two launches and now, in us: 300 x 300 of
-  // 8,000 x 64 11.5, 9.6; 600 x 600 of 8,000 x 384 11.9, 9.6; 1,000 x 1,000 of 1,000 x 96 11.1, 8.9).  Beyond, it is the slots that take long to
-  // read and what waits for them (300 x 300 of 20,000 x 384 11.6 both ways, of 120,000 x 64 11.1 and 21.4; 2,500 x 700 of 12,000 x 200 11.3, 12.3).
-  if (norm_groups <= ONCE_SLOTS && 4 * (groups + norm_groups) <= 5 * ctx->num_cu) {
+  static_assert(dense_waves<128>() == 8 && dense_waves<64>() == 4, "as dense_norm_groups has them");
+  const bool wide = dense_wide(ctx->num_cu, rows, cols);
+  const int64_t groups = dense_groups(wide ? 128 : 64, rows, cols);
+  if (const int64_t norm_groups = dense_norm_groups(ctx->num_cu, n, rows, cols)) {
     const DenseOneArgs one{w.s, (uint32_t)norm_groups, k_blocks(d), reinterpret_cast<unsigned long long*>(ctx->once), reinterpret_cast<uint32_t*>(ctx->once + ONCE_STATE_BYTES)};
     hipLaunchKernelGGL((wide ? k_dist2_tile<128, true> : k_dist2_tile<64, true>), dim3((unsigned)(groups + norm_groups)),
                        dim3(64 * (wide ? dense_waves<128>() : dense_waves<64>())), (wide ? dense_lds_bytes<128>() : dense_lds_bytes<64>()), st, a, one);
@@ -4296,11 +4292,14 @@ int ejoin_join_work(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int
 }
 
 int ejoin_join_kernel(const ejoin_ctx* ctx, int64_t np, int64_t nq, int32_t d, int32_t split, int32_t count, int32_t* kernel) {
-  int32_t edge, steps;
-  int64_t tiles;
-  if (!kernel) return EJOIN_EINVAL;
-  EJ_RC(ejoin_join_work(ctx, np, nq, d, split, &edge, &steps, &tiles));
-  *kernel = edge < TILE ? EJOIN_KERNEL_SMALL : (!split && plan_strip(ctx, np, nq ? nq : np, nq == 0, steps, count != 0).use ? EJOIN_KERNEL_STRIP : EJOIN_KERNEL_TILES);
+  if (!ctx || !kernel || np < 1 || nq < 0 || d < 1 || d > 65536 || (split == 2 ? nq == 0 : split && nq)) return EJOIN_EINVAL;
+  const bool self = nq == 0, prepared = split == 2, fp32 = split && !prepared;
+  const int nkb = fp32 ? 3 * ((d + KSLICE - 1) / KSLICE) : k_blocks(d);
+  const int64_t nB = self ? np : nq;
+  if (!split && once_edge(ctx, np, nB, self, nkb, count != 0)) *kernel = EJOIN_KERNEL_ONCE;
+  else if (prepared && few_groups(np, nq, nkb, count != 0)) *kernel = EJOIN_KERNEL_FEW;
+  else if (small_tile(ctx, np, nB, self, nkb)) *kernel = EJOIN_KERNEL_SMALL;
+  else *kernel = !fp32 && plan_strip(ctx, np, nB, self, nkb, count != 0).use ? EJOIN_KERNEL_STRIP : EJOIN_KERNEL_TILES;
   return EJOIN_OK;
 }
 

@@ -3,6 +3,7 @@
 #define EJOIN_RULES_H
 
 #include <stdint.h>
+#include "tile_cursor.h"
 
 constexpr int64_t EJ_MEMORY_SIDE_CACHE = 256ll << 20;  // bytes of it
 
@@ -39,6 +40,18 @@ inline int once_tile_edge(int num_cu, int64_t a, int64_t b, bool self, int nkb, 
   if (count ? t64 <= held : t64 <= 2 * num_cu && t64 - t128 <= 123 + 15 * nkb) return 64;
   const int most_kb = count ? (self ? 36 : 24) : 16;
   return t128 <= (nkb <= most_kb ? held : nkb <= 128 ? 2 * num_cu : 0) ? 128 : 0;
+}
+
+// The dense block: workgroups in tiles of edge x edge, and whether in tiles of 128 (see k_dist2_tile) or of 64.
+inline int64_t dense_groups(int edge, int64_t rows, int64_t cols) { return (tiles_of(edge, rows, cols, false) + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD; }
+inline bool dense_wide(int num_cu, int64_t rows, int64_t cols) { return 4 * dense_groups(128, rows, cols) >= 3 * num_cu; }
+// Workgroups for the norms of n points in the launch of the block itself, or 0: a launch of their own.  One launch where there is about one workgroup a CU
+// in all (a call among others, two launches and one, in us: 300 x 300 of 8,000 x 64 9.5 and 7.3; 600 x 600 of 8,000 x 384 10.6 and 9.6; 1,000 x 1,000 of 1,000 x 96 10.8 and 7.7).  Beyond, it is the slots that take long to
+// read and what waits for them (300 x 300 of 20,000 x 384 11.6 both ways, of 120,000 x 64 11.1 and 21.4; 2,500 x 700 of 12,000 x 200 11.3, 12.3).
+inline int64_t dense_norm_groups(int num_cu, int64_t n, int64_t rows, int64_t cols) {
+  const bool wide = dense_wide(num_cu, rows, cols);
+  const int64_t per = 16 * (wide ? 8 : 4), groups = ((n + per - 1) / per + EJ_NUM_XCD - 1) / EJ_NUM_XCD * EJ_NUM_XCD;
+  return groups <= ONCE_SLOTS && 4 * (groups + dense_groups(wide ? 128 : 64, rows, cols)) <= 5 * num_cu ? groups : 0;
 }
 
 // A prepared set of n points against few query points: groups of 16 of them that k_join_few is built for (0: too many) ...

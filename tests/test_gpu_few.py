@@ -17,7 +17,20 @@ def both():
     e.close()
 
 
+def rules_say(n, nq, d):
+    """Whether lists and counts go to the kernel of few query points (see the rules' own test)."""
+    groups, blocks = (2 if nq <= 32 else 4 if nq <= 64 else 8 if nq <= 128 else 16), max(2, -(-d // 32))
+    kb = groups * blocks
+    if nq > 256 or groups * 16 * (blocks * 64 + 24) + 128 + 8 * 128 * 12 > 159 * 1024:
+        return [False, False]
+    if groups == 16:
+        return [n >= 14000 + 300 * kb, n >= 9 * kb * kb // 5]
+    return [-(-n // 64) * -(-nq // 64) > 300 or n >= (300 if groups == 4 else 600) * (kb - 32)] * 2
+
+
 def compare(both, P, Q, eps, d):
+    (n, nq), few = (P.shape[0], Q.shape[0]), rules_say(P.shape[0], Q.shape[0], d)
+    assert [both[1].join_kernel(n, d, nq, count=c, prepared=True) == "few" for c in (False, True)] == few
     sets = [e.prepare(P, d=d) for e in both]
     want = sets[0].join_count(Q, eps)
     cap = int(want[2])

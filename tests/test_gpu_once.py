@@ -25,12 +25,17 @@ def once(request):
     e.close()
 
 
-# one tile; edges of tiles; the last list in tiles of 64 and the first of 128 (d = 96: 1,216 and 1,217 points); the last counts in tiles of 64
-# (2,432) and the first of 128; the last problem of all (4,864; of many coordinates 3,968, two tiles a CU), and one of the kernel after it
+LAST_IN_64 = {1: 1216, 64: 1216, 96: 1344, 130: 1472, 960: 1984}  # (lists)
+
+
+# one tile; edges of tiles; the last list in tiles of 64 and the first of 128; the last counts in tiles of 64
+# (2,432) and the first of 128; the last problem of all (4,864; lists of many coordinates 3,968, two tiles a CU), and one of the kernel after it
 @pytest.mark.parametrize("d", [1, 64, 96, 130, 960])
-@pytest.mark.parametrize("n,share", [(1, 0.5), (63, 0.3), (65, 0.3), (129, 1.0), (1216, 0.01), (1217, 0.01), (2432, 0.003), (2433, 0.003), (3968, 0.0005), (3969, 0.0005), (4864, 0.0005), (4865, 0.0005)])
+@pytest.mark.parametrize("n,share", [(1, 0.5), (63, 0.3), (65, 0.3), (129, 1.0), (1216, 0.01), (1217, 0.01), (1344, 0.01), (1345, 0.01), (1472, 0.01), (1473, 0.01), (1984, 0.01), (1985, 0.01), (2432, 0.003), (2433, 0.003), (3968, 0.0005), (3969, 0.0005), (4864, 0.0005), (4865, 0.0005)])
 def test_self_join(general, once, n, d, share):
     print(f"once self n={n} d={d} share={share}", flush=True)
+    assert (once.join_kernel(n, d) == "once") == (n <= (3968 if d == 960 else 4864)) and (once.join_kernel(n, d, count=True) == "once") == (n <= 4864)
+    assert n > 3968 or once.join_work(n, d)[0] == (64 if n <= LAST_IN_64[d] else 128)
     X = rows(n, d, seed=n + d)
     eps = epsilon(X, d, share)
     cap = n + int(general.selfjoin_count(X, eps, d=d)[1])
@@ -42,9 +47,10 @@ def test_self_join(general, once, n, d, share):
 
 
 @pytest.mark.parametrize("d", [40, 200])
-@pytest.mark.parametrize("n,nq", [(1, 1), (64, 1), (65, 63), (1000, 10), (10, 1000), (4000, 500), (20000, 60), (700, 7000), (3000, 1900), (300, 90000)])
+@pytest.mark.parametrize("n,nq", [(1, 1), (64, 1), (65, 63), (1000, 10), (10, 1000), (4000, 500), (20000, 60), (700, 7000), (3000, 1900), (300, 20000), (300, 90000)])
 def test_two_sets(general, once, n, nq, d):
     print(f"once two sets n={n} nq={nq} d={d}", flush=True)
+    assert (once.join_kernel(n, d, nq) == "once") == (once.join_kernel(n, d, nq, count=True) == "once") == (nq < 90000)  # (2,112 tiles of 128: another kernel)
     P, Q = rows(n, d, seed=d), rows(nq, d, seed=d + 1)
     Q[:min(n, nq) // 3] = P[:min(n, nq) // 3]
     eps = epsilon(Q, d, 0.01)
@@ -150,9 +156,10 @@ def general_count(X):
     return counts
 
 
-# the norms by workgroups of the launch: one tile; tiles of 64, ragged; of 128; the last block and set in one launch (320 workgroups) and the first in two
+# the norms by workgroups of the launch: one tile; tiles of 64, ragged; of 128; the last block and set in one launch (320 workgroups, 312 of them
+# for the norms, more than a workgroup has threads) and the first in two
 @pytest.mark.parametrize("n,d,i0,j0,rows_,cols", [(1, 20, 0, 0, 1, 1), (300, 70, 7, 100, 3, 200), (2000, 384, 1, 700, 501, 499), (8000, 100, 1000, 3000, 1800, 1750),
-                                                  (20480, 64, 0, 20000, 20, 300), (20481, 64, 0, 20000, 20, 300)])
+                                                  (19968, 64, 0, 19600, 20, 300), (19969, 64, 0, 19600, 20, 300)])
 def test_dense_block(general, once, n, d, i0, j0, rows_, cols):
     """The distances of the joins, zero on the diagonal; and data out of range is reported."""
     print(f"once dense n={n} d={d} rows={rows_} cols={cols}", flush=True)

@@ -655,7 +655,7 @@ def test_join_work_names_the_tiles_of_a_problem(ej, n, nq, d, split, want):
 def test_candidate_queue_at_every_density(ej, n, share):
     """From a lane here and there to every lane of every region holding candidates, with ragged edges and the diagonal (the last
     epsilon reaches the marker of the rows past the end), in pair, count and two-set mode: in the general kernel less, exactly
-    and several times what the queue of a wavefront takes (16 lanes), in the small kernel (tiles of 64) none to all of a lane's
+    and several times what the queue of a wavefront takes (16 lanes), in the one-launch join (tiles of 64) none to all of a lane's
     registers."""
     print(f"candidate queue n={n} share={share}", flush=True)
     rng = np.random.default_rng(n)
@@ -723,9 +723,9 @@ SMALL_SIZES = [1, 2, 63, 64, 65, 127, 129, 255, 257, 1000, 1537, 2500, 4097, 650
 @pytest.mark.parametrize("n,share", [(n, 0.003) for n in SMALL_SIZES] + [(n, 0.2) for n in SMALL_SIZES if n <= 2500])
 @pytest.mark.parametrize("d", [20, 96, 130])
 def test_small_problems_give_the_results_of_the_general_kernel(ej, general, n, d, share):
-    """Tiles of 64 and of 128, one and several per workgroup, ragged edges, sparse and dense results: pairs, distances and
-    counts of the general kernel, bit for bit."""
-    assert ej.join_work(n, d)[0] < 256
+    """The one-launch join up to 4,864 points, the small kernel from there on: tiles of 64 and of 128, one and several per workgroup, ragged edges, sparse and
+    dense results: pairs, distances and counts of the general kernel, bit for bit."""
+    assert ej.join_work(n, d)[0] < 256 and ej.join_kernel(n, d) == ej.join_kernel(n, d, count=True) == ("once" if n <= 4864 else "small")
     print(f"small n={n} d={d} share={share}", flush=True)
     rng = np.random.default_rng(n + d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
@@ -802,7 +802,7 @@ def test_counts_of_dense_tiles(ej, d, share):
     print(f"dense counts d={d} share={share}", flush=True)
     n, nq = 14501, 9001
     assert ej.join_work(n, d)[0] == ej.join_work(n, d, nq)[0] == 256 and n <= 32768
-    general = d > 320 or ej.join_kernel(100, d) != "small"
+    general = d > 320 or ej.join_kernel(100, d) != "once"
     assert not general or ej.join_kernel(n, d, count=True) == ej.join_kernel(n, d, nq, count=True) == "tiles"
     rng = np.random.default_rng(d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)
@@ -840,7 +840,7 @@ def test_counts_of_dense_tiles_of_large_sets(ej, d, share):
     print(f"dense counts of a large set d={d} share={share}", flush=True)
     n, nq = 33001, 700
     assert ej.join_work(n, d)[0] == ej.join_work(n, d, nq)[0] == ej.join_work(nq, d, n)[0] == 256 and n > 32768
-    general = d > 320 or ej.join_kernel(100, d) != "small"
+    general = d > 320 or ej.join_kernel(100, d) != "once"
     assert not general or ej.join_kernel(n, d, count=True) == ej.join_kernel(n, d, nq, count=True) == ej.join_kernel(nq, d, n, count=True) == "tiles"
     rng = np.random.default_rng(d)
     X = rng.random((n, d), dtype=np.float32).astype(np.float16).view(np.uint16)

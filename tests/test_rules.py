@@ -17,6 +17,7 @@ def rules(tmp_path_factory):
     lib.ejoin_test_norms_from_the_end.argtypes = [ctypes.c_int64] * 2
     lib.ejoin_test_few_pays.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2
     lib.ejoin_test_once_edge.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2
+    lib.ejoin_test_dense_norm_groups.argtypes, lib.ejoin_test_dense_norm_groups.restype = [ctypes.c_int64] * 3, ctypes.c_int64
     lib.ejoin_test_few_groups_of.argtypes = [ctypes.c_int64]
     return lib
 
@@ -51,3 +52,9 @@ def test_tiles_of_the_one_launch_join(rules):
                                   (3968, 0, 1153, 1, 128), (3968, 0, 4096, 0, 128), (3968, 0, 4097, 0, 0), (4000, 3000, 768, 1, 128), (4000, 3000, 769, 1, 0), (4000, 3000, 512, 0, 128),
                                   (4000, 3000, 513, 0, 0), (300, 90000, 40, 0, 0), (300, 20000, 40, 0, 128), (100, 60000, 40, 1, 128), (10, 131062, 40, 1, 0)):
         assert rules.ejoin_test_once_edge(n, nq, d, count) == edge, (n, nq, d, count)
+
+
+def test_dense_blocks_whose_norms_are_worked_out_in_their_launch(rules):
+    """(n, rows, columns): the workgroups for the norms; the last set of a block of five tiles, blocks of tiles of 64 and of 128, and what takes two launches."""
+    for n, rows, cols, groups in ((1, 1, 1, 8), (19968, 20, 300, 312), (19969, 20, 300, 0), (8000, 300, 300, 128), (8000, 1800, 1750, 64), (8000, 600, 600, 128), (20000, 4000, 5000, 0), (120000, 300, 300, 0)):
+        assert rules.ejoin_test_dense_norm_groups(n, rows, cols) == groups, (n, rows, cols)
