@@ -54,7 +54,7 @@ extern "C" {
 typedef struct ejoin_ctx ejoin_ctx;
 
 /* Create a context on HIP device `device`.  The context owns some 600 KB of device
- * status words and counters and a workspace: 20 bytes per point (the norms s_i and their FP16 split; 4 more per 32 points) plus, for
+ * status words and counters and a workspace: 4 bytes per point (the norms s_i; 4 more per 32 points) plus, for
  * the join calls, room for a re-laid-out copy of X (roundup(n,256) * (roundup(d,64) + 32) * 2 bytes).  The workspace
  * is grown on demand with hipMalloc, or ahead of time by ejoin_reserve.  A call that has to grow the
  * workspace frees the old one first, which waits for the device to be idle: only calls that find the
