@@ -5,11 +5,10 @@ One "step" = one pass of the whole hot path over one synthetic workload that is 
 in HBM: norms + re-layout, FP16 split of the norm terms, Gram + threshold + compaction kernel (pair
 list with dist2, or per-point counts).  Prints ONE JSON line.
 
-With no flags the line's headline is configs[3] of the benchmark spec (n = 2*10^6, d = 384, S = 16, pair list), the
-larger of the two d >= 384 configurations the target is stated for, timed for --steps steps; `per_config`
-then holds every configuration and mode of the benchmark spec (configs[0..4], configs[3] at its three
-selectivities, configs[4] in pair and count mode), each timed for at least three steps with the shader
-clock and socket power sampled while it ran.  `--workload W` times one configuration only (profiling runs).
+With no flags the line's headline is the pair list of n = 2*10^6 points, d = 384, S = 16, the larger of the two
+workloads with d >= 384, timed for --steps steps; `per_config` then holds all five workloads of datagen.py in
+every mode (n = 2*10^6 at its three selectivities, n = 5*10^6 in pair and count mode), each timed for at least
+three steps with the shader clock and socket power sampled while it ran.  `--workload W` times one configuration only (profiling runs).
 
 `value` is the paper's derived throughput 2*n^2*d / t (Section 4.1.1: total operations of the all-pairs
 comparison divided by the measured time), which credits the use of symmetry as speed; `roofline.achieved`
@@ -35,7 +34,7 @@ if ROOT not in sys.path:
 PEAK_FP16_TFLOPS = 2500.0  # MI355X dense FP16 MFMA, published
 PEAK_CLOCK_MHZ = 2400.0
 HEADLINE = (4, 16, "pairs")
-# every configuration and mode the benchmark spec names: (workload id = configs index + 1, selectivity, mode)
+# every workload in every mode: (workload of datagen.py, selectivity, mode)
 ALL_CASES = [(1, 32, "pairs"), (2, 64, "pairs"), (3, 16, "pairs"), (4, 16, "pairs"), (4, 128, "pairs"), (4, 1024, "pairs"),
              (4, 1024, "count"), (5, 64, "pairs"), (5, 64, "count")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_join_workload4_hbm_counters.txt")
@@ -130,7 +129,7 @@ def cpu_baseline(X, workload, eps, budget_rows):
     dt = time.perf_counter() - t0
     evals = 2 * rows.size * (n - 1)
     return dict(value=2.0 * d * evals / dt / 1e12, unit="TFLOP/s", cores=orc.num_threads(), kind="oracle",
-                sample=f"configs[{workload - 1}]: {rows.size} seeded query rows x all {n} points, FP64 difference form, evaluated twice "
+                sample=f"n={n}, d={d}: {rows.size} seeded query rows x all {n} points, FP64 difference form, evaluated twice "
                        f"(size pass + fill pass): {evals} distance evaluations in {dt:.2f} s; extrapolated full n(n-1)/2 join: "
                        f"{n * (n - 1) / 2 / (evals / dt):.0f} s",
                 distance_evals_per_s=evals / dt)
@@ -184,7 +183,7 @@ class Case:
             self.step = lambda: ej.selfjoin_pairs(self.Xd, self.eps, cap, **out)
 
     def label(self):
-        return (f"configs[{self.w - 1}]: n={self.n}, d={self.d}, {self.spec['kind']}, S={self.S}, eps={self.eps:.7g}, mode={self.mode}")
+        return (f"n={self.n}, d={self.d}, {self.spec['kind']}, S={self.S}, eps={self.eps:.7g}, mode={self.mode}")
 
     def flops(self, ej):
         edge, steps, tiles = ej.join_work(self.n, self.d, self.nq if self.mode == "join" else 0, self.mode == "split")
@@ -415,7 +414,7 @@ def main():
     cpu_X = head_case.X[:head_case.n] if (not args.no_cpu_baseline and hmode in ("pairs", "count")) else None
     cpu_eps, cpu_n, cpu_d = head_case.eps, head_case.n, head_case.d
     if not single:
-        # every configuration and mode of the benchmark spec, the headline's own line first
+        # every workload in every mode, the headline's own line first
         per = []
         cache = {hw: head_case.X}
         del head_case
@@ -428,7 +427,7 @@ def main():
                     cache.clear()
                     cache[w] = datagen.generate(w)
                 c = Case(ej, w, S, mode, X=cache[w])
-                # small workloads: enough steps for a stable mean (a step of configs[0] is tens of microseconds)
+                # small workloads: enough steps for a stable mean (a step of 4,096 points is tens of microseconds)
                 steps = max(3, min(200, int(0.25 / max(1e-5, _estimate_s(c)))))
                 r = time_case(ej, c, steps, 1)
                 del c
