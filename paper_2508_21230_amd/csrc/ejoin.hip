@@ -439,11 +439,11 @@ typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 // Input that the memory-side cache (256 MB) cannot hold is read past the caches (NT), which leaves them to the result: what comes next,
 // norms or a join, reads that.  Then it has to be four columns a thread, whose loads are whole lines: 5 10^5 x 200 100 us, with the
 // norms after it 161 us, now 135; 10^6 x 128 176, now 148; eight columns (half lines) 151.  Smaller input may well be in that cache
-// already (10^5 x 128 again and again, with the norms: 19.7 us, 20.3 past the caches; 2 10^5 x 200 57, 60), and keeps eight columns.  Rows that
+// already (10^5 x 128 again and again, with the norms: 19.7 us, 20.3 past the caches; 2 10^5 x 200 57, 60), and keeps eight columns; so do rows whose lines would be fetched
+// twice (ingest_past_the_caches: 256,233 x 668 with the norms 267 us, 297 past the caches).  Rows that
 // are not 16-byte aligned have lines that two loads share: 4 10^5 x 333 158 us with eight columns, 184 past the caches with four,
 // 146 through them.
 constexpr int CONVERT_ROWS = 4;
-constexpr int64_t CONVERT_CACHED = 256ll << 20;  // bytes of input
 template <int COLS, bool NT>
 __global__ __launch_bounds__(256) void k_convert_f32(const float* __restrict__ X32, int64_t n, int32_t d, int64_t ld32,
                                                      const float* __restrict__ center, float scale, uint16_t* __restrict__ X16, int64_t ld16,
@@ -4193,14 +4193,13 @@ int ejoin_convert_f32(ejoin_ctx* ctx, const float* X32, int64_t n, int32_t d, in
   if (!guard.ok) return EJOIN_EHIP;
   const int64_t per_row = ld16 / 8;
   if ((n * per_row + 255) / 256 > 0x7FFFFFFFll) return EJOIN_EUNSUPPORTED;
-  // (a grid has fewer than 2^32 threads; at few coordinates most of a row of the result is padding, and eight columns are the better ones)
-  const bool large = n * d * (int64_t)sizeof(float) > CONVERT_CACHED && d > 32 && n * per_row < (1ll << 32);
-  const bool past = large && ld32 % 4 == 0 && (reinterpret_cast<uintptr_t>(X32) & 15) == 0;
-  const int64_t chunks = large ? ld16 / 4 : per_row;  // of a row
-  uint32_t wide_log2 = 3;  // (a row is a multiple of 64 columns)
-  while (wide_log2 < 6 && chunks % (2ll << wide_log2) == 0) ++wide_log2;
+  const uintptr_t at = reinterpret_cast<uintptr_t>(X32);
+  const bool past = ingest_past_the_caches(n, d, ld32, at, ld16);
+  const bool four = past || (ingest_large(n, d, ld16) && (ld32 % 4 != 0 || at % 16 != 0));
+  const int64_t chunks = four ? ld16 / 4 : per_row;  // of a row
+  const uint32_t wide_log2 = (uint32_t)__builtin_ctz(ingest_wide(chunks));
   const int64_t rows = (256 >> wide_log2) * CONVERT_ROWS;
-  hipLaunchKernelGGL((past ? k_convert_f32<4, true> : large ? k_convert_f32<4, false> : k_convert_f32<8, false>),
+  hipLaunchKernelGGL((past ? k_convert_f32<4, true> : four ? k_convert_f32<4, false> : k_convert_f32<8, false>),
                      dim3((unsigned)((n + rows - 1) / rows * (chunks >> wide_log2))), dim3(256), 0, static_cast<hipStream_t>(stream), X32,
                      n, d, ld32, center, scale, X16, ld16, wide_log2, (uint32_t)(chunks >> wide_log2));
   EJ_TRY(hipGetLastError());

@@ -17,6 +17,36 @@ inline bool norms_from_the_end(int64_t n, int64_t ld) {
   return bytes > EJ_MEMORY_SIDE_CACHE / 16 * 15 && bytes <= EJ_MEMORY_SIDE_CACHE * 3;
 }
 
+// Ingestion: threads side by side on a row of `chunks` (a power of two that divides them, 8 to 64).
+inline uint32_t ingest_wide(int64_t chunks) {
+  const int64_t two = chunks & -chunks;
+  return (uint32_t)(two < 64 ? two : 64);
+}
+// Ingestion with four columns a thread.  Input that the memory-side cache cannot hold only; at few coordinates most of a row of the result is padding, and
+// eight columns are the better ones.  (A grid has fewer than 2^32 threads.)
+inline bool ingest_large(int64_t n, int32_t d, int64_t ld16) {
+  return n * d * 4 > EJ_MEMORY_SIDE_CACHE && d > 32 && n * (ld16 / 8) < (1ll << 32);
+}
+// ... and past the caches: rows that are 16-byte aligned, where a line is rarely read twice.  A row is read in pieces of 16 * ingest_wide bytes by wavefronts that know
+// nothing of each other; where there are several and the rows do not begin at lines, the pieces share their first and last ones, and past the caches a shared line
+// is fetched twice.  Converted, and converted and normed, past the caches over eight columns through them:
+// one piece a row (d = 48, 100, 200), 400 MB 0.87, 0.82, 0.86 and 0.86, 0.84, 0.84; 1,700 MB 0.91, 0.89, 0.93 and 0.98, 0.97, 1.00;
+// whole lines (d = 192, 640, 960), 400 MB 0.86, 0.90, 0.88 and 0.83, 0.85, 0.84; 700 MB 0.98, 1.03, 0.99 and 0.94, 1.00, 0.99; 1,000 MB 0.98, 1.03, 1.00 and 0.98, 1.02, 1.01; 1,700 MB 0.99, 1.06,
+// 1.02 and 1.01, 1.06, 1.03, d = 768 1.02 and 1.04; rows of a power of two (d = 512, 1,024, 2,048) 1,700 MB 0.97, 0.94, 0.92 and 1.01, 0.96, 0.99;
+// shared lines, pieces of 256 bytes (d = 132, 300, 784), 330 MB 1.07, 1.07, 1.02 and 0.91, 0.95, 0.94; 520 MB 1.30, 1.15, 1.08 and 1.16, 1.08, 1.04; 700 MB 1.33, 1.27, 1.21 and 1.18, 1.17, 1.14; of 512
+// (d = 324, 600), 460 MB 0.98, 0.97 and 0.97, 0.93; 520 MB 1.07, 1.03 and 1.01, 1.01; 700 MB 1.13, 1.16 and 1.07, 1.10; of 1 KB (d = 980, 1,000, 2,000), 550 MB 0.96, 0.96, 0.98 and 0.96, 0.96, 0.91;
+// 600 MB 1.00, 1.01, 1.02 and 0.98, 0.98, 0.96.
+inline bool ingest_past_the_caches(int64_t n, int32_t d, int64_t ld32, uint64_t address, int64_t ld16) {
+  if (!ingest_large(n, d, ld16) || ld32 % 4 != 0 || address % 16 != 0) return false;
+  const int64_t chunks = ld16 / 4;
+  const uint32_t wide = ingest_wide(chunks);
+  if (chunks == wide) return true;
+  const bool whole_lines = ld32 % 32 == 0 && address % 128 == 0;
+  if (whole_lines && (chunks & (chunks - 1)) == 0) return true;
+  const int64_t eighths = whole_lines ? 24 : wide == 64 ? 18 : wide == 32 ? 15 : 0;  // of the cache
+  return n * d * 4 <= EJ_MEMORY_SIDE_CACHE / 8 * eighths;
+}
+
 // Tiles of edge x edge points of a self-join of a points, or of a and b points.
 inline int64_t tiles_of(int64_t edge, int64_t a, int64_t b, bool self) {
   const int64_t ta = (a + edge - 1) / edge, tb = (b + edge - 1) / edge;

@@ -18,6 +18,11 @@ CACHED = (256 << 20) // 4  # values
     (CACHED // 192 + 1, 192, 192, 0),  # 48 chunks a row: sixteen threads side by side
     (CACHED // 32 + 1, 32, 32, 0),     # few coordinates: eight columns a thread
     (CACHED // 33 + 1, 33, 36, 0),
+    (CACHED // 300 + 1, 300, 300, 0),  # pieces of rows that share lines: eight columns a thread, through the caches
+    (CACHED // 324 + 1, 324, 324, 0),  # fewer of those: past them
+    (CACHED // 324 * 15 // 8 + 9, 324, 324, 0),  # ... but not as large
+    (CACHED // 192 + 1, 192, 192, 4),  # whole lines but for the first row's place
+    (CACHED // 1000 + 1, 1000, 1000, 0),
 ])
 def test_conversion_by_size_and_alignment(n, d, ld, offset):
     """Every step rounded in FP32, then to FP16: to the bit."""

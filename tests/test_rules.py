@@ -15,6 +15,8 @@ def rules(tmp_path_factory):
                     os.path.join(ROOT, "tests", "host", "rules_dump.cpp"), "-o", str(out)], check=True)
     lib = ctypes.CDLL(str(out))
     lib.ejoin_test_norms_from_the_end.argtypes = [ctypes.c_int64] * 2
+    lib.ejoin_test_ingest_wide.argtypes, lib.ejoin_test_ingest_wide.restype = [ctypes.c_int64], ctypes.c_uint32
+    lib.ejoin_test_ingest_past_the_caches.argtypes = [ctypes.c_int64, ctypes.c_int32, ctypes.c_int64, ctypes.c_uint64]
     lib.ejoin_test_few_pays.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2
     lib.ejoin_test_once_edge.argtypes = [ctypes.c_int64] * 2 + [ctypes.c_int32] * 2
     lib.ejoin_test_dense_norm_groups.argtypes, lib.ejoin_test_dense_norm_groups.restype = [ctypes.c_int64] * 3, ctypes.c_int64
@@ -27,6 +29,15 @@ def test_norms_start_at_the_end_only_of_rows_that_the_memory_side_cache_does_not
         assert not rules.ejoin_test_norms_from_the_end(n, ld)
     for n, ld in ((2_000_000, 64), (500000, 256), (10**6, 256), (6_290_000, 64)):  # from 256 MB on
         assert rules.ejoin_test_norms_from_the_end(n, ld)
+
+
+def test_ingestion_past_the_caches_only_where_lines_are_rarely_read_twice(rules):
+    assert [rules.ejoin_test_ingest_wide(c) for c in (8, 16, 24, 32, 40, 48, 64, 80, 96, 128, 176, 192, 8192)] == [8, 16, 8, 32, 8, 16, 64, 16, 32, 64, 16, 64, 64]
+    # (d, stride, address, MB of input): one piece a row; whole lines; pieces of 1 KB, 512 and 256 bytes that share lines; rows that are not 16-byte aligned
+    for d, ld, address, mb, past in ((100, 100, 0, 250, 0), (100, 100, 0, 260, 1), (200, 200, 16, 2000, 1), (200, 200, 8, 2000, 0), (32, 32, 0, 2000, 0), (101, 101, 0, 400, 0),
+                                     (192, 192, 0, 760, 1), (192, 192, 0, 780, 0), (192, 192, 64, 300, 0), (180, 192, 128, 400, 1), (512, 512, 0, 2000, 1), (768, 768, 0, 700, 1), (768, 768, 0, 1700, 0),
+                                     (1000, 1000, 0, 570, 1), (1000, 1000, 0, 580, 0), (324, 324, 0, 470, 1), (324, 324, 0, 490, 0), (300, 300, 0, 260, 0), (668, 668, 0, 653, 0)):
+        assert rules.ejoin_test_ingest_past_the_caches((mb << 20) // (4 * d), d, ld, address) == past, (d, ld, address, mb)
 
 
 def test_few_query_points_against_sets_where_that_is_the_better_kernel(rules):
