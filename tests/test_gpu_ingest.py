@@ -1,4 +1,4 @@
-"""Ingestion of inputs on either side of what the memory-side cache holds: aligned rows are read past the caches, four columns a thread."""
+"""Ingestion of inputs on either side of what the memory-side cache holds: aligned rows whose pieces share few lines are read past the caches, four columns a thread."""
 import pytest
 import torch
 
